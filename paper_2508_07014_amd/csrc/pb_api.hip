@@ -211,7 +211,7 @@ int pb_fuse_step_select(const pb_tree* tree, const float* d_logp, int64_t row_st
   if (!d_logp || !d_states_in || !d_tokens || !d_states_out || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size) return PB_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::wave_path_ok(tree->dev, d_logp, 0, row_stride))
+  if (pb::wave_path_ok(tree->dev))
     return pb::launch_step_wave(tree->dev, pb::TreePick{}, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode, d_tokens,
                                 d_states_out, d_scores, stream);
   return pb::launch_fuse(tree->dev, pb::TreePick{}, d_logp, 0, row_stride, d_states_in, d_last_tokens, alpha, 1, B, mode, d_tokens,
@@ -240,7 +240,7 @@ int fuse_frames_any(const pb_tree* tree, const float* d_logp, int64_t frame_stri
   if (row_stride < tree->dev.vocab_size || frame_stride < 0) return PB_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   // (the segment decoder keeps a flag in bit 30 of the state words it stores: larger trees take the plain kernel)
-  if (pb::wave_path_ok(tree->dev, d_logp, frame_stride, row_stride) && tree->dev.num_states < (1 << 30))
+  if (pb::wave_path_ok(tree->dev) && tree->dev.num_states < (1 << 30))
     return pb::launch_frames_wave(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
                                   d_tokens, d_states, d_scores, d_patches, stream);
   return pb::launch_fuse(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
@@ -273,8 +273,7 @@ int pb_fuse_frames_plan(const pb_tree* tree, int32_t T, int32_t B, int32_t* n_se
     if (bounds) bounds[0] = 0;
     return PB_OK;
   }
-  const bool wide = tree->host.vocab_size > 1024;  // (rows wider than a chunk aim for fewer, longer chains)
-  const pb::SegPlan plan = pb::plan_segments(T, B, wide ? pb::kWideTargetChains : pb::kTargetChains);
+  const pb::SegPlan plan = pb::plan_segments(T, B, pb::target_chains(tree->host.vocab_size));
   *n_segments = plan.nseg;
   if (bounds)
     for (int j = 0; j <= plan.nseg; ++j) bounds[j] = pb::seg_begin(j, T, plan.nseg);
@@ -409,7 +408,7 @@ int pb_fuse_step_forest(const pb_forest* forest, const float* d_logp, int64_t ro
   if (row_stride < forest->proto.vocab_size) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::wave_path_ok(forest->proto, d_logp, 0, row_stride))  // members share the vocabulary, so one answer fits all
+  if (pb::wave_path_ok(forest->proto))  // members share the vocabulary, so one answer fits all
     return pb::launch_step_wave(forest->proto, pick, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode,
                                 d_tokens, d_states_out, d_scores, stream);
   return pb::launch_fuse(forest->proto, pick, d_logp, 0, row_stride, d_states_in, d_last_tokens, alpha, 1, B, mode,
@@ -427,7 +426,7 @@ int pb_fuse_frames_forest(const pb_forest* forest, const float* d_logp, int64_t 
   if (row_stride < forest->proto.vocab_size || frame_stride < 0) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::wave_path_ok(forest->proto, d_logp, frame_stride, row_stride) && forest->proto.num_states < (1 << 30))
+  if (pb::wave_path_ok(forest->proto) && forest->proto.num_states < (1 << 30))
     return pb::launch_frames_wave(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B,
                                   mode, d_tokens, d_states, d_scores, nullptr, stream);
   return pb::launch_fuse(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,

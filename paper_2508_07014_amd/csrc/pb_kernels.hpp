@@ -30,7 +30,7 @@ int launch_fuse(const DeviceTree& t, const TreePick& pick, const float* d_logp, 
                 const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B, int sel,
                 int32_t* d_tokens, int32_t* d_states, float* d_scores, hipStream_t stream);
 
-// Wave-per-hypothesis greedy kernels (pb_frames.hip); usable when rows are 16-byte aligned and V % 4 == 0.
+// Wave-per-hypothesis greedy kernels (pb_frames.hip, pb_narrow.hpp, pb_wide.hip).
 #ifndef PB_TARGET_CHAINS
 #define PB_TARGET_CHAINS 4096
 #endif
@@ -38,6 +38,7 @@ constexpr int kTargetChains = PB_TARGET_CHAINS;  // concurrent decode chains aim
 constexpr int kMinSegLen = 8;        // shortest speculative segment, in frames
 constexpr int kMaxSegments = 64;     // segments per hypothesis (one lane each in the validation pass)
 
+constexpr int kNarrowMaxV = 1280;    // widest row that one wave holds in registers
 constexpr int kWideMaxV = 16384;     // widest row of the wave kernels (the root scores of a row live in LDS)
 #ifndef PB_WIDE_TARGET_CHAINS
 #define PB_WIDE_TARGET_CHAINS 1024
@@ -62,9 +63,13 @@ __host__ __device__ inline int seg_begin(int j, int T, int nseg) {
   return static_cast<int>(even + bulge);
 }
 SegPlan plan_segments(int32_t T, int32_t B, int target_chains);
+// The chains aimed for by vocabulary size: what the chip holds at the kernels' waves per SIMD.
+inline int narrow_target_chains(int V) { return V <= 1024 ? kTargetChains : kTargetChains / 2; }
+inline int target_chains(int V) { return V <= kNarrowMaxV ? narrow_target_chains(V) : kWideTargetChains; }
 
-bool wave_path_ok(const DeviceTree& t, const float* d_logp, int64_t frame_stride, int64_t row_stride);
-// Rows wider than 1024 tokens (pb_wide.hip); same arguments as the calls below, which forward to them.
+// Rows of any stride and alignment, for vocabularies of 4 .. kWideMaxV tokens.
+bool wave_path_ok(const DeviceTree& t);
+// Rows wider than kNarrowMaxV tokens (pb_wide.hip); same arguments as the calls below, which forward to them.
 int prepare_wide_kernels(int max_lds_bytes);
 int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride,
                      const int32_t* d_states_in, const int32_t* d_last, float alpha, int32_t B, int sel,
@@ -77,6 +82,16 @@ int launch_step_wave(const DeviceTree& t, const TreePick& pick, const float* d_l
                      const int32_t* d_states_in,
                      const int32_t* d_last, float alpha, int32_t B, int sel, int32_t* d_tokens, int32_t* d_states_out,
                      float* d_scores, hipStream_t stream);
+// The narrow kernels, one instantiation per row shape (pb_narrow.hpp).
+template <int ROW>
+int launch_step_row(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride,
+                    const int32_t* d_states_in, const int32_t* d_last, float alpha, int32_t B, int sel,
+                    int32_t* d_tokens, int32_t* d_states_out, float* d_scores, hipStream_t stream);
+template <int ROW>
+int launch_frames_row(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,
+                      int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T,
+                      int32_t B, int sel, unsigned tag_lo, int32_t* d_tokens, int32_t* d_states, float* d_scores,
+                      int32_t* d_patches, hipStream_t stream);
 // d_patches: optional workspace of frames_workspace_bytes(t, T, B) bytes (null: wrong boundary guesses are
 // repaired by re-runs in pass 2 instead of patches from pass 1).
 int64_t frames_workspace_bytes(const DeviceTree& t, int32_t T, int32_t B);

@@ -31,6 +31,7 @@ struct TreeView {
   const ArcRec* arc;
   const float* root_score;
   int num_states, V, blank, eos;
+  int split, pad;  // ragged rows: see token_pos
 };
 
 __device__ __forceinline__ TreeView make_view(const DeviceTree& t) {
@@ -46,7 +47,27 @@ __device__ __forceinline__ TreeView make_view(const DeviceTree& t) {
   v.V = t.vocab_size;
   v.blank = t.blank_id;
   v.eos = t.eos_id;
+  v.split = t.vocab_size & ~3;
+  v.pad = -t.vocab_size & 3;
   return v;
+}
+
+// Row positions.  Lane l of a wave owns positions 256*i + 4*l + {0..3} of a chunk, four to a 16-byte load.  A row of
+// any length V >= 4 at any (4-byte) alignment is read without a branch and without touching a byte outside it by
+// clamping the first token of a group to V - 4: the group that straddles the end (V % 4 != 0) then holds the last
+// four tokens, the first `pad` of which the group before it holds already, and groups behind the end hold copies of
+// the same four.  Every token has exactly one position of its own, in ascending order:
+//   position(v) = v for v < split = V rounded down to a multiple of 4, v + pad for the 1..3 tokens behind it.
+// Copies never change a maximum, and the token's own position comes first; where a candidate must be counted once
+// (boosted selections) the copies carry a base boost of -inf or NaN.
+// FULL rows (the chunks tile the row, 16-byte aligned) have no copies: position == token.
+template <bool FULL>
+__device__ __forceinline__ int token_pos(const TreeView& t, int v) {
+  return FULL ? v : v + (v >= t.split ? t.pad : 0);
+}
+template <bool FULL>
+__device__ __forceinline__ int pos_token(const TreeView& t, int q) {  // of a token's own position
+  return FULL ? q : q - (q >= t.split ? t.pad : 0);
 }
 
 // Values that are wave-uniform by construction, told to the compiler (keeps them in SGPRs and the
@@ -96,8 +117,8 @@ __device__ __forceinline__ int tok_of(int j, int lane) { return 256 * (j >> 2) +
 // Does the lane's slot j hold chunk-relative token `rel` (wave-uniform)?  Written so that the slot
 // test stays on the scalar side and no per-slot token ids have to live in vector registers.
 __device__ __forceinline__ bool slot_is(int j, int lane, int rel) {
-  const int slot = ((rel >> 8) << 2) | (rel & 3);  // uniform
-  return (slot == j) && (lane == ((rel >> 2) & 63)) && (static_cast<unsigned>(rel) < static_cast<unsigned>(kChunk));
+  const int slot = ((rel >> 8) << 2) | (rel & 3);  // uniform; (a position behind the lanes' slots, or -1, matches none)
+  return (slot == j) && (lane == ((rel >> 2) & 63));
 }
 
 // The slot in which this lane holds chunk-relative token `rel` (wave-uniform), -1 in every other lane: a test of
@@ -173,79 +194,40 @@ __device__ __forceinline__ Cursor cursor_from_root_rec(const v8i& r) {
   return c;
 }
 
+// Puts `fill` into the slots of a row of one chunk that hold copies (see token_pos); a group of 256 positions that
+// lies inside the row is skipped by a uniform branch.
+template <bool FULL, int NS>
+__device__ __forceinline__ void drop_copies(int V, int lane, float fill, float (&c)[NS]) {
+  if constexpr (!FULL) {
+#pragma unroll
+    for (int i = 0; i < NS / 4; ++i) {
+      if (256 * (i + 1) > V) {
+        const int u = 256 * i + 4 * lane, held = u - min(u, V - 4);  // tokens of the group that lie before its own first
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[4 * i + k] = k < held ? fill : c[4 * i + k];
+      }
+    }
+  }
+}
+
 // Selection rule (enum pb_select_mode): 0 = single-stage fused arg-max, 1 = two-stage, 2 = two-stage
 // with the CTC repeat rule (Sec. II-C).  In the two-stage modes the blank is never a candidate of
 // the boosted re-selection: its column carries NaN, which neither fmaxf nor an equality test ever
 // selects, so an excluded token costs nothing in the reductions.
 //
-// alpha * (p_root + root_score[v]) for the lane's 16 tokens; the blank column boosts by 0 (SEL == 0)
-// or is excluded (SEL != 0).
-template <int SEL>
-__device__ __forceinline__ void make_base_boost(int cb, int lane, int blank, float p_root, float alpha,
-                                                const float (&rw)[16], float (&c)[16]) {
+// alpha * (p_root + root_score[v]) for the lane's positions of a row of one chunk; the blank column boosts by 0
+// (SEL == 0) or is excluded (SEL != 0), copies behind the end of the row carry -inf.
+template <bool FULL, int SEL, int NS>
+__device__ __forceinline__ void make_base_boost(const TreeView& t, int lane, float p_root, float alpha,
+                                                const float (&rw)[NS], float (&c)[NS]) {
+  const int blank = token_pos<FULL>(t, t.blank);
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const float boost = slot_is(j, lane, blank - cb) ? (SEL == 0 ? 0.0f : NAN) : __fadd_rn(p_root, rw[j]);
+  for (int j = 0; j < NS; ++j) {
+    const float boost = slot_is(j, lane, blank) ? (SEL == 0 ? 0.0f : NAN) : __fadd_rn(p_root, rw[j]);
     c[j] = __fmul_rn(alpha, boost);
   }
+  drop_copies<FULL>(t.V, lane, -INFINITY, c);
 }
-
-// Loads the lane's 16 values of chunk `cb` of a V-long fp32 array; positions >= V read as `fill`.
-template <bool FULL>
-__device__ __forceinline__ void load16(const float* __restrict__ base, int cb, int V, int lane, float fill,
-                                       float (&x)[16]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = cb + 256 * i + 4 * lane;
-    if (FULL || v < V) {  // V % 4 == 0: a 16-byte group is entirely inside or outside the row
-      const float4 q = *reinterpret_cast<const float4*>(base + v);
-      x[4 * i + 0] = q.x; x[4 * i + 1] = q.y; x[4 * i + 2] = q.z; x[4 * i + 3] = q.w;
-    } else {
-      x[4 * i + 0] = x[4 * i + 1] = x[4 * i + 2] = x[4 * i + 3] = fill;
-    }
-  }
-}
-
-__device__ __forceinline__ void store_row_lds(float* row, int lane, const float (&x)[16]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    *reinterpret_cast<float4*>(row + 256 * i + 4 * lane) = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
-}
-
-// Lowest token (chunk-relative) whose fused value equals M; g are the lane's four group maxima.
-__device__ __forceinline__ int first_token_equal(const float (&f)[16], const float (&g)[4], float M, int lane) {
-  const u64 b0 = __ballot(g[0] == M), b1 = __ballot(g[1] == M), b2 = __ballot(g[2] == M), b3 = __ballot(g[3] == M);
-  int gi;
-  u64 bm, e0, e1, e2;  // the fourth token of a group needs no ballot: it is the one left
-  if (b0) {
-    gi = 0; bm = b0;
-    e0 = __ballot(f[0] == M); e1 = __ballot(f[1] == M); e2 = __ballot(f[2] == M);
-  } else if (b1) {
-    gi = 1; bm = b1;
-    e0 = __ballot(f[4] == M); e1 = __ballot(f[5] == M); e2 = __ballot(f[6] == M);
-  } else if (b2) {
-    gi = 2; bm = b2;
-    e0 = __ballot(f[8] == M); e1 = __ballot(f[9] == M); e2 = __ballot(f[10] == M);
-  } else if (b3) {
-    gi = 3; bm = b3;
-    e0 = __ballot(f[12] == M); e1 = __ballot(f[13] == M); e2 = __ballot(f[14] == M);
-  } else {
-    return 0;  // only with NaN inputs (precondition violation): stay in range
-  }
-  const int L = first_lane(bm);
-  const u64 bit = 1ull << L;
-  const int k = (e0 & bit) ? 0 : (e1 & bit) ? 1 : (e2 & bit) ? 2 : 3;
-  return 256 * gi + 4 * L + k;
-}
-
-// Per-wave token marks: one bit per token of the current chunk (32 dwords of LDS).  LDS operations
-// of one wave execute in order, so clear -> set -> test needs no barrier inside the wave.
-constexpr int kTagWords = kChunk / 32;
-__device__ __forceinline__ void tags_clear(unsigned* bits, int lane) {
-  if (lane < kTagWords) bits[lane] = 0u;
-}
-__device__ __forceinline__ void tag_set(unsigned* bits, int tk) { atomicOr(&bits[tk >> 5], 1u << (tk & 31)); }
-__device__ __forceinline__ bool tag_test(const unsigned* bits, int tk) { return ((bits[tk >> 5] >> (tk & 31)) & 1u) != 0u; }
 
 // Maximum of four values in two instructions.  Written out because the compiler puts a canonicalising
 // max(x, x) in front of every operand of fmaxf whose origin it cannot see, which doubles the count; the
@@ -256,14 +238,92 @@ __device__ __forceinline__ float max4(float a, float b, float c, float d) {
   asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(m), "v"(d));
   return m;
 }
+__device__ __forceinline__ float max2(float a, float b) {
+  float m;
+  asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+  return m;
+}
+
+// Maxima of the lane's 256-token groups and of all its values.
+template <int NS>
+__device__ __forceinline__ float group_maxima(const float (&f)[NS], float (&g)[NS / 4]) {
+#pragma unroll
+  for (int i = 0; i < NS / 4; ++i) g[i] = max4(f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
+  float m = g[0];
+  if constexpr (NS >= 16) {
+    m = max4(g[0], g[1], g[2], g[3]);
+    for (int i = 4; i < NS / 4; ++i) m = max2(m, g[i]);
+  } else {
+    for (int i = 1; i < NS / 4; ++i) m = max2(m, g[i]);
+  }
+  return m;
+}
+
+// Loads the lane's NS values of the positions of chunk `cb` from a V-long fp32 array (see token_pos).
+template <bool FULL, int NS>
+__device__ __forceinline__ void load_row(const float* __restrict__ base, int cb, int V, int lane, float (&x)[NS]) {
+  typedef float vf4 __attribute__((ext_vector_type(4)));
+  typedef float vf4_any __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+  for (int i = 0; i < NS / 4; ++i) {
+    const int u = cb + 256 * i + 4 * lane;
+    vf4 q;
+    if constexpr (FULL) {
+      q = *reinterpret_cast<const vf4*>(base + u);
+    } else {
+      q = *reinterpret_cast<const vf4_any*>(base + static_cast<unsigned>(min(u, V - 4)));
+    }
+    x[4 * i + 0] = q.x; x[4 * i + 1] = q.y; x[4 * i + 2] = q.z; x[4 * i + 3] = q.w;
+  }
+}
+
+template <int NS>
+__device__ __forceinline__ void store_row_lds(float* row, int lane, const float (&x)[NS]) {
+#pragma unroll
+  for (int i = 0; i < NS / 4; ++i)
+    *reinterpret_cast<float4*>(row + 256 * i + 4 * lane) = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+}
+
+// Lowest position whose fused value equals M; g are the lane's group maxima.
+template <int NS>
+__device__ __forceinline__ int first_pos_equal(const float (&f)[NS], const float (&g)[NS / 4], float M, int lane) {
+  u64 b[NS / 4];
+#pragma unroll
+  for (int i = 0; i < NS / 4; ++i) b[i] = __ballot(g[i] == M);
+  int gi = -1;
+  u64 bm = 0, e0 = 0, e1 = 0, e2 = 0;  // the fourth token of a group needs no ballot: it is the one left
+#pragma unroll
+  for (int i = 0; i < NS / 4; ++i) {
+    if (gi < 0 && b[i] != 0) {
+      gi = i;
+      bm = b[i];
+      e0 = __ballot(f[4 * i] == M);
+      e1 = __ballot(f[4 * i + 1] == M);
+      e2 = __ballot(f[4 * i + 2] == M);
+    }
+  }
+  if (gi < 0) return 0;  // only with NaN inputs (precondition violation): stay in range
+  const int L = first_lane(bm);
+  const u64 bit = 1ull << L;
+  const int k = (e0 & bit) ? 0 : (e1 & bit) ? 1 : (e2 & bit) ? 2 : 3;
+  return 256 * gi + 4 * L + k;
+}
+
+// Per-wave token marks: one bit per position of the current chunk.  LDS operations of one wave execute in order, so
+// clear -> set -> test needs no barrier inside the wave.
+constexpr int kTagWords = kChunk / 32;
+__device__ __forceinline__ void tags_clear(unsigned* bits, int lane, int words = kTagWords) {
+  if (lane < words) bits[lane] = 0u;
+}
+__device__ __forceinline__ void tag_set(unsigned* bits, int tk) { atomicOr(&bits[tk >> 5], 1u << (tk & 31)); }
+__device__ __forceinline__ bool tag_test(const unsigned* bits, int tk) { return ((bits[tk >> 5] >> (tk & 31)) & 1u) != 0u; }
 
 // Stage 1 of the two-stage rule on one chunk: the unboosted row maximum and its lowest token.
-__device__ __forceinline__ void plain_argmax(const float (&x)[16], int lane, float& M0, int& v0) {
-  float g[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) g[i] = max4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
-  M0 = ukey_val(wave_max_u(ukey(max4(g[0], g[1], g[2], g[3]))));
-  v0 = first_token_equal(x, g, M0, lane);
+template <bool FULL, int NS>
+__device__ __forceinline__ void plain_argmax(const TreeView& t, const float (&x)[NS], int lane, float& M0, int& v0) {
+  float g[NS / 4];
+  M0 = ukey_val(wave_max_u(ukey(group_maxima(x, g))));
+  v0 = pos_token<FULL>(t, first_pos_equal(x, g, M0, lane));
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -34,13 +34,12 @@ namespace {
 
 using namespace wv;
 
-#ifndef PB_WIDE_RING
-#define PB_WIDE_RING 4
-#endif
 #ifndef PB_WIDE_WAVES_EU
 #define PB_WIDE_WAVES_EU 2
 #endif
-constexpr int kRing = PB_WIDE_RING;  // chunks in flight or in use per wave
+// RING: chunks in flight or in use per wave.  A row is padded to whole turns of the ring, so the launch picks the
+// ring that pads it least: four buffers, three (5, 6 and 9 chunks), or two (rows of two chunks).
+constexpr int ring_of(int nch) { return nch == 2 ? 2 : (nch + 2) / 3 * 3 < (nch + 3) / 4 * 4 ? 3 : 4; }
 
 // Running arg-max of a lane over its tokens of a row; code = 16 * chunk + slot of the lane's token.
 struct LaneBest {
@@ -48,30 +47,32 @@ struct LaneBest {
   int code;
 };
 __device__ __forceinline__ LaneBest lane_best_init() { return LaneBest{-INFINITY, 0}; }
-__device__ __forceinline__ int code_token(int code, int lane) { return (code >> 4) * kChunk + tok_of(code & 15, lane); }
+__device__ __forceinline__ int code_pos(int code, int lane) { return (code >> 4) * kChunk + tok_of(code & 15, lane); }
 
 // Row maximum and its lowest token from the lanes' running maxima.  A row whose candidates are all -inf (or
 // excluded) comes back as M == -inf with a token that means nothing: the caller takes the second pass then.
-__device__ __forceinline__ void wave_pick(const LaneBest& lb, int lane, float& M, int& tok) {
+template <bool FULL>
+__device__ __forceinline__ void wave_pick(const TreeView& t, const LaneBest& lb, int lane, float& M, int& tok) {
   M = ukey_val(wave_max_u(ukey(lb.m)));
-  tok = wave_min_nn(lb.m == M ? code_token(lb.code, lane) : INT_MAX);
+  tok = pos_token<FULL>(t, wave_min_nn(lb.m == M ? code_pos(lb.code, lane) : INT_MAX));
 }
 
 // Boosts alpha * (p_root + root_score[v]) of the lane's 16 tokens of chunk `cb`; the blank boosts by 0
 // (SEL == 0) or is excluded (NaN), the EOS token by `ce` = alpha * (EOS boost of the state) when `ce_on`.
-template <int SEL>
+template <bool FULL, int SEL>
 __device__ __forceinline__ void chunk_boosts(const TreeView& t, int cb, int lane, float p_root, float alpha, bool ce_on,
                                              float ce, const float (&rw)[16], float (&bo)[16]) {
 #pragma unroll
   for (int j = 0; j < 16; ++j) bo[j] = __fmul_rn(alpha, __fadd_rn(p_root, rw[j]));
-  const bool has_blank = static_cast<unsigned>(t.blank - cb) < static_cast<unsigned>(kChunk);
-  const bool has_eos = ce_on && static_cast<unsigned>(t.eos - cb) < static_cast<unsigned>(kChunk);
+  const int blank = token_pos<FULL>(t, t.blank) - cb, eos = token_pos<FULL>(t, t.eos) - cb;
+  const bool has_blank = static_cast<unsigned>(blank) < static_cast<unsigned>(kChunk);
+  const bool has_eos = ce_on && static_cast<unsigned>(eos) < static_cast<unsigned>(kChunk);
   if (has_blank || has_eos) {  // uniform, and false for most chunks
     const int ln = opaque(lane);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      if (has_blank && slot_is(j, ln, t.blank - cb)) bo[j] = SEL == 0 ? __fmul_rn(alpha, 0.0f) : NAN;
-      if (has_eos && slot_is(j, ln, t.eos - cb)) bo[j] = ce;
+      if (has_blank && slot_is(j, ln, blank)) bo[j] = SEL == 0 ? __fmul_rn(alpha, 0.0f) : NAN;
+      if (has_eos && slot_is(j, ln, eos)) bo[j] = ce;
     }
   }
 }
@@ -180,14 +181,16 @@ __device__ __forceinline__ FrameOut slow_frame(const TreeView& t, const Cursor& 
   for (int ch = 0; ch < nch; ++ch) {
     const int cb = ch * kChunk;
     float x[16], rw[16], bo[16];
-    load16<FULL>(rowp, cb, t.V, lane, -INFINITY, x);
-    load16<FULL>(t.root_score, cb, t.V, lane, 0.0f, rw);
-    chunk_boosts<SEL>(t, cb, lane, cur.p_root, alpha, t.eos >= 0, ce, rw, bo);
+    load_row<FULL>(rowp, cb, t.V, lane, x);
+    load_row<FULL>(t.root_score, cb, t.V, lane, rw);
+    chunk_boosts<FULL, SEL>(t, cb, lane, cur.p_root, alpha, t.eos >= 0, ce, rw, bo);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      const int v = cb + tok_of(j, lane);
+      const int q = cb + tok_of(j, lane), first = q & ~3, held = FULL ? 0 : first - min(first, t.V - 4);
+      const int v = min(q - held, t.V - 1);
       const float f = __fadd_rn(x[j], bo[j]);
-      const bool out = v >= t.V || f != f || (SEL == 2 && v == excl) || tag_test(tags, min(v, t.V - 1));
+      const bool copy = !FULL && (j & 3) < held;  // (the token has a position of its own before this one)
+      const bool out = copy || f != f || (SEL == 2 && v == excl) || tag_test(tags, v);
       if (!out && (!has || f > m)) {
         has = true;
         m = f;
@@ -337,12 +340,12 @@ __device__ __forceinline__ void advance(const TreeView& t, Cursor& cur, const Fr
 
 // Winner under root-state boosts from the lanes' running maxima `gb`; under the single-stage rule the blank
 // (kept out of the pass) competes with boost 0.
-template <int SEL>
+template <bool FULL, int SEL>
 __device__ __forceinline__ int root_winner(const TreeView& t, const LaneBest& gb, const float* __restrict__ rowp,
                                            float alpha, int lane) {
   float M;
   int w;
-  wave_pick(gb, lane, M, w);
+  wave_pick<FULL>(t, gb, lane, M, w);
   w = uniform_i(w);
   if (SEL == 0 && t.blank >= 0) {
     const float fb = __fadd_rn(uniform_f(rowp[t.blank]), __fmul_rn(alpha, 0.0f));
@@ -357,24 +360,24 @@ __device__ __forceinline__ void row_winners(const TreeView& t, const float* __re
                                             const float* rs, int nch, int lane, int& v0, int& w) {
   LaneBest fb = lane_best_init(), rb = lane_best_init(), gb = lane_best_init();
   float x[2][16];
-  load16<FULL>(rowp, 0, t.V, lane, -INFINITY, x[0]);
+  load_row<FULL>(rowp, 0, t.V, lane, x[0]);
   for (int ch0 = 0; ch0 < nch; ch0 += 2) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int ch = ch0 + u;
       if (ch < nch) {
-        if (ch + 1 < nch) load16<FULL>(rowp, (ch + 1) * kChunk, t.V, lane, -INFINITY, x[(u + 1) % 2]);
+        if (ch + 1 < nch) load_row<FULL>(rowp, (ch + 1) * kChunk, t.V, lane, x[(u + 1) % 2]);
         float rw[16];
         read_rs_lds(rs, ch * kChunk, lane, rw);
         wide_chunk<SEL, true>(x[u], rw, ch, 0.0f, alpha, fb, rb, gb);
       }
     }
   }
-  w = root_winner<SEL>(t, gb, rowp, alpha, lane);
+  w = root_winner<FULL, SEL>(t, gb, rowp, alpha, lane);
   v0 = -1;
   if (SEL != 0) {
     float M;
-    wave_pick(rb, lane, M, v0);
+    wave_pick<FULL>(t, rb, lane, M, v0);
     v0 = uniform_i(v0);
   }
 }
@@ -416,9 +419,9 @@ __device__ __forceinline__ void guess_boundary_wide(const TreeView& t, int v0, i
 }
 
 // Decodes frames [f0, f1) of hypothesis b, as run_frames_1k does for narrow rows (same arguments and rules).
-//   rs: root scores of the row in LDS, zero-padded to nchp chunks; tags: this wave's token marks (32 * nchp words)
-//   nchp: chunks per row rounded up to a whole turn of the ring (chunks past the row load nothing)
-template <bool COMPARE, bool FULL, int SEL, bool EDGE>
+//   rs: root scores of the row in LDS, for the positions of nchp chunks; tags: this wave's token marks (32 * nchp words)
+//   nchp: chunks per row rounded up to a whole turn of the ring (chunks past the row hold copies of its end)
+template <bool COMPARE, bool FULL, int RING, int SEL, bool EDGE>
 __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* __restrict__ logp, int64_t frame_stride,
                                                 int64_t row_stride, float alpha, int B, int b, int f0, int f1, int s_in,
                                                 int last_in, int T, const int32_t* __restrict__ states0,
@@ -431,11 +434,11 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
   const int nch = (V + kChunk - 1) / kChunk;
   const int tag_words = nchp * kTagWords;
   const float* rp = logp + static_cast<size_t>(b) * row_stride + static_cast<size_t>(f0) * frame_stride;
-  // The ring: buffer u holds chunk ch with ch % kRing == u.  A chunk is requested kRing - 1 chunks ahead, into
+  // The ring: buffer u holds chunk ch with ch % RING == u.  A chunk is requested RING - 1 chunks ahead, into
   // the buffer the chunk before the current one has just left, at the start of a chunk's turn.
-  float xb[kRing][16];
+  float xb[RING][16];
 #pragma unroll
-  for (int u = 0; u + 1 < kRing; ++u) load16<FULL>(rp, u * kChunk, V, lane, -INFINITY, xb[u]);
+  for (int u = 0; u + 1 < RING; ++u) load_row<FULL>(rp, u * kChunk, V, lane, xb[u]);
   StoredLane<SEL == 2> stored;
   if (COMPARE) stored.fetch(lane, f0, f1, B, b, tokens, states);
   int s = uniform_i(s_in);
@@ -467,16 +470,16 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
     float early_x = 0.0f;  // log-prob of the early arc's token: gathered after the first turn of the ring, when the arc is there
     auto pass = [&](auto track_c) {
       constexpr bool TRACK = decltype(track_c)::value;
-      auto turn = [&](int g) {  // one turn of the ring: kRing chunks, straight-line code
+      auto turn = [&](int g) {  // one turn of the ring: RING chunks, straight-line code
 #pragma unroll
-        for (int u = 0; u < kRing; ++u) {
+        for (int u = 0; u < RING; ++u) {
           const int ch = g + u;
-          // Request the chunk kRing - 1 ahead, of this row or of the next, without a condition (after the last
+          // Request the chunk RING - 1 ahead, of this row or of the next, without a condition (after the last
           // frame of the range the row in hand is asked for again, from cache): straight-line code lets the
           // compiler wait for exactly the chunk it needs and keep the others in flight.
-          const int nx = ch + kRing - 1;
+          const int nx = ch + RING - 1;
           const bool wrap = nx >= nchp;
-          load16<FULL>(wrap ? rpn : rp, (wrap ? nx - nchp : nx) * kChunk, V, lane, -INFINITY, xb[(u + kRing - 1) % kRing]);
+          load_row<FULL>(wrap ? rpn : rp, (wrap ? nx - nchp : nx) * kChunk, V, lane, xb[(u + RING - 1) % RING]);
           float rw[16];
           read_rs_lds(rs, ch * kChunk, lane, rw);
           wide_chunk<SEL, TRACK>(xb[u], rw, ch, cur.p_root, alpha, fb, rb, gb);
@@ -486,7 +489,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
       turn(0);
       // the early arc is there by now: the log-prob of its token is gathered while the rest of the row streams
       early_x = rp[lane < cur.rec.count ? early.token : 0];
-      for (int g = kRing; g < nchp; g += kRing) turn(g);
+      for (int g = RING; g < nchp; g += RING) turn(g);
     };
     if (track) {
       pass(std::integral_constant<bool, true>{});
@@ -495,13 +498,13 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
     }
     float M;
     int vb;
-    wave_pick(fb, lane, M, vb);
+    wave_pick<FULL>(t, fb, lane, M, vb);
     int v0 = -1;
     FrameOut o;
     bool stage1 = false;
     if (SEL != 0) {  // stage 1: selection without boosting; a blank (or a CTC repeat) is emitted as it is
       float M0;
-      wave_pick(rb, lane, M0, v0);
+      wave_pick<FULL>(t, rb, lane, M0, v0);
       v0 = uniform_i(v0);
       if (v0 == t.blank || (SEL == 2 && v0 == last)) {
         o = FrameOut{uniform_f(M0), v0, false, 0};
@@ -526,7 +529,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
       // the guess the next range starts from, made from the same rows; if it is what this range really ends
       // in, the last state word says so
       int g, glabel;
-      const int w = root_winner<SEL>(t, gb, rp, alpha, lane);
+      const int w = root_winner<FULL, SEL>(t, gb, rp, alpha, lane);
       guess_boundary_wide<FULL, SEL>(t, v0, w, rp, frame_stride, f, states0, b, alpha, rs, nch, lane, g, glabel);
       if (g == cur.s && (SEL != 2 || glabel == o.tok)) {
         if (lane == slot) out.st |= kGuessOk;
@@ -544,32 +547,35 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
   return false;  // (a re-run: the end of the range was reached without meeting the stored trajectory)
 }
 
-// Root scores of a row for the pass over it: zero beyond V, NaN in the blank and EOS columns (those two tokens
-// are candidates of their own, see special_candidate).
+// Root scores of four positions (from i, a multiple of 4) for the pass over a row: NaN in the blank and EOS columns
+// (those two tokens are candidates of their own, see special_candidate) and in the copies behind the end of the row.
+template <bool FULL>
 __device__ __forceinline__ float4 mask_special(const TreeView& t, int i, float4 q) {
+  const int first = FULL ? i : min(i, t.V - 4);
   float e[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k)
-    if (i + k == t.blank || i + k == t.eos) e[k] = NAN;
+    if (first + k == t.blank || first + k == t.eos || (!FULL && k < i - first)) e[k] = NAN;
   return make_float4(e[0], e[1], e[2], e[3]);
 }
+template <bool FULL>
 __device__ __forceinline__ float4 staged_root_scores(const TreeView& t, int i) {
-  float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  if (i < t.V) q = *reinterpret_cast<const float4*>(t.root_score + i);  // V % 4 == 0
-  return mask_special(t, i, q);
+  const float* p = t.root_score + min(i, t.V - 4);
+  return mask_special<FULL>(t, i, make_float4(p[0], p[1], p[2], p[3]));
 }
 
 // The same into LDS for a whole row, by the whole workgroup; ends with a barrier.
+template <bool FULL>
 __device__ __forceinline__ void stage_root_scores(const TreeView& t, float* rs, int nchp) {
   const int n = nchp * kChunk;
   for (int i = 4 * static_cast<int>(threadIdx.x); i < n; i += 4 * static_cast<int>(blockDim.x))
-    *reinterpret_cast<float4*>(rs + i) = staged_root_scores(t, i);
+    *reinterpret_cast<float4*>(rs + i) = staged_root_scores<FULL>(t, i);
   __syncthreads();
 }
 
 // Pass 1 (see frames_spec_kernel of the narrow rows).  With a table of trees the workgroup's waves may use
 // different trees, so each wave then keeps its own copy of the root scores.
-template <bool FULL, int SEL, bool FOREST>
+template <bool FULL, int RING, int SEL, bool FOREST>
 __global__ void __launch_bounds__(256, PB_WIDE_WAVES_EU) wide_spec_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
                                                          int64_t frame_stride, int64_t row_stride,
                                                          const int32_t* __restrict__ states0,
@@ -592,11 +598,11 @@ __global__ void __launch_bounds__(256, PB_WIDE_WAVES_EU) wide_spec_kernel(Device
     rs = lds + wave * (row_floats + nchp * kTagWords);
     tags = reinterpret_cast<unsigned*>(rs + row_floats);
     if (tree_ok) {
-      for (int i = 4 * lane; i < row_floats; i += 256) *reinterpret_cast<float4*>(rs + i) = staged_root_scores(t, i);
+      for (int i = 4 * lane; i < row_floats; i += 256) *reinterpret_cast<float4*>(rs + i) = staged_root_scores<FULL>(t, i);
     }
   } else {
     tags = reinterpret_cast<unsigned*>(lds + row_floats) + wave * nchp * kTagWords;
-    stage_root_scores(t, rs, nchp);
+    stage_root_scores<FULL>(t, rs, nchp);
   }
   if (!live) return;
   const int f0 = seg_begin(j, T, nseg), f1 = seg_begin(j + 1, T, nseg);
@@ -606,12 +612,12 @@ __global__ void __launch_bounds__(256, PB_WIDE_WAVES_EU) wide_spec_kernel(Device
     if (SEL == 2 && last0 != nullptr) last = last0[b];
   }
   if (!tree_ok) s = -1;  // an unknown tree marks every frame of the hypothesis like an invalid state
-  run_frames_wide<false, FULL, SEL, true>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1, s, last, T, states0,
+  run_frames_wide<false, FULL, RING, SEL, true>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1, s, last, T, states0,
                                           tokens, states, scores, rs, tags, nchp, lane);
 }
 
 // Pass 2: one workgroup per hypothesis (one tree, so the root scores are shared).
-template <bool FULL, int SEL, bool FOREST>
+template <bool FULL, int RING, int SEL, bool FOREST>
 __global__ void __launch_bounds__(512) wide_fix_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
                                                         int64_t frame_stride, int64_t row_stride, float alpha, int T,
                                                         int B, int seg_len, int nseg, int nchp,
@@ -629,12 +635,12 @@ __global__ void __launch_bounds__(512) wide_fix_kernel(DeviceTree dt, TreePick p
   const TreeView t = make_view(mine);
   float* rs = lds;
   unsigned* tags = reinterpret_cast<unsigned*>(lds + nchp * kChunk) + wave * nchp * kTagWords;
-  stage_root_scores(t, rs, nchp);
+  stage_root_scores<FULL>(t, rs, nchp);
   fix_segments<SEL == 2>(T, B, b, seg_len, nseg, tokens, states, scores, nullptr, assumed, assumed_tok, bad_words, lane,
                          wave, nwaves,
                          [&](int seg, int s, int last) {
                            const int f0 = seg_begin(seg, T, nseg), f1 = seg_begin(seg + 1, T, nseg);
-                           return run_frames_wide<true, FULL, SEL, false>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1,
+                           return run_frames_wide<true, FULL, RING, SEL, false>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1,
                                                                    s, last, T, nullptr, tokens, states, scores, rs, tags,
                                                                    nchp, lane);
                          });
@@ -669,8 +675,8 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   const float* rowp = logp + static_cast<size_t>(b) * row_stride;
   const float* rsp = LEAN ? root_score : t.root_score;
   float x[16], rw[16];
-  load16<FULL>(rsp, wave * kChunk, t.V, lane, 0.0f, rw);
-  load16<FULL>(rowp, wave * kChunk, t.V, lane, -INFINITY, x);
+  load_row<FULL>(rsp, wave * kChunk, t.V, lane, rw);
+  load_row<FULL>(rowp, wave * kChunk, t.V, lane, x);
   int s = tree_ok ? states_in[b] : -1;  // an unknown tree marks the hypothesis like an invalid state
   __builtin_amdgcn_sched_barrier(0);
   s = uniform_i(s);
@@ -686,7 +692,7 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   if (!ok) s = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {  // NaN in the blank and EOS columns: those two are candidates of their own
-    const float4 q = mask_special(t, wave * kChunk + 256 * i + 4 * lane,
+    const float4 q = mask_special<FULL>(t, wave * kChunk + 256 * i + 4 * lane,
                                   make_float4(rw[4 * i], rw[4 * i + 1], rw[4 * i + 2], rw[4 * i + 3]));
     rw[4 * i + 0] = q.x; rw[4 * i + 1] = q.y; rw[4 * i + 2] = q.z; rw[4 * i + 3] = q.w;
   }
@@ -705,8 +711,8 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   LaneBest fb = lane_best_init(), rb = lane_best_init(), gb = lane_best_init();
   wide_chunk<SEL, false>(x, rw, wave, p_root, alpha, fb, rb, gb);
   StepPart mine_part{0.0f, 0.0f, 0, 0};
-  wave_pick(fb, lane, mine_part.M, mine_part.vb);
-  if (SEL != 0) wave_pick(rb, lane, mine_part.M0, mine_part.v0);
+  wave_pick<FULL>(t, fb, lane, mine_part.M, mine_part.vb);
+  if (SEL != 0) wave_pick<FULL>(t, rb, lane, mine_part.M0, mine_part.v0);
   if (lane == 0) part[wave] = mine_part;
   __syncthreads();
   if (wave != 0) return;
@@ -747,22 +753,26 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
 int g_wide_fix_waves = 8;   // waves per fix-up workgroup the device's LDS allows for the widest row, set once
 int g_wide_max_lds = 64 * 1024;
 
-inline int padded_chunks(int V) {
-  const int nch = (V + kChunk - 1) / kChunk;
-  return (nch + kRing - 1) / kRing * kRing;
-}
+inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 }  // namespace
 
-// Expands to one launch per (row shape, selection rule) pair; FULL: V a multiple of a whole ring turn of chunks.
-#define PB_DISPATCH(full, sel, LAUNCH)   \
-  switch ((full ? 0 : 3) + (sel)) {      \
-    case 0: LAUNCH(true, 0); break;      \
-    case 1: LAUNCH(true, 1); break;      \
-    case 2: LAUNCH(true, 2); break;      \
-    case 3: LAUNCH(false, 0); break;     \
-    case 4: LAUNCH(false, 1); break;     \
-    default: LAUNCH(false, 2); break;    \
+// Expands to one launch per (row kind, selection rule) pair.  Kinds of the multi-frame kernels: 0 = whole ring turns of
+// full chunks in 16-byte aligned rows, 1 .. 3 = any row through a ring of four, three or two buffers.
+#define PB_DISPATCH(kind, sel, LAUNCH)     \
+  switch (3 * (kind) + (sel)) {            \
+    case 0: LAUNCH(true, 4, 0); break;     \
+    case 1: LAUNCH(true, 4, 1); break;     \
+    case 2: LAUNCH(true, 4, 2); break;     \
+    case 3: LAUNCH(false, 4, 0); break;    \
+    case 4: LAUNCH(false, 4, 1); break;    \
+    case 5: LAUNCH(false, 4, 2); break;    \
+    case 6: LAUNCH(false, 3, 0); break;    \
+    case 7: LAUNCH(false, 3, 1); break;    \
+    case 8: LAUNCH(false, 3, 2); break;    \
+    case 9: LAUNCH(false, 2, 0); break;    \
+    case 10: LAUNCH(false, 2, 1); break;   \
+    default: LAUNCH(false, 2, 2); break;   \
   }
 
 int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride,
@@ -770,7 +780,7 @@ int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_l
                      int32_t* d_tokens, int32_t* d_states_out, float* d_scores, hipStream_t stream) {
   const int V = t.vocab_size;
   const int nch = (V + kChunk - 1) / kChunk;  // <= 16 (kWideMaxV)
-  const bool full = V % kChunk == 0;
+  const bool full = V % kChunk == 0 && row_stride % 4 == 0 && aligned16(d_logp) && aligned16(t.root_score);
   const size_t lds = static_cast<size_t>(nch) * kTagWords * sizeof(unsigned);
   const dim3 grid(static_cast<unsigned>(B)), block(static_cast<unsigned>(64 * nch));
   const bool lean = pick.table == nullptr;
@@ -783,7 +793,14 @@ int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_l
   } else {                     \
     PB_STEP(FULL, SEL, false); \
   }
-  PB_DISPATCH(full, sel, PB_LAUNCH)
+  switch ((full ? 0 : 3) + sel) {
+    case 0: PB_LAUNCH(true, 0); break;
+    case 1: PB_LAUNCH(true, 1); break;
+    case 2: PB_LAUNCH(true, 2); break;
+    case 3: PB_LAUNCH(false, 0); break;
+    case 4: PB_LAUNCH(false, 1); break;
+    default: PB_LAUNCH(false, 2); break;
+  }
 #undef PB_LAUNCH
 #undef PB_STEP
   return hipGetLastError() == hipSuccess ? PB_OK : PB_EHIP;
@@ -793,8 +810,10 @@ int launch_frames_wide(const DeviceTree& t, const TreePick& pick, const float* d
                        int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T,
                        int32_t B, int sel, int32_t* d_tokens, int32_t* d_states, float* d_scores, hipStream_t stream) {
   const int V = t.vocab_size;
-  const int nchp = padded_chunks(V);
-  const bool full = V % (kRing * kChunk) == 0;
+  const int nch = (V + kChunk - 1) / kChunk, ring = ring_of(nch), nchp = (nch + ring - 1) / ring * ring;
+  const bool full = V % (4 * kChunk) == 0 && row_stride % 4 == 0 && frame_stride % 4 == 0 && aligned16(d_logp) &&
+                    aligned16(t.root_score);
+  const int kind = full ? 0 : 5 - ring;
   const bool forest = pick.table != nullptr;
   const size_t row_bytes = static_cast<size_t>(nchp) * kChunk * sizeof(float);
   const size_t tag_bytes = static_cast<size_t>(nchp) * kTagWords * sizeof(unsigned);
@@ -811,16 +830,16 @@ int launch_frames_wide(const DeviceTree& t, const TreePick& pick, const float* d
   const int64_t chains = static_cast<int64_t>(B) * nseg;
   const int64_t blocks = (chains + waves - 1) / waves;
   if (blocks > INT32_MAX) return PB_EUNSUPPORTED;
-#define PB_SPEC(FULL, SEL, FOREST)                                                                                 \
-  hipLaunchKernelGGL((wide_spec_kernel<FULL, SEL, FOREST>), dim3(static_cast<unsigned>(blocks)), dim3(64 * waves), \
+#define PB_SPEC(FULL, RING, SEL, FOREST)                                                                                 \
+  hipLaunchKernelGGL((wide_spec_kernel<FULL, RING, SEL, FOREST>), dim3(static_cast<unsigned>(blocks)), dim3(64 * waves), \
                      lds, stream, t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B,      \
                      seg_len, nseg, nchp, d_tokens, d_states, d_scores)
-#define PB_LAUNCH(FULL, SEL) PB_SPEC(FULL, SEL, false)
-#define PB_LAUNCH_F(FULL, SEL) PB_SPEC(FULL, SEL, true)
+#define PB_LAUNCH(FULL, RING, SEL) PB_SPEC(FULL, RING, SEL, false)
+#define PB_LAUNCH_F(FULL, RING, SEL) PB_SPEC(FULL, RING, SEL, true)
   if (forest) {
-    PB_DISPATCH(full, sel, PB_LAUNCH_F)
+    PB_DISPATCH(kind, sel, PB_LAUNCH_F)
   } else {
-    PB_DISPATCH(full, sel, PB_LAUNCH)
+    PB_DISPATCH(kind, sel, PB_LAUNCH)
   }
 #undef PB_LAUNCH
 #undef PB_LAUNCH_F
@@ -831,16 +850,16 @@ int launch_frames_wide(const DeviceTree& t, const TreePick& pick, const float* d
     while (fw > 1 && row_bytes + fw * tag_bytes > static_cast<size_t>(g_wide_max_lds)) --fw;
     const size_t lds2 = row_bytes + fw * tag_bytes;
     if (lds2 > static_cast<size_t>(g_wide_max_lds)) return PB_EUNSUPPORTED;
-#define PB_FIX(FULL, SEL, FOREST)                                                                                   \
-  hipLaunchKernelGGL((wide_fix_kernel<FULL, SEL, FOREST>), dim3(static_cast<unsigned>(B)), dim3(64 * fw), lds2,     \
+#define PB_FIX(FULL, RING, SEL, FOREST)                                                                                   \
+  hipLaunchKernelGGL((wide_fix_kernel<FULL, RING, SEL, FOREST>), dim3(static_cast<unsigned>(B)), dim3(64 * fw), lds2,     \
                      stream, t, pick, d_logp, frame_stride, row_stride, alpha, T, B, seg_len, nseg, nchp, d_tokens, \
                      d_states, d_scores)
-#define PB_LAUNCH(FULL, SEL) PB_FIX(FULL, SEL, false)
-#define PB_LAUNCH_F(FULL, SEL) PB_FIX(FULL, SEL, true)
+#define PB_LAUNCH(FULL, RING, SEL) PB_FIX(FULL, RING, SEL, false)
+#define PB_LAUNCH_F(FULL, RING, SEL) PB_FIX(FULL, RING, SEL, true)
     if (forest) {
-      PB_DISPATCH(full, sel, PB_LAUNCH_F)
+      PB_DISPATCH(kind, sel, PB_LAUNCH_F)
     } else {
-      PB_DISPATCH(full, sel, PB_LAUNCH)
+      PB_DISPATCH(kind, sel, PB_LAUNCH)
     }
 #undef PB_LAUNCH
 #undef PB_LAUNCH_F
@@ -854,18 +873,18 @@ int prepare_wide_kernels(int max_lds_bytes) {
   // The widest row needs 64 KiB of root scores plus the waves' token marks: past 64 KiB of dynamic LDS the
   // limit of each kernel must be raised.
   constexpr int kPlainLimit = 64 * 1024 - 1024;  // static LDS of the kernels included
-  const int want = (padded_chunks(kWideMaxV) * kChunk + 8 * padded_chunks(kWideMaxV) * kTagWords) * 4 + 1024;
+  const int want = ((kWideMaxV / kChunk) * kChunk + 8 * (kWideMaxV / kChunk) * kTagWords) * 4 + 1024;
   int limit = kPlainLimit;
   if (max_lds_bytes > kPlainLimit) {
     const int bytes = (want < max_lds_bytes ? want : max_lds_bytes) - 1024;
     const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
     bool ok = true;
-#define PB_SET(FULL, SEL)                                                                                               \
-  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FULL, SEL, false>), attr, bytes) == hipSuccess && \
-       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FULL, SEL, true>), attr, bytes) == hipSuccess &&        \
-       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FULL, SEL, false>), attr, bytes) == hipSuccess &&      \
-       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FULL, SEL, true>), attr, bytes) == hipSuccess
-    for (int ms = 0; ms < 6; ++ms) PB_DISPATCH(ms < 3, ms % 3, PB_SET)
+#define PB_SET(FULL, RING, SEL)                                                                                               \
+  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FULL, RING, SEL, false>), attr, bytes) == hipSuccess && \
+       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FULL, RING, SEL, true>), attr, bytes) == hipSuccess &&        \
+       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FULL, RING, SEL, false>), attr, bytes) == hipSuccess &&      \
+       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FULL, RING, SEL, true>), attr, bytes) == hipSuccess
+    for (int ms = 0; ms < 12; ++ms) PB_DISPATCH(ms / 3, ms % 3, PB_SET)
 #undef PB_SET
     if (ok) {
       limit = bytes;
