@@ -211,7 +211,7 @@ int pb_fuse_step_select(const pb_tree* tree, const float* d_logp, int64_t row_st
   if (!d_logp || !d_states_in || !d_tokens || !d_states_out || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size) return PB_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::wave_path_ok(tree->dev))
+  if (pb::step_wave_ok(tree->dev))
     return pb::launch_step_wave(tree->dev, pb::TreePick{}, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode, d_tokens,
                                 d_states_out, d_scores, stream);
   return pb::launch_fuse(tree->dev, pb::TreePick{}, d_logp, 0, row_stride, d_states_in, d_last_tokens, alpha, 1, B, mode, d_tokens,
@@ -408,7 +408,7 @@ int pb_fuse_step_forest(const pb_forest* forest, const float* d_logp, int64_t ro
   if (row_stride < forest->proto.vocab_size) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::wave_path_ok(forest->proto))  // members share the vocabulary, so one answer fits all
+  if (pb::step_wave_ok(forest->proto))  // members share the vocabulary, so one answer fits all
     return pb::launch_step_wave(forest->proto, pick, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode,
                                 d_tokens, d_states_out, d_scores, stream);
   return pb::launch_fuse(forest->proto, pick, d_logp, 0, row_stride, d_states_in, d_last_tokens, alpha, 1, B, mode,

@@ -163,6 +163,10 @@ bool wave_path_ok(const DeviceTree& t) {
   return t.p_root != nullptr && t.root_rec != nullptr && t.vocab_size >= 4 && t.vocab_size <= kWideMaxV;
 }
 
+bool step_wave_ok(const DeviceTree& t) {
+  return t.p_root != nullptr && t.root_rec != nullptr && t.vocab_size >= 4 && t.vocab_size <= kStepMaxV;
+}
+
 SegPlan plan_segments(int32_t T, int32_t B, int target_chains) {
   // Segments: enough concurrent chains to cover the memory latency, at most kMaxSegments per
   // hypothesis, at least kMinSegLen frames long.

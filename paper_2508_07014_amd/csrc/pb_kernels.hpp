@@ -39,7 +39,8 @@ constexpr int kMinSegLen = 8;        // shortest speculative segment, in frames
 constexpr int kMaxSegments = 64;     // segments per hypothesis (one lane each in the validation pass)
 
 constexpr int kNarrowMaxV = 1280;    // widest row that one wave holds in registers
-constexpr int kWideMaxV = 16384;     // widest row of the wave kernels (the root scores of a row live in LDS)
+constexpr int kWideMaxV = 16384;     // widest row of the multi-frame wave kernels (the root scores of a row live in LDS)
+constexpr int kStepMaxV = 65536;     // widest row of the single step that one workgroup holds in registers
 #ifndef PB_WIDE_TARGET_CHAINS
 #define PB_WIDE_TARGET_CHAINS 1024
 #endif
@@ -67,8 +68,9 @@ SegPlan plan_segments(int32_t T, int32_t B, int target_chains);
 inline int narrow_target_chains(int V) { return V <= 1024 ? kTargetChains : kTargetChains / 2; }
 inline int target_chains(int V) { return V <= kNarrowMaxV ? narrow_target_chains(V) : kWideTargetChains; }
 
-// Rows of any stride and alignment, for vocabularies of 4 .. kWideMaxV tokens.
+// Rows of any stride and alignment, for vocabularies of 4 .. kWideMaxV (single step: kStepMaxV) tokens.
 bool wave_path_ok(const DeviceTree& t);
+bool step_wave_ok(const DeviceTree& t);
 // Rows wider than kNarrowMaxV tokens (pb_wide.hip); same arguments as the calls below, which forward to them.
 int prepare_wide_kernels(int max_lds_bytes);
 int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride,

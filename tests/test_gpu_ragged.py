@@ -133,3 +133,39 @@ def test_ragged_rows_with_a_table_of_trees(V):
             _check([g[:, b:b + 1] for g in o], want, [0], (V, mode, b))
             _check([g[b:b + 1] for g in p], [w[0] for w in want], [0], (V, mode, b, "step"))
     pb.pb_forest_free(forest)
+
+
+@pytest.mark.parametrize("V", [16385, 32768, 32771, 49152, 49153, 65533, 65536, 65537])
+def test_step_on_very_wide_rows(V):
+    """The single step with two, three and four chunks per wave, and the first width past them."""
+    rng = np.random.default_rng(33000 + V)
+    for case in range(2):
+        blank, eos = int(rng.choice([0, -1, V - 1])), int(rng.choice([-1, V - 2]))
+        toks, offs, ot, tr = _tree(rng, V, blank, eos, case, float(rng.choice([0.0, -0.25])))
+        B, stride, shift = 5, V + int(rng.choice([0, 3])), int(rng.integers(0, 4))
+        x = _rows(rng, 1, B, V, blank, toks, offs)
+        buf, _ = _on_device(x, stride, shift)
+        s0 = rng.integers(0, ot.num_states, B).astype(np.int32)
+        s0[2] = ot.num_states
+        last = rng.integers(-1, V, B).astype(np.int32)
+        ok = [b for b in range(B) if b != 2]
+        forest = pb.pb_forest_build([tr]) if eos < 0 else None
+        for mode in (0, 1, 2):
+            want = ot.fuse_step_select(np.ascontiguousarray(x[0, ok]), s0[ok], last[ok], 0.5, mode)
+            for table in ([False, True] if forest else [False]):
+                o = [torch.full((B,), -7, dtype=torch.int32, device=DEV), torch.full((B,), -7, dtype=torch.int32, device=DEV),
+                     torch.zeros(B, device=DEV)]
+                where = dict(V=V, case=case, blank=blank, eos=eos, mode=mode, stride=stride, shift=shift, table=table)
+                print("step", where, flush=True)
+                ptr = buf.data_ptr() + 4 * shift
+                if table:
+                    pb.pb_fuse_step_forest(forest, ptr, stride, dev(np.zeros(B, np.int32)), dev(s0), dev(last), 0.5, B, mode,
+                                           o[0], o[1], o[2], 0)
+                else:
+                    pb.pb_fuse_step_select(tr, ptr, stride, dev(s0), dev(last), 0.5, B, mode, o[0], o[1], o[2], 0)
+                torch.cuda.synchronize()
+                _check(o, want, ok, where)
+                assert int(o[0][2]) == -1 and int(o[1][2]) == -1 and torch.isnan(o[2][2]), where
+        if forest:
+            pb.pb_forest_free(forest)
+        pb.pb_free(tr)
