@@ -2,7 +2,9 @@
 // the compiled tree, and dispatch to the kernel launchers.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -89,6 +91,10 @@ int upload(pb_tree* tr, int device) {
     tr->dev.num_states = static_cast<int32_t>(h.state.size());
     tr->dev.vocab_size = h.vocab_size;
     tr->dev.blank_id = h.blank_id;
+    float reach_p = 0.0f, reach_r = 0.0f;
+    for (const float x : h.p_root) reach_p = std::max(reach_p, std::fabs(x));
+    for (const float x : h.root_score) reach_r = std::max(reach_r, std::fabs(x));
+    tr->dev.reach = reach_p + reach_r;
     if (rc != PB_OK) {
       (void)hipGetLastError();
       (void)hipFree(slab);
@@ -239,6 +245,9 @@ int fuse_frames_any(const pb_tree* tree, const float* d_logp, int64_t frame_stri
   if (!d_logp || !d_states0 || !d_tokens || !d_states || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size || frame_stride < 0) return PB_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (pb::frames_rows_ok(tree->dev, d_states0, d_last0, T, B, d_tokens, d_states, d_scores))
+    return pb::launch_frames_rows(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
+                                  d_tokens, d_states, d_scores, stream);
   // (the segment decoder keeps a flag in bit 30 of the state words it stores: larger trees take the plain kernel)
   if (pb::wave_path_ok(tree->dev) && tree->dev.num_states < (1 << 30))
     return pb::launch_frames_wave(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
@@ -426,6 +435,9 @@ int pb_fuse_frames_forest(const pb_forest* forest, const float* d_logp, int64_t 
   if (row_stride < forest->proto.vocab_size || frame_stride < 0) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (pb::frames_rows_ok(forest->proto, d_states0, d_last0, T, B, d_tokens, d_states, d_scores))
+    return pb::launch_frames_rows(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
+                                  d_tokens, d_states, d_scores, stream);
   if (pb::wave_path_ok(forest->proto) && forest->proto.num_states < (1 << 30))
     return pb::launch_frames_wave(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B,
                                   mode, d_tokens, d_states, d_scores, nullptr, stream);

@@ -268,7 +268,8 @@ int prepare_wave_kernels() {
     else
       (void)hipGetLastError();
   }
-  return prepare_wide_kernels(max_lds);
+  const int rc = prepare_wide_kernels(max_lds);
+  return rc == PB_OK ? prepare_rows_kernels(max_lds) : rc;
 }
 
 }  // namespace pb

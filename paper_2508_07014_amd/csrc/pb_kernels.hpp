@@ -102,6 +102,16 @@ int launch_frames_wave(const DeviceTree& t, const TreePick& pick, const float* d
                        const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B, int sel,
                        int32_t* d_tokens, int32_t* d_states, float* d_scores, int32_t* d_patches, hipStream_t stream);
 
+// Multi-frame decoding in two passes, all rows and then the automaton (pb_rows.hip): whether a call can take it -- the
+// outputs hold the rows' winners in between, so they must not overlap the start states, the previous labels or each
+// other -- and the launch.
+int prepare_rows_kernels(int max_lds_bytes);
+bool frames_rows_ok(const DeviceTree& t, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B,
+                    const int32_t* d_tokens, const int32_t* d_states, const float* d_scores);
+int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,
+                       int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T,
+                       int32_t B, int sel, int32_t* d_tokens, int32_t* d_states, float* d_scores, hipStream_t stream);
+
 // Wave-per-beam kernel (pb_frames.hip): rows as for the wave path, V <= 1024 and a beam the LDS can hold.
 bool beam_wave_ok(const DeviceTree& t, const float* d_logp, int64_t row_stride, int32_t K);
 int launch_beam_wave(const DeviceTree& t, const float* d_logp, int64_t row_stride, const float* d_hyp,

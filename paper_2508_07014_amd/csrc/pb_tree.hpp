@@ -55,6 +55,7 @@ struct DeviceTree {
   int32_t vocab_size = 0;
   int32_t blank_id = -1;
   int32_t eos_id = -1;
+  float reach = 0.0f;  // bound of |p_root + root_score| over all states and tokens (largest |p_root| plus largest |root_score|)
 };
 
 // Per-row choice among several trees (a different context list per hypothesis or utterance): row i uses
