@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.environ.get("PB_LIBRARY") or os.path.join(PKG, "libpb.so")
 PROBE_LIB = os.path.join(PKG, "libpb_probe.so")  # measurement probes of bench.py, not part of the product library
 SOURCES = ["pb_narrow_1024.hip", "pb_narrow_any.hip", "pb_narrow_1280.hip", "pb_narrow_256.hip", "pb_narrow_512.hip",
-           "pb_wide.hip", "pb_rows.hip", "pb_frames.hip", "pb_kernels.hip", "pb_compile.cpp", "pb_api.hip"]
+           "pb_wide.hip", "pb_rows.hip", "pb_beam.hip", "pb_frames.hip", "pb_kernels.hip", "pb_compile.cpp", "pb_api.hip"]
 HEADERS = ["pb_tree.hpp", "pb_kernels.hpp", "pb_wave.hpp", "pb_chunk.hpp", "pb_narrow.hpp", os.path.join(ROOT, "include", "pb.h")]
 OBJDIR = os.path.join(PKG, "_build")
 

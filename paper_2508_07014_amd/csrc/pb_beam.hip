@@ -1,0 +1,671 @@
+// Beam step (gfx950, wave64): the K best of an utterance's K * V totals, in order, with the state gather by parent
+// (Alg. 1 Stage 3: hyps_expansion_score, prune_expanded, S[t]).
+//
+// One workgroup per utterance.  Neither the rows nor the survivors are sorted:
+//
+//  * The beams' rows are spread over up to 16 waves.  Every lane forms the totals of its tokens (base boosts in
+//    registers; tokens that an arc of the failure chain overrides are marked in LDS by the first wave of the beam,
+//    which evaluates the arcs one per lane) and keeps their maximum.
+//  * Bound.  The maxima of the lanes meet in 64 slots; the K-th largest of these, which is no larger than the K-th best
+//    total, is bounded from below (joint_bound).
+//  * Totals that reach the bound -- K and a few more -- go to a list in LDS, and their ranks come from counting: a
+//    thread per entry compares it with all others by (total descending, k * V + v ascending).
+//  * A list that overflows (more totals than it holds tie with the bound: an utterance of dead beams) is replaced by K
+//    rounds of arg-max over all totals (select_by_rounds).
+//
+// U x K, V: 32 x 4, 1024 7.8 -> 7.0 us against a kernel with a wave per beam and K rounds of arg-max in each; against the
+// workgroup-per-utterance row build (launch_beam) 16 x 8, 1025, a table of trees 35.9 -> 8.2, 32 x 8, 8192 81.9 -> 17.8,
+// 16 x 16, 50000 1130 -> 99.  With thousands of utterances of one or two beams (4096 x 2, V = 1024) the wave-per-beam
+// kernel was up to 6 % faster (14.5 us against 15.4), with four beams it was slower (34.4 against 27).
+//
+// Rows whose share of a wave fits its registers are read once (beam_regs_kernel); longer ones are streamed, with the
+// maximum of every chunk kept, and only the chunks that reach the bound are read again (beam_stream_kernel).
+#include <hip/hip_runtime.h>
+
+#include <climits>
+#include <cmath>
+#include <cstdint>
+
+#include "pb_chunk.hpp"
+#include "pb_kernels.hpp"
+#include "pb_wave.hpp"
+
+namespace pb {
+
+namespace {
+
+using namespace wv;
+
+constexpr int kBeamMax = 32;     // beams of an utterance at most
+constexpr int kBeamWaves = 16;   // waves of a workgroup at most
+constexpr unsigned kKeyNegInf = 0x007fffffu;  // ukey(-inf)
+
+struct BeamOut {
+  int32_t *tokens, *parents, *states;
+  float* scores;
+  __device__ __forceinline__ void put(int slot, int tok, int parent, int state, float score) const {
+    tokens[slot] = tok;
+    parents[slot] = parent;
+    states[slot] = state;
+    scores[slot] = score;
+  }
+};
+
+// (total, flat index) as one number that is larger for the better candidate.
+__device__ __forceinline__ u64 cand_key(float total, int flat) {
+  return (static_cast<u64>(ukey(__fadd_rn(total, 0.0f))) << 32) | static_cast<unsigned>(~flat);  // (-0 ties with +0)
+}
+
+struct Small {  // the fixed part of the workgroup's LDS
+  unsigned lane_best[64];
+  u64 best[kBeamWaves];
+  float hyp[kBeamMax];  // (the outputs may be the hypothesis scores' own buffer)
+  int count;
+};
+struct Shared {  // the list of survivors (the first part of the dynamic LDS) and the fixed part
+  u64* key;
+  int4* entry;  // bits of the total, token, beam, next state of an arc's candidate (-1 for a base candidate)
+  int cap;
+  Small* s;
+};
+// Entries of the list: 64 per wave of the workgroup, at least 128 (a multiple of what reaches the bound).  The list is
+// part of what limits the utterances a CU holds at once: with room for 1024 entries in every workgroup 8192 utterances
+// of one beam (V = 1024) took 20.5 us instead of 14.
+__host__ __device__ constexpr int list_cap(int waves) { return waves <= 2 ? 128 : 64 * waves; }
+__host__ __device__ constexpr size_t list_bytes(int waves) { return static_cast<size_t>(list_cap(waves)) * 24; }
+__device__ __forceinline__ Shared shared_at(char* lds, Small* s, int nwaves) {
+  const int cap = list_cap(nwaves);
+  int4* entry = reinterpret_cast<int4*>(lds);
+  return Shared{reinterpret_cast<u64*>(entry + cap), entry, cap, s};
+}
+
+// Adds a candidate to the list (called by the lanes that have one).
+__device__ __forceinline__ void push(const Shared& sh, float total, int k, int v, int V, int child) {
+  const int i = atomicAdd(&sh.s->count, 1);
+  if (i < sh.cap) {
+    sh.key[i] = cand_key(total, k * V + v);
+    sh.entry[i] = make_int4(__float_as_int(total), v, k, child);
+  }
+}
+
+// The bound.  The lanes' maxima are collected in 64 slots (as keys, zero before the barrier that precedes post_lane; the
+// lanes of a wave are rotated against those of the others, so that rows too short for all lanes still fill the slots).
+// Every slot that is not empty holds the total of a candidate of its own, so the K-th largest slot is no larger than the
+// K-th best total.  It is approached from below: the smallest of a few distances from the best slot within which at
+// least K slots lie, counted side by side, first in powers of two, then in eighths.  A binary search over the keys, the
+// other way, is a chain of ballots (16 of them took 1700 cycles of the 13000 of a step); it is left for slots that lie
+// further apart.
+__device__ __forceinline__ void post_lane(const Shared& sh, int lane, int wave, int nwaves, float m) {
+  atomicMax(&sh.s->lane_best[(lane + wave * (64 / nwaves)) & 63], ukey(m));
+}
+__device__ __forceinline__ float joint_bound(const Shared& sh, int lane, int K) {  // after the barrier that follows
+  const unsigned key = max(sh.s->lane_best[lane], kKeyNegInf);  // (keys below that of -inf are no numbers)
+  const unsigned top = wave_max_u(key);
+  const float v = ukey_val(key), M = ukey_val(top);
+  if (K == 1 || top == kKeyNegInf) return M;
+  auto reach = [&](float d) { return static_cast<int>(__popcll(__ballot(v >= M - d))) >= K; };
+  float d = 0.0f;
+#pragma unroll
+  for (int e = 7; e >= -3; --e) {
+    const float step = e >= 0 ? static_cast<float>(1 << e) : 1.0f / static_cast<float>(1 << -e);
+    d = reach(step) ? step : d;
+  }
+  if (d > 0.0f) {
+    const float e0 = d, e1 = 0.875f * d, e2 = 0.75f * d, e3 = 0.625f * d;
+    d = reach(e3) ? e3 : reach(e2) ? e2 : reach(e1) ? e1 : e0;
+    return M - d;
+  }
+  unsigned T = 0;
+#pragma unroll 1
+  for (int bit = 31; bit >= 12; --bit) {
+    const unsigned c = T | (1u << bit);
+    if (static_cast<int>(__popcll(__ballot(key >= c))) >= K) T = c;
+  }
+  return ukey_val(T < kKeyNegInf ? kKeyNegInf : T);
+}
+
+// What a beam's row needs besides its log-probs.
+struct Beam {
+  int k, s;
+  float hyp, p_root, eos_boost;
+};
+__device__ __forceinline__ Beam beam_at(const TreeView& t, int k, int s, float hyp) {
+  Beam b{k, s, hyp, t.p_root[s], 0.0f};
+  if (t.eos >= 0) b.eos_boost = t.eos_score[s];
+  return b;
+}
+
+// Walks the failure chain of the beam, deepest state first, one arc per lane, marking tokens as it goes (the marks are
+// clear before): `use(total, token, child)` for every arc that no deeper state shadows.  LDS operations of one wave
+// execute in order, and the tokens of one state are distinct, so marks need no barrier inside the wave.  The first arcs
+// of a state and of the one behind its failure link, which share a record, are requested together.
+template <typename Use>
+__device__ __forceinline__ void walk_mark(const TreeView& t, const Beam& b, const float* __restrict__ row, float alpha,
+                                          unsigned* marks, int lane, Use&& use) {
+  float p = 0.0f;
+  auto one = [&](const ArcRec& a, float xv, float back, int child) {
+    const int pos = token_pos<false>(t, a.token);
+    if (!tag_test(marks, pos)) {
+      tag_set(marks, pos);
+      use(__fadd_rn(b.hyp, __fadd_rn(xv, __fmul_rn(alpha, __fadd_rn(back, a.score)))), a.token, child);
+    }
+  };
+  auto rest = [&](const Rec& r, float back) {
+#pragma unroll 1
+    for (int j = 64 + lane; j < r.count; j += 64) {
+      const ArcRec a = t.arc[r.begin + j];
+      one(a, row[a.token], back, r.begin + j + 1);
+    }
+  };
+#pragma unroll 1
+  for (int x = b.s; x != 0;) {
+    const Rec2 r = load_rec2(t, x);
+    const bool two = r.a.fail != 0, has0 = lane < r.a.count, has1 = two && lane < r.b.count;
+    const ArcRec a0 = t.arc[r.a.begin + max(0, min(lane, r.a.count - 1))];
+    ArcRec a1 = a0;
+    if (two) a1 = t.arc[r.b.begin + max(0, min(lane, r.b.count - 1))];
+    const float x0 = row[has0 ? a0.token : 0], x1 = row[has1 ? a1.token : 0];
+    if (has0) one(a0, x0, p, r.a.begin + lane + 1);
+    rest(r.a, p);
+    if (!two) return;
+    p = __fadd_rn(p, r.a.backoff);
+    if (has1) one(a1, x1, p, r.b.begin + lane + 1);
+    rest(r.b, p);
+    p = __fadd_rn(p, r.b.backoff);
+    x = uniform_i(r.b.fail);
+  }
+}
+
+// The same walk again, clearing the marks the first one has left: an arc whose mark is gone already is shadowed.
+template <typename Use>
+__device__ __forceinline__ void walk_clear(const TreeView& t, const Beam& b, const float* __restrict__ row, float alpha,
+                                           unsigned* marks, int lane, Use&& use) {
+  float p = 0.0f;
+#pragma unroll 1
+  for (int x = b.s; x != 0;) {
+    const Rec r = load_rec(t, x);
+#pragma unroll 1
+    for (int j = lane; j < r.count; j += 64) {
+      const ArcRec a = t.arc[r.begin + j];
+      const int pos = token_pos<false>(t, a.token);
+      if (tag_test(marks, pos)) {
+        atomicAnd(&marks[pos >> 5], ~(1u << (pos & 31)));
+        use(__fadd_rn(b.hyp, __fadd_rn(row[a.token], __fmul_rn(alpha, __fadd_rn(p, a.score)))), a.token, r.begin + j + 1);
+      }
+    }
+    p = __fadd_rn(p, r.backoff);
+    x = uniform_i(r.fail);
+  }
+}
+
+// Totals of the lane's NS positions from `cb` on, from their log-probs and root scores, in place of the log-probs: the
+// blank boosts by 0, the EOS token by the value tabulated for the state; copies behind the end become NaN.
+template <int NS>
+__device__ __forceinline__ void piece_totals(const TreeView& t, const Beam& b, int cb, float alpha, int lane,
+                                             const float (&rw)[NS], float (&x)[NS]) {
+  const int blank = (t.blank >= 0 ? token_pos<false>(t, t.blank) : -1) - cb;
+  const int eos = (t.eos >= 0 ? token_pos<false>(t, t.eos) : -1) - cb;
+  float bo[NS];
+#pragma unroll
+  for (int j = 0; j < NS; ++j) bo[j] = __fmul_rn(alpha, __fadd_rn(b.p_root, rw[j]));
+  const bool has_blank = static_cast<unsigned>(blank) < 64u * NS, has_eos = static_cast<unsigned>(eos) < 64u * NS;
+  if (has_blank || has_eos || cb + 64 * NS > t.V) {  // uniform, and false for most pieces
+    const int ln = opaque(lane);
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      if (has_blank && slot_is(j, ln, blank)) bo[j] = __fmul_rn(alpha, 0.0f);
+      if (has_eos && slot_is(j, ln, eos)) bo[j] = __fmul_rn(alpha, b.eos_boost);
+      const int u = cb + 256 * (j >> 2) + 4 * ln;
+      if ((j & 3) < u - min(u, t.V - 4)) bo[j] = NAN;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NS; ++j) x[j] = __fadd_rn(b.hyp, __fadd_rn(x[j], bo[j]));
+}
+
+// NaN into the totals of marked positions.
+template <int NS>
+__device__ __forceinline__ void drop_marked(const unsigned* marks, int cb, int lane, float (&x)[NS]) {
+#pragma unroll
+  for (int i = 0; i < NS / 4; ++i) {
+    const int pos = cb + 256 * i + 4 * lane;
+    const unsigned bits = marks[pos >> 5] >> (pos & 31);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[4 * i + k] = (bits >> k) & 1u ? NAN : x[4 * i + k];
+  }
+}
+
+template <int NS>
+__device__ __forceinline__ float piece_max(const float (&x)[NS]) {  // (NaN entries are passed over; all NaN: -inf)
+  float g[NS / 4];
+  return max2(group_maxima(x, g), -INFINITY);
+}
+
+// Puts the survivors of a piece (pmax: the lane's largest total of it) on the list: a bit per slot, then a turn of a
+// loop per slot that has any.  (The push written out for every slot made 13 to 34 KB of code per kernel, and a step of
+// few utterances waits for its instructions, too; a loop over all slots took 0.5 us longer.)
+template <int NS>
+__device__ __forceinline__ void push_piece(const Shared& sh, const TreeView& t, int k, int cb, int lane, float bound,
+                                           float pmax, const float (&x)[NS]) {
+  if (__ballot(pmax >= bound) == 0) return;
+  float y[NS];  // (a copy: indexed by a number that is not a constant, it must not take the whole row out of registers)
+  unsigned hits = 0;
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    y[j] = x[j];
+    hits |= x[j] >= bound ? 1u << j : 0u;
+  }
+  for (u64 left = __ballot(hits != 0); left != 0; left = __ballot(hits != 0)) {
+    const int j = __builtin_ctz(__builtin_amdgcn_readlane(static_cast<int>(hits), first_lane(left)));
+    if ((hits >> j) & 1u) push(sh, y[j], k, pos_token<false>(t, cb + tok_of(j, lane)), t.V, -1);
+    hits &= ~(1u << j);
+  }
+}
+
+// The arcs of a wave's beams: every lane keeps its best and the value of its second best, so that a second walk is
+// needed only where a lane holds two survivors.
+struct ArcBest {
+  float best = -INFINITY, second = -INFINITY;
+  int k = 0, tok = 0, child = -1;  // (child < 0: none)
+  __device__ __forceinline__ void add(float total, int beam, int token, int c) {
+    const bool up = total > best || child < 0;
+    second = up ? (child < 0 ? second : best) : max2(second, total);
+    best = up ? total : best;
+    k = up ? beam : k;
+    tok = up ? token : tok;
+    child = up ? c : child;
+  }
+};
+
+// The list is complete (a barrier lies behind the last push): rank every entry by counting and write the first K.
+__device__ __forceinline__ void write_ranked(const Shared& sh, const TreeView& t, int u, int K, const int32_t* states_in,
+                                             const BeamOut& out) {
+  const int n = sh.s->count;
+#pragma unroll 1
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const u64 key = sh.key[i];
+    const int4 e = sh.entry[i];
+    const int v = e.y, k = e.z, child = e.w;
+    int next = child;
+    if (child < 0) next = v == t.blank || v == t.eos ? states_in[u * K + k] : t.root_next[v];  // (in flight below)
+    int rank = 0;
+#pragma unroll 4
+    for (int q = 0; q < n; ++q) rank += sh.key[q] > key ? 1 : 0;
+    if (rank < K) out.put(u * K + rank, v, k, next, __int_as_float(e.x));
+  }
+  for (int r = n + static_cast<int>(threadIdx.x); r < K; r += blockDim.x) out.put(u * K + r, -1, -1, -1, NAN);  // (NaN rows)
+}
+
+// K rounds of arg-max over all totals, each over what comes after the winner before it: any input, no list.  (Rows as
+// chunks with clamped loads; the marks of a beam have room for whole chunks.)
+__device__ void select_by_rounds(const Shared& sh, const TreeView& t, const float* __restrict__ logp, int64_t row_stride,
+                                 const int32_t* __restrict__ states_in, float alpha, int u,
+                                 int K, unsigned* marks, int words, int lane, int wave, int nwaves, const BeamOut& out) {
+  const int nch = (t.V + kChunk - 1) / kChunk;
+  u64 prev = ~0ull;
+#pragma unroll 1
+  for (int r = 0; r < K; ++r) {
+    u64 best = 0;
+    int child = -1;
+    float value = 0.0f;
+#pragma unroll 1
+    for (int k = wave; k < K; k += nwaves) {
+      const Beam b = beam_at(t, k, uniform_i(states_in[u * K + k]), uniform_f(sh.s->hyp[k]));
+      const float* row = logp + static_cast<size_t>(u * K + k) * row_stride;
+      unsigned* m = marks + static_cast<size_t>(k) * words;
+      tags_clear_n(m, words, lane);
+      walk_mark(t, b, row, alpha, m, lane, [&](float total, int tok, int next) {
+        const u64 key = total == total ? cand_key(total, k * t.V + tok) : 0;
+        if (key < prev && key > best) {
+          best = key;
+          child = next;
+          value = total;
+        }
+      });
+#pragma unroll 1
+      for (int ch = 0; ch < nch; ++ch) {
+        float x[16], rw[16];
+        load_row<false>(row, ch * kChunk, t.V, lane, x);
+        load_row<false>(t.root_score, ch * kChunk, t.V, lane, rw);
+        piece_totals(t, b, ch * kChunk, alpha, lane, rw, x);
+        drop_marked(m, ch * kChunk, lane, x);
+#pragma unroll 1
+        for (int j = 0; j < 16; ++j) {
+          const u64 key = x[j] == x[j] ? cand_key(x[j], k * t.V + pos_token<false>(t, ch * kChunk + tok_of(j, lane))) : 0;
+          if (key < prev && key > best) {
+            best = key;
+            child = -1;
+            value = x[j];
+          }
+        }
+      }
+    }
+    u64 wb = best;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const u64 o = __shfl_xor(wb, off);
+      wb = o > wb ? o : wb;
+    }
+    __syncthreads();  // (the round before has read its winners)
+    if (lane == 0) sh.s->best[wave] = wb;
+    __syncthreads();
+    u64 top = 0;
+#pragma unroll 1
+    for (int w = 0; w < nwaves; ++w) top = sh.s->best[w] > top ? sh.s->best[w] : top;
+    if (top == 0) {  // fewer than K totals are numbers
+      if (threadIdx.x == 0) out.put(u * K + r, -1, -1, -1, NAN);
+    } else if (best == top) {
+      const int flat = static_cast<int>(~static_cast<unsigned>(top));
+      const int k = flat / t.V, v = flat - k * t.V;
+      int next = child;
+      if (child < 0) next = v == t.blank || v == t.eos ? states_in[u * K + k] : t.root_next[v];
+      out.put(u * K + r, v, k, next, value);
+    }
+    prev = top == 0 ? 1 : top;  // (1: nothing comes after)
+  }
+}
+
+// The tree and the validity of an utterance (uniform over the workgroup); an utterance with an invalid state or tree
+// is marked as a whole.
+__device__ __forceinline__ bool utterance_ok(const TreePick& pick, DeviceTree& mine, const int32_t* states_in, int u, int K,
+                                             int lane, const BeamOut& out) {
+  const bool tree_ok = pick_tree(pick, u, mine);
+  const int s = states_in[u * K + min(lane, K - 1)];
+  const bool ok = tree_ok && __ballot(static_cast<unsigned>(s) >= static_cast<unsigned>(mine.num_states)) == 0;
+  const int slot = threadIdx.x;
+  if (!ok && slot < K) out.put(u * K + slot, -1, -1, -1, NAN);
+  return ok;
+}
+
+// ---- rows held in registers ---------------------------------------------------------------------------------------------
+// A beam has `parts` waves, each with 64 * NS positions of its row.  ONE: a single beam in a single wave.  A step is
+// latency-bound, so the requests go out in the order of the single greedy step: root scores, row, states and hypothesis
+// score before the first wait (with a table of trees the root scores follow the table), and an utterance with an invalid
+// state is decoded from the root and marked at the end, so that no early exit separates the wave start from the requests.
+template <bool FOREST, int NS, bool ONE>
+__global__ void __launch_bounds__(64 * kBeamWaves) beam_regs_kernel(
+    const float* __restrict__ logp, int64_t row_stride, const float* hyp,
+    const int32_t* __restrict__ states_in, const float* __restrict__ root_score, float alpha, int K, int parts, int words,
+    int32_t* __restrict__ tokens, int32_t* __restrict__ parents, int32_t* __restrict__ states_out,
+    float* scores_out, DeviceTree dt, TreePick pick) {
+  constexpr int PS = NS < 16 ? NS : 16, NP = NS / PS;  // positions per lane of a piece, pieces
+  extern __shared__ __align__(16) char lds[];
+  __shared__ Small small;
+  const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+  const int u = blockIdx.x, k = wave / parts, part = wave - k * parts, P0 = part * 64 * NS, V = dt.vocab_size;
+  const float* row = logp + static_cast<size_t>(u * K + k) * row_stride;
+  float x[NP][PS], rw[PS];
+  if constexpr (!FOREST) load_row<false>(root_score, P0, V, lane, rw);
+#pragma unroll
+  for (int c = 0; c < NP; ++c) load_row<false>(row, P0 + c * 64 * PS, V, lane, x[c]);
+  const int sk = states_in[u * K + min(lane, K - 1)];  // every wave sees all K states
+  const float hyp_in = hyp[u * K + k];
+  __builtin_amdgcn_sched_barrier(0);  // (all of the above is in flight before the first wait)
+  const Shared sh = shared_at(lds, &small, nwaves);
+  unsigned* marks = reinterpret_cast<unsigned*>(lds + list_bytes(nwaves));
+  const BeamOut out{tokens, parents, states_out, scores_out};
+  const int slot = threadIdx.x;
+  DeviceTree mine = dt;
+  if constexpr (FOREST) {
+    if (!pick_tree(pick, u, mine)) {  // (uniform over the workgroup)
+      if (slot < K) out.put(u * K + slot, -1, -1, -1, NAN);
+      return;
+    }
+  }
+  const TreeView t = make_view(mine);
+  if constexpr (FOREST) load_row<false>(t.root_score, P0, V, lane, rw);
+  if (slot == 0) sh.s->count = 0;
+  if (slot < 64) sh.s->lane_best[slot] = 0;
+  if (slot < K) sh.s->hyp[slot] = hyp[u * K + slot];
+  unsigned* m = marks + k * words;
+  const bool bad = __ballot(!valid_state(t, sk)) != 0;
+  const Beam b = beam_at(t, k, bad ? 0 : __builtin_amdgcn_readlane(sk, k), uniform_f(hyp_in));
+  ArcBest arcs;
+  if (part == 0 && b.s != 0) {
+    tags_clear_n(m, words, lane);
+    walk_mark(t, b, row, alpha, m, lane,
+                          [&](float total, int tok, int child) { arcs.add(total, k, tok, child); });
+  }
+#pragma unroll
+  for (int c = 0; c < NP; ++c) {
+    if (c > 0) load_row<false>(t.root_score, P0 + c * 64 * PS, V, lane, rw);
+    piece_totals(t, b, P0 + c * 64 * PS, alpha, lane, rw, x[c]);
+  }
+  __syncthreads();  // the marks are set
+  float top = max2(arcs.best, -INFINITY), pmax[NP];
+#pragma unroll
+  for (int c = 0; c < NP; ++c) {
+    if (b.s != 0) drop_marked(m, P0 + c * 64 * PS, lane, x[c]);
+    pmax[c] = piece_max(x[c]);
+    top = max2(top, pmax[c]);
+  }
+  if constexpr (ONE) {
+    // the best total itself, whose lowest token needs no list
+    const float bound = ukey_val(wave_max_u(ukey(top)));
+    if (__ballot(arcs.second >= bound) == 0) {
+      int flat = arcs.child >= 0 && arcs.best == bound ? arcs.tok : INT_MAX, child = arcs.child;
+#pragma unroll
+      for (int c = NP - 1; c >= 0; --c)
+#pragma unroll
+        for (int j = PS - 1; j >= 0; --j) {
+          const int v = pos_token<false>(t, P0 + c * 64 * PS + tok_of(j, lane));
+          if (x[c][j] == bound && v < flat) {
+            flat = v;
+            child = -1;
+          }
+        }
+      const int v = wave_min_nn(flat);
+      if (bad || v == INT_MAX) {
+        if (lane == 0) out.put(u, -1, -1, -1, NAN);  // (no number in the row, for one)
+      } else if (flat == v) {
+        out.put(u, v, 0, child >= 0 ? child : v == t.blank || v == t.eos ? b.s : t.root_next[v], bound);
+      }
+      return;
+    }
+  }
+  post_lane(sh, lane, wave, nwaves, top);
+  __syncthreads();
+  const float bound = joint_bound(sh, lane, K);
+  if (__ballot(top >= bound) != 0) {
+#pragma unroll
+    for (int c = 0; c < NP; ++c) push_piece(sh, t, k, P0 + c * 64 * PS, lane, bound, pmax[c], x[c]);
+    if (part == 0 && b.s != 0 && __ballot(arcs.second >= bound) != 0) {
+      walk_clear(t, b, row, alpha, m, lane, [&](float total, int tok, int child) {
+        if (total >= bound) push(sh, total, k, tok, t.V, child);
+      });
+    } else if (arcs.child >= 0 && arcs.best >= bound) {
+      push(sh, arcs.best, arcs.k, arcs.tok, t.V, arcs.child);
+    }
+  }
+  __syncthreads();
+  if (bad) {
+    if (slot < K) out.put(u * K + slot, -1, -1, -1, NAN);
+  } else if (sh.s->count > sh.cap)
+    select_by_rounds(sh, t, logp, row_stride, states_in, alpha, u, K, marks, words, lane, wave, nwaves, out);
+  else
+    write_ranked(sh, t, u, K, states_in, out);
+}
+
+// ---- rows streamed -------------------------------------------------------------------------------------------------------
+// Beam k has max(1, nwaves / K) waves, which take its chunks in turn; with more beams than waves a wave has several.
+__global__ void __launch_bounds__(64 * kBeamWaves) beam_stream_kernel(
+    const float* __restrict__ logp, int64_t row_stride, const float* hyp,
+    const int32_t* __restrict__ states_in, float alpha, int K, int32_t* __restrict__ tokens,
+    int32_t* __restrict__ parents, int32_t* __restrict__ states_out, float* scores_out, DeviceTree dt,
+    TreePick pick) {
+  extern __shared__ __align__(16) char lds[];
+  __shared__ Small small;
+  const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+  const Shared sh = shared_at(lds, &small, nwaves);
+  unsigned* marks = reinterpret_cast<unsigned*>(lds + list_bytes(nwaves));
+  const int u = blockIdx.x;
+  const BeamOut out{tokens, parents, states_out, scores_out};
+  DeviceTree mine = dt;
+  if (!utterance_ok(pick, mine, states_in, u, K, lane, out)) return;
+  const TreeView t = make_view(mine);
+  const int nch = (t.V + kChunk - 1) / kChunk, words = nch * kTagWords, last_ch = nch - 1;
+  float* cmax = reinterpret_cast<float*>(marks + static_cast<size_t>(K) * words);  // [K][nch]
+  const int parts = K < nwaves ? nwaves / K : 1, k0 = wave / parts, part = wave - k0 * parts;
+  auto beam = [&](int k) { return beam_at(t, k, uniform_i(states_in[u * K + k]), uniform_f(hyp[u * K + k])); };
+  auto row_of = [&](int k) { return logp + static_cast<size_t>(u * K + k) * row_stride; };
+  const int slot = threadIdx.x;
+  if (slot == 0) sh.s->count = 0;
+  if (slot < 64) sh.s->lane_best[slot] = 0;
+  if (slot < K) sh.s->hyp[slot] = hyp[u * K + slot];
+  ArcBest arcs;
+  if (part == 0) {
+    for (int k = k0; k < K; k += nwaves) {
+      const Beam b = beam(k);
+      unsigned* m = marks + static_cast<size_t>(k) * words;
+      tags_clear_n(m, words, lane);
+      walk_mark(t, b, row_of(k), alpha, m, lane,
+                            [&](float total, int tok, int child) { arcs.add(total, k, tok, child); });
+    }
+  }
+  __syncthreads();  // the marks are set
+  float top = max2(arcs.best, -INFINITY);
+  for (int k = k0; k < K; k += nwaves) {
+    const Beam b = beam(k);
+    const float* row = row_of(k);
+    const unsigned* m = marks + static_cast<size_t>(k) * words;
+    float x[2][16], rw[2][16];
+    load_row<false>(row, min(part, last_ch) * kChunk, t.V, lane, x[0]);
+    load_row<false>(t.root_score, min(part, last_ch) * kChunk, t.V, lane, rw[0]);
+    for (int ch0 = part; ch0 < nch; ch0 += 2 * parts) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int ch = ch0 + q * parts, nx = min(ch + parts, last_ch) * kChunk;
+        load_row<false>(row, nx, t.V, lane, x[(q + 1) % 2]);  // (without a condition: behind the end the last one again)
+        load_row<false>(t.root_score, nx, t.V, lane, rw[(q + 1) % 2]);
+        if (ch < nch) {
+          piece_totals(t, b, ch * kChunk, alpha, lane, rw[q], x[q]);
+          if (b.s != 0) drop_marked(m, ch * kChunk, lane, x[q]);
+          const float cm = piece_max(x[q]);
+          top = max2(top, cm);
+          const float wm = ukey_val(wave_max_u(ukey(cm)));
+          if (lane == 0) cmax[k * nch + ch] = wm;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  post_lane(sh, lane, wave, nwaves, top);
+  __syncthreads();
+  const float bound = joint_bound(sh, lane, K);
+  for (int k = k0; k < K; k += nwaves) {
+    const Beam b = beam(k);
+    const unsigned* m = marks + static_cast<size_t>(k) * words;
+#pragma unroll 1
+    for (int ch = part; ch < nch; ch += parts) {
+      if (uniform_f(cmax[k * nch + ch]) >= bound) {
+        float x[16], rw[16];
+        load_row<false>(row_of(k), ch * kChunk, t.V, lane, x);
+        load_row<false>(t.root_score, ch * kChunk, t.V, lane, rw);
+        piece_totals(t, b, ch * kChunk, alpha, lane, rw, x);
+        if (b.s != 0) drop_marked(m, ch * kChunk, lane, x);
+        push_piece(sh, t, k, ch * kChunk, lane, bound, piece_max(x), x);
+      }
+    }
+  }
+  __syncthreads();  // (the second walk clears marks that the other waves of the beam have read until here)
+  if (part == 0 && __ballot(arcs.second >= bound) != 0) {
+    for (int k = k0; k < K; k += nwaves)
+      walk_clear(t, beam(k), row_of(k), alpha, marks + static_cast<size_t>(k) * words, lane,
+                             [&](float total, int tok, int child) {
+                               if (total >= bound) push(sh, total, k, tok, t.V, child);
+                             });
+  } else if (arcs.child >= 0 && arcs.best >= bound) {
+    push(sh, arcs.best, arcs.k, arcs.tok, t.V, arcs.child);
+  }
+  __syncthreads();
+  if (sh.s->count > sh.cap)
+    select_by_rounds(sh, t, logp, row_stride, states_in, alpha, u, K, marks, words, lane, wave, nwaves, out);
+  else
+    write_ranked(sh, t, u, K, states_in, out);
+}
+
+int g_beam_max_lds = 48 * 1024;  // dynamic LDS the device allows these kernels, set once
+
+struct BeamPlan {
+  int ns, parts, waves;  // ns == 0: streamed
+  int words;             // marks of a beam
+  size_t lds;
+};
+// Positions per lane: the fewest that spread a beam's row over as many waves as the workgroup takes -- a step of few
+// utterances is latency-bound, so it wants little to do in each wave -- but no more than kBeamFill waves over all
+// utterances: past that a row cut finer only brings more barriers, bounds and lists.  (V = 1024, K = 4: U = 128 7.1 us
+// with 8 positions, 7.7 with 16; U = 1024 9.8 us with 16, 12.5 with 8, 21.5 with 4.  V = 4096, K = 4, U = 512: 11.8 us
+// with 32, 17.3 with 16.)  A single beam stays in one wave where 16 positions hold it.  Rows that do not fit at 64 positions are streamed.
+constexpr int kBeamFill = 4096;
+BeamPlan plan_beam(int V, int K, int64_t U) {
+  const int nch = (V + kChunk - 1) / kChunk;
+  BeamPlan p{0, 0, kBeamWaves, nch * kTagWords, 0};
+  for (const int ns : {4, 8, 16, 32, 64}) {
+    const int parts = (V + 64 * ns - 1) / (64 * ns);
+    if (K * parts > kBeamWaves || (ns == 64 && p.ns == 32)) continue;
+    const int words = parts * 2 * ns > nch * kTagWords ? parts * 2 * ns : nch * kTagWords;
+    p = BeamPlan{ns, parts, K * parts, words, 0};
+    if (parts == 1 || (U * K * parts <= kBeamFill && (K > 1 || ns >= 16))) break;
+  }
+  // (streamed: the maxima of a beam's chunks behind the marks)
+  p.lds = list_bytes(p.waves) + static_cast<size_t>(K) * (p.words + (p.ns ? 0 : nch)) * sizeof(unsigned);
+  return p;
+}
+
+}  // namespace
+
+bool beam_wave_ok(const DeviceTree& t, int32_t U, int32_t K) {
+  return t.p_root != nullptr && t.vocab_size >= 4 && plan_beam(t.vocab_size, K, U).lds <= static_cast<size_t>(g_beam_max_lds);
+}
+
+int launch_beam_wave(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride, const float* d_hyp,
+                     const int32_t* d_states_in, float alpha, int32_t U, int32_t K, int32_t* d_tokens,
+                     int32_t* d_parents, int32_t* d_states_out, float* d_scores_out, hipStream_t stream) {
+  const int V = t.vocab_size;
+  const BeamPlan p = plan_beam(V, K, U);
+  const dim3 grid(static_cast<unsigned>(U)), block(static_cast<unsigned>(64 * p.waves));
+  const bool forest = pick.table != nullptr;
+#define PB_REGS(FOREST, NS, ONE)                                                                                     \
+  hipLaunchKernelGGL((beam_regs_kernel<FOREST, NS, ONE>), grid, block, p.lds, stream, d_logp, row_stride, d_hyp,     \
+                     d_states_in, t.root_score, alpha, K, p.parts, p.words, d_tokens, d_parents, d_states_out,       \
+                     d_scores_out, t, pick)
+#define PB_SHAPE(NS, ONE)     \
+  if (forest) {               \
+    PB_REGS(true, NS, ONE);   \
+  } else {                    \
+    PB_REGS(false, NS, ONE);  \
+  }
+  switch (p.ns + (p.waves == 1 ? 1 : 0)) {  // (one wave: K == 1; a row of up to 1024 tokens then, see plan_beam)
+    case 5: PB_SHAPE(4, true) break;
+    case 9: PB_SHAPE(8, true) break;
+    case 17: PB_SHAPE(16, true) break;
+    case 4: PB_SHAPE(4, false) break;
+    case 8: PB_SHAPE(8, false) break;
+    case 16: PB_SHAPE(16, false) break;
+    case 32: case 33: PB_SHAPE(32, false) break;
+    case 64: case 65: PB_SHAPE(64, false) break;
+    default:
+      hipLaunchKernelGGL(beam_stream_kernel, grid, block, p.lds, stream, d_logp, row_stride, d_hyp, d_states_in, alpha, K,
+                         d_tokens, d_parents, d_states_out, d_scores_out, t, pick);
+  }
+#undef PB_SHAPE
+#undef PB_REGS
+  return hipGetLastError() == hipSuccess ? PB_OK : PB_EHIP;
+}
+
+int prepare_beam_kernels(int max_lds_bytes) {
+  constexpr int kStatic = sizeof(Small) + 1024;
+  const int bytes = max_lds_bytes - kStatic;
+  int limit = 64 * 1024 - kStatic;
+  if (bytes > limit) {
+    const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(beam_stream_kernel), attr, bytes) == hipSuccess)
+      limit = bytes;
+    else
+      (void)hipGetLastError();
+  }
+  g_beam_max_lds = limit;
+  return PB_OK;
+}
+
+}  // namespace pb

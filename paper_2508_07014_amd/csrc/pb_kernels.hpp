@@ -112,9 +112,11 @@ int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d
                        int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T,
                        int32_t B, int sel, int32_t* d_tokens, int32_t* d_states, float* d_scores, hipStream_t stream);
 
-// Wave-per-beam kernel (pb_frames.hip): rows as for the wave path, V <= 1024 and a beam the LDS can hold.
-bool beam_wave_ok(const DeviceTree& t, const float* d_logp, int64_t row_stride, int32_t K);
-int launch_beam_wave(const DeviceTree& t, const float* d_logp, int64_t row_stride, const float* d_hyp,
+// Beam step on waves (pb_beam.hip): rows of any stride and alignment, vocabularies of 4 tokens up to what the token
+// marks of the beams leave room for in LDS; launch_beam takes the rest.
+int prepare_beam_kernels(int max_lds_bytes);
+bool beam_wave_ok(const DeviceTree& t, int32_t U, int32_t K);
+int launch_beam_wave(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride, const float* d_hyp,
                      const int32_t* d_states_in, float alpha, int32_t U, int32_t K, int32_t* d_tokens,
                      int32_t* d_parents, int32_t* d_states_out, float* d_scores_out, hipStream_t stream);
 
