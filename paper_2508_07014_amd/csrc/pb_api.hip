@@ -245,7 +245,7 @@ int fuse_frames_any(const pb_tree* tree, const float* d_logp, int64_t frame_stri
   if (!d_logp || !d_states0 || !d_tokens || !d_states || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size || frame_stride < 0) return PB_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::frames_rows_ok(tree->dev, d_states0, d_last0, T, B, d_tokens, d_states, d_scores))
+  if (pb::frames_rows_ok(tree->dev, d_states0, d_last0, T, B, mode, d_tokens, d_states, d_scores))
     return pb::launch_frames_rows(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
                                   d_tokens, d_states, d_scores, stream);
   // (the segment decoder keeps a flag in bit 30 of the state words it stores: larger trees take the plain kernel)
@@ -435,7 +435,7 @@ int pb_fuse_frames_forest(const pb_forest* forest, const float* d_logp, int64_t 
   if (row_stride < forest->proto.vocab_size || frame_stride < 0) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::frames_rows_ok(forest->proto, d_states0, d_last0, T, B, d_tokens, d_states, d_scores))
+  if (pb::frames_rows_ok(forest->proto, d_states0, d_last0, T, B, mode, d_tokens, d_states, d_scores))
     return pb::launch_frames_rows(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
                                   d_tokens, d_states, d_scores, stream);
   if (pb::wave_path_ok(forest->proto) && forest->proto.num_states < (1 << 30))

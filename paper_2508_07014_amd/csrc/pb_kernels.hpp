@@ -106,7 +106,7 @@ int launch_frames_wave(const DeviceTree& t, const TreePick& pick, const float* d
 // outputs hold the rows' winners in between, so they must not overlap the start states, the previous labels or each
 // other -- and the launch.
 int prepare_rows_kernels(int max_lds_bytes);
-bool frames_rows_ok(const DeviceTree& t, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B,
+bool frames_rows_ok(const DeviceTree& t, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B, int sel,
                     const int32_t* d_tokens, const int32_t* d_states, const float* d_scores);
 int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,
                        int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T,

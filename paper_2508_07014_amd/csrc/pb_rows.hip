@@ -16,8 +16,9 @@
 //    own, as they are for most exact ties: equal operands give equal values in every state, and the lower token wins.
 //  * Pass 2 (walk_kernel; one workgroup per hypothesis) runs the automaton on the winners: a wave per segment, from
 //    the state the last winner before it leads to.  A frame gathers a handful of log-probs (winner, blank, the arcs
-//    of the chain) instead of a row, and those of eight frames are requested at once for the states the winners lead
-//    to.  The outcomes sit in LDS; segments that started from a wrong guess are decoded again until they meet what
+//    of the chain) instead of a row, and those of sixteen frames are requested at once for the states the winners lead
+//    to.  Runs of frames whose outcomes fit together are taken over whole, the others -- inside a spoken phrase,
+//    mostly -- are decided one after the other.  The outcomes sit in LDS; segments that started from a wrong guess are decoded again until they meet what
 //    is there (equal state and label: equal future), in rounds between barriers.
 //
 // Between the passes the winners travel in the call's own outputs: tokens holds w (~w for a marked row), states the
@@ -233,7 +234,7 @@ __global__ void __launch_bounds__(1024) rows_wide_kernel(DeviceTree dt, TreePick
 
 // ---- pass 2 --------------------------------------------------------------------------------------------------------------
 constexpr int kWalkBlock = 1024;  // frames whose winners and outcomes sit in LDS at a time
-constexpr int kWalkGroup = 8;     // frames whose arcs and log-probs are requested together
+constexpr int kWalkGroup = 16;    // frames whose arcs and log-probs are requested together
 constexpr int kWalkLook = 64;     // frames a segment's guess may look back over (one per lane)
 
 struct WalkLds {  // per block of frames; `tags` is this wave's
@@ -272,9 +273,14 @@ struct Walker {
 
   // Decodes frames [f0, f1) of the block from (s, last).  COMPARE: stops at the frame that meets the stored outcome
   // and returns true; false when the end was reached.
+  //   Frames are first decided side by side, a lane holding one, from the states the winners before them lead to; then
+  //   runs of frames whose outcome is the state the next one was decided from are taken over whole, and what lies
+  //   between them -- mostly inside a spoken phrase -- is decided frame by frame.  (Frame by frame throughout took
+  //   about 1 us a frame, a chain of dependent reductions.)
   template <bool COMPARE>
   __device__ __forceinline__ bool run(int f0, int f1, int s, int last) const {
     Cursor cur = cursor_at(t, s);
+#pragma unroll 1
     for (int fb = f0; fb < f1; fb += 64) {
       const int n = min(64, f1 - fb);
       // ---- one frame per lane: its winner and what the winner's value and target need --------------------------
@@ -287,70 +293,63 @@ struct Walker {
       const float xe = t.eos >= 0 ? lrow[t.eos] : 0.0f;
       const float rsw = t.root_score[w];
       const v8i rr = reinterpret_cast<const v8i*>(root_rec)[w];
-      // where each frame is expected to start: in the state the last moving frame before it leads to
-      bool moves = v0 != t.blank;
-      const int pv = __shfl_up(v0, 1), pw = __shfl_up(w, 1);
-      if (SEL == 2 && lane > 0) moves = moves && v0 != pv && v0 != pw;
-      const u64 before = __ballot(moves) & ((1ull << lane) - 1);
-      const int src = before ? 63 - __builtin_clzll(before) : 0;
-      int gs = __shfl(rr.s0, src), gbegin = __shfl(rr.s1, src), gcount = __shfl(rr.s2, src);
-      if (!before) {
-        gs = cur.s;
-        gbegin = cur.rec.begin;
-        gcount = cur.rec.count;
-      }
       int out_st = 0, out_tok = 0;
       float out_sc = 0.0f;
+      Ahead g{};
+      if constexpr (!COMPARE) g = decide_ahead(cur, last, fb, n, wm, w, v0, xw, x0, xe, rsw, rr);
       int met = -1;
-      for (int l0 = 0; l0 < n && met < 0; l0 += kWalkGroup) {
-        ArcRec arcs[kWalkGroup];
-        float xa[kWalkGroup];
-#pragma unroll
-        for (int i = 0; i < kWalkGroup; ++i) {
-          const int l = min(l0 + i, n - 1);
-          const int gb = __builtin_amdgcn_readlane(gbegin, l), gc = __builtin_amdgcn_readlane(gcount, l);
-          arcs[i] = t.arc[gb + max(0, min(lane, gc - 1))];
+#pragma unroll 1
+      for (int l = 0; l < n && met < 0;) {
+        if (!COMPARE && ((g.settled >> l) & 1) && cur.s == __builtin_amdgcn_readlane(g.s, l) &&
+            (SEL != 2 || last == __builtin_amdgcn_readlane(g.label, l))) {
+          const int e = min(n - 1, l + __builtin_ctzll(~(g.linked >> l)));  // (linked has no bit for the last lane)
+          const bool in = lane >= l && lane <= e;
+          out_st = in ? g.next : out_st;
+          out_tok = in ? g.tok : out_tok;
+          out_sc = in ? g.val : out_sc;
+          const int kind = __builtin_amdgcn_readlane(g.kind, e);
+          if (kind == kByArc) {
+            cur = cursor_at(t, __builtin_amdgcn_readlane(g.next, e));
+          } else if (kind == kByRoot) {
+            cur = cursor_from_root_rec(lane_rec(rr, e));
+          } else {
+            cur = Cursor{__builtin_amdgcn_readlane(g.s, e), Rec{__builtin_amdgcn_readlane(g.begin, e),
+                         __builtin_amdgcn_readlane(g.count, e), 0, 0.0f}, Rec{0, 0, 0, 0.0f}, lane_f(g.p_root, e),
+                         lane_f(g.eos_boost, e)};
+          }
+          last = __builtin_amdgcn_readlane(g.tok, e);
+          l = e + 1;
+          continue;
         }
-#pragma unroll
-        for (int i = 0; i < kWalkGroup; ++i) {
-          const int l = min(l0 + i, n - 1);
-          const int gc = __builtin_amdgcn_readlane(gcount, l);
-          const float* row = hyp + static_cast<int64_t>(fb + l) * frame_stride;
-          xa[i] = row[lane < gc ? arcs[i].token : 0];
-        }
-#pragma unroll
-        for (int i = 0; i < kWalkGroup; ++i) {
-          const int l = l0 + i;
-          if (l < n && met < 0) {
-            const float* row = hyp + static_cast<int64_t>(fb + l) * frame_stride;
-            const int fw = __builtin_amdgcn_readlane(w, l), fv0 = __builtin_amdgcn_readlane(v0, l);
-            const float fx0 = lane_f(x0, l);
-            FrameOut o{fx0, fv0, false, 0};
-            if (SEL == 0 || (fv0 != t.blank && (SEL != 2 || fv0 != last))) {
-              const bool ahead = cur.s == __builtin_amdgcn_readlane(gs, l);
-              const bool marked = __builtin_amdgcn_readlane(wm, l) < 0;
-              const float M = __fadd_rn(lane_f(xw, l), __fmul_rn(alpha, __fadd_rn(cur.p_root, lane_f(rsw, l))));
-              o = decide(cur, row, M, fw, marked, ahead, arcs[i], xa[i], fx0, lane_f(xe, l), last);
-              if (o.arc) {
-                cur = cursor_at(t, o.child);
-              } else if (o.tok == fw && fw != t.blank && fw != t.eos) {
-                cur = cursor_from_root_rec(lane_rec(rr, l));
-              } else if (o.tok != t.blank && o.tok != t.eos) {
-                const v8i r = t.root_rec[o.tok];
-                cur = cursor_from_root_rec(r);
-              }
-            }
-            if (lane == l) {
-              out_st = cur.s;
-              out_tok = o.tok;
-              out_sc = o.val;
-            }
-            last = o.tok;
-            if (COMPARE && __builtin_amdgcn_readlane(old_st, l) == cur.s &&
-                (SEL != 2 || __builtin_amdgcn_readlane(old_tok, l) == o.tok))
-              met = l;  // (this frame is written too, its score may differ; the rest stands)
+        const float* row = hyp + static_cast<int64_t>(fb + l) * frame_stride;
+        const int fw = __builtin_amdgcn_readlane(w, l), fv0 = __builtin_amdgcn_readlane(v0, l);
+        const float fx0 = lane_f(x0, l);
+        FrameOut o{fx0, fv0, false, 0};
+        if (SEL == 0 || (fv0 != t.blank && (SEL != 2 || fv0 != last))) {
+          const bool marked = __builtin_amdgcn_readlane(wm, l) < 0;
+          const float M = __fadd_rn(lane_f(xw, l), __fmul_rn(alpha, __fadd_rn(cur.p_root, lane_f(rsw, l))));
+          Cursor child;
+          bool child_known;
+          o = decide(cur, row, M, fw, marked, fx0, lane_f(xe, l), last, child, child_known);
+          if (o.arc) {
+            cur = child_known ? child : cursor_at(t, o.child);
+          } else if (o.tok == fw && fw != t.blank && fw != t.eos) {
+            cur = cursor_from_root_rec(lane_rec(rr, l));
+          } else if (o.tok != t.blank && o.tok != t.eos) {
+            const v8i r = t.root_rec[o.tok];
+            cur = cursor_from_root_rec(r);
           }
         }
+        if (lane == l) {
+          out_st = cur.s;
+          out_tok = o.tok;
+          out_sc = o.val;
+        }
+        last = o.tok;
+        if (COMPARE && __builtin_amdgcn_readlane(old_st, l) == cur.s &&
+            (SEL != 2 || __builtin_amdgcn_readlane(old_tok, l) == o.tok))
+          met = l;  // (this frame is written too, its score may differ; the rest stands)
+        ++l;
       }
       if (lane < (met >= 0 ? met + 1 : n)) {
         L.st[fb + lane] = out_st;
@@ -362,8 +361,154 @@ struct Walker {
     return false;
   }
 
-  const RootRec* root_rec;
+  // Outcomes of a batch of frames, one per lane, each decided from the state the winners before it lead to.
+  enum Kind { kKeep = 0, kByArc = 1, kByRoot = 2 };
+  struct Ahead {
+    u64 settled, linked;            // decided; and: the next frame is decided, from this frame's outcome
+    int s, begin, count;            // the state it was decided from
+    float p_root, eos_boost;
+    int label;                      // ... and the label before it (CTC rule)
+    int tok, next, kind;
+    float val;
+  };
+  __device__ __forceinline__ Ahead decide_ahead(const Cursor& cur, int last, int fb, int n, int wm, int w, int v0, float xw,
+                                                float x0, float xe, float rsw, const v8i& rr) const {
+    Ahead g;
+    // ---- where each frame starts: in the state the last moving frame before it leads to, else in the batch's own ----
+    bool moves = v0 != t.blank;
+    const int pv = __shfl_up(v0, 1), pw = __shfl_up(w, 1);
+    if (SEL == 2) moves = moves && (lane == 0 ? v0 != last : v0 != pv && v0 != pw);
+    const u64 before = __ballot(moves) & ((1ull << lane) - 1);
+    const int src = before ? 63 - __builtin_clzll(before) : 0;
+    g.s = __shfl(rr.s0, src);
+    g.begin = __shfl(rr.s1, src);
+    g.count = __shfl(rr.s2, src);
+    g.p_root = __int_as_float(__shfl(rr.s5, src));
+    g.eos_boost = __int_as_float(__shfl(rr.s6, src));
+    bool settled = wm >= 0 && lane < n;
+    if (!before) {
+      g.s = cur.s;
+      g.begin = cur.rec.begin;
+      g.count = cur.rec.count;
+      g.p_root = cur.p_root;
+      g.eos_boost = cur.eos_boost;
+      settled = settled && (cur.s == 0 || cur.rec.fail == 0);  // (one level of arcs: all that is looked at here)
+    }
+    if (g.s == 0) g.count = 0;  // (the root's arcs are the root row)
+    // ---- the best arc of every frame's state: the arcs of a frame on the lanes, kWalkGroup frames at a time -----------
+    float am = -INFINITY;
+    int at = INT_MAX, ac = -1;
+    bool overridden = false;
+    const u64 with_arcs = __ballot(g.count > 0 && lane < n);
+#pragma unroll 1
+    for (int l0 = 0; l0 < n; l0 += kWalkGroup) {
+      if (((with_arcs >> l0) & ((1ull << kWalkGroup) - 1)) == 0) continue;
+      ArcRec arcs[kWalkGroup];
+      float xa[kWalkGroup];
+#pragma unroll
+      for (int i = 0; i < kWalkGroup; ++i) {
+        const int gb = __builtin_amdgcn_readlane(g.begin, l0 + i), gc = __builtin_amdgcn_readlane(g.count, l0 + i);
+        arcs[i] = t.arc[gb + max(0, min(lane, gc - 1))];
+      }
+#pragma unroll
+      for (int i = 0; i < kWalkGroup; ++i) {
+        const int gc = __builtin_amdgcn_readlane(g.count, l0 + i);
+        const float* row = hyp + static_cast<int64_t>(fb + min(l0 + i, n - 1)) * frame_stride;
+        xa[i] = row[lane < gc ? arcs[i].token : 0];
+      }
+#pragma unroll
+      for (int i = 0; i < kWalkGroup; ++i) {
+        const int l = l0 + i, gb = __builtin_amdgcn_readlane(g.begin, l), gc = __builtin_amdgcn_readlane(g.count, l);
+        const int fw = __builtin_amdgcn_readlane(w, l);
+        float best = lane < gc ? __fadd_rn(xa[i], __fmul_rn(alpha, __fadd_rn(0.0f, arcs[i].score))) : -INFINITY;
+        int tok = lane < gc ? arcs[i].token : INT_MAX, child = gb + lane + 1;
+        bool hit = tok == fw;
+        if (gc > 64) {  // uniform
+          const float* row = hyp + static_cast<int64_t>(fb + min(l, n - 1)) * frame_stride;
+#pragma unroll 1
+          for (int j = 64 + lane; j < gc; j += 64) {
+            const ArcRec a = t.arc[gb + j];
+            hit = hit || a.token == fw;
+            const float fa = __fadd_rn(row[a.token], __fmul_rn(alpha, __fadd_rn(0.0f, a.score)));
+            if (fa > best) {  // (tokens ascend with j: an equal one stays behind)
+              best = fa;
+              tok = a.token;
+              child = gb + j + 1;
+            }
+          }
+        }
+        const float top = ukey_val(wave_max_u(ukey(best)));
+        u64 who = __ballot(best == top && tok != INT_MAX);
+        if (gc > 64 && (who & (who - 1)) != 0) {  // equal ones in two lanes: the lower token need not be in the lower lane
+          const int low = wave_min_nn(best == top ? tok : INT_MAX);
+          who = __ballot(best == top && tok == low);
+        }
+        const int from = who != 0 ? first_lane(who) : 0;
+        const bool any_hit = __ballot(hit) != 0;
+        const int wtok = __builtin_amdgcn_readlane(tok, from), wchild = __builtin_amdgcn_readlane(child, from);
+        if (lane == l && who != 0) {
+          am = top;
+          at = wtok;
+          ac = wchild;
+          overridden = any_hit;
+        }
+      }
+    }
+    // ---- the frames' decisions, as in decide(), one per lane ------------------------------------------------------------
+    const float M = __fadd_rn(xw, __fmul_rn(alpha, __fadd_rn(g.p_root, rsw)));
+    settled = settled && M != -INFINITY;
+    auto special = [&](int token, float fv) {
+      const bool take = fv > am || (fv == am && token < at);
+      am = take ? fv : am;
+      at = take ? token : at;
+      ac = take ? -1 : ac;
+    };
+    if (SEL == 0 && t.blank >= 0) special(t.blank, __fadd_rn(x0, __fmul_rn(alpha, 0.0f)));
+    if (t.eos >= 0) special(t.eos, __fadd_rn(xe, __fmul_rn(alpha, g.eos_boost)));
+    const bool take = at != INT_MAX && (am > M || (!overridden && am == M && at < w));
+    settled = settled && !(overridden && !take);
+    const int dtok = take ? at : w;
+    bool kept = false;
+    g.tok = dtok;
+    g.label = -1;
+    if (SEL != 0) {
+      kept = v0 == t.blank;
+      g.tok = kept ? v0 : dtok;
+      if (SEL == 2) {
+        // repeats depend on the labels before them: taken from the outcomes without repeats, then checked
+        int prev = __shfl_up(g.tok, 1);
+        prev = lane == 0 ? last : prev;
+        const bool repeat = v0 == prev;
+        g.tok = kept || repeat ? v0 : dtok;
+        prev = __shfl_up(g.tok, 1);
+        g.label = lane == 0 ? last : prev;
+        const bool blank_frame = kept;
+        kept = kept || repeat;
+        // (a frame whose repeat this gets wrong, or whose token the rule bars, is decided frame by frame)
+        settled = kept ? lane < n && (blank_frame || repeat == (v0 == g.label))
+                       : settled && v0 != g.label && dtok != g.label;
+      } else if (kept) {
+        settled = lane < n;
+      }
+    }
+    g.val = kept ? x0 : take ? am : M;
+    g.kind = kept ? kKeep : take ? (ac >= 0 ? kByArc : kKeep) : kByRoot;
+    g.next = g.kind == kByArc ? ac : g.kind == kByRoot ? rr.s0 : g.s;
+    if (kept && !before && cur.s != 0 && cur.rec.fail != 0) settled = false;  // (its record is not a single level)
+    g.settled = __ballot(settled);
+    const int next_s = __shfl_down(g.s, 1);
+    g.linked = __ballot(g.next == next_s && lane + 1 < n) & (g.settled >> 1);
+    return g;
+  }
 
+  const RootRec* root_rec;  // (of the tree, for accesses that differ from lane to lane)
+  const StateRec* states;
+  const float *p_root, *eos_score;
+
+  __device__ __forceinline__ static Rec lane_half(const v4i& r, int l) {
+    return Rec{__builtin_amdgcn_readlane(r.x, l), __builtin_amdgcn_readlane(r.y, l), __builtin_amdgcn_readlane(r.z, l),
+               __int_as_float(__builtin_amdgcn_readlane(r.w, l))};
+  }
   __device__ __forceinline__ static float lane_f(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
   }
@@ -381,50 +526,84 @@ struct Walker {
   }
 
   // One frame from state cur whose base winner is w with value M (marked: not certain, see near_band).
-  //   ahead: early / early_x are the first 64 arcs of cur's state (clamped) and the log-probs of their tokens
   //   x_blank, x_eos: log-probs of those columns
-  __device__ __forceinline__ FrameOut decide(const Cursor& cur, const float* row, float M, int w, bool marked, bool ahead,
-                                             const ArcRec& early, float early_x, float x_blank, float x_eos,
-                                             int last) const {
+  //   An arc's target comes back in `child` when `child_known` (o.arc): its record is requested with the log-probs of
+  //   the arcs, so that following a phrase costs no access of its own.
+  __device__ __forceinline__ FrameOut decide(const Cursor& cur, const float* row, float M, int w, bool marked, float x_blank,
+                                             float x_eos, int last, Cursor& child, bool& child_known) const {
     const Rec rec0 = cur.rec;
     const bool chain = cur.s != 0, multi = chain && rec0.fail != 0;
     float bf = -INFINITY;
     int btok = INT_MAX, bchild = 0;
     bool hit = false;
     bool settled = !marked && M != -INFINITY;
+    v4i kid0 = {0, 0, 0, 0}, kid1 = kid0;  // the record of this lane's first arc's target
+    float kid_p = 0.0f, kid_e = 0.0f;
+    int kid = -1;
     if (settled && chain) {
-      // the marks are all clear between frames; a walk that leaves some clears them again behind it
-      Rec r = rec0;
-      float p = 0.0f;
-      for (int level = 0;; ++level) {
-        for (int j0 = 0; j0 < r.count; j0 += 64) {
-          const int j = j0 + lane;
-          const bool valid = j < r.count;
-          ArcRec a = early;
-          float xv = early_x;
-          if (!(ahead && level == 0 && j0 == 0)) {
-            a = t.arc[r.begin + min(j, r.count - 1)];
-            xv = row[valid ? a.token : 0];
+      // The first four levels of the chain (two records) as one list of arcs, deepest state first: their arcs and
+      // their log-probs are two accesses, however many levels there are.
+      const Rec none{0, 0, 0, 0.0f};
+      const Rec r1 = multi ? cur.rec1 : none;
+      Rec2 r23{none, none};
+      if (multi && r1.fail != 0) r23 = load_rec2(t, r1.fail);
+      if (r23.a.fail == 0) r23.b = none;
+      const int c0 = rec0.count, c1 = c0 + r1.count, c2 = c1 + r23.a.count, total = c2 + r23.b.count;
+      const float p1 = __fadd_rn(0.0f, rec0.backoff), p2 = __fadd_rn(p1, r1.backoff), p3 = __fadd_rn(p2, r23.a.backoff);
+      auto consider = [&](int tk, float score, float xv, float p, int next, bool valid, bool shadowed) {
+        hit = hit || (valid && tk == w);
+        const float fa = __fadd_rn(xv, __fmul_rn(alpha, __fadd_rn(p, score)));
+        const bool take = valid && !shadowed && (fa > bf || (fa == bf && tk < btok));
+        bf = take ? fa : bf;
+        btok = take ? tk : btok;
+        bchild = take ? next : bchild;
+      };
+#pragma unroll 1
+      for (int j0 = 0; j0 < total; j0 += 64) {
+        const int i = j0 + lane;
+        const bool valid = i < total;
+        const int lv = (i >= c0 ? 1 : 0) + (i >= c1 ? 1 : 0) + (i >= c2 ? 1 : 0);
+        const int at = i < c0 ? rec0.begin + i : i < c1 ? r1.begin + i - c0 : i < c2 ? r23.a.begin + i - c1 : r23.b.begin + i - c2;
+        const ArcRec a = t.arc[valid ? at : rec0.begin];
+        const int tk = valid ? a.token : 0;  // an unused entry may hold anything: keep the indices in range
+        const float xv = row[tk];
+        if (j0 == 0) {
+          kid = valid ? at + 1 : 0;
+          const StateRec* k = states + kid;
+          kid0 = reinterpret_cast<const v4i*>(k)[0];
+          kid1 = reinterpret_cast<const v4i*>(k)[1];
+          kid_p = p_root[kid];
+          if (t.eos >= 0) kid_e = eos_score[kid];
+        }
+        bool shadowed = false;
+        if (multi) {  // a deeper chain state owns its tokens (the marks are all clear between frames)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (valid && lv == q) {
+              if (q > 0) shadowed = tag_test(L.tags, tk);
+              tag_set(L.tags, tk);
+            }
           }
-          const int tk = valid ? a.token : 0;  // an unused entry may hold anything: keep the indices in range
-          bool out = !valid;
-          if (multi) {
-            if (level > 0) out = out || tag_test(L.tags, tk);  // a deeper chain state owns this token
-            if (valid) tag_set(L.tags, tk);
-          }
-          hit = hit || (valid && tk == w);
-          const float fa = __fadd_rn(xv, __fmul_rn(alpha, __fadd_rn(p, a.score)));
-          const bool take = !out && (fa > bf || (fa == bf && tk < btok));
-          bf = take ? fa : bf;
-          btok = take ? tk : btok;
-          bchild = take ? r.begin + j + 1 : bchild;
+        }
+        consider(tk, a.score, xv, lv == 0 ? 0.0f : lv == 1 ? p1 : lv == 2 ? p2 : p3, at + 1, valid, shadowed);
+      }
+      float p = __fadd_rn(p3, r23.b.backoff);
+#pragma unroll 1
+      for (int x = r23.b.fail; x != 0;) {  // longer chains, level by level
+        const Rec r = load_rec(t, x);
+#pragma unroll 1
+        for (int j = lane; j < r.count; j += 64) {
+          const ArcRec a = t.arc[r.begin + j];
+          const bool shadowed = tag_test(L.tags, a.token);
+          tag_set(L.tags, a.token);
+          consider(a.token, a.score, row[a.token], p, r.begin + j + 1, true, shadowed);
         }
         p = __fadd_rn(p, r.backoff);
-        if (r.fail == 0) break;
-        r = load_rec(t, r.fail);
+        x = uniform_i(r.fail);
       }
       if (multi) tags_clear_n(L.tags, tag_words, lane);
     }
+    child_known = false;
     // the blank (single-stage rule: boost 0, state kept) and the EOS token (boost tabulated per state, state kept)
     if (SEL == 0 && t.blank >= 0 && lane == 63) {
       const float fv = __fadd_rn(x_blank, __fmul_rn(alpha, 0.0f));
@@ -448,9 +627,15 @@ struct Walker {
       if (overridden || MA >= M) {
         const bool mine = mine0 && bf == MA;
         const int va = wave_min_nn(mine ? btok : INT_MAX);
-        const int child = __builtin_amdgcn_readlane(bchild, first_lane(__ballot(mine && btok == va)));
+        const int next = __builtin_amdgcn_readlane(bchild, first_lane(__ballot(mine && btok == va)));
         if (MA > M || (!overridden && MA == M && va < w)) {
-          o = FrameOut{MA, va, child >= 0, child};
+          o = FrameOut{MA, va, next >= 0, next};
+          const u64 holds = __ballot(kid == next && next > 0);
+          if (holds != 0) {
+            const int q = first_lane(holds);
+            child = Cursor{next, lane_half(kid0, q), lane_half(kid1, q), lane_f(kid_p, q), lane_f(kid_e, q)};
+            child_known = true;
+          }
         } else if (overridden) {
           settled = false;  // the base winner is shadowed by an arc that does not beat it
         }
@@ -458,6 +643,7 @@ struct Walker {
     }
     if (settled && SEL == 2 && o.tok == last) settled = false;  // the CTC rule bars the previous label
     if (!settled) {
+      child_known = false;
       // (CTC: first without the exclusion -- the label may not even win -- then, if it does win, without the label)
       o = slow_frame<false, SEL>(t, cur, row, alpha, -1, L.tags, tag_words, nch, lane);
       if (SEL == 2 && o.tok == last) o = slow_frame<false, SEL>(t, cur, row, alpha, last, L.tags, tag_words, nch, lane);
@@ -483,6 +669,8 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
   const bool tree_ok = pick_tree(pick, b, mine);
   const TreeView t = make_view(mine);
   const RootRec* root_rec = mine.root_rec;
+  const StateRec* state_recs = mine.state;
+  const float *p_root = mine.p_root, *eos_score = mine.eos_score;
   int s = tree_ok ? uniform_i(states0[b]) : -1;  // an unknown tree marks the hypothesis like an invalid state
   int last = SEL == 2 && last0 != nullptr ? uniform_i(last0[b]) : -1;
   if (!tree_ok || !valid_state(t, s)) {
@@ -512,7 +700,7 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
     }
     __syncthreads();
     const Walker<SEL> walk{t, logp + static_cast<int64_t>(F0) * frame_stride + static_cast<int64_t>(b) * row_stride,
-                           frame_stride, alpha, L, tag_words, nch, lane, root_rec};
+                           frame_stride, alpha, L, tag_words, nch, lane, root_rec, state_recs, p_root, eos_score};
     const int f0 = static_cast<int>(static_cast<int64_t>(wave) * n / nwaves);
     const int f1 = static_cast<int>(static_cast<int64_t>(wave + 1) * n / nwaves);
     int from = s, from_tok = last;
@@ -555,12 +743,28 @@ size_t walk_lds_bytes(int V, int T, int waves) {
 
 }  // namespace
 
-bool frames_rows_ok(const DeviceTree& t, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B,
+// Which calls the two passes are for.  Pass 1 reads the rows at the chip's rate whatever T and B are; pass 2 costs about
+// 10 us and 0.5 to 1 us for every 16 frames of a hypothesis.  The segment decoders need some thousand segments for that
+// rate and read again what a wrong guess has spoilt, but have no second pass over the frames.  Measured (us, segment
+// decoders / two passes; random rows, then rows with 20 % of the frames inside listed phrases):
+//   V > 16384 (no segment decoder): 32001, 100 frames x 16: 3340 / 70
+//   V = 16000: 800 x 1 140/45, 174/55; 200 x 8 109/38, 168/106; 400 x 16 123/102, 200/174
+//   V = 8192: 400 x 1 51/29, 68/30; 200 x 32 83/53, 108/87; 400 x 16 74/57, 117/125; 200 x 256 300/318
+//   V = 2500: 100 x 1 26/19, 31/20; 100 x 128 53/44, 68/63; 400 x 16 37/47, 55/77
+//   V = 1025: 250 x 32 40/36, 79/74 (CTC rule 47/30, 103/53); 500 x 32 45/50, 75/88 (54/45, 115/78); 1000 x 16 51/68, 90/125
+//   V = 129: 96 x 8 22/26, 28/28; 96 x 512 40/69, 58/78
+// so: never up to 1024 tokens; past that up to the number of rows the passes take at once and the frames the table gives.
+static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
+  const int64_t rows = static_cast<int64_t>(T) * B;
+  if (V > kWideMaxV) return rows <= INT32_MAX;
+  if (V <= 1024 || rows > 16384) return false;
+  if (V <= kNarrowMaxV) return T <= (sel == 0 ? 256 : 512);
+  return T <= (V / 16 > 128 ? V / 16 : 128) || (V >= 4096 && B <= 4);
+}
+
+bool frames_rows_ok(const DeviceTree& t, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B, int sel,
                     const int32_t* d_tokens, const int32_t* d_states, const float* d_scores) {
-  // Rows of up to kWideMaxV tokens stay with the segment decoders.  (V = 32001, 100 frames x 16 utterances: 3334 us with
-  // the frames of an utterance in series on the workgroup-per-row kernel, 75 us with the two passes.)
-  if (t.p_root == nullptr || t.root_rec == nullptr || t.vocab_size <= kWideMaxV) return false;
-  if (static_cast<int64_t>(T) * B > INT32_MAX) return false;
+  if (t.p_root == nullptr || t.root_rec == nullptr || !rows_pay(t.vocab_size, T, B, sel)) return false;
   if (walk_lds_bytes(t.vocab_size, T, 1) > static_cast<size_t>(g_walk_max_lds)) return false;
   const size_t out = static_cast<size_t>(T) * static_cast<size_t>(B) * 4, in = static_cast<size_t>(B) * 4;
   auto apart = [](const void* a, size_t na, const void* b, size_t nb) {

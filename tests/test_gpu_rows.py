@@ -107,3 +107,33 @@ def test_a_table_of_trees_and_overlapping_outputs():
                 else:
                     _check([g[:, b:b + 1] for g in o], want[b], [0], (mode, inside, b))
     pb.pb_forest_free(forest)
+
+
+@pytest.mark.parametrize("V,T,B", [(1024, 40, 3), (1025, 255, 2), (1025, 257, 2), (1025, 512, 1), (1025, 513, 1), (1280, 60, 5),
+                                   (1281, 128, 2), (1281, 129, 2), (2500, 156, 2), (2500, 157, 2), (4095, 300, 2), (4096, 300, 2),
+                                   (4096, 300, 5), (1100, 33, 500)])
+def test_both_sides_of_the_dispatch(V, T, B):
+    """Sizes on either side of every line between the two passes and the segment decoders, phrases spoken, every rule."""
+    rng = np.random.default_rng(44000 + V + T)
+    blank = V - 1
+    toks, offs, ot, tr = _tree(rng, V, blank, -1, T % 3, 0.0)
+    shape = W.Config(9, "rows", V, blank, 1, 1, 8, "uniform", 1.1, B, 1, T, 2.0)
+    x = W.make_logp(shape, seed=V + T, planting=W.Planting(toks, offs, cover=0.5, bump=10.0), blank_bias=6.0, blank_frac=0.3)
+    x = x.astype(np.float32)
+    s0 = rng.integers(0, ot.num_states, B).astype(np.int32)
+    last0 = rng.integers(-1, V, B).astype(np.int32)
+    d_x = dev(x)
+    for mode in (0, 1, 2):
+        want = ot.fuse_frames_select(x, s0, last0, 0.5, mode)
+        need = pb.pb_fuse_frames_workspace_bytes(tr, T, B)
+        ws = torch.full((max(need, 8) // 4,), 0x7f7f7f7f, dtype=torch.int32, device=DEV)
+        for with_ws in (False, True):
+            o = _outputs(T, B)
+            print("dispatch", V, T, B, mode, with_ws, flush=True)
+            if with_ws:
+                pb.pb_fuse_frames_ws(tr, d_x, B * V, V, dev(s0), dev(last0), 0.5, T, B, mode, o[0], o[1], o[2], ws, need, 0)
+            else:
+                pb.pb_fuse_frames_select(tr, d_x, B * V, V, dev(s0), dev(last0), 0.5, T, B, mode, o[0], o[1], o[2], 0)
+            torch.cuda.synchronize()
+            _check(o, want, list(range(B)), (V, T, B, mode, with_ws))
+    pb.pb_free(tr)
