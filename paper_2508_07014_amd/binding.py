@@ -53,7 +53,12 @@ class pb_host_view(C.Structure):
                 ("p_root", C.POINTER(C.c_float)), ("eos_score", C.POINTER(C.c_float))]
 
 
+HOT = ["pb_score", "pb_fuse_step", "pb_fuse_frames", "pb_fuse_step_select", "pb_fuse_frames_select", "pb_fuse_frames_ws",
+       "pb_fuse_frames_static", "pb_fuse_step_beam", "pb_score_forest", "pb_fuse_step_forest", "pb_fuse_frames_forest",
+       "pb_fuse_step_beam_forest"]  # called once per decoding step: they go through _pbcall (see pb_python.cpp)
+
 _lib = None
+_hot = None  # the HOT entry points, taking device buffers as they come and returning a status code
 
 
 def library_path() -> str:
@@ -126,8 +131,33 @@ def load():
     lib.pb_validate_states.argtypes = [vp, i32p, C.c_int64, i64p]
     lib.pb_strerror.restype = C.c_char_p
     lib.pb_strerror.argtypes = [C.c_int]
+    global _hot
+    _hot = _bind_hot(lib)
     _lib = lib
     return lib
+
+
+def _bind_hot(lib):
+    try:
+        from . import _pbcall
+    except ImportError:
+        return _CtypesCalls(lib)
+    for name in HOT:
+        _pbcall.bind(name, C.cast(getattr(lib, name), C.c_void_p).value)
+    return _pbcall
+
+
+class _CtypesCalls:
+    """The same calls through ctypes, where the extension module has not been built."""
+
+    def __init__(self, lib):
+        for name in HOT:
+            setattr(self, name, self._call(getattr(lib, name)))
+
+    @staticmethod
+    def _call(fn):
+        buffers = [t is C.c_void_p for t in fn.argtypes]
+        return lambda *args: fn(*[_dptr(a) if is_buffer else a for a, is_buffer in zip(args, buffers)])
 
 
 def strerror(code: int) -> str:
@@ -234,37 +264,40 @@ def pb_state_prefix(tree: Tree, state: int) -> tuple:
     return tuple(buf[:ln.value])
 
 
+def _load_hot():
+    load()
+    return _hot
+
+
 def pb_score(tree: Tree, d_states, B: int, d_scores, d_next=None, stream: int = 0):
-    _check(load().pb_score(tree.handle, _dptr(d_states), B, _dptr(d_scores), _dptr(d_next), stream or None),
-           "pb_score")
+    _check((_hot or _load_hot()).pb_score(tree.handle, d_states, B, d_scores, d_next, stream), "pb_score")
 
 
 def pb_fuse_step(tree: Tree, d_logp, row_stride: int, d_states_in, alpha: float, B: int, d_tokens, d_states_out,
                  d_scores, stream: int = 0):
-    _check(load().pb_fuse_step(tree.handle, _dptr(d_logp), row_stride, _dptr(d_states_in), alpha, B,
-                               _dptr(d_tokens), _dptr(d_states_out), _dptr(d_scores), stream or None),
-           "pb_fuse_step")
+    _check((_hot or _load_hot()).pb_fuse_step(
+        tree.handle, d_logp, row_stride, d_states_in, alpha, B, d_tokens, d_states_out, d_scores, stream), "pb_fuse_step")
 
 
 def pb_fuse_frames(tree: Tree, d_logp, frame_stride: int, row_stride: int, d_states0, alpha: float, T: int, B: int,
                    d_tokens, d_states, d_scores, stream: int = 0):
-    _check(load().pb_fuse_frames(tree.handle, _dptr(d_logp), frame_stride, row_stride, _dptr(d_states0), alpha, T, B,
-                                 _dptr(d_tokens), _dptr(d_states), _dptr(d_scores), stream or None),
-           "pb_fuse_frames")
+    _check((_hot or _load_hot()).pb_fuse_frames(
+        tree.handle, d_logp, frame_stride, row_stride, d_states0, alpha, T, B, d_tokens, d_states, d_scores,
+        stream), "pb_fuse_frames")
 
 
 def pb_fuse_step_select(tree: Tree, d_logp, row_stride: int, d_states_in, d_last_tokens, alpha: float, B: int,
                         mode: int, d_tokens, d_states_out, d_scores, stream: int = 0):
-    _check(load().pb_fuse_step_select(tree.handle, _dptr(d_logp), row_stride, _dptr(d_states_in),
-                                      _dptr(d_last_tokens), alpha, B, mode, _dptr(d_tokens), _dptr(d_states_out),
-                                      _dptr(d_scores), stream or None), "pb_fuse_step_select")
+    _check((_hot or _load_hot()).pb_fuse_step_select(
+        tree.handle, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode, d_tokens, d_states_out,
+        d_scores, stream), "pb_fuse_step_select")
 
 
 def pb_fuse_frames_select(tree: Tree, d_logp, frame_stride: int, row_stride: int, d_states0, d_last0, alpha: float,
                           T: int, B: int, mode: int, d_tokens, d_states, d_scores, stream: int = 0):
-    _check(load().pb_fuse_frames_select(tree.handle, _dptr(d_logp), frame_stride, row_stride, _dptr(d_states0),
-                                        _dptr(d_last0), alpha, T, B, mode, _dptr(d_tokens), _dptr(d_states),
-                                        _dptr(d_scores), stream or None), "pb_fuse_frames_select")
+    _check((_hot or _load_hot()).pb_fuse_frames_select(
+        tree.handle, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
+        d_states, d_scores, stream), "pb_fuse_frames_select")
 
 
 def pb_fuse_frames_plan(tree: Tree, T: int, B: int):
@@ -285,24 +318,23 @@ def pb_fuse_frames_workspace_bytes(tree: Tree, T: int, B: int) -> int:
 def pb_fuse_frames_ws(tree: Tree, d_logp, frame_stride: int, row_stride: int, d_states0, d_last0, alpha: float,
                       T: int, B: int, mode: int, d_tokens, d_states, d_scores, d_workspace, workspace_bytes: int,
                       stream: int = 0):
-    _check(load().pb_fuse_frames_ws(tree.handle, _dptr(d_logp), frame_stride, row_stride, _dptr(d_states0),
-                                    _dptr(d_last0), alpha, T, B, mode, _dptr(d_tokens), _dptr(d_states),
-                                    _dptr(d_scores), _dptr(d_workspace), workspace_bytes, stream or None),
-           "pb_fuse_frames_ws")
+    _check((_hot or _load_hot()).pb_fuse_frames_ws(
+        tree.handle, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
+        d_states, d_scores, d_workspace, workspace_bytes, stream), "pb_fuse_frames_ws")
 
 
 def pb_fuse_frames_static(tree: Tree, d_logp, frame_stride: int, row_stride: int, d_states0, d_last0, alpha: float,
                           T: int, B: int, mode: int, d_tokens, d_states, d_scores, stream: int = 0):
-    _check(load().pb_fuse_frames_static(tree.handle, _dptr(d_logp), frame_stride, row_stride, _dptr(d_states0),
-                                        _dptr(d_last0), alpha, T, B, mode, _dptr(d_tokens), _dptr(d_states),
-                                        _dptr(d_scores), stream or None), "pb_fuse_frames_static")
+    _check((_hot or _load_hot()).pb_fuse_frames_static(
+        tree.handle, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
+        d_states, d_scores, stream), "pb_fuse_frames_static")
 
 
 def pb_fuse_step_beam(tree: Tree, d_logp, row_stride: int, d_hyp_scores, d_states_in, alpha: float, U: int, K: int,
                       d_tokens, d_parents, d_states_out, d_scores_out, stream: int = 0):
-    _check(load().pb_fuse_step_beam(tree.handle, _dptr(d_logp), row_stride, _dptr(d_hyp_scores), _dptr(d_states_in),
-                                    alpha, U, K, _dptr(d_tokens), _dptr(d_parents), _dptr(d_states_out),
-                                    _dptr(d_scores_out), stream or None), "pb_fuse_step_beam")
+    _check((_hot or _load_hot()).pb_fuse_step_beam(
+        tree.handle, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens, d_parents,
+        d_states_out, d_scores_out, stream), "pb_fuse_step_beam")
 
 
 class Forest:
@@ -336,28 +368,27 @@ def pb_forest_free(forest: Forest):
 
 
 def pb_score_forest(forest: Forest, d_tree_ids, d_states, B: int, d_scores, d_next=None, stream: int = 0):
-    _check(load().pb_score_forest(forest.handle, _dptr(d_tree_ids), _dptr(d_states), B, _dptr(d_scores), _dptr(d_next),
-                                  stream or None), "pb_score_forest")
+    _check((_hot or _load_hot()).pb_score_forest(
+        forest.handle, d_tree_ids, d_states, B, d_scores, d_next, stream), "pb_score_forest")
 
 
 def pb_fuse_step_forest(forest: Forest, d_logp, row_stride: int, d_tree_ids, d_states_in, d_last_tokens, alpha: float,
                         B: int, mode: int, d_tokens, d_states_out, d_scores, stream: int = 0):
-    _check(load().pb_fuse_step_forest(forest.handle, _dptr(d_logp), row_stride, _dptr(d_tree_ids), _dptr(d_states_in),
-                                      _dptr(d_last_tokens), alpha, B, mode, _dptr(d_tokens), _dptr(d_states_out),
-                                      _dptr(d_scores), stream or None), "pb_fuse_step_forest")
+    _check((_hot or _load_hot()).pb_fuse_step_forest(
+        forest.handle, d_logp, row_stride, d_tree_ids, d_states_in, d_last_tokens, alpha, B, mode, d_tokens,
+        d_states_out, d_scores, stream), "pb_fuse_step_forest")
 
 
 def pb_fuse_frames_forest(forest: Forest, d_logp, frame_stride: int, row_stride: int, d_tree_ids, d_states0, d_last0,
                           alpha: float, T: int, B: int, mode: int, d_tokens, d_states, d_scores, stream: int = 0):
-    _check(load().pb_fuse_frames_forest(forest.handle, _dptr(d_logp), frame_stride, row_stride, _dptr(d_tree_ids),
-                                        _dptr(d_states0), _dptr(d_last0), alpha, T, B, mode, _dptr(d_tokens),
-                                        _dptr(d_states), _dptr(d_scores), stream or None), "pb_fuse_frames_forest")
+    _check((_hot or _load_hot()).pb_fuse_frames_forest(
+        forest.handle, d_logp, frame_stride, row_stride, d_tree_ids, d_states0, d_last0, alpha, T, B, mode,
+        d_tokens, d_states, d_scores, stream), "pb_fuse_frames_forest")
 
 
 def pb_fuse_step_beam_forest(forest: Forest, d_logp, row_stride: int, d_tree_ids, d_hyp_scores, d_states_in,
                              alpha: float, U: int, K: int, d_tokens, d_parents, d_states_out, d_scores_out,
                              stream: int = 0):
-    _check(load().pb_fuse_step_beam_forest(forest.handle, _dptr(d_logp), row_stride, _dptr(d_tree_ids),
-                                           _dptr(d_hyp_scores), _dptr(d_states_in), alpha, U, K, _dptr(d_tokens),
-                                           _dptr(d_parents), _dptr(d_states_out), _dptr(d_scores_out), stream or None),
-           "pb_fuse_step_beam_forest")
+    _check((_hot or _load_hot()).pb_fuse_step_beam_forest(
+        forest.handle, d_logp, row_stride, d_tree_ids, d_hyp_scores, d_states_in, alpha, U, K, d_tokens,
+        d_parents, d_states_out, d_scores_out, stream), "pb_fuse_step_beam_forest")

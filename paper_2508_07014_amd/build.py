@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -13,6 +14,8 @@ LIB = os.environ.get("PB_LIBRARY") or os.path.join(PKG, "libpb.so")
 PROBE_LIB = os.path.join(PKG, "libpb_probe.so")  # measurement probes of bench.py, not part of the product library
 SOURCES = ["pb_narrow_1024.hip", "pb_narrow_any.hip", "pb_narrow_1280.hip", "pb_narrow_256.hip", "pb_narrow_512.hip",
            "pb_wide.hip", "pb_rows.hip", "pb_beam.hip", "pb_frames.hip", "pb_kernels.hip", "pb_compile.cpp", "pb_api.hip"]
+# the Python side of the entry points that are called once per step (host code only, loads beside the library)
+CALL_LIB = os.path.join(PKG, "_pbcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 HEADERS = ["pb_tree.hpp", "pb_kernels.hpp", "pb_wave.hpp", "pb_chunk.hpp", "pb_narrow.hpp", os.path.join(ROOT, "include", "pb.h")]
 OBJDIR = os.path.join(PKG, "_build")
 
@@ -59,6 +62,8 @@ def build(force: bool = True, verbose: bool = False, extra=(), out: str = LIB) -
             print(" ".join(cmd), file=sys.stderr)
         subprocess.run(cmd, check=True)
 
+    if out == LIB:
+        build_calls(verbose)
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
         list(pool.map(one, zip(SOURCES, objs)))
     cmd = link_command(objs, out)
@@ -66,6 +71,19 @@ def build(force: bool = True, verbose: bool = False, extra=(), out: str = LIB) -
         print(" ".join(cmd), file=sys.stderr)
     subprocess.run(cmd, check=True)
     return out
+
+
+def build_calls(verbose: bool = False):
+    """Compiles the extension module; None where this Python has no headers (the binding then goes through ctypes)."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        return None
+    cmd = ["g++", "-shared", "-fPIC", "-O2", "-std=c++17", "-Wall", "-Wextra", "-I", include, "-I", os.path.join(ROOT, "include"),
+           "-o", CALL_LIB, os.path.join(CSRC, "pb_python.cpp")]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    subprocess.run(cmd, check=True)
+    return CALL_LIB
 
 
 def build_probe(force: bool = True, verbose: bool = False) -> str:
