@@ -115,8 +115,8 @@ __device__ __forceinline__ void block_best(float& val, int& idx, float* sv, int*
 // pb_score: one workgroup per (group of `per` consecutive hypotheses, vocabulary tile).  The tile of
 // the dense root row is read once per workgroup and kept in registers (VEC == 4: up to 8 tokens per
 // thread).  A hypothesis in the root state has no chain: its row is
-// the root row itself and skips LDS and barriers.  PAST: the rows are written past the caches (see launch_score).
-template <int VEC, bool PAST>
+// the root row itself and skips LDS and barriers.
+template <int VEC>
 __global__ void __launch_bounds__(256) score_kernel(DeviceTree t0, TreePick pick, const int32_t* __restrict__ states,
                                                     int B, float* __restrict__ scores, int32_t* __restrict__ next,
                                                     int tile, int tiles, int per) {
@@ -183,13 +183,8 @@ __global__ void __launch_bounds__(256) score_kernel(DeviceTree t0, TreePick pick
           typedef int vi4 __attribute__((ext_vector_type(4)));
           const vf4 so = {sc[0], sc[1], sc[2], sc[3]};
           const vi4 no = {nx[0], nx[1], nx[2], nx[3]};
-          if constexpr (PAST) {
-            __builtin_nontemporal_store(so, reinterpret_cast<vf4*>(scores + base + i));
-            if (next) __builtin_nontemporal_store(no, reinterpret_cast<vi4*>(next + base + i));
-          } else {
-            *reinterpret_cast<vf4*>(scores + base + i) = so;
-            if (next) *reinterpret_cast<vi4*>(next + base + i) = no;
-          }
+          *reinterpret_cast<vf4*>(scores + base + i) = so;
+          if (next) *reinterpret_cast<vi4*>(next + base + i) = no;
         }
       }
     } else {
@@ -484,21 +479,12 @@ int launch_score(const DeviceTree& t, const TreePick& pick, const int32_t* d_sta
   const dim3 grid(static_cast<unsigned>(groups * tiles));
   const size_t lds = static_cast<size_t>(tile) * sizeof(u64);
   const bool vec = (V % 4 == 0) && aligned16(d_scores) && (d_next == nullptr || aligned16(d_next));
-  // Outputs that the last-level cache (256 MiB) would not keep for the reader anyway go past the caches: V = 8192,
-  // B = 4096 52.0 us, 5.2 TB/s, against 64.9.  (Smaller ones gain little by it, V = 8192, B = 1024 14.1 against 14.8, and
-  // whoever reads them next finds them in the cache.)
-  const bool past = static_cast<double>(B) * V * (d_next ? 8 : 4) > 192.0 * (1 << 20);
-#define PB_SCORE(VEC, PAST)                                                                                               \
-  hipLaunchKernelGGL((score_kernel<VEC, PAST>), grid, dim3(256), lds, stream, t, pick, d_states, B, d_scores, d_next, tile, \
-                     tiles, per)
-  if (vec && past) {
-    PB_SCORE(4, true);
-  } else if (vec) {
-    PB_SCORE(4, false);
-  } else {
-    PB_SCORE(1, false);
-  }
-#undef PB_SCORE
+  if (vec)
+    hipLaunchKernelGGL(score_kernel<4>, grid, dim3(256), lds, stream, t, pick, d_states, B, d_scores, d_next, tile,
+                       tiles, per);
+  else
+    hipLaunchKernelGGL(score_kernel<1>, grid, dim3(256), lds, stream, t, pick, d_states, B, d_scores, d_next, tile,
+                       tiles, per);
   return check_launch();
 }
 
