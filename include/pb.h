@@ -228,6 +228,7 @@ int pb_fuse_frames_ws(const pb_tree* tree, const float* d_logp, int64_t frame_st
  * only, nothing is launched; for tests and for sizing).  Writes the number of segments to *n_segments and, if
  * `bounds` is not NULL, n_segments + 1 frame indices to it (host array with room for 65 entries): segment j covers
  * frames bounds[j] .. bounds[j + 1] - 1, bounds[0] = 0, bounds[n_segments] = T; every hypothesis is cut the same way.
+ * (Calls of few or very wide rows are not cut: they find the winners of all rows first and run the states over those.)
  * T == 0 or B == 0 gives zero segments.  PB_EINVAL for a null tree or n_segments, or negative sizes.
  */
 int pb_fuse_frames_plan(const pb_tree* tree, int32_t T, int32_t B, int32_t* n_segments, int32_t* bounds);
