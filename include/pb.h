@@ -170,6 +170,10 @@ int pb_fuse_step(const pb_tree* tree, const float* d_logp, int64_t row_stride, c
  * states produced by frame t-1 (d_states0 for t = 0).  Outputs are [T,B] row-major: the token,
  * the state after the frame and the fused score of every frame; identical to T calls of
  * pb_fuse_step.  T == 0 or B == 0 is a no-op.
+ * d_states0 may be a row of d_states (and, in the calls below, the previous labels and the tree ids a row of d_tokens or
+ * d_states): element b is read before anything of hypothesis b is written.  Such a call takes the plain kernel, one
+ * workgroup per hypothesis and frame after frame; with start states of their own the faster decoders run.  No other
+ * overlap of the outputs with the inputs or with each other is supported.
  */
 int pb_fuse_frames(const pb_tree* tree, const float* d_logp, int64_t frame_stride, int64_t row_stride,
                    const int32_t* d_states0, float alpha, int32_t T, int32_t B, int32_t* d_tokens,

@@ -235,7 +235,26 @@ int pb_fuse_step(const pb_tree* tree, const float* d_logp, int64_t row_stride, c
 
 namespace {
 
-// pb_fuse_frames_select and pb_fuse_frames_ws: d_patches is the optional workspace (null: none).
+// The kernels of a multi-frame call (d_patches: the optional workspace, null: none).
+int launch_frames(const pb::DeviceTree& t, const pb::TreePick& pick, const float* d_logp, int64_t frame_stride,
+                  int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B,
+                  int32_t mode, int32_t* d_tokens, int32_t* d_states, float* d_scores, int32_t* d_patches,
+                  hipStream_t stream) {
+  if (pb::frames_apart(pick, d_states0, d_last0, T, B, d_tokens, d_states, d_scores)) {
+    if (pb::frames_rows_ok(t, T, B, mode))
+      return pb::launch_frames_rows(t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
+                                    d_tokens, d_states, d_scores, stream);
+    // (the segment decoder keeps a flag in bit 30 of the state words it stores: larger trees take the plain kernel; the
+    // largest member of a table decides for all)
+    if (pb::wave_path_ok(t) && t.num_states < (1 << 30))
+      return pb::launch_frames_wave(t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
+                                    d_tokens, d_states, d_scores, d_patches, stream);
+  }
+  return pb::launch_fuse(t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
+                         d_states, d_scores, stream);
+}
+
+// pb_fuse_frames_select and pb_fuse_frames_ws.
 int fuse_frames_any(const pb_tree* tree, const float* d_logp, int64_t frame_stride, int64_t row_stride,
                     const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B, int32_t mode,
                     int32_t* d_tokens, int32_t* d_states, float* d_scores, int32_t* d_patches, void* hip_stream) {
@@ -244,16 +263,8 @@ int fuse_frames_any(const pb_tree* tree, const float* d_logp, int64_t frame_stri
   if (B == 0 || T == 0) return PB_OK;
   if (!d_logp || !d_states0 || !d_tokens || !d_states || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size || frame_stride < 0) return PB_EINVAL;
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::frames_rows_ok(tree->dev, d_states0, d_last0, T, B, mode, d_tokens, d_states, d_scores))
-    return pb::launch_frames_rows(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
-                                  d_tokens, d_states, d_scores, stream);
-  // (the segment decoder keeps a flag in bit 30 of the state words it stores: larger trees take the plain kernel)
-  if (pb::wave_path_ok(tree->dev) && tree->dev.num_states < (1 << 30))
-    return pb::launch_frames_wave(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
-                                  d_tokens, d_states, d_scores, d_patches, stream);
-  return pb::launch_fuse(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
-                         d_states, d_scores, stream);
+  return launch_frames(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
+                       d_tokens, d_states, d_scores, d_patches, static_cast<hipStream_t>(hip_stream));
 }
 
 }  // namespace
@@ -434,15 +445,8 @@ int pb_fuse_frames_forest(const pb_forest* forest, const float* d_logp, int64_t 
   if (!d_logp || !d_tree_ids || !d_states0 || !d_tokens || !d_states || !d_scores) return PB_EINVAL;
   if (row_stride < forest->proto.vocab_size || frame_stride < 0) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::frames_rows_ok(forest->proto, d_states0, d_last0, T, B, mode, d_tokens, d_states, d_scores))
-    return pb::launch_frames_rows(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
-                                  d_tokens, d_states, d_scores, stream);
-  if (pb::wave_path_ok(forest->proto) && forest->proto.num_states < (1 << 30))
-    return pb::launch_frames_wave(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B,
-                                  mode, d_tokens, d_states, d_scores, nullptr, stream);
-  return pb::launch_fuse(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
-                         d_tokens, d_states, d_scores, stream);
+  return launch_frames(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
+                       d_states, d_scores, nullptr, static_cast<hipStream_t>(hip_stream));
 }
 
 int pb_fuse_step_beam_forest(const pb_forest* forest, const float* d_logp, int64_t row_stride,

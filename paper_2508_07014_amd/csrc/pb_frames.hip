@@ -29,6 +29,25 @@ bool step_wave_ok(const DeviceTree& t) {
   return t.p_root != nullptr && t.root_rec != nullptr && t.vocab_size >= 4 && t.vocab_size <= kStepMaxV;
 }
 
+bool frames_apart(const TreePick& pick, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B,
+                  const int32_t* d_tokens, const int32_t* d_states, const float* d_scores) {
+  struct Range {
+    uintptr_t at;
+    size_t bytes;
+  };
+  auto range = [](const void* p, size_t n) { return Range{reinterpret_cast<uintptr_t>(p), p != nullptr ? n * 4 : 0}; };
+  const size_t n = static_cast<size_t>(T) * static_cast<size_t>(B), rows = static_cast<size_t>(B);
+  const Range out[] = {range(d_tokens, n), range(d_states, n), range(d_scores, n)};
+  const Range in[] = {range(d_states0, rows), range(d_last0, rows), range(pick.ids, rows)};
+  auto apart = [](const Range& a, const Range& b) {
+    return a.bytes == 0 || b.bytes == 0 || a.at + a.bytes <= b.at || b.at + b.bytes <= a.at;
+  };
+  bool ok = apart(out[0], out[1]) && apart(out[0], out[2]) && apart(out[1], out[2]);
+  for (const Range& o : out)
+    for (const Range& i : in) ok = ok && apart(o, i);
+  return ok;
+}
+
 SegPlan plan_segments(int32_t T, int32_t B, int target_chains) {
   // Segments: enough concurrent chains to cover the memory latency, at most kMaxSegments per
   // hypothesis, at least kMinSegLen frames long.

@@ -265,11 +265,9 @@ __device__ __forceinline__ void fused_row(const DeviceTree& t, const float* __re
 // sel: 0 single-stage, 1 two-stage, 2 two-stage with the CTC repeat rule (Sec. II-C).
 template <int VEC>
 __global__ void __launch_bounds__(1024) fuse_kernel(DeviceTree t0, TreePick pick, const float* __restrict__ logp,
-                                                    int64_t frame_stride, int64_t row_stride,
-                                                    const int32_t* __restrict__ states0,
-                                                    const int32_t* __restrict__ last0, float alpha, int T, int B, int sel,
-                                                    int32_t* __restrict__ tokens, int32_t* __restrict__ states,
-                                                    float* __restrict__ scores, int chunk) {
+                                                    int64_t frame_stride, int64_t row_stride, const int32_t* states0,
+                                                    const int32_t* last0, float alpha, int T, int B, int sel,
+                                                    int32_t* tokens, int32_t* states, float* scores, int chunk) {
   extern __shared__ u64 row[];
   __shared__ float sv[16];
   __shared__ int si[16];
@@ -280,6 +278,7 @@ __global__ void __launch_bounds__(1024) fuse_kernel(DeviceTree t0, TreePick pick
   const int V = t.vocab_size;
   int s = tree_ok ? states0[b] : -1;  // an unknown tree marks the hypothesis like an invalid state
   int last = (sel == 2 && last0 != nullptr) ? last0[b] : -1;
+  __syncthreads();  // (the outputs may overlap what has just been read, see frames_apart: all waves have read it here)
   for (int f = 0; f < T; ++f) {
     const size_t o = static_cast<size_t>(f) * B + b;
     if (static_cast<unsigned>(s) >= static_cast<unsigned>(t.num_states)) {

@@ -102,12 +102,17 @@ int launch_frames_wave(const DeviceTree& t, const TreePick& pick, const float* d
                        const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B, int sel,
                        int32_t* d_tokens, int32_t* d_states, float* d_scores, int32_t* d_patches, hipStream_t stream);
 
-// Multi-frame decoding in two passes, all rows and then the automaton (pb_rows.hip): whether a call can take it -- the
-// outputs hold the rows' winners in between, so they must not overlap the start states, the previous labels or each
-// other -- and the launch.
+// Whether the outputs of a multi-frame call lie apart from its start states, previous labels and tree ids and from each
+// other.  Those that do not go to launch_fuse, whose workgroups read what they start from before they write: the others
+// decode a hypothesis in several waves, which write later frames while the first one, or a boundary guess, may still
+// have the start states to read.
+bool frames_apart(const TreePick& pick, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B,
+                  const int32_t* d_tokens, const int32_t* d_states, const float* d_scores);
+
+// Multi-frame decoding in two passes, all rows and then the automaton (pb_rows.hip): whether a call takes it, and the
+// launch.  The outputs hold the rows' winners in between: calls with frames_apart only.
 int prepare_rows_kernels(int max_lds_bytes);
-bool frames_rows_ok(const DeviceTree& t, const int32_t* d_states0, const int32_t* d_last0, int32_t T, int32_t B, int sel,
-                    const int32_t* d_tokens, const int32_t* d_states, const float* d_scores);
+bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel);
 int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,
                        int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T,
                        int32_t B, int sel, int32_t* d_tokens, int32_t* d_states, float* d_scores, hipStream_t stream);
