@@ -756,7 +756,7 @@ size_t walk_lds_bytes(int V, int T, int waves) {
 // so: never up to 1024 tokens; past that up to the number of rows the passes take at once and the frames the table gives.
 static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
   const int64_t rows = static_cast<int64_t>(T) * B;
-  if (V > kWideMaxV) return rows <= INT32_MAX;
+  if (V > kWideMaxV) return rows <= kMaxWorkgroups;
   if (V <= 1024 || rows > 16384) return false;
   if (V <= kNarrowMaxV) return T <= (sel == 0 ? 256 : 512);
   return T <= (V / 16 > 128 ? V / 16 : 128) || (V >= 4096 && B <= 4);
