@@ -112,6 +112,60 @@ int upload(pb_tree* tr, int device) {
 
 bool on_device(const pb_tree* t) { return t && t->slab != nullptr; }
 
+// launch(first, count) over 0 .. n - 1 in slices of `most` (see kMaxWorkgroups; one slice for all but absurd sizes).
+template <typename Launch>
+int in_slices(int32_t n, int64_t most, Launch&& launch) {
+  for (int64_t at = 0; at < n; at += most) {
+    const int rc = launch(static_cast<size_t>(at), static_cast<int32_t>(std::min<int64_t>(n - at, most)));
+    if (rc != PB_OK) return rc;
+  }
+  return PB_OK;
+}
+pb::TreePick shifted(pb::TreePick pick, size_t at) {
+  if (pick.ids) pick.ids += at;
+  return pick;
+}
+
+// The kernels of the per-step calls, with the arguments of the C ABI.
+int score_rows(const pb::DeviceTree& t, const pb::TreePick& pick, const int32_t* d_states, int32_t B, float* d_scores,
+               int32_t* d_next, hipStream_t stream) {
+  const size_t V = static_cast<size_t>(t.vocab_size);
+  const int64_t tiles = (t.vocab_size + pb::kScoreTile - 1) / pb::kScoreTile;  // (workgroups per row at most)
+  return in_slices(B, std::max<int64_t>(1, pb::kMaxWorkgroups / tiles), [&](size_t b, int32_t n) {
+    return pb::launch_score(t, shifted(pick, b), d_states + b, n, d_scores + b * V, d_next ? d_next + b * V : nullptr, stream);
+  });
+}
+
+int launch_step(const pb::DeviceTree& t, const pb::TreePick& pick, const float* d_logp, int64_t row_stride,
+                const int32_t* d_states_in, const int32_t* d_last, float alpha, int32_t B, int32_t mode, int32_t* d_tokens,
+                int32_t* d_states_out, float* d_scores, void* hip_stream) {
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  return in_slices(B, pb::kMaxWorkgroups, [&](size_t b, int32_t n) {
+    const float* logp = d_logp + b * static_cast<size_t>(row_stride);
+    const int32_t* last = d_last ? d_last + b : nullptr;
+    if (pb::step_wave_ok(t))  // (members of a table share the vocabulary, so one answer fits all)
+      return pb::launch_step_wave(t, shifted(pick, b), logp, row_stride, d_states_in + b, last, alpha, n, mode, d_tokens + b,
+                                  d_states_out + b, d_scores + b, stream);
+    return pb::launch_fuse(t, shifted(pick, b), logp, 0, row_stride, d_states_in + b, last, alpha, 1, n, mode, d_tokens + b,
+                           d_states_out + b, d_scores + b, stream);
+  });
+}
+
+int launch_beam_step(const pb::DeviceTree& t, const pb::TreePick& pick, const float* d_logp, int64_t row_stride,
+                     const float* d_hyp, const int32_t* d_states_in, float alpha, int32_t U, int32_t K, int32_t* d_tokens,
+                     int32_t* d_parents, int32_t* d_states_out, float* d_scores_out, void* hip_stream) {
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  return in_slices(U, pb::kMaxWorkgroups, [&](size_t u, int32_t n) {
+    const size_t h = u * static_cast<size_t>(K);
+    const float* logp = d_logp + h * static_cast<size_t>(row_stride);
+    if (pb::beam_wave_ok(t, n, K))  // (members of a table share the vocabulary)
+      return pb::launch_beam_wave(t, shifted(pick, u), logp, row_stride, d_hyp + h, d_states_in + h, alpha, n, K, d_tokens + h,
+                                  d_parents + h, d_states_out + h, d_scores_out + h, stream);
+    return pb::launch_beam(t, shifted(pick, u), logp, row_stride, d_hyp + h, d_states_in + h, alpha, n, K, d_tokens + h,
+                           d_parents + h, d_states_out + h, d_scores_out + h, stream);
+  });
+}
+
 }  // namespace
 
 extern "C" {
@@ -204,8 +258,7 @@ int pb_score(const pb_tree* tree, const int32_t* d_states, int32_t B, float* d_s
   if (!on_device(tree) || B < 0) return PB_EINVAL;
   if (B == 0) return PB_OK;
   if (!d_states || !d_scores) return PB_EINVAL;
-  return pb::launch_score(tree->dev, pb::TreePick{}, d_states, B, d_scores, d_next,
-                          static_cast<hipStream_t>(hip_stream));
+  return score_rows(tree->dev, pb::TreePick{}, d_states, B, d_scores, d_next, static_cast<hipStream_t>(hip_stream));
 }
 
 int pb_fuse_step_select(const pb_tree* tree, const float* d_logp, int64_t row_stride, const int32_t* d_states_in,
@@ -216,12 +269,8 @@ int pb_fuse_step_select(const pb_tree* tree, const float* d_logp, int64_t row_st
   if (B == 0) return PB_OK;
   if (!d_logp || !d_states_in || !d_tokens || !d_states_out || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size) return PB_EINVAL;
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::step_wave_ok(tree->dev))
-    return pb::launch_step_wave(tree->dev, pb::TreePick{}, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode, d_tokens,
-                                d_states_out, d_scores, stream);
-  return pb::launch_fuse(tree->dev, pb::TreePick{}, d_logp, 0, row_stride, d_states_in, d_last_tokens, alpha, 1, B, mode, d_tokens,
-                         d_states_out, d_scores, stream);
+  return launch_step(tree->dev, pb::TreePick{}, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode, d_tokens,
+                     d_states_out, d_scores, hip_stream);
 }
 
 int pb_fuse_step(const pb_tree* tree, const float* d_logp, int64_t row_stride, const int32_t* d_states_in,
@@ -344,11 +393,8 @@ int pb_fuse_step_beam(const pb_tree* tree, const float* d_logp, int64_t row_stri
   if (d_states_out == d_states_in) return PB_EINVAL;
   if (static_cast<int64_t>(K) * tree->dev.vocab_size >= INT32_MAX) return PB_EUNSUPPORTED;
   if (static_cast<int64_t>(U) * K > INT32_MAX) return PB_EUNSUPPORTED;
-  if (pb::beam_wave_ok(tree->dev, U, K))
-    return pb::launch_beam_wave(tree->dev, pb::TreePick{}, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens,
-                                d_parents, d_states_out, d_scores_out, static_cast<hipStream_t>(hip_stream));
-  return pb::launch_beam(tree->dev, pb::TreePick{}, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens, d_parents,
-                         d_states_out, d_scores_out, static_cast<hipStream_t>(hip_stream));
+  return launch_beam_step(tree->dev, pb::TreePick{}, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens,
+                          d_parents, d_states_out, d_scores_out, hip_stream);
 }
 
 int pb_forest_build(const pb_tree* const* trees, int32_t n_trees, pb_forest** out) {
@@ -415,7 +461,7 @@ int pb_score_forest(const pb_forest* forest, const int32_t* d_tree_ids, const in
   if (B == 0) return PB_OK;
   if (!d_tree_ids || !d_states || !d_scores) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
-  return pb::launch_score(forest->proto, pick, d_states, B, d_scores, d_next, static_cast<hipStream_t>(hip_stream));
+  return score_rows(forest->proto, pick, d_states, B, d_scores, d_next, static_cast<hipStream_t>(hip_stream));
 }
 
 int pb_fuse_step_forest(const pb_forest* forest, const float* d_logp, int64_t row_stride, const int32_t* d_tree_ids,
@@ -427,12 +473,8 @@ int pb_fuse_step_forest(const pb_forest* forest, const float* d_logp, int64_t ro
   if (!d_logp || !d_tree_ids || !d_states_in || !d_tokens || !d_states_out || !d_scores) return PB_EINVAL;
   if (row_stride < forest->proto.vocab_size) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pb::step_wave_ok(forest->proto))  // members share the vocabulary, so one answer fits all
-    return pb::launch_step_wave(forest->proto, pick, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode,
-                                d_tokens, d_states_out, d_scores, stream);
-  return pb::launch_fuse(forest->proto, pick, d_logp, 0, row_stride, d_states_in, d_last_tokens, alpha, 1, B, mode,
-                         d_tokens, d_states_out, d_scores, stream);
+  return launch_step(forest->proto, pick, d_logp, row_stride, d_states_in, d_last_tokens, alpha, B, mode, d_tokens,
+                     d_states_out, d_scores, hip_stream);
 }
 
 int pb_fuse_frames_forest(const pb_forest* forest, const float* d_logp, int64_t frame_stride, int64_t row_stride,
@@ -463,11 +505,8 @@ int pb_fuse_step_beam_forest(const pb_forest* forest, const float* d_logp, int64
   if (static_cast<int64_t>(K) * forest->proto.vocab_size >= INT32_MAX) return PB_EUNSUPPORTED;
   if (static_cast<int64_t>(U) * K > INT32_MAX) return PB_EUNSUPPORTED;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
-  if (pb::beam_wave_ok(forest->proto, U, K))  // (members share the vocabulary)
-    return pb::launch_beam_wave(forest->proto, pick, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens,
-                                d_parents, d_states_out, d_scores_out, static_cast<hipStream_t>(hip_stream));
-  return pb::launch_beam(forest->proto, pick, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens,
-                         d_parents, d_states_out, d_scores_out, static_cast<hipStream_t>(hip_stream));
+  return launch_beam_step(forest->proto, pick, d_logp, row_stride, d_hyp_scores, d_states_in, alpha, U, K, d_tokens, d_parents,
+                          d_states_out, d_scores_out, hip_stream);
 }
 
 int pb_validate(const pb_tree* tree) {

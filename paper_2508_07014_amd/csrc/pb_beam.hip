@@ -615,7 +615,7 @@ BeamPlan plan_beam(int V, int K, int64_t U) {
 }  // namespace
 
 bool beam_wave_ok(const DeviceTree& t, int32_t U, int32_t K) {
-  return t.p_root != nullptr && t.vocab_size >= 4 && U <= kMaxWorkgroups && plan_beam(t.vocab_size, K, U).lds <= static_cast<size_t>(g_beam_max_lds);
+  return t.p_root != nullptr && t.vocab_size >= 4 && plan_beam(t.vocab_size, K, U).lds <= static_cast<size_t>(g_beam_max_lds);
 }
 
 int launch_beam_wave(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride, const float* d_hyp,

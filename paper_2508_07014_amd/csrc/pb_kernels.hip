@@ -474,7 +474,7 @@ int launch_score(const DeviceTree& t, const TreePick& pick, const int32_t* d_sta
   const int64_t wgs = static_cast<int64_t>(B) * tiles;
   const int per = pick.table ? 1 : static_cast<int>(std::min<int64_t>(8, std::max<int64_t>(1, wgs / 16384)));
   const int64_t groups = (static_cast<int64_t>(B) + per - 1) / per;
-  if (groups * tiles > INT32_MAX) return PB_EUNSUPPORTED;
+  if (!grid_fits(groups * tiles, 256)) return PB_EUNSUPPORTED;
   const dim3 grid(static_cast<unsigned>(groups * tiles));
   const size_t lds = static_cast<size_t>(tile) * sizeof(u64);
   const bool vec = (V % 4 == 0) && aligned16(d_scores) && (d_next == nullptr || aligned16(d_next));
@@ -495,6 +495,7 @@ int launch_fuse(const DeviceTree& t, const TreePick& pick, const float* d_logp, 
   const size_t lds = static_cast<size_t>(chunk) * sizeof(u64);
   const bool vec = (V % 4 == 0) && (row_stride % 4 == 0) && (frame_stride % 4 == 0) && aligned16(d_logp);
   const dim3 grid(static_cast<unsigned>(B)), block(static_cast<unsigned>(pick_threads(V)));
+  if (!grid_fits(B, block.x)) return PB_EUNSUPPORTED;
   if (vec)
     hipLaunchKernelGGL(fuse_kernel<4>, grid, block, lds, stream, t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0,
                        alpha, T, B, sel, d_tokens, d_states, d_scores, chunk);

@@ -102,9 +102,12 @@ int launch_frames_wave(const DeviceTree& t, const TreePick& pick, const float* d
                        const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B, int sel,
                        int32_t* d_tokens, int32_t* d_states, float* d_scores, int32_t* d_patches, hipStream_t stream);
 
-// Workgroups of up to 1024 threads that one launch may have: a grid counts its threads in 32 bits.  Calls past it keep the
-// kernels with the smaller workgroups.
-constexpr int64_t kMaxWorkgroups = 0xffffffffll / 1024;
+// A grid counts its threads in 32 bits, and a larger one is cut without an error: the workgroups behind the cut never
+// run.  kMaxWorkgroups of any size fit; steps, beam steps and dense rows of more rows go out in slices, and the
+// multi-frame kernels, whose outputs interleave the hypotheses, check (grid_fits).
+constexpr int64_t kMaxThreads = 0xffffffffll;
+constexpr int64_t kMaxWorkgroups = kMaxThreads / 1024;
+inline bool grid_fits(int64_t groups, int64_t threads) { return groups <= kMaxThreads / threads; }
 
 // Whether the outputs of a multi-frame call lie apart from its start states, previous labels and tree ids and from each
 // other.  Those that do not go to launch_fuse, whose workgroups read what they start from before they write: the others

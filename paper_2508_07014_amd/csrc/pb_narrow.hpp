@@ -852,7 +852,7 @@ int launch_frames_row(const DeviceTree& t, const TreePick& pick, const float* d_
   const int64_t chains = static_cast<int64_t>(B) * nseg;
   const int waves = 4;
   const int64_t blocks = (chains + waves - 1) / waves;
-  if (blocks > INT32_MAX) return PB_EUNSUPPORTED;
+  if (!grid_fits(blocks, 64 * waves)) return PB_EUNSUPPORTED;
   const size_t lds = static_cast<size_t>(waves) * wave_lds_bytes(ROW);
   const bool forest = pick.table != nullptr;
 #define PB_SPEC(SEL, FOREST)                                                                                        \

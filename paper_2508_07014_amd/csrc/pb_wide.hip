@@ -666,7 +666,7 @@ int launch_frames_wide(const DeviceTree& t, const TreePick& pick, const float* d
   const int nseg = plan.nseg, seg_len = plan.seg_len;
   const int64_t chains = static_cast<int64_t>(B) * nseg;
   const int64_t blocks = (chains + waves - 1) / waves;
-  if (blocks > INT32_MAX) return PB_EUNSUPPORTED;
+  if (!grid_fits(blocks, 64 * waves)) return PB_EUNSUPPORTED;
 #define PB_SPEC(FULL, RING, SEL, FOREST)                                                                                 \
   hipLaunchKernelGGL((wide_spec_kernel<FULL, RING, SEL, FOREST>), dim3(static_cast<unsigned>(blocks)), dim3(64 * waves), \
                      lds, stream, t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B,      \

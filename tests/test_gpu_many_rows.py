@@ -53,3 +53,22 @@ def test_frames_of_one_row_repeated():
     want = ot.fuse_frames(np.broadcast_to(x[7].cpu().numpy(), (20, 1, V)).copy(), s0[7:8].cpu().numpy(), 0.5)
     assert np.array_equal(o[0][:20, 7].cpu().numpy(), want[0][:, 0]) and np.array_equal(o[1][:20, 7].cpu().numpy(), want[1][:, 0])
     pb.pb_free(tr)
+
+
+def test_step_of_seventy_million_hypotheses():
+    rng = np.random.default_rng(73000)
+    V, B = 5, 70_000_000
+    toks, offs, ot, tr = _tree(rng, V, 0, -1, 0, 0.0)
+    x = torch.randn((B, V), device=DEV)
+    st = torch.randint(0, ot.num_states, (B,), dtype=torch.int32, device=DEV)
+    o = [torch.full((B,), -7, dtype=torch.int32, device=DEV) for _ in range(2)] + [torch.zeros(B, device=DEV)]
+    print("step", V, B, flush=True)
+    pb.pb_fuse_step(tr, x, V, st, 0.5, B, o[0], o[1], o[2], 0)
+    torch.cuda.synchronize()
+    assert not bool((o[0] == -7).any()) and not bool((o[1] == -7).any())
+    rows = np.array([0, 1, 4_194_302, 4_194_303, 4_194_304, 67_108_863, 67_108_864, B - 1])
+    d_rows = torch.from_numpy(rows).to(DEV)
+    xs, ss = x[d_rows].cpu().numpy(), st[d_rows].cpu().numpy()
+    for g, w in zip(o, ot.fuse_step(xs, ss, 0.5)):
+        assert np.allclose(g[d_rows].cpu().numpy(), w, atol=1e-5, rtol=0)
+    pb.pb_free(tr)
