@@ -138,17 +138,19 @@ def load():
 
 
 def _bind_hot(lib):
+    calls = _CtypesCalls(lib)
     try:
         from . import _pbcall
     except ImportError:
-        return _CtypesCalls(lib)
+        return calls
     for name in HOT:
-        _pbcall.bind(name, C.cast(getattr(lib, name), C.c_void_p).value)
+        _pbcall.bind(name, C.cast(getattr(lib, name), C.c_void_p).value, getattr(calls, name))
     return _pbcall
 
 
 class _CtypesCalls:
-    """The same calls through ctypes, where the extension module has not been built."""
+    """The same calls through ctypes: where the extension module has not been built, and for arguments it leaves alone.
+    The first argument is the handle, the last the stream; the other pointers are device buffers."""
 
     def __init__(self, lib):
         for name in HOT:
@@ -156,8 +158,16 @@ class _CtypesCalls:
 
     @staticmethod
     def _call(fn):
-        buffers = [t is C.c_void_p for t in fn.argtypes]
-        return lambda *args: fn(*[_dptr(a) if is_buffer else a for a, is_buffer in zip(args, buffers)])
+        buffers = [i for i, t in enumerate(fn.argtypes) if t is C.c_void_p][1:-1]
+
+        def call(*args):
+            a = list(args)
+            if len(a) == len(fn.argtypes):
+                for i in buffers:
+                    a[i] = _dptr(a[i])
+                a[-1] = a[-1] or None
+            return fn(*a)
+        return call
 
 
 def strerror(code: int) -> str:

@@ -2,10 +2,12 @@
 //
 // A step takes 3 to 5 us on the GPU, and marshalling its ten arguments through ctypes took about 2.2 us of host time
 // (a Python-level conversion per device buffer, then ctypes' own) on top of the launch, so the calls were bound by the
-// host.  Here an argument is converted by the type the C declaration gives it: device buffers are None, anything with a
-// data_ptr() or an address; the interpreter lock is released during the call, as ctypes does.  (0.8 us a call instead of
-// 2.2; greedy steps back to back, B = 32, V = 1024: 5.1 -> 4.0 us.)  The functions are bound
-// by address to the library that the package has loaded, and return its status code.
+// host.  Here the arguments such a caller passes are converted directly: device buffers as None, an int address or
+// anything whose data_ptr() is an int, numbers as int and float; the interpreter lock is released during the call, as
+// ctypes does.  (0.8 us a call instead of 2.2; greedy steps back to back, B = 32, V = 1024: 5.1 -> 4.0 us.)  A call with
+// an argument of any other kind -- numpy scalars, ctypes objects, something wrong -- goes to the ctypes form of the entry
+// point as it is, so both accept and refuse the same.  The functions are bound by address to the library that the
+// package has loaded, and return its status code.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -19,36 +21,20 @@ namespace {
 
 PyObject* g_data_ptr = nullptr;  // interned method name
 
-bool as_bits(PyObject* o, unsigned long long& out) {  // an integer or an object with __index__
-  if (PyLong_Check(o)) {
-    out = PyLong_AsUnsignedLongLongMask(o);
-  } else {
-    PyObject* i = PyNumber_Index(o);
-    if (!i) return false;
-    out = PyLong_AsUnsignedLongLongMask(i);
-    Py_DECREF(i);
-  }
+// The conversions: false (with or without a Python error set) for an argument that is not of the plain kind.
+bool get(PyObject* o, unsigned long long& out) {  // (bits of an int of any size, as ctypes takes them)
+  if (!PyLong_Check(o)) return false;
+  out = PyLong_AsUnsignedLongLongMask(o);
   return !(out == ~0ull && PyErr_Occurred());
 }
-
 template <typename T>
 bool get(PyObject* o, T*& out) {
   unsigned long long bits = 0;
-  if (o == Py_None) {
-    out = nullptr;
-    return true;
-  }
-  if (PyLong_Check(o)) {
-    if (!as_bits(o, bits)) return false;
-  } else {
+  if (o != Py_None && !get(o, bits)) {
+    if (PyLong_Check(o)) return false;
     PyObject* r = PyObject_CallMethodNoArgs(o, g_data_ptr);
-    if (!r && PyErr_ExceptionMatches(PyExc_AttributeError)) {
-      PyErr_Clear();
-      r = PyNumber_Long(o);
-    }
-    if (!r) return false;
-    const bool ok = as_bits(r, bits);
-    Py_DECREF(r);
+    const bool ok = r && get(r, bits);
+    Py_XDECREF(r);
     if (!ok) return false;
   }
   out = reinterpret_cast<T*>(static_cast<uintptr_t>(bits));
@@ -56,17 +42,18 @@ bool get(PyObject* o, T*& out) {
 }
 bool get(PyObject* o, int32_t& out) {
   unsigned long long bits = 0;
-  if (!as_bits(o, bits)) return false;
+  const bool ok = get(o, bits);
   out = static_cast<int32_t>(bits);
-  return true;
+  return ok;
 }
 bool get(PyObject* o, int64_t& out) {
   unsigned long long bits = 0;
-  if (!as_bits(o, bits)) return false;
+  const bool ok = get(o, bits);
   out = static_cast<int64_t>(bits);
-  return true;
+  return ok;
 }
 bool get(PyObject* o, float& out) {
+  if (!PyFloat_Check(o) && !PyLong_Check(o)) return false;
   const double d = PyFloat_AsDouble(o);
   out = static_cast<float>(d);
   return !(d == -1.0 && PyErr_Occurred());
@@ -75,17 +62,21 @@ bool get(PyObject* o, float& out) {
 template <int ID, typename... A>
 struct Entry {
   static inline int (*fn)(A...) = nullptr;
+  static inline PyObject* other = nullptr;  // the ctypes form
   template <std::size_t... I>
   static bool unpack(PyObject* const* args, std::tuple<A...>& v, std::index_sequence<I...>) {
     return (get(args[I], std::get<I>(v)) && ...);
   }
   static PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    if (n != static_cast<Py_ssize_t>(sizeof...(A)) || !fn) {
-      PyErr_Format(PyExc_TypeError, "expected %zu arguments of a bound entry point, got %zd", sizeof...(A), n);
+    if (!fn) {
+      PyErr_SetString(PyExc_RuntimeError, "the entry point is not bound");
       return nullptr;
     }
     std::tuple<A...> v;
-    if (!unpack(args, v, std::index_sequence_for<A...>{})) return nullptr;
+    if (n != static_cast<Py_ssize_t>(sizeof...(A)) || !unpack(args, v, std::index_sequence_for<A...>{})) {
+      PyErr_Clear();
+      return PyObject_Vectorcall(other, args, static_cast<std::size_t>(n), nullptr);
+    }
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = std::apply(fn, v);
@@ -102,14 +93,17 @@ Entry<ID, A...> entry_of(int (*)(A...));
   X(9, pb_fuse_step_forest) X(10, pb_fuse_frames_forest) X(11, pb_fuse_step_beam_forest)
 #define PB_ENTRY(id, name) decltype(entry_of<id>(&name))
 
-// bind(name, address): binds an entry point.
+// bind(name, address, other): binds an entry point and its ctypes form.
 PyObject* bind(PyObject*, PyObject* args) {
   const char* name = nullptr;
   unsigned long long address = 0;
-  if (!PyArg_ParseTuple(args, "sK", &name, &address)) return nullptr;
+  PyObject* other = nullptr;
+  if (!PyArg_ParseTuple(args, "sKO", &name, &address, &other)) return nullptr;
 #define PB_BIND(id, f)                                                                             \
   if (PyUnicode_CompareWithASCIIString(PyTuple_GET_ITEM(args, 0), #f) == 0) {                      \
     PB_ENTRY(id, f)::fn = reinterpret_cast<decltype(&f)>(static_cast<uintptr_t>(address));         \
+    Py_INCREF(other);                                                                              \
+    Py_XSETREF(PB_ENTRY(id, f)::other, other);                                                     \
     Py_RETURN_NONE;                                                                                \
   }
   PB_ENTRIES(PB_BIND)
@@ -122,7 +116,7 @@ PyMethodDef g_methods[] = {
 #define PB_METHOD(id, f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&PB_ENTRY(id, f)::call)), METH_FASTCALL, nullptr},
     PB_ENTRIES(PB_METHOD)
 #undef PB_METHOD
-    {"bind", bind, METH_VARARGS, "bind(name, address): binds an entry point of the loaded library."},
+    {"bind", bind, METH_VARARGS, "bind(name, address, other): binds an entry point of the loaded library."},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_pbcall", "Entry points of libpb.so by address.", -1, g_methods,
