@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -16,6 +17,7 @@ SOURCES = ["pb_narrow_1024.hip", "pb_narrow_any.hip", "pb_narrow_1280.hip", "pb_
            "pb_wide.hip", "pb_rows.hip", "pb_beam.hip", "pb_frames.hip", "pb_kernels.hip", "pb_compile.cpp", "pb_api.hip"]
 # the Python side of the entry points that are called once per step (host code only, loads beside the library)
 CALL_LIB = os.path.join(PKG, "_pbcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+CALL_SOURCES = [os.path.join(CSRC, "pb_python.cpp"), os.path.join(ROOT, "include", "pb.h")]
 HEADERS = ["pb_tree.hpp", "pb_kernels.hpp", "pb_wave.hpp", "pb_chunk.hpp", "pb_narrow.hpp", os.path.join(ROOT, "include", "pb.h")]
 OBJDIR = os.path.join(PKG, "_build")
 
@@ -39,16 +41,21 @@ def link_command(objs, out: str = LIB) -> list:
     return ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out] + list(objs)
 
 
+def _older(built: str, deps) -> bool:
+    return not os.path.exists(built) or any(os.path.getmtime(d) > os.path.getmtime(built) for d in deps)
+
+
 def stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
+    """Whether the library or (where it can be built) the extension module is missing or older than its sources."""
     deps = [os.path.join(CSRC, s) for s in SOURCES] + [h if os.path.isabs(h) else os.path.join(CSRC, h) for h in HEADERS]
-    return any(os.path.getmtime(d) > t for d in deps)
+    return _older(LIB, deps) or (calls_compiler() is not None and _older(CALL_LIB, CALL_SOURCES))
 
 
 def build(force: bool = True, verbose: bool = False, extra=(), out: str = LIB) -> str:
-    """Compiles the library (one hipcc process per source, side by side); with force=False only when it is missing."""
+    """Compiles the library (one hipcc process per source, side by side) and the extension module; with force=False each
+    only where it is missing."""
+    if out == LIB and (force or not os.path.exists(CALL_LIB)):
+        build_calls(verbose)
     if not force and os.path.exists(out):
         return out
     from concurrent.futures import ThreadPoolExecutor
@@ -62,8 +69,6 @@ def build(force: bool = True, verbose: bool = False, extra=(), out: str = LIB) -
             print(" ".join(cmd), file=sys.stderr)
         subprocess.run(cmd, check=True)
 
-    if out == LIB:
-        build_calls(verbose)
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
         list(pool.map(one, zip(SOURCES, objs)))
     cmd = link_command(objs, out)
@@ -73,13 +78,22 @@ def build(force: bool = True, verbose: bool = False, extra=(), out: str = LIB) -
     return out
 
 
-def build_calls(verbose: bool = False):
-    """Compiles the extension module; None where this Python has no headers (the binding then goes through ctypes)."""
-    include = sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(include, "Python.h")):
+def calls_compiler():
+    """The host compiler of the extension module; None where it cannot be built (no compiler, or a Python without
+    headers): the binding then goes through ctypes, which is slower and otherwise the same."""
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
         return None
-    cmd = ["g++", "-shared", "-fPIC", "-O2", "-std=c++17", "-Wall", "-Wextra", "-I", include, "-I", os.path.join(ROOT, "include"),
-           "-o", CALL_LIB, os.path.join(CSRC, "pb_python.cpp")]
+    return shutil.which("g++") or shutil.which("c++")
+
+
+def build_calls(verbose: bool = False):
+    """Compiles the extension module; says so and returns None where it cannot be built."""
+    cxx = calls_compiler()
+    if cxx is None:
+        print("no host compiler or Python headers: the per-step calls go through ctypes", file=sys.stderr)
+        return None
+    cmd = [cxx, "-shared", "-fPIC", "-O2", "-std=c++17", "-Wall", "-Wextra", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), "-o", CALL_LIB, CALL_SOURCES[0]]
     if verbose:
         print(" ".join(cmd), file=sys.stderr)
     subprocess.run(cmd, check=True)
