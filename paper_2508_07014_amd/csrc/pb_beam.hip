@@ -10,13 +10,19 @@
 //    total, is bounded from below (joint_bound).
 //  * Totals that reach the bound -- K and a few more -- go to a list in LDS, and their ranks come from counting: a
 //    thread per entry compares it with all others by (total descending, k * V + v ascending).
-//  * A list that overflows (more totals than it holds tie with the bound: an utterance of dead beams) is replaced by K
-//    rounds of arg-max over all totals (select_by_rounds).
+//  * A list that overflows (rows that are flat, or tie: more totals reach the bound than it holds) is itself a sample of
+//    the totals: the K-th best of its entries, by the same order, is a higher bound, and the totals are collected again
+//    until they fit (raised_bound).
+//  * An utterance of dead beams (hypothesis scores of -inf: a finished one in a batch, mostly) has only totals of -inf, so
+//    its survivors are the first K flat indices; the rows are not looked at (put_dead).
 //
 // U x K, V: 32 x 4, 1024 7.8 -> 7.0 us against a kernel with a wave per beam and K rounds of arg-max in each; against the
 // workgroup-per-utterance row build (launch_beam) 16 x 8, 1025, a table of trees 35.9 -> 8.2, 32 x 8, 8192 81.9 -> 17.8,
-// 16 x 16, 50000 1130 -> 99.  With thousands of utterances of one or two beams (4096 x 2, V = 1024) the wave-per-beam
-// kernel was up to 6 % faster (14.5 us against 15.4), with four beams it was slower (34.4 against 27).
+// 16 x 16, 50000 1130 -> 99.  With one dead utterance among
+// 32 a step takes what it takes without (32 x 8, 8192: 17 us; K rounds of arg-max over its rows took 182), with constant
+// rows everywhere about twice that (38; rounds 187).  With thousands of utterances of one or two beams (4096 x 2,
+// V = 1024) the wave-per-beam kernel was up to 6 % faster (14.5 us against 15.4), with four beams it was slower (34.4
+// against 27).
 //
 // Rows whose share of a wave fits its registers are read once (beam_regs_kernel); longer ones are streamed, with the
 // maximum of every chunk kept, and only the chunks that reach the bound are read again (beam_stream_kernel).
@@ -58,8 +64,7 @@ __device__ __forceinline__ u64 cand_key(float total, int flat) {
 
 struct Small {  // the fixed part of the workgroup's LDS
   unsigned lane_best[64];
-  u64 best[kBeamWaves];
-  float hyp[kBeamMax];  // (the outputs may be the hypothesis scores' own buffer)
+  int child[kBeamMax];  // put_dead: the arcs of a beam's first tokens
   int count;
 };
 struct Shared {  // the list of survivors (the first part of the dynamic LDS) and the fixed part
@@ -87,6 +92,27 @@ __device__ __forceinline__ void push(const Shared& sh, float total, int k, int v
     sh.entry[i] = make_int4(__float_as_int(total), v, k, child);
   }
 }
+
+__device__ __forceinline__ bool overflowed(const Shared& sh) {
+  return __hip_atomic_load(&sh.s->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > sh.cap;
+}
+// Of a list of n >= 64 entries (a barrier lies behind the last push): a key that at least K of them reach and that is
+// higher than most of them: the K-th largest of the maxima of 64 disjoint parts of the list.
+__device__ __forceinline__ u64 raised_bound(const Shared& sh, int lane, int n, int K) {
+  u64 best = 0;
+  for (int i = lane; i < n; i += 64) best = sh.key[i] > best ? sh.key[i] : best;
+  int rank = 0;  // (the keys are all different)
+#pragma unroll 8
+  for (int l = 0; l < 64; ++l) {
+    const u64 o = (static_cast<u64>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(best >> 32), l))) << 32) |
+                  static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(best), l));
+    rank += o > best ? 1 : 0;
+  }
+  const int from = first_lane(__ballot(rank == K - 1));
+  return (static_cast<u64>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(best >> 32), from))) << 32) |
+         static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(best), from));
+}
+__device__ __forceinline__ float key_total(u64 key) { return ukey_val(static_cast<unsigned>(key >> 32)); }
 
 // The bound.  The lanes' maxima are collected in 64 slots (as keys, zero before the barrier that precedes post_lane; the
 // lanes of a wave are rotated against those of the others, so that rows too short for all lanes still fill the slots).
@@ -243,23 +269,43 @@ __device__ __forceinline__ float piece_max(const float (&x)[NS]) {  // (NaN entr
 
 // Puts the survivors of a piece (pmax: the lane's largest total of it) on the list: a bit per slot, then a turn of a
 // loop per slot that has any.  (The push written out for every slot made 13 to 34 KB of code per kernel, and a step of
-// few utterances waits for its instructions, too; a loop over all slots took 0.5 us longer.)
-template <int NS>
-__device__ __forceinline__ void push_piece(const Shared& sh, const TreeView& t, int k, int cb, int lane, float bound,
-                                           float pmax, const float (&x)[NS]) {
-  if (__ballot(pmax >= bound) == 0) return;
+// few utterances waits for its instructions, too; a loop over all slots took 0.5 us longer.)  MAY_STOP: once the list has
+// overflowed the rest is left out.  (Not the first time: looking at the count costs a step of 16 beams 1.5 %.)
+template <bool MAY_STOP, int NS>
+__device__ __forceinline__ void push_hits(const Shared& sh, const TreeView& t, int k, int cb, int lane, unsigned hits,
+                                          const float (&x)[NS]) {
   float y[NS];  // (a copy: indexed by a number that is not a constant, it must not take the whole row out of registers)
-  unsigned hits = 0;
 #pragma unroll
-  for (int j = 0; j < NS; ++j) {
-    y[j] = x[j];
-    hits |= x[j] >= bound ? 1u << j : 0u;
-  }
+  for (int j = 0; j < NS; ++j) y[j] = x[j];
   for (u64 left = __ballot(hits != 0); left != 0; left = __ballot(hits != 0)) {
     const int j = __builtin_ctz(__builtin_amdgcn_readlane(static_cast<int>(hits), first_lane(left)));
     if ((hits >> j) & 1u) push(sh, y[j], k, pos_token<false>(t, cb + tok_of(j, lane)), t.V, -1);
     hits &= ~(1u << j);
+    if (MAY_STOP && overflowed(sh)) break;
   }
+}
+template <int NS>
+__device__ __forceinline__ void push_piece(const Shared& sh, const TreeView& t, int k, int cb, int lane, float bound,
+                                           float pmax, const float (&x)[NS]) {
+  if (__ballot(pmax >= bound) == 0) return;
+  unsigned hits = 0;
+#pragma unroll
+  for (int j = 0; j < NS; ++j) hits |= x[j] >= bound ? 1u << j : 0u;
+  push_hits<false>(sh, t, k, cb, lane, hits, x);
+}
+// The same for a bound on (total, flat index).
+template <int NS>
+__device__ __forceinline__ void push_piece(const Shared& sh, const TreeView& t, int k, int cb, int lane, u64 bound,
+                                           float pmax, const float (&x)[NS]) {
+  const float total = key_total(bound);
+  if (__ballot(pmax >= total) == 0 || overflowed(sh)) return;
+  unsigned hits = 0;
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    const u64 key = cand_key(x[j], k * t.V + pos_token<false>(t, cb + tok_of(j, lane)));
+    hits |= x[j] >= total && key >= bound ? 1u << j : 0u;
+  }
+  push_hits<true>(sh, t, k, cb, lane, hits, x);
 }
 
 // The arcs of a wave's beams: every lane keeps its best and the value of its second best, so that a second walk is
@@ -277,10 +323,29 @@ struct ArcBest {
   }
 };
 
-// The list is complete (a barrier lies behind the last push): rank every entry by counting and write the first K.
-__device__ __forceinline__ void write_ranked(const Shared& sh, const TreeView& t, int u, int K, const int32_t* states_in,
-                                             const BeamOut& out) {
-  const int n = sh.s->count;
+// A long list costs in ranks what it has saved in passes (1024 entries: 20 us): it is cut above a raised bound first.
+constexpr int kRankMost = 192;
+__device__ __forceinline__ int shorten(const Shared& sh, int lane, int n, int K) {
+  const int i = threadIdx.x;  // (a list that is long has no more entries than the workgroup has threads)
+  const u64 bound = raised_bound(sh, lane, n, K), key = i < n ? sh.key[i] : 0;
+  const int4 e = i < n ? sh.entry[i] : make_int4(0, 0, 0, 0);
+  __syncthreads();
+  if (threadIdx.x == 0) sh.s->count = 0;
+  __syncthreads();
+  if (key >= bound) {
+    const int at = atomicAdd(&sh.s->count, 1);
+    sh.key[at] = key;
+    sh.entry[at] = e;
+  }
+  __syncthreads();
+  return sh.s->count;
+}
+
+// The list is complete with n entries (a barrier lies behind the last push): rank every entry by counting and write the
+// first K.
+__device__ __forceinline__ void write_ranked(const Shared& sh, const TreeView& t, int u, int n, int K,
+                                             const int32_t* states_in, const BeamOut& out) {
+  if (n > kRankMost) n = shorten(sh, threadIdx.x & 63, n, K);  // (uniform)
 #pragma unroll 1
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const u64 key = sh.key[i];
@@ -296,72 +361,45 @@ __device__ __forceinline__ void write_ranked(const Shared& sh, const TreeView& t
   for (int r = n + static_cast<int>(threadIdx.x); r < K; r += blockDim.x) out.put(u * K + r, -1, -1, -1, NAN);  // (NaN rows)
 }
 
-// K rounds of arg-max over all totals, each over what comes after the winner before it: any input, no list.  (Rows as
-// chunks with clamped loads; the marks of a beam have room for whole chunks.)
-__device__ void select_by_rounds(const Shared& sh, const TreeView& t, const float* __restrict__ logp, int64_t row_stride,
-                                 const int32_t* __restrict__ states_in, float alpha, int u,
-                                 int K, unsigned* marks, int words, int lane, int wave, int nwaves, const BeamOut& out) {
-  const int nch = (t.V + kChunk - 1) / kChunk;
-  u64 prev = ~0ull;
-#pragma unroll 1
-  for (int r = 0; r < K; ++r) {
-    u64 best = 0;
-    int child = -1;
-    float value = 0.0f;
-#pragma unroll 1
-    for (int k = wave; k < K; k += nwaves) {
-      const Beam b = beam_at(t, k, uniform_i(states_in[u * K + k]), uniform_f(sh.s->hyp[k]));
-      const float* row = logp + static_cast<size_t>(u * K + k) * row_stride;
-      unsigned* m = marks + static_cast<size_t>(k) * words;
-      tags_clear_n(m, words, lane);
-      walk_mark(t, b, row, alpha, m, lane, [&](float total, int tok, int next) {
-        const u64 key = total == total ? cand_key(total, k * t.V + tok) : 0;
-        if (key < prev && key > best) {
-          best = key;
-          child = next;
-          value = total;
-        }
-      });
-#pragma unroll 1
-      for (int ch = 0; ch < nch; ++ch) {
-        float x[16], rw[16];
-        load_row<false>(row, ch * kChunk, t.V, lane, x);
-        load_row<false>(t.root_score, ch * kChunk, t.V, lane, rw);
-        piece_totals(t, b, ch * kChunk, alpha, lane, rw, x);
-        drop_marked(m, ch * kChunk, lane, x);
-#pragma unroll 1
-        for (int j = 0; j < 16; ++j) {
-          const u64 key = x[j] == x[j] ? cand_key(x[j], k * t.V + pos_token<false>(t, ch * kChunk + tok_of(j, lane))) : 0;
-          if (key < prev && key > best) {
-            best = key;
-            child = -1;
-            value = x[j];
-          }
-        }
-      }
-    }
-    u64 wb = best;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const u64 o = __shfl_xor(wb, off);
-      wb = o > wb ? o : wb;
-    }
-    __syncthreads();  // (the round before has read its winners)
-    if (lane == 0) sh.s->best[wave] = wb;
+// An overflowed list is collected again above a raised bound, until it fits: `again(bound)` pushes every candidate that
+// reaches the bound (by key) and may stop once the list overflows.  Called by all threads, after the barrier behind the
+// last push; ends with one and returns the number of entries.
+template <typename Again>
+__device__ __forceinline__ int collect_again(const Shared& sh, int lane, int K, Again&& again) {
+  int n;
+  while ((n = sh.s->count) > sh.cap) {  // (uniform)
+    const u64 bound = raised_bound(sh, lane, sh.cap, K);
+    __syncthreads();  // every wave has read the list
+    if (threadIdx.x == 0) sh.s->count = 0;
     __syncthreads();
-    u64 top = 0;
+    again(bound);
+    __syncthreads();
+  }
+  return n;
+}
+
+// Survivors of an utterance whose hypothesis scores are all -inf: flat indices 0 .. K - 1, with totals of -inf.  One wave.
+// The arcs of a state ascend by token, so those on the first n tokens are among its first n.
+__device__ __forceinline__ void put_dead(const Shared& sh, const TreeView& t, int u, int K, const int32_t* states_in, int lane,
+                                         const BeamOut& out) {
 #pragma unroll 1
-    for (int w = 0; w < nwaves; ++w) top = sh.s->best[w] > top ? sh.s->best[w] : top;
-    if (top == 0) {  // fewer than K totals are numbers
-      if (threadIdx.x == 0) out.put(u * K + r, -1, -1, -1, NAN);
-    } else if (best == top) {
-      const int flat = static_cast<int>(~static_cast<unsigned>(top));
-      const int k = flat / t.V, v = flat - k * t.V;
-      int next = child;
-      if (child < 0) next = v == t.blank || v == t.eos ? states_in[u * K + k] : t.root_next[v];
-      out.put(u * K + r, v, k, next, value);
+  for (int k = 0; k * t.V < K; ++k) {
+    const int s = uniform_i(states_in[u * K + k]), n = min(t.V, K - k * t.V);
+    if (lane < n) sh.s->child[lane] = -1;
+#pragma unroll 1
+    for (int x = s; x != 0;) {  // deepest state first
+      const Rec r = load_rec(t, x);
+      if (lane < min(r.count, n)) {
+        const int v = t.arc[r.begin + lane].token;
+        if (v < n && sh.s->child[v] < 0) sh.s->child[v] = r.begin + lane + 1;
+      }
+      x = uniform_i(r.fail);
     }
-    prev = top == 0 ? 1 : top;  // (1: nothing comes after)
+    if (lane < n) {
+      int next = sh.s->child[lane];
+      if (next < 0) next = lane == t.blank || lane == t.eos ? s : t.root_next[lane];
+      out.put(u * K + k * t.V + lane, lane, k, next, -INFINITY);
+    }
   }
 }
 
@@ -389,6 +427,9 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_regs_kernel(
     int32_t* __restrict__ tokens, int32_t* __restrict__ parents, int32_t* __restrict__ states_out,
     float* scores_out, DeviceTree dt, TreePick pick) {
   constexpr int PS = NS < 16 ? NS : 16, NP = NS / PS;  // positions per lane of a piece, pieces
+  // Whether the totals stay in registers for a list that overflows: with 16 positions that costs every step registers
+  // (96 instead of 68, U x K, V = 4096 x 8, 1024 60 us instead of 49).
+  constexpr bool KEPT = NS <= 8;
   extern __shared__ __align__(16) char lds[];
   __shared__ Small small;
   const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
@@ -399,10 +440,10 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_regs_kernel(
 #pragma unroll
   for (int c = 0; c < NP; ++c) load_row<false>(row, P0 + c * 64 * PS, V, lane, x[c]);
   const int sk = states_in[u * K + min(lane, K - 1)];  // every wave sees all K states
-  const float hyp_in = hyp[u * K + k];
+  const float hk = hyp[u * K + min(lane, K - 1)];    // ... and hypothesis scores
   __builtin_amdgcn_sched_barrier(0);  // (all of the above is in flight before the first wait)
   const Shared sh = shared_at(lds, &small, nwaves);
-  unsigned* marks = reinterpret_cast<unsigned*>(lds + list_bytes(nwaves));
+  unsigned* marks = reinterpret_cast<unsigned*>(lds + (ONE ? 0 : list_bytes(nwaves)));
   const BeamOut out{tokens, parents, states_out, scores_out};
   const int slot = threadIdx.x;
   DeviceTree mine = dt;
@@ -416,10 +457,14 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_regs_kernel(
   if constexpr (FOREST) load_row<false>(t.root_score, P0, V, lane, rw);
   if (slot == 0) sh.s->count = 0;
   if (slot < 64) sh.s->lane_best[slot] = 0;
-  if (slot < K) sh.s->hyp[slot] = hyp[u * K + slot];
   unsigned* m = marks + k * words;
   const bool bad = __ballot(!valid_state(t, sk)) != 0;
-  const Beam b = beam_at(t, k, bad ? 0 : __builtin_amdgcn_readlane(sk, k), uniform_f(hyp_in));
+  if (!bad && __ballot(hk != -INFINITY) == 0) {  // (a wave that reads `hyp` after this has overwritten it sees the same)
+    if (wave == 0) put_dead(sh, t, u, K, states_in, lane, out);
+    return;
+  }
+  const Beam b = beam_at(t, k, bad ? 0 : __builtin_amdgcn_readlane(sk, k),
+                         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hk), k)));
   ArcBest arcs;
   if (part == 0 && b.s != 0) {
     tags_clear_n(m, words, lane);
@@ -440,28 +485,34 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_regs_kernel(
     top = max2(top, pmax[c]);
   }
   if constexpr (ONE) {
-    // the best total itself, whose lowest token needs no list
+    // the best total itself, of which only the lowest token is wanted: no list
     const float bound = ukey_val(wave_max_u(ukey(top)));
-    if (__ballot(arcs.second >= bound) == 0) {
-      int flat = arcs.child >= 0 && arcs.best == bound ? arcs.tok : INT_MAX, child = arcs.child;
-#pragma unroll
-      for (int c = NP - 1; c >= 0; --c)
-#pragma unroll
-        for (int j = PS - 1; j >= 0; --j) {
-          const int v = pos_token<false>(t, P0 + c * 64 * PS + tok_of(j, lane));
-          if (x[c][j] == bound && v < flat) {
-            flat = v;
-            child = -1;
-          }
+    int flat = arcs.child >= 0 && arcs.best == bound ? arcs.tok : INT_MAX, child = arcs.child;
+    if (b.s != 0 && __ballot(arcs.second >= bound) != 0) {
+      walk_clear(t, b, row, alpha, m, lane, [&](float total, int tok, int c) {
+        if (total == bound && tok < flat) {
+          flat = tok;
+          child = c;
         }
-      const int v = wave_min_nn(flat);
-      if (bad || v == INT_MAX) {
-        if (lane == 0) out.put(u, -1, -1, -1, NAN);  // (no number in the row, for one)
-      } else if (flat == v) {
-        out.put(u, v, 0, child >= 0 ? child : v == t.blank || v == t.eos ? b.s : t.root_next[v], bound);
-      }
-      return;
+      });
     }
+#pragma unroll
+    for (int c = NP - 1; c >= 0; --c)
+#pragma unroll
+      for (int j = PS - 1; j >= 0; --j) {
+        const int v = pos_token<false>(t, P0 + c * 64 * PS + tok_of(j, lane));
+        if (x[c][j] == bound && v < flat) {
+          flat = v;
+          child = -1;
+        }
+      }
+    const int v = wave_min_nn(flat);
+    if (bad || v == INT_MAX) {
+      if (lane == 0) out.put(u, -1, -1, -1, NAN);  // (no number in the row, for one)
+    } else if (flat == v) {
+      out.put(u, v, 0, child >= 0 ? child : v == t.blank || v == t.eos ? b.s : t.root_next[v], bound);
+    }
+    return;
   }
   post_lane(sh, lane, wave, nwaves, top);
   __syncthreads();
@@ -480,10 +531,34 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_regs_kernel(
   __syncthreads();
   if (bad) {
     if (slot < K) out.put(u * K + slot, -1, -1, -1, NAN);
-  } else if (sh.s->count > sh.cap)
-    select_by_rounds(sh, t, logp, row_stride, states_in, alpha, u, K, marks, words, lane, wave, nwaves, out);
-  else
-    write_ranked(sh, t, u, K, states_in, out);
+    return;
+  }
+  const int n = collect_again(sh, lane, K, [&](u64 floor) {
+    const float total = key_total(floor);
+    if (part == 0 && b.s != 0 && (!KEPT || __ballot(arcs.second >= total) != 0)) {
+      tags_clear_n(m, words, lane);
+      walk_mark(t, b, row, alpha, m, lane, [&](float v, int tok, int child) {
+        if (v >= total && cand_key(v, k * V + tok) >= floor) push(sh, v, k, tok, V, child);
+      });
+    } else if (arcs.child >= 0 && arcs.best >= total && cand_key(arcs.best, k * V + arcs.tok) >= floor) {
+      push(sh, arcs.best, k, arcs.tok, V, arcs.child);
+    }
+    if constexpr (KEPT) {
+      push_piece(sh, t, k, P0, lane, floor, pmax[0], x[0]);
+    } else {  // from memory again, 256 positions at a time
+      __syncthreads();  // the marks are set
+#pragma unroll 1
+      for (int p0 = P0; p0 < P0 + 64 * NS; p0 += 256) {
+        float y[4], ry[4];
+        load_row<false>(row, p0, V, lane, y);
+        load_row<false>(t.root_score, p0, V, lane, ry);
+        piece_totals(t, b, p0, alpha, lane, ry, y);
+        if (b.s != 0) drop_marked(m, p0, lane, y);
+        push_piece(sh, t, k, p0, lane, floor, piece_max(y), y);
+      }
+    }
+  });
+  write_ranked(sh, t, u, n, K, states_in, out);
 }
 
 // ---- rows streamed -------------------------------------------------------------------------------------------------------
@@ -503,6 +578,10 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_stream_kernel(
   DeviceTree mine = dt;
   if (!utterance_ok(pick, mine, states_in, u, K, lane, out)) return;
   const TreeView t = make_view(mine);
+  if (__ballot(hyp[u * K + min(lane, K - 1)] != -INFINITY) == 0) {
+    if (wave == 0) put_dead(sh, t, u, K, states_in, lane, out);
+    return;
+  }
   const int nch = (t.V + kChunk - 1) / kChunk, words = nch * kTagWords, last_ch = nch - 1;
   float* cmax = reinterpret_cast<float*>(marks + static_cast<size_t>(K) * words);  // [K][nch]
   const int parts = K < nwaves ? nwaves / K : 1, k0 = wave / parts, part = wave - k0 * parts;
@@ -511,7 +590,6 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_stream_kernel(
   const int slot = threadIdx.x;
   if (slot == 0) sh.s->count = 0;
   if (slot < 64) sh.s->lane_best[slot] = 0;
-  if (slot < K) sh.s->hyp[slot] = hyp[u * K + slot];
   ArcBest arcs;
   if (part == 0) {
     for (int k = k0; k < K; k += nwaves) {
@@ -552,21 +630,25 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_stream_kernel(
   post_lane(sh, lane, wave, nwaves, top);
   __syncthreads();
   const float bound = joint_bound(sh, lane, K);
-  for (int k = k0; k < K; k += nwaves) {
-    const Beam b = beam(k);
-    const unsigned* m = marks + static_cast<size_t>(k) * words;
+  auto push_rows = [&](auto floor, float least) {  // what reaches `floor`, of the chunks whose best total is not below `least`
+    for (int k = k0; k < K; k += nwaves) {
+      const Beam b = beam(k);
+      const unsigned* m = marks + static_cast<size_t>(k) * words;
 #pragma unroll 1
-    for (int ch = part; ch < nch; ch += parts) {
-      if (uniform_f(cmax[k * nch + ch]) >= bound) {
-        float x[16], rw[16];
-        load_row<false>(row_of(k), ch * kChunk, t.V, lane, x);
-        load_row<false>(t.root_score, ch * kChunk, t.V, lane, rw);
-        piece_totals(t, b, ch * kChunk, alpha, lane, rw, x);
-        if (b.s != 0) drop_marked(m, ch * kChunk, lane, x);
-        push_piece(sh, t, k, ch * kChunk, lane, bound, piece_max(x), x);
+      for (int ch = part; ch < nch; ch += parts) {
+        if (uniform_f(cmax[k * nch + ch]) >= least) {
+          float x[16], rw[16];
+          load_row<false>(row_of(k), ch * kChunk, t.V, lane, x);
+          load_row<false>(t.root_score, ch * kChunk, t.V, lane, rw);
+          piece_totals(t, b, ch * kChunk, alpha, lane, rw, x);
+          if (b.s != 0) drop_marked(m, ch * kChunk, lane, x);
+          push_piece(sh, t, k, ch * kChunk, lane, floor, piece_max(x), x);
+          if (sizeof(floor) == sizeof(u64) && overflowed(sh)) return;
+        }
       }
     }
-  }
+  };
+  push_rows(bound, bound);
   __syncthreads();  // (the second walk clears marks that the other waves of the beam have read until here)
   if (part == 0 && __ballot(arcs.second >= bound) != 0) {
     for (int k = k0; k < K; k += nwaves)
@@ -578,10 +660,20 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_stream_kernel(
     push(sh, arcs.best, arcs.k, arcs.tok, t.V, arcs.child);
   }
   __syncthreads();
-  if (sh.s->count > sh.cap)
-    select_by_rounds(sh, t, logp, row_stride, states_in, alpha, u, K, marks, words, lane, wave, nwaves, out);
-  else
-    write_ranked(sh, t, u, K, states_in, out);
+  const int n = collect_again(sh, lane, K, [&](u64 floor) {
+    if (part == 0) {
+      for (int k = k0; k < K; k += nwaves) {
+        unsigned* m = marks + static_cast<size_t>(k) * words;
+        tags_clear_n(m, words, lane);
+        walk_mark(t, beam(k), row_of(k), alpha, m, lane, [&](float v, int tok, int child) {
+          if (v >= key_total(floor) && cand_key(v, k * t.V + tok) >= floor) push(sh, v, k, tok, t.V, child);
+        });
+      }
+    }
+    __syncthreads();  // the marks are set
+    push_rows(floor, key_total(floor));
+  });
+  write_ranked(sh, t, u, n, K, states_in, out);
 }
 
 int g_beam_max_lds = 48 * 1024;  // dynamic LDS the device allows these kernels, set once
@@ -590,6 +682,7 @@ struct BeamPlan {
   int ns, parts, waves;  // ns == 0: streamed
   int words;             // marks of a beam
   size_t lds;
+  bool one() const { return waves == 1 && ns >= 4 && ns <= 16; }  // (K == 1, a row of up to 1024 tokens)
 };
 // Positions per lane: the fewest that spread a beam's row over as many waves as the workgroup takes -- a step of few
 // utterances is latency-bound, so it wants little to do in each wave -- but no more than kBeamFill waves over all
@@ -608,7 +701,7 @@ BeamPlan plan_beam(int V, int K, int64_t U) {
     if (parts == 1 || (U * K * parts <= kBeamFill && (K > 1 || ns >= 16))) break;
   }
   // (streamed: the maxima of a beam's chunks behind the marks)
-  p.lds = list_bytes(p.waves) + static_cast<size_t>(K) * (p.words + (p.ns ? 0 : nch)) * sizeof(unsigned);
+  p.lds = (p.one() ? 0 : list_bytes(p.waves)) + static_cast<size_t>(K) * (p.words + (p.ns ? 0 : nch)) * sizeof(unsigned);
   return p;
 }
 
@@ -635,15 +728,15 @@ int launch_beam_wave(const DeviceTree& t, const TreePick& pick, const float* d_l
   } else {                    \
     PB_REGS(false, NS, ONE);  \
   }
-  switch (p.ns + (p.waves == 1 ? 1 : 0)) {  // (one wave: K == 1; a row of up to 1024 tokens then, see plan_beam)
+  switch (p.ns + (p.one() ? 1 : 0)) {
     case 5: PB_SHAPE(4, true) break;
     case 9: PB_SHAPE(8, true) break;
     case 17: PB_SHAPE(16, true) break;
     case 4: PB_SHAPE(4, false) break;
     case 8: PB_SHAPE(8, false) break;
     case 16: PB_SHAPE(16, false) break;
-    case 32: case 33: PB_SHAPE(32, false) break;
-    case 64: case 65: PB_SHAPE(64, false) break;
+    case 32: PB_SHAPE(32, false) break;
+    case 64: PB_SHAPE(64, false) break;
     default:
       hipLaunchKernelGGL(beam_stream_kernel, grid, block, p.lds, stream, d_logp, row_stride, d_hyp, d_states_in, alpha, K,
                          d_tokens, d_parents, d_states_out, d_scores_out, t, pick);

@@ -118,3 +118,68 @@ def test_scores_written_over_the_hypothesis_scores(V, K):
     torch.cuda.synchronize()
     _compare(o[:3] + [d_hyp], want, list(range(U * K)), (V, K))
     pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("kind", ["dead", "const", "flat", "few finite", "steps"])
+@pytest.mark.parametrize("V,K", [(4, 32), (5, 3), (40, 16), (256, 1), (300, 8), (1024, 4), (1025, 16), (1030, 1), (2050, 2), (4100, 8),
+                                 (9000, 8), (16390, 16), (33000, 16), (70000, 2)])
+def test_totals_that_do_not_fit_the_list(V, K, kind):
+    """Dead utterances and rows that are flat or tie: far more totals reach any bound than the list of survivors holds."""
+    rng = np.random.default_rng(54000 + 40 * V + K)
+    blank, eos = (0, V - 2) if V > 8 else (V - 1, -1)
+    toks, offs, ot, tr = _tree(rng, V, blank, eos, 0, 0.0)
+    U = 3
+    x = (rng.standard_normal((U * K, V)) * 2 - 8).astype(np.float32)
+    hyp = (-3 * rng.random(U * K)).astype(np.float32)
+    u = slice(K, 2 * K)                        # the utterance in the middle
+    if kind == "dead":
+        hyp[u] = -np.inf
+    elif kind == "const":
+        x[u], hyp[u] = -3.0, -1.0
+    elif kind == "flat":                       # all within 0.01: below the finest distance the first bound looks at
+        x[u] = (-7 + 0.01 * rng.random((K, V))).astype(np.float32)
+        hyp[u] = -2.0
+    elif kind == "few finite":
+        keep = x[u].reshape(-1)[:max(1, K - 1)].copy()
+        x[u] = -np.inf
+        x[u].reshape(-1)[np.arange(len(keep)) * (K * V // len(keep))] = keep
+    else:                                      # eight values in all
+        x[u], hyp[u] = -rng.integers(1, 9, (K, V)).astype(np.float32), 0.0
+    states = rng.integers(0, ot.num_states, U * K).astype(np.int32)
+    deg = pb.pb_host_arrays(tr)["arc_count"]
+    states[K:K + max(1, K // 2)] = np.argsort(-deg)[:max(1, K // 2)] % ot.num_states if len(deg) > K else 0
+    d_x, d_st = dev(x), dev(states)
+    for alpha in (0.5, 0.0):
+        want = ot.fuse_step_beam(x, hyp, states, alpha, U, K)
+        for in_place in (False, True):
+            o, d_hyp = _outputs(U * K), dev(hyp)
+            scores = d_hyp if in_place else o[3]
+            print("list", V, K, kind, alpha, in_place, flush=True)
+            pb.pb_fuse_step_beam(tr, d_x, V, d_hyp, d_st, alpha, U, K, o[0], o[1], o[2], scores, 0)
+            torch.cuda.synchronize()
+            _compare(o[:3] + [scores], want, list(range(U * K)), (V, K, kind, alpha, in_place))
+    pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("V,K", [(6, 8), (1025, 8), (6000, 12), (33000, 20)])
+def test_dead_utterances_with_a_table_of_trees(V, K):
+    rng = np.random.default_rng(55000 + V)
+    pairs = [_tree(rng, V, V - 1, -1, i % 3, 0.0) for i in range(3)]
+    forest = pb.pb_forest_build([p[3] for p in pairs])
+    ids = np.array([1, 2, 9, 0], dtype=np.int32)   # (9: no such tree)
+    U = len(ids)
+    x = _rows(rng, 1, U * K, V, V - 1, pairs[0][0], pairs[0][1])[0]
+    states = np.concatenate([rng.integers(0, pairs[i % 3][2].num_states, K) for i in ids]).astype(np.int32)
+    states[3 * K + K - 1] = -1                     # a dead utterance with an invalid state
+    hyp = np.full(U * K, -np.inf, np.float32)
+    hyp[:K] = -1.0
+    o = _outputs(U * K)
+    print("dead forest", V, K, flush=True)
+    pb.pb_fuse_step_beam_forest(forest, dev(x), V, dev(ids), dev(hyp), dev(states), 0.5, U, K, o[0], o[1], o[2], o[3], 0)
+    torch.cuda.synchronize()
+    for u in (0, 1):
+        rows = list(range(u * K, u * K + K))
+        want = pairs[ids[u]][2].fuse_step_beam(np.ascontiguousarray(x[rows]), hyp[rows], states[rows], 0.5, 1, K)
+        _compare(o, want, rows, (V, K, u))
+    assert all(bool((g[2 * K:] == -1).all()) for g in o[:3]) and bool(torch.isnan(o[3][2 * K:]).all())
+    pb.pb_forest_free(forest)
