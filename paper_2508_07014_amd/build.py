@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG, "csrc")
 # (PB_LIBRARY: load another build of the library, e.g. one compiled with different tuning constants for a sweep)
 LIB = os.environ.get("PB_LIBRARY") or os.path.join(PKG, "libpb.so")
 PROBE_LIB = os.path.join(PKG, "libpb_probe.so")  # measurement probes of bench.py, not part of the product library
-SOURCES = ["pb_narrow_1024.hip", "pb_narrow_any.hip", "pb_narrow_1280.hip", "pb_narrow_256.hip", "pb_narrow_512.hip",
+SOURCES = ["pb_narrow_1024.hip", "pb_narrow_any.hip", "pb_narrow_groups.hip", "pb_narrow_1280.hip", "pb_narrow_256.hip", "pb_narrow_512.hip",
            "pb_wide.hip", "pb_rows.hip", "pb_beam.hip", "pb_frames.hip", "pb_kernels.hip", "pb_compile.cpp", "pb_api.hip"]
 # the Python side of the entry points that are called once per step (host code only, loads beside the library)
 CALL_LIB = os.path.join(PKG, "_pbcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))

@@ -22,20 +22,20 @@ __device__ __forceinline__ int code_pos(int code, int lane) { return (code >> 4)
 
 // Row maximum and its lowest token from the lanes' running maxima.  A row whose candidates are all -inf (or
 // excluded) comes back as M == -inf with a token that means nothing: the caller takes the second pass then.
-template <bool FULL>
+template <int FORM>
 __device__ __forceinline__ void wave_pick(const TreeView& t, const LaneBest& lb, int lane, float& M, int& tok) {
   M = ukey_val(wave_max_u(ukey(lb.m)));
-  tok = pos_token<FULL>(t, wave_min_nn(lb.m == M ? code_pos(lb.code, lane) : INT_MAX));
+  tok = pos_token<FORM>(t, wave_min_nn(lb.m == M ? code_pos(lb.code, lane) : INT_MAX));
 }
 
 // Boosts alpha * (p_root + root_score[v]) of the lane's 16 tokens of chunk `cb`; the blank boosts by 0
 // (SEL == 0) or is excluded (NaN), the EOS token by `ce` = alpha * (EOS boost of the state) when `ce_on`.
-template <bool FULL, int SEL>
+template <int FORM, int SEL>
 __device__ __forceinline__ void chunk_boosts(const TreeView& t, int cb, int lane, float p_root, float alpha, bool ce_on,
                                              float ce, const float (&rw)[16], float (&bo)[16]) {
 #pragma unroll
   for (int j = 0; j < 16; ++j) bo[j] = __fmul_rn(alpha, __fadd_rn(p_root, rw[j]));
-  const int blank = token_pos<FULL>(t, t.blank) - cb, eos = token_pos<FULL>(t, t.eos) - cb;
+  const int blank = token_pos<FORM>(t, t.blank) - cb, eos = token_pos<FORM>(t, t.eos) - cb;
   const bool has_blank = static_cast<unsigned>(blank) < static_cast<unsigned>(kChunk);
   const bool has_eos = ce_on && static_cast<unsigned>(eos) < static_cast<unsigned>(kChunk);
   if (has_blank || has_eos) {  // uniform, and false for most chunks
@@ -117,7 +117,7 @@ struct FrameOut {  // wave-uniform outcome of one frame
 // The whole decision of a frame by a plain second pass (any case, no speculation): every token that some
 // chain state overrides is marked, the arcs are evaluated deepest state first, and the base arg-max runs
 // over the unmarked tokens only.  `excl` (CTC rule): a token barred from the selection, or -1.
-template <bool FULL, int SEL>
+template <int FORM, int SEL>
 __device__ __forceinline__ FrameOut slow_frame(const TreeView& t, const Cursor& cur, const float* __restrict__ rowp,
                                                float alpha, int excl, unsigned* tags, int tag_words, int nch, int lane) {
   tags_clear_n(tags, tag_words, lane);
@@ -152,15 +152,16 @@ __device__ __forceinline__ FrameOut slow_frame(const TreeView& t, const Cursor& 
   for (int ch = 0; ch < nch; ++ch) {
     const int cb = ch * kChunk;
     float x[16], rw[16], bo[16];
-    load_row<FULL>(rowp, cb, t.V, lane, x);
-    load_row<FULL>(t.root_score, cb, t.V, lane, rw);
-    chunk_boosts<FULL, SEL>(t, cb, lane, cur.p_root, alpha, t.eos >= 0, ce, rw, bo);
+    load_row<FORM>(rowp, cb, t.V, lane, x);
+    load_row<FORM>(t.root_score, cb, t.V, lane, rw, 0.0f);
+    chunk_boosts<FORM, SEL>(t, cb, lane, cur.p_root, alpha, t.eos >= 0, ce, rw, bo);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      const int q = cb + tok_of(j, lane), first = q & ~3, held = FULL ? 0 : first - min(first, t.V - 4);
+      const int q = cb + tok_of(j, lane), first = q & ~3, held = FORM != kAny ? 0 : first - min(first, t.V - 4);
       const int v = min(q - held, t.V - 1);
       const float f = __fadd_rn(x[j], bo[j]);
-      const bool copy = !FULL && (j & 3) < held;  // (the token has a position of its own before this one)
+      // (the token has a position of its own before this one, or there is none here)
+      const bool copy = FORM == kAny ? (j & 3) < held : FORM == kGroups && q >= t.V;
       const bool out = copy || f != f || (SEL == 2 && v == excl) || tag_test(tags, v);
       if (!out && (!has || f > m)) {
         has = true;
@@ -200,13 +201,13 @@ __device__ __forceinline__ FrameOut slow_frame(const TreeView& t, const Cursor& 
 
 // Root scores of four positions (from i, a multiple of 4) for the pass over a row: NaN in the blank and EOS columns
 // (those two tokens are candidates of their own, see special_candidate) and in the copies behind the end of the row.
-template <bool FULL>
+template <int FORM>
 __device__ __forceinline__ float4 mask_special(const TreeView& t, int i, float4 q) {
-  const int first = FULL ? i : min(i, t.V - 4);
+  const int first = FORM != kAny ? i : min(i, t.V - 4);
   float e[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k)
-    if (first + k == t.blank || first + k == t.eos || (!FULL && k < i - first)) e[k] = NAN;
+    if (first + k == t.blank || first + k == t.eos || (FORM == kAny && k < i - first)) e[k] = NAN;
   return make_float4(e[0], e[1], e[2], e[3]);
 }
 

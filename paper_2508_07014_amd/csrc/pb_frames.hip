@@ -59,14 +59,16 @@ SegPlan plan_segments(int32_t T, int32_t B, int target_chains) {
   return SegPlan{nseg, seg_len};
 }
 
-// Row shape of a narrow row (see pb_narrow.hpp).  Aligned rows of 1024 tokens keep the form without clamps and copies;
-// everything else runs the clamped form with as many positions per lane as it needs (V = 193, B = 804, a table of
+// Row shape of a narrow row (see pb_narrow.hpp).  Aligned rows of 513 .. 1024 tokens keep the forms without clamps and
+// copies (the clamped one spills in the multi-frame decoder: V = 1000, 1000 frames x 128 128 us against 109, under the CTC
+// rule 205 against 127); everything else runs the clamped form with as many positions per lane as it needs (V = 193, B = 804, a table of
 // trees: 6.2 us with four, 7.1 with sixteen, 6.6 with the workgroup-per-row kernel it replaces; V = 1025: a step of
 // B = 128 8.0 -> 4.8 us, 500 frames x 32 utterances under the CTC rule 1880 -> 119 us).
 static int narrow_shape(const DeviceTree& t, const float* d_logp, int64_t frame_stride, int64_t row_stride) {
   if (t.vocab_size <= 512) return t.vocab_size <= 256 ? 3 : 4;
   if (t.vocab_size > 1024) return 2;
-  return t.vocab_size == 1024 && row_stride % 4 == 0 && frame_stride % 4 == 0 && aligned16(d_logp) && aligned16(t.root_score) ? 0 : 1;
+  const bool aligned = t.vocab_size % 4 == 0 && row_stride % 4 == 0 && frame_stride % 4 == 0 && aligned16(d_logp) && aligned16(t.root_score);
+  return !aligned ? 1 : t.vocab_size == 1024 ? 0 : 5;
 }
 
 int launch_step_wave(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride,
@@ -77,7 +79,7 @@ int launch_step_wave(const DeviceTree& t, const TreePick& pick, const float* d_l
                             d_scores, stream);
   const int row = narrow_shape(t, d_logp, 0, row_stride);
   constexpr decltype(&launch_step_row<0>) by_shape[] = {launch_step_row<0>, launch_step_row<1>, launch_step_row<2>,
-                                                        launch_step_row<3>, launch_step_row<4>};
+                                                        launch_step_row<3>, launch_step_row<4>, launch_step_row<5>};
   return by_shape[row](t, pick, d_logp, row_stride, d_states_in, d_last, alpha, B, sel, d_tokens, d_states_out, d_scores, stream);
 }
 
@@ -107,7 +109,7 @@ int launch_frames_wave(const DeviceTree& t, const TreePick& pick, const float* d
   const unsigned tag_lo = static_cast<unsigned>(next_call_tag());  // marks the start records of this call (see kStartInts)
   const int row = narrow_shape(t, d_logp, frame_stride, row_stride);
   constexpr decltype(&launch_frames_row<0>) by_shape[] = {launch_frames_row<0>, launch_frames_row<1>, launch_frames_row<2>,
-                                                          launch_frames_row<3>, launch_frames_row<4>};
+                                                          launch_frames_row<3>, launch_frames_row<4>, launch_frames_row<5>};
   return by_shape[row](t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, sel, tag_lo, d_tokens,
                        d_states, d_scores, d_patches, stream);
 }

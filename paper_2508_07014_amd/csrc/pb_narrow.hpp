@@ -61,8 +61,8 @@ using namespace wv;
 // Row shapes a wave owns whole: 0 = exactly 1024 tokens in 16-byte aligned rows, 1 = any 513 .. 1024 tokens, 2 = any
 // 1025 .. 1280 tokens (a tokenizer's 1024 and a blank, mostly: 20 instead of 16 positions per lane cost a narrow row
 // less than a second chunk would), 3 = any 4 .. 256, 4 = any 257 .. 512 (a lone wave pays for every instruction, so
-// positions that hold nothing are left out).
-constexpr bool row_full(int row) { return row == 0; }
+// positions that hold nothing are left out), 5 = 516 .. 1020 tokens, a multiple of 4, in 16-byte aligned rows.
+constexpr int row_form(int row) { return row == 0 ? kWhole : row == 5 ? kGroups : kAny; }
 constexpr int row_slots(int row) { return row == 2 ? 20 : row == 3 ? 4 : row == 4 ? 8 : 16; }
 // Waves per SIMD the multi-frame decoder is compiled for: four fill the 128 registers of a 16-slot row, 20 slots need
 // more (at four waves 100 to 380 of them went to scratch).
@@ -74,11 +74,11 @@ constexpr int spec_waves(int row) { return row == 2 ? 2 : 4; }
 template <int ROW, int SEL>
 __device__ __forceinline__ void rebuild_base_boost(const TreeView& t, int lane, float p_root, float alpha,
                                                    float (&c)[row_slots(ROW)]) {
-  constexpr bool FULL = row_full(ROW);
+  constexpr int FORM = row_form(ROW);
   const int ln = opaque(lane);
   float rw[row_slots(ROW)];
-  load_row<FULL>(t.root_score, 0, t.V, ln, rw);
-  make_base_boost<FULL, SEL>(t, ln, p_root, alpha, rw, c);
+  load_row<FORM>(t.root_score, 0, t.V, ln, rw, 0.0f);
+  make_base_boost<FORM, SEL>(t, ln, p_root, alpha, rw, c);
 }
 
 // One frame of a row with V <= 1024 (a single chunk).  `cur` is the hypothesis' state with its
@@ -94,7 +94,7 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
                                          float& c_p, float alpha, float* row, unsigned* tags, int lane, int last,
                                          bool need_record, NextRow&& next_row, float& out_val, int& out_tok,
                                          bool& row_in_lds) {
-  constexpr bool FULL = row_full(ROW);
+  constexpr int FORM = row_form(ROW);
   constexpr int NS = row_slots(ROW);
   constexpr int kTags = NS * 2;  // words of the token marks
   const int s = cur.s;
@@ -126,7 +126,7 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
     // stage 1: selection without boosting; a blank (or a CTC repeat) is emitted as it is
     float M0;
     int v0;
-    plain_argmax<FULL>(t, x, lane, M0, v0);
+    plain_argmax<FORM>(t, x, lane, M0, v0);
     if (v0 == t.blank || (SEL == 2 && v0 == last)) {
       out_val = uniform_f(M0);
       out_tok = uniform_i(v0);
@@ -143,7 +143,7 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
   for (int j = 0; j < NS; ++j) f[j] = __fadd_rn(x[j], c[j]);
   if (t.eos >= 0) {  // EOS rule (Sec. II-C): the EOS token is boosted by the value tabulated for the state
     const float ce = __fmul_rn(alpha, cur.eos_boost);
-    const int ln = opaque(lane), eos = token_pos<FULL>(t, t.eos);
+    const int ln = opaque(lane), eos = token_pos<FORM>(t, t.eos);
 #pragma unroll
     for (int j = 0; j < NS; ++j) f[j] = slot_is(j, ln, eos) ? __fadd_rn(x[j], ce) : f[j];
   }
@@ -161,12 +161,12 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
     // ---- base candidates -------------------------------------------------------------------------
     float g[NS / 4];
     if (SEL == 2 && excl >= 0) {
-      const int barred = token_pos<FULL>(t, excl);
+      const int barred = token_pos<FORM>(t, excl);
 #pragma unroll
       for (int j = 0; j < NS; ++j) f[j] = slot_is(j, opaque(lane), barred) ? NAN : f[j];
     }
     const float M = ukey_val(wave_max_u(ukey(group_maxima(f, g))));
-    const int vb = pos_token<FULL>(t, first_pos_equal(f, g, M, lane));
+    const int vb = pos_token<FORM>(t, first_pos_equal(f, g, M, lane));
     const v8i rr = t.root_rec[vb];  // record of the state the base winner leads to (speculative)
 
     // ---- arc candidates along the failure chain --------------------------------------------------
@@ -186,7 +186,7 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
         const int tk = valid ? a.token : 0;  // an unused entry may hold anything: keep the LDS index in range
         bool shadowed = !valid;
         if (SEL == 2) shadowed = shadowed || tk == excl;
-        const int pos = token_pos<FULL>(t, tk);
+        const int pos = token_pos<FORM>(t, tk);
         if (!MARK_IN_ROW && multi) {
           if (level > 0) shadowed = shadowed || tag_test(tags, pos);
           if (valid) tag_set(tags, pos);
@@ -286,18 +286,18 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
         tags_clear(tags, lane, kTags);
         for (int xs = s; xs != 0;) {
           const Rec r = load_rec(t, xs);
-          for (int j = lane; j < r.count; j += 64) tag_set(tags, token_pos<FULL>(t, t.arc[r.begin + j].token));
+          for (int j = lane; j < r.count; j += 64) tag_set(tags, token_pos<FORM>(t, t.arc[r.begin + j].token));
           xs = uniform_i(r.fail);
         }
         const int ln = opaque(lane);
         float own[NS];  // (the row without its copies behind the end)
 #pragma unroll
         for (int j = 0; j < NS; ++j) own[j] = f[j];
-        drop_copies<FULL>(t.V, ln, NAN, own);
+        drop_copies<FORM>(t.V, ln, NAN, own);
         unsigned k[NS], mk = 0u;
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-          const bool out = tag_test(tags, tok_of(j, ln)) || ((SEL != 0 || !FULL) && own[j] != own[j]);
+          const bool out = tag_test(tags, tok_of(j, ln)) || ((SEL != 0 || FORM == kAny) && own[j] != own[j]);
           k[j] = out ? 0u : ukey(f[j]);
           mk = max(mk, k[j]);
         }
@@ -310,7 +310,7 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
           for (int j = NS - 1; j >= 0; --j) l2 = (k[j] != 0u && f[j] == base_val) ? tok_of(j, ln) : l2;
           base_tok = wave_min_nn(l2);
           have_base = base_tok != INT_MAX;
-          base_tok = pos_token<FULL>(t, base_tok);
+          base_tok = pos_token<FORM>(t, base_tok);
         }
         arc_wins = !have_base || MA > base_val || (MA == base_val && va < base_tok);
       }
@@ -365,7 +365,7 @@ template <int ROW, int SEL>
 __device__ __forceinline__ void guess_boundary_1k(const TreeView& t, float (&x)[row_slots(ROW)], const float* rp,
                                                   int64_t frame_stride, int f, const int32_t* __restrict__ states0,
                                                   int b, const float (&c0)[row_slots(ROW)], int lane, int& state, int& label) {
-  constexpr bool FULL = row_full(ROW);
+  constexpr int FORM = row_form(ROW);
   constexpr int NS = row_slots(ROW);
   label = -1;
   for (int k = 0;; ++k) {
@@ -373,7 +373,7 @@ __device__ __forceinline__ void guess_boundary_1k(const TreeView& t, float (&x)[
     int w = 0;
     if constexpr (SEL != 0) {
       float M0;
-      plain_argmax<FULL>(t, x, lane, M0, w);
+      plain_argmax<FORM>(t, x, lane, M0, w);
       w = uniform_i(w);
       keep = w == t.blank;
     }
@@ -382,7 +382,7 @@ __device__ __forceinline__ void guess_boundary_1k(const TreeView& t, float (&x)[
 #pragma unroll
       for (int j = 0; j < NS; ++j) fz[j] = __fadd_rn(x[j], c0[j]);
       const float M = ukey_val(wave_max_u(ukey(group_maxima(fz, g))));
-      w = uniform_i(pos_token<FULL>(t, first_pos_equal(fz, g, M, lane)));
+      w = uniform_i(pos_token<FORM>(t, first_pos_equal(fz, g, M, lane)));
       keep = w == t.blank || w == t.eos;
     }
     if (k == 0) label = w;
@@ -400,7 +400,7 @@ __device__ __forceinline__ void guess_boundary_1k(const TreeView& t, float (&x)[
       return;
     }
     rp -= frame_stride;
-    load_row<FULL>(rp, 0, t.V, lane, x);
+    load_row<FORM>(rp, 0, t.V, lane, x);
   }
 }
 
@@ -418,13 +418,13 @@ __device__ __forceinline__ int run_on_1k(const TreeView& t, const float* __restr
                                          float alpha, int sA, float (&c)[row_slots(ROW)], float& c_p, int lastA, int n_max,
                                          int32_t* __restrict__ patch, float* row, unsigned* tags, int lane,
                                          const int32_t* start_rec, unsigned tag_lo) {
-  constexpr bool FULL = row_full(ROW);
+  constexpr int FORM = row_form(ROW);
   constexpr int NS = row_slots(ROW);
   if (n_max <= 0 || start_rec == nullptr) return 0;
   const unsigned tag_hi = start_tag_hi(tag_lo);
   const int V = t.V;
   float x[row_slots(ROW)], xn[row_slots(ROW)];
-  load_row<FULL>(rp, 0, V, lane, x);  // (requested before the record is waited for)
+  load_row<FORM>(rp, 0, V, lane, x);  // (requested before the record is waited for)
   Cursor ca = cursor_at(t, sA);
   int b_st = 0, b_tok = 0;  // lane i: state and token of the guessed trajectory after frame i
   const bool b_mine = read_start_frame(start_rec, min(lane, kPatchMax - 1), tag_lo, tag_hi, b_st, b_tok);
@@ -437,7 +437,7 @@ __device__ __forceinline__ int run_on_1k(const TreeView& t, const float* __restr
     bool in_lds;
     const float* rpn = rp + static_cast<int64_t>(min(i + 1, n_max - 1)) * frame_stride;  // (the last frame asks for its own row again)
     frame_1k<ROW, SEL, 1, 1, 4>(t, ca, x, c, c_p, alpha, row, tags, lane, lastA, true,
-                                 [&]() { load_row<FULL>(rpn, 0, V, lane, xn); }, valA, tokA, in_lds);
+                                 [&]() { load_row<FORM>(rpn, 0, V, lane, xn); }, valA, tokA, in_lds);
     if (((there >> i) & 1ull) == 0) {  // not there when first looked at: look once more
       int st1, tok1;
       const bool now = read_start_frame(start_rec, i, tag_lo, tag_hi, st1, tok1);
@@ -489,7 +489,7 @@ __device__ __forceinline__ bool run_frames_1k(const TreeView& t, const float* __
                                               int32_t* __restrict__ tokens, int32_t* __restrict__ states,
                                               float* __restrict__ scores, float* row, unsigned* tags, int lane,
                                               int32_t* start_rec = nullptr, unsigned tag_lo = 0u) {
-  constexpr bool FULL = row_full(ROW);
+  constexpr int FORM = row_form(ROW);
   constexpr int NS = row_slots(ROW);
   if (f0 >= f1) return true;
   constexpr bool GUESS = EDGE && !COMPARE;
@@ -507,10 +507,10 @@ __device__ __forceinline__ bool run_frames_1k(const TreeView& t, const float* __
   constexpr int kEarlyBatches1 = COMPARE ? 4 : (SEL == 0 ? 4 : (SEL == 1 ? 2 : 0));
   constexpr int kArcGroup = COMPARE ? 8 : 4;
   float xb[NB][row_slots(ROW)], c[row_slots(ROW)];
-  load_row<FULL>(rp, 0, V, lane, xb[0]);
-  if (f0 + 1 < f1) load_row<FULL>(rp + frame_stride, 0, V, lane, xb[1]);
-  if (NB > 3 && f0 + 2 < f1) load_row<FULL>(rp + 2 * frame_stride, 0, V, lane, xb[2]);
-  load_row<FULL>(t.root_score, 0, V, lane, c);  // needs no state: requested before the state is looked at
+  load_row<FORM>(rp, 0, V, lane, xb[0]);
+  if (f0 + 1 < f1) load_row<FORM>(rp + frame_stride, 0, V, lane, xb[1]);
+  if (NB > 3 && f0 + 2 < f1) load_row<FORM>(rp + 2 * frame_stride, 0, V, lane, xb[2]);
+  load_row<FORM>(t.root_score, 0, V, lane, c, 0.0f);  // needs no state: requested before the state is looked at
   StoredLane<SEL == 2> stored;
   if (COMPARE) stored.fetch(lane, f0, f1, B, b, tokens, states);
   int s = uniform_i(s_in);
@@ -519,8 +519,8 @@ __device__ __forceinline__ bool run_frames_1k(const TreeView& t, const float* __
   const bool guessable = GUESS && t.num_states < kGuessOk;
   if (guessable && f0 > 0 && s == 0) {  // (an invalid start state, e.g. of an unknown tree, is left as it is)
     float xw[row_slots(ROW)], c0[row_slots(ROW)];
-    load_row<FULL>(rp - frame_stride, 0, V, lane, xw);
-    make_base_boost<FULL, SEL>(t, lane, 0.0f, alpha, c, c0);
+    load_row<FORM>(rp - frame_stride, 0, V, lane, xw);
+    make_base_boost<FORM, SEL>(t, lane, 0.0f, alpha, c, c0);
     int label;
     guess_boundary_1k<ROW, SEL>(t, xw, rp - frame_stride, frame_stride, f0 - 1, states0, b, c0, lane, s, label);
     if (SEL == 2) last = label;
@@ -532,7 +532,7 @@ __device__ __forceinline__ bool run_frames_1k(const TreeView& t, const float* __
   }
   Cursor cur = cursor_at(t, s);
   float c_p = cur.p_root;
-  make_base_boost<FULL, SEL>(t, lane, c_p, alpha, c, c);  // element-wise, in place
+  make_base_boost<FORM, SEL>(t, lane, c_p, alpha, c, c);  // element-wise, in place
   // Outputs: those of up to 64 consecutive frames are kept in the lanes and written together, so that no store
   // sits in the in-order queue of the loads (measured on the two-stage rules: pass 1 of config 3 109 -> 102 us).
   LaneOut out{f0, 0, 0, 0.0f};
@@ -555,7 +555,7 @@ __device__ __forceinline__ bool run_frames_1k(const TreeView& t, const float* __
     int tok;
     frame_1k<ROW, SEL, kEarlyBatches, kEarlyBatches1, kArcGroup>(t, cur, xb[U], c, c_p, alpha, row, tags, lane, last, f + 1 < f1,
                         [&]() {
-                          if (STEADY || more) load_row<FULL>(rpn, 0, V, lane, xb[(U + NB - 1) % NB]);
+                          if (STEADY || more) load_row<FORM>(rpn, 0, V, lane, xb[(U + NB - 1) % NB]);
                         },
                         val, tok, row_in_lds);
     const int word = cur.s;
@@ -610,7 +610,7 @@ __device__ __forceinline__ bool run_frames_1k(const TreeView& t, const float* __
         xl[4 * i + 0] = q.x; xl[4 * i + 1] = q.y; xl[4 * i + 2] = q.z; xl[4 * i + 3] = q.w;
       }
     } else {
-      load_row<FULL>(rp - frame_stride, 0, V, lane, xl);
+      load_row<FORM>(rp - frame_stride, 0, V, lane, xl);
     }
     rebuild_base_boost<ROW, SEL>(t, opaque(lane), 0.0f, alpha, c0);
     int g, glabel;
@@ -739,14 +739,14 @@ __global__ void __launch_bounds__(LEAN ? 64 : 256) step_wave_kernel(
   // batch up front measured fastest there under every rule (3.11 against 3.21 us per step with four and four).
   constexpr int kEarlyBatches = LEAN ? 1 : (SEL == 0 ? 4 : 2);
   constexpr int kEarlyBatches1 = LEAN ? 0 : (SEL == 0 ? 4 : (SEL == 1 ? 2 : 0));
-  constexpr bool FULL = row_full(ROW);
+  constexpr int FORM = row_form(ROW);
   constexpr int NS = row_slots(ROW);
   float x[NS], c[NS];
   // (loads retire in order: the root scores come from a cache and are worked on while the row is on its way)
   // (`root_score` is the tree's array again, as an argument of its own: the leading arguments are in registers
   // when the wave starts, the tree structure has to be fetched)
-  load_row<FULL>(LEAN ? root_score : t.root_score, 0, t.V, lane, c);
-  load_row<FULL>(logp + static_cast<size_t>(b) * row_stride, 0, t.V, lane, x);
+  load_row<FORM>(LEAN ? root_score : t.root_score, 0, t.V, lane, c, 0.0f);
+  load_row<FORM>(logp + static_cast<size_t>(b) * row_stride, 0, t.V, lane, x);
   int s = tree_ok ? states_in[b] : -1;  // an unknown tree marks the hypothesis like an invalid state
   int last = -1;
   if (SEL == 2 && last_in != nullptr) last = last_in[b];
@@ -760,14 +760,14 @@ __global__ void __launch_bounds__(LEAN ? 64 : 256) step_wave_kernel(
   // (Copies behind the end of a ragged row get the boost 1 * (p_root + -inf): -inf for every alpha.)
   float am[LEAN ? NS : 1];
   if constexpr (LEAN) {
-    const int bp = token_pos<FULL>(t, blank);
+    const int bp = token_pos<FORM>(t, blank);
 #pragma unroll
     for (int j = 0; j < NS; ++j) am[j] = slot_is(j, lane, bp) ? (SEL == 0 ? 0.0f : NAN) : alpha;
-    drop_copies<FULL>(t.V, lane, 1.0f, am);
+    drop_copies<FORM>(t.V, lane, 1.0f, am);
 #pragma unroll
     for (int j = 0; j < NS; ++j) asm volatile("" : "+v"(am[j]));  // (formed here, not where it is used)
     __builtin_amdgcn_sched_barrier(0);
-    drop_copies<FULL>(t.V, lane, -INFINITY, c);
+    drop_copies<FORM>(t.V, lane, -INFINITY, c);
   }
   s = uniform_i(s);
   last = uniform_i(last);
@@ -789,7 +789,7 @@ __global__ void __launch_bounds__(LEAN ? 64 : 256) step_wave_kernel(
 #pragma unroll
     for (int j = 0; j < NS; ++j) c[j] = __fmul_rn(am[j], __fadd_rn(c_p, c[j]));  // base boosts, in place
   } else {
-    make_base_boost<FULL, SEL>(t, lane, c_p, alpha, c, c);  // element-wise, in place
+    make_base_boost<FORM, SEL>(t, lane, c_p, alpha, c, c);  // element-wise, in place
   }
   float val;
   int tok;

@@ -60,14 +60,19 @@ __device__ __forceinline__ TreeView make_view(const DeviceTree& t) {
 //   position(v) = v for v < split = V rounded down to a multiple of 4, v + pad for the 1..3 tokens behind it.
 // Copies never change a maximum, and the token's own position comes first; where a candidate must be counted once
 // (boosted selections) the copies carry a base boost of -inf or NaN.
-// FULL rows (the chunks tile the row, 16-byte aligned) have no copies: position == token.
-template <bool FULL>
+// Rows whose 16-byte groups are aligned and lie inside or outside as a whole have no copies, and position == token.  Where
+// the chunks tile the row nothing needs a test (kWhole); where they do not, a group behind the end is not loaded and
+// reads as -inf (kGroups: no clamps, no copies to drop -- 1000 frames x 128 of V = 1000 take 109 us, 128 as kAny, under
+// the CTC rule 127 against 205).
+enum RowForm : int { kAny = 0, kWhole = 1, kGroups = 2 };
+template <int FORM>
 __device__ __forceinline__ int token_pos(const TreeView& t, int v) {
-  return FULL ? v : v + (v >= t.split ? t.pad : 0);
+  return FORM != kAny ? v : v + (v >= t.split ? t.pad : 0);
 }
-template <bool FULL>
+template <int FORM>
 __device__ __forceinline__ int pos_token(const TreeView& t, int q) {  // of a token's own position
-  return FULL ? q : q - (q >= t.split ? t.pad : 0);
+  if (FORM == kGroups) return min(q, t.V - 1);  // (a row of nothing but NaN, a precondition violation: stay in range)
+  return FORM == kWhole ? q : q - (q >= t.split ? t.pad : 0);
 }
 
 // Values that are wave-uniform by construction, told to the compiler (keeps them in SGPRs and the
@@ -196,9 +201,9 @@ __device__ __forceinline__ Cursor cursor_from_root_rec(const v8i& r) {
 
 // Puts `fill` into the slots of a row of one chunk that hold copies (see token_pos); a group of 256 positions that
 // lies inside the row is skipped by a uniform branch.
-template <bool FULL, int NS>
+template <int FORM, int NS>
 __device__ __forceinline__ void drop_copies(int V, int lane, float fill, float (&c)[NS]) {
-  if constexpr (!FULL) {
+  if constexpr (FORM == kAny) {
 #pragma unroll
     for (int i = 0; i < NS / 4; ++i) {
       if (256 * (i + 1) > V) {
@@ -217,16 +222,16 @@ __device__ __forceinline__ void drop_copies(int V, int lane, float fill, float (
 //
 // alpha * (p_root + root_score[v]) for the lane's positions of a row of one chunk; the blank column boosts by 0
 // (SEL == 0) or is excluded (SEL != 0), copies behind the end of the row carry -inf.
-template <bool FULL, int SEL, int NS>
+template <int FORM, int SEL, int NS>
 __device__ __forceinline__ void make_base_boost(const TreeView& t, int lane, float p_root, float alpha,
                                                 const float (&rw)[NS], float (&c)[NS]) {
-  const int blank = token_pos<FULL>(t, t.blank);
+  const int blank = token_pos<FORM>(t, t.blank);
 #pragma unroll
   for (int j = 0; j < NS; ++j) {
     const float boost = slot_is(j, lane, blank) ? (SEL == 0 ? 0.0f : NAN) : __fadd_rn(p_root, rw[j]);
     c[j] = __fmul_rn(alpha, boost);
   }
-  drop_copies<FULL>(t.V, lane, -INFINITY, c);
+  drop_copies<FORM>(t.V, lane, -INFINITY, c);
 }
 
 // Maximum of four values in two instructions.  Written out because the compiler puts a canonicalising
@@ -259,17 +264,25 @@ __device__ __forceinline__ float group_maxima(const float (&f)[NS], float (&g)[N
   return m;
 }
 
-// Loads the lane's NS values of the positions of chunk `cb` from a V-long fp32 array (see token_pos).
-template <bool FULL, int NS>
-__device__ __forceinline__ void load_row(const float* __restrict__ base, int cb, int V, int lane, float (&x)[NS]) {
+// Loads the lane's NS values of the positions of chunk `cb` from a V-long fp32 array (see token_pos).  kGroups: `fill`
+// behind the end, -inf for log-probs; root scores take 0, which every alpha leaves finite.
+template <int FORM, int NS>
+__device__ __forceinline__ void load_row(const float* __restrict__ base, int cb, int V, int lane, float (&x)[NS],
+                                         float fill = -INFINITY) {
   typedef float vf4 __attribute__((ext_vector_type(4)));
   typedef float vf4_any __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
   for (int i = 0; i < NS / 4; ++i) {
     const int u = cb + 256 * i + 4 * lane;
     vf4 q;
-    if constexpr (FULL) {
+    if constexpr (FORM == kWhole) {
       q = *reinterpret_cast<const vf4*>(base + u);
+    } else if constexpr (FORM == kGroups) {
+      if (u < V) {
+        q = *reinterpret_cast<const vf4*>(base + u);
+      } else {
+        q = vf4{fill, fill, fill, fill};
+      }
     } else {
       q = *reinterpret_cast<const vf4_any*>(base + static_cast<unsigned>(min(u, V - 4)));
     }
@@ -319,11 +332,11 @@ __device__ __forceinline__ void tag_set(unsigned* bits, int tk) { atomicOr(&bits
 __device__ __forceinline__ bool tag_test(const unsigned* bits, int tk) { return ((bits[tk >> 5] >> (tk & 31)) & 1u) != 0u; }
 
 // Stage 1 of the two-stage rule on one chunk: the unboosted row maximum and its lowest token.
-template <bool FULL, int NS>
+template <int FORM, int NS>
 __device__ __forceinline__ void plain_argmax(const TreeView& t, const float (&x)[NS], int lane, float& M0, int& v0) {
   float g[NS / 4];
   M0 = ukey_val(wave_max_u(ukey(group_maxima(x, g))));
-  v0 = pos_token<FULL>(t, first_pos_equal(x, g, M0, lane));
+  v0 = pos_token<FORM>(t, first_pos_equal(x, g, M0, lane));
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -46,7 +46,7 @@ constexpr int ring_of(int nch) { return nch == 2 ? 2 : (nch + 2) / 3 * 3 < (nch 
 //   early: arc number `lane` of the state (clamped into its arc range), requested before the row pass, and
 //   early_x: the log-prob of that arc's token, gathered during the pass
 //   last:  label of the previous frame (SEL == 2; any value outside [0, V) = none)
-template <bool FULL, int SEL>
+template <int FORM, int SEL>
 __device__ __forceinline__ FrameOut decide_wide(const TreeView& t, const Cursor& cur, const float* __restrict__ rowp,
                                                 float alpha, float M, int vb, const ArcRec& early, float early_x, int last,
                                                 unsigned* tags, int tag_words, int nch, int lane) {
@@ -119,11 +119,11 @@ __device__ __forceinline__ FrameOut decide_wide(const TreeView& t, const Cursor&
     int excl = -1;
     if (SEL == 2) {
       // first without the exclusion (the label may not even win), then, if it does win, without the label
-      o = slow_frame<FULL, SEL>(t, cur, rowp, alpha, -1, tags, tag_words, nch, lane);
+      o = slow_frame<FORM, SEL>(t, cur, rowp, alpha, -1, tags, tag_words, nch, lane);
       if (o.tok != last) return o;
       excl = last;
     }
-    o = slow_frame<FULL, SEL>(t, cur, rowp, alpha, excl, tags, tag_words, nch, lane);
+    o = slow_frame<FORM, SEL>(t, cur, rowp, alpha, excl, tags, tag_words, nch, lane);
     return o;
   }
   o.val = uniform_f(o.val);
@@ -155,12 +155,12 @@ __device__ __forceinline__ void advance(const TreeView& t, Cursor& cur, const Fr
 
 // Winner under root-state boosts from the lanes' running maxima `gb`; under the single-stage rule the blank
 // (kept out of the pass) competes with boost 0.
-template <bool FULL, int SEL>
+template <int FORM, int SEL>
 __device__ __forceinline__ int root_winner(const TreeView& t, const LaneBest& gb, const float* __restrict__ rowp,
                                            float alpha, int lane) {
   float M;
   int w;
-  wave_pick<FULL>(t, gb, lane, M, w);
+  wave_pick<FORM>(t, gb, lane, M, w);
   w = uniform_i(w);
   if (SEL == 0 && t.blank >= 0) {
     const float fb = __fadd_rn(uniform_f(rowp[t.blank]), __fmul_rn(alpha, 0.0f));
@@ -170,29 +170,29 @@ __device__ __forceinline__ int root_winner(const TreeView& t, const LaneBest& gb
 }
 
 // Raw arg-max v0 (two-stage rules) and winner w under root-state boosts of one row, by a plain pass.
-template <bool FULL, int SEL>
+template <int FORM, int SEL>
 __device__ __forceinline__ void row_winners(const TreeView& t, const float* __restrict__ rowp, float alpha,
                                             const float* rs, int nch, int lane, int& v0, int& w) {
   LaneBest fb = lane_best_init(), rb = lane_best_init(), gb = lane_best_init();
   float x[2][16];
-  load_row<FULL>(rowp, 0, t.V, lane, x[0]);
+  load_row<FORM>(rowp, 0, t.V, lane, x[0]);
   for (int ch0 = 0; ch0 < nch; ch0 += 2) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int ch = ch0 + u;
       if (ch < nch) {
-        if (ch + 1 < nch) load_row<FULL>(rowp, (ch + 1) * kChunk, t.V, lane, x[(u + 1) % 2]);
+        if (ch + 1 < nch) load_row<FORM>(rowp, (ch + 1) * kChunk, t.V, lane, x[(u + 1) % 2]);
         float rw[16];
         read_rs_lds(rs, ch * kChunk, lane, rw);
         wide_chunk<SEL, true>(x[u], rw, ch, 0.0f, alpha, fb, rb, gb);
       }
     }
   }
-  w = root_winner<FULL, SEL>(t, gb, rowp, alpha, lane);
+  w = root_winner<FORM, SEL>(t, gb, rowp, alpha, lane);
   v0 = -1;
   if (SEL != 0) {
     float M;
-    wave_pick<FULL>(t, rb, lane, M, v0);
+    wave_pick<FORM>(t, rb, lane, M, v0);
     v0 = uniform_i(v0);
   }
 }
@@ -200,7 +200,7 @@ __device__ __forceinline__ void row_winners(const TreeView& t, const float* __re
 // Boundary guess for wide rows, the scheme of the narrow kernels: (v0, w) are the winners of frame f, the one
 // before the boundary; frames that keep the state are skipped going back, up to kLookBack frames or the start
 // of the call.  Both neighbours of a boundary compute it from the same rows with the same arithmetic.
-template <bool FULL, int SEL>
+template <int FORM, int SEL>
 __device__ __forceinline__ void guess_boundary_wide(const TreeView& t, int v0, int w, const float* __restrict__ rowp,
                                                     int64_t frame_stride, int f, const int32_t* __restrict__ states0,
                                                     int b, float alpha, const float* rs, int nch, int lane, int& state,
@@ -229,14 +229,14 @@ __device__ __forceinline__ void guess_boundary_wide(const TreeView& t, int v0, i
       return;
     }
     rowp -= frame_stride;
-    row_winners<FULL, SEL>(t, rowp, alpha, rs, nch, lane, v0, w);
+    row_winners<FORM, SEL>(t, rowp, alpha, rs, nch, lane, v0, w);
   }
 }
 
 // Decodes frames [f0, f1) of hypothesis b, as run_frames_1k does for narrow rows (same arguments and rules).
 //   rs: root scores of the row in LDS, for the positions of nchp chunks; tags: this wave's token marks (32 * nchp words)
 //   nchp: chunks per row rounded up to a whole turn of the ring (chunks past the row hold copies of its end)
-template <bool COMPARE, bool FULL, int RING, int SEL, bool EDGE>
+template <bool COMPARE, bool FORM, int RING, int SEL, bool EDGE>
 __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* __restrict__ logp, int64_t frame_stride,
                                                 int64_t row_stride, float alpha, int B, int b, int f0, int f1, int s_in,
                                                 int last_in, int T, const int32_t* __restrict__ states0,
@@ -253,7 +253,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
   // the buffer the chunk before the current one has just left, at the start of a chunk's turn.
   float xb[RING][16];
 #pragma unroll
-  for (int u = 0; u + 1 < RING; ++u) load_row<FULL>(rp, u * kChunk, V, lane, xb[u]);
+  for (int u = 0; u + 1 < RING; ++u) load_row<FORM>(rp, u * kChunk, V, lane, xb[u]);
   StoredLane<SEL == 2> stored;
   if (COMPARE) stored.fetch(lane, f0, f1, B, b, tokens, states);
   int s = uniform_i(s_in);
@@ -262,8 +262,8 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
   const bool guessable = GUESS && t.num_states < kGuessOk;
   if (guessable && f0 > 0 && s == 0) {  // (an invalid start state, e.g. of an unknown tree, is left as it is)
     int v0, w, label;
-    row_winners<FULL, SEL>(t, rp - frame_stride, alpha, rs, nch, lane, v0, w);
-    guess_boundary_wide<FULL, SEL>(t, v0, w, rp - frame_stride, frame_stride, f0 - 1, states0, b, alpha, rs, nch, lane,
+    row_winners<FORM, SEL>(t, rp - frame_stride, alpha, rs, nch, lane, v0, w);
+    guess_boundary_wide<FORM, SEL>(t, v0, w, rp - frame_stride, frame_stride, f0 - 1, states0, b, alpha, rs, nch, lane,
                                    s, label);
     if (SEL == 2) last = label;
   }
@@ -294,7 +294,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
           // compiler wait for exactly the chunk it needs and keep the others in flight.
           const int nx = ch + RING - 1;
           const bool wrap = nx >= nchp;
-          load_row<FULL>(wrap ? rpn : rp, (wrap ? nx - nchp : nx) * kChunk, V, lane, xb[(u + RING - 1) % RING]);
+          load_row<FORM>(wrap ? rpn : rp, (wrap ? nx - nchp : nx) * kChunk, V, lane, xb[(u + RING - 1) % RING]);
           float rw[16];
           read_rs_lds(rs, ch * kChunk, lane, rw);
           wide_chunk<SEL, TRACK>(xb[u], rw, ch, cur.p_root, alpha, fb, rb, gb);
@@ -313,13 +313,13 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
     }
     float M;
     int vb;
-    wave_pick<FULL>(t, fb, lane, M, vb);
+    wave_pick<FORM>(t, fb, lane, M, vb);
     int v0 = -1;
     FrameOut o;
     bool stage1 = false;
     if (SEL != 0) {  // stage 1: selection without boosting; a blank (or a CTC repeat) is emitted as it is
       float M0;
-      wave_pick<FULL>(t, rb, lane, M0, v0);
+      wave_pick<FORM>(t, rb, lane, M0, v0);
       v0 = uniform_i(v0);
       if (v0 == t.blank || (SEL == 2 && v0 == last)) {
         o = FrameOut{uniform_f(M0), v0, false, 0};
@@ -327,7 +327,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
       }
     }
     if (!stage1) {
-      o = decide_wide<FULL, SEL>(t, cur, rp, alpha, M, uniform_i(vb), early, early_x, last, tags, tag_words, nch, lane);
+      o = decide_wide<FORM, SEL>(t, cur, rp, alpha, M, uniform_i(vb), early, early_x, last, tags, tag_words, nch, lane);
       advance(t, cur, o, more);
     }
     const int word = cur.s;
@@ -344,8 +344,8 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
       // the guess the next range starts from, made from the same rows; if it is what this range really ends
       // in, the last state word says so
       int g, glabel;
-      const int w = root_winner<FULL, SEL>(t, gb, rp, alpha, lane);
-      guess_boundary_wide<FULL, SEL>(t, v0, w, rp, frame_stride, f, states0, b, alpha, rs, nch, lane, g, glabel);
+      const int w = root_winner<FORM, SEL>(t, gb, rp, alpha, lane);
+      guess_boundary_wide<FORM, SEL>(t, v0, w, rp, frame_stride, f, states0, b, alpha, rs, nch, lane, g, glabel);
       if (g == cur.s && (SEL != 2 || glabel == o.tok)) {
         if (lane == slot) out.st |= kGuessOk;
       }
@@ -362,24 +362,24 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
   return false;  // (a re-run: the end of the range was reached without meeting the stored trajectory)
 }
 
-template <bool FULL>
+template <int FORM>
 __device__ __forceinline__ float4 staged_root_scores(const TreeView& t, int i) {
   const float* p = t.root_score + min(i, t.V - 4);
-  return mask_special<FULL>(t, i, make_float4(p[0], p[1], p[2], p[3]));
+  return mask_special<FORM>(t, i, make_float4(p[0], p[1], p[2], p[3]));
 }
 
 // The same into LDS for a whole row, by the whole workgroup; ends with a barrier.
-template <bool FULL>
+template <int FORM>
 __device__ __forceinline__ void stage_root_scores(const TreeView& t, float* rs, int nchp) {
   const int n = nchp * kChunk;
   for (int i = 4 * static_cast<int>(threadIdx.x); i < n; i += 4 * static_cast<int>(blockDim.x))
-    *reinterpret_cast<float4*>(rs + i) = staged_root_scores<FULL>(t, i);
+    *reinterpret_cast<float4*>(rs + i) = staged_root_scores<FORM>(t, i);
   __syncthreads();
 }
 
 // Pass 1 (see frames_spec_kernel of the narrow rows).  With a table of trees the workgroup's waves may use
 // different trees, so each wave then keeps its own copy of the root scores.
-template <bool FULL, int RING, int SEL, bool FOREST>
+template <int FORM, int RING, int SEL, bool FOREST>
 __global__ void __launch_bounds__(256, PB_WIDE_WAVES_EU) wide_spec_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
                                                          int64_t frame_stride, int64_t row_stride,
                                                          const int32_t* __restrict__ states0,
@@ -402,11 +402,11 @@ __global__ void __launch_bounds__(256, PB_WIDE_WAVES_EU) wide_spec_kernel(Device
     rs = lds + wave * (row_floats + nchp * kTagWords);
     tags = reinterpret_cast<unsigned*>(rs + row_floats);
     if (tree_ok) {
-      for (int i = 4 * lane; i < row_floats; i += 256) *reinterpret_cast<float4*>(rs + i) = staged_root_scores<FULL>(t, i);
+      for (int i = 4 * lane; i < row_floats; i += 256) *reinterpret_cast<float4*>(rs + i) = staged_root_scores<FORM>(t, i);
     }
   } else {
     tags = reinterpret_cast<unsigned*>(lds + row_floats) + wave * nchp * kTagWords;
-    stage_root_scores<FULL>(t, rs, nchp);
+    stage_root_scores<FORM>(t, rs, nchp);
   }
   if (!live) return;
   const int f0 = seg_begin(j, T, nseg), f1 = seg_begin(j + 1, T, nseg);
@@ -416,12 +416,12 @@ __global__ void __launch_bounds__(256, PB_WIDE_WAVES_EU) wide_spec_kernel(Device
     if (SEL == 2 && last0 != nullptr) last = last0[b];
   }
   if (!tree_ok) s = -1;  // an unknown tree marks every frame of the hypothesis like an invalid state
-  run_frames_wide<false, FULL, RING, SEL, true>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1, s, last, T, states0,
+  run_frames_wide<false, FORM, RING, SEL, true>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1, s, last, T, states0,
                                           tokens, states, scores, rs, tags, nchp, lane);
 }
 
 // Pass 2: one workgroup per hypothesis (one tree, so the root scores are shared).
-template <bool FULL, int RING, int SEL, bool FOREST>
+template <int FORM, int RING, int SEL, bool FOREST>
 __global__ void __launch_bounds__(512) wide_fix_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
                                                         int64_t frame_stride, int64_t row_stride, float alpha, int T,
                                                         int B, int seg_len, int nseg, int nchp,
@@ -439,12 +439,12 @@ __global__ void __launch_bounds__(512) wide_fix_kernel(DeviceTree dt, TreePick p
   const TreeView t = make_view(mine);
   float* rs = lds;
   unsigned* tags = reinterpret_cast<unsigned*>(lds + nchp * kChunk) + wave * nchp * kTagWords;
-  stage_root_scores<FULL>(t, rs, nchp);
+  stage_root_scores<FORM>(t, rs, nchp);
   fix_segments<SEL == 2>(T, B, b, seg_len, nseg, tokens, states, scores, nullptr, assumed, assumed_tok, bad_words, lane,
                          wave, nwaves,
                          [&](int seg, int s, int last) {
                            const int f0 = seg_begin(seg, T, nseg), f1 = seg_begin(seg + 1, T, nseg);
-                           return run_frames_wide<true, FULL, RING, SEL, false>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1,
+                           return run_frames_wide<true, FORM, RING, SEL, false>(t, logp, frame_stride, row_stride, alpha, B, b, f0, f1,
                                                                    s, last, T, nullptr, tokens, states, scores, rs, tags,
                                                                    nchp, lane);
                          });
@@ -465,7 +465,7 @@ struct StepPart {
 // first, with the state id, before anything is waited for.  LEAN: one tree for all rows; the leading arguments,
 // the root-score array among them, are then in registers when the wave starts, and an invalid state is decoded as
 // the root and marked at the end, so that no early exit stands between the wave start and the requests.)
-template <bool FULL, int CPW, int SEL, bool LEAN>
+template <int FORM, int CPW, int SEL, bool LEAN>
 __global__ void __launch_bounds__(1024) step_wide_kernel(
     const float* __restrict__ logp, int64_t row_stride, const int32_t* __restrict__ states_in,
     const float* __restrict__ root_score, const int32_t* __restrict__ last_in, float alpha, int B,
@@ -483,9 +483,9 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   const float* rowp = logp + static_cast<size_t>(b) * row_stride;
   const float* rsp = LEAN ? root_score : t.root_score;
   float x[CPW][16], rw[16];
-  load_row<FULL>(rsp, wave * CPW * kChunk, t.V, lane, rw);
+  load_row<FORM>(rsp, wave * CPW * kChunk, t.V, lane, rw);
 #pragma unroll
-  for (int c = 0; c < CPW; ++c) load_row<FULL>(rowp, (wave * CPW + c) * kChunk, t.V, lane, x[c]);
+  for (int c = 0; c < CPW; ++c) load_row<FORM>(rowp, (wave * CPW + c) * kChunk, t.V, lane, x[c]);
   int s = tree_ok ? states_in[b] : -1;  // an unknown tree marks the hypothesis like an invalid state
   __builtin_amdgcn_sched_barrier(0);
   s = uniform_i(s);
@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   auto mask_row = [&](int ch) {  // NaN in the blank and EOS columns: those two are candidates of their own
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float4 q = mask_special<FULL>(t, ch * kChunk + 256 * i + 4 * lane,
+      const float4 q = mask_special<FORM>(t, ch * kChunk + 256 * i + 4 * lane,
                                           make_float4(rw[4 * i], rw[4 * i + 1], rw[4 * i + 2], rw[4 * i + 3]));
       rw[4 * i + 0] = q.x; rw[4 * i + 1] = q.y; rw[4 * i + 2] = q.z; rw[4 * i + 3] = q.w;
     }
@@ -524,7 +524,7 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
 #pragma unroll
   for (int c = 0; c < CPW; ++c) {
     float next_rw[16];
-    if (c + 1 < CPW) load_row<FULL>(rsp, (wave * CPW + c + 1) * kChunk, t.V, lane, next_rw);
+    if (c + 1 < CPW) load_row<FORM>(rsp, (wave * CPW + c + 1) * kChunk, t.V, lane, next_rw);
     wide_chunk<SEL, false>(x[c], rw, wave * CPW + c, p_root, alpha, fb, rb, gb);
     if (c + 1 < CPW) {
 #pragma unroll
@@ -533,8 +533,8 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
     }
   }
   StepPart mine_part{0.0f, 0.0f, 0, 0};
-  wave_pick<FULL>(t, fb, lane, mine_part.M, mine_part.vb);
-  if (SEL != 0) wave_pick<FULL>(t, rb, lane, mine_part.M0, mine_part.v0);
+  wave_pick<FORM>(t, fb, lane, mine_part.M, mine_part.vb);
+  if (SEL != 0) wave_pick<FORM>(t, rb, lane, mine_part.M0, mine_part.v0);
   if (lane == 0) part[wave] = mine_part;
   __syncthreads();
   if (wave != 0) return;
@@ -558,7 +558,7 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   }
   if (!stage1) {
     unsigned* tags = reinterpret_cast<unsigned*>(lds);
-    o = decide_wide<FULL, SEL>(t, cur, rowp, alpha, M, vb, early, early_x, last, tags, nch * kTagWords, nch, lane);
+    o = decide_wide<FORM, SEL>(t, cur, rowp, alpha, M, vb, early, early_x, last, tags, nch * kTagWords, nch, lane);
     if (!o.arc && o.tok == vb && vb != t.blank && vb != t.eos) {
       cur.s = uniform_i(vb_next);  // only the state id leaves the kernel
     } else {
@@ -583,18 +583,18 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // full chunks in 16-byte aligned rows, 1 .. 3 = any row through a ring of four, three or two buffers.
 #define PB_DISPATCH(kind, sel, LAUNCH)     \
   switch (3 * (kind) + (sel)) {            \
-    case 0: LAUNCH(true, 4, 0); break;     \
-    case 1: LAUNCH(true, 4, 1); break;     \
-    case 2: LAUNCH(true, 4, 2); break;     \
-    case 3: LAUNCH(false, 4, 0); break;    \
-    case 4: LAUNCH(false, 4, 1); break;    \
-    case 5: LAUNCH(false, 4, 2); break;    \
-    case 6: LAUNCH(false, 3, 0); break;    \
-    case 7: LAUNCH(false, 3, 1); break;    \
-    case 8: LAUNCH(false, 3, 2); break;    \
-    case 9: LAUNCH(false, 2, 0); break;    \
-    case 10: LAUNCH(false, 2, 1); break;   \
-    default: LAUNCH(false, 2, 2); break;   \
+    case 0: LAUNCH(kWhole, 4, 0); break;     \
+    case 1: LAUNCH(kWhole, 4, 1); break;     \
+    case 2: LAUNCH(kWhole, 4, 2); break;     \
+    case 3: LAUNCH(kAny, 4, 0); break;    \
+    case 4: LAUNCH(kAny, 4, 1); break;    \
+    case 5: LAUNCH(kAny, 4, 2); break;    \
+    case 6: LAUNCH(kAny, 3, 0); break;    \
+    case 7: LAUNCH(kAny, 3, 1); break;    \
+    case 8: LAUNCH(kAny, 3, 2); break;    \
+    case 9: LAUNCH(kAny, 2, 0); break;    \
+    case 10: LAUNCH(kAny, 2, 1); break;   \
+    default: LAUNCH(kAny, 2, 2); break;   \
   }
 
 int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t row_stride,
@@ -608,20 +608,20 @@ int launch_step_wide(const DeviceTree& t, const TreePick& pick, const float* d_l
   const size_t lds = static_cast<size_t>(waves) * cpw * kTagWords * sizeof(unsigned);
   const dim3 grid(static_cast<unsigned>(B)), block(static_cast<unsigned>(64 * waves));
   const bool lean = pick.table == nullptr;
-#define PB_STEP(FULL, CPW, SEL, LEAN)                                                                              \
-  hipLaunchKernelGGL((step_wide_kernel<FULL, CPW, SEL, LEAN>), grid, block, lds, stream, d_logp, row_stride,       \
+#define PB_STEP(FORM, CPW, SEL, LEAN)                                                                              \
+  hipLaunchKernelGGL((step_wide_kernel<FORM, CPW, SEL, LEAN>), grid, block, lds, stream, d_logp, row_stride,       \
                      d_states_in, t.root_score, d_last, alpha, B, d_tokens, d_states_out, d_scores, t, pick)
-#define PB_LAUNCH(FULL, CPW, SEL)   \
+#define PB_LAUNCH(FORM, CPW, SEL)   \
   if (lean) {                       \
-    PB_STEP(FULL, CPW, SEL, true);  \
+    PB_STEP(FORM, CPW, SEL, true);  \
   } else {                          \
-    PB_STEP(FULL, CPW, SEL, false); \
+    PB_STEP(FORM, CPW, SEL, false); \
   }
-#define PB_SELECTION(FULL, CPW)               \
+#define PB_SELECTION(FORM, CPW)               \
   switch (sel) {                              \
-    case 0: PB_LAUNCH(FULL, CPW, 0); break;   \
-    case 1: PB_LAUNCH(FULL, CPW, 1); break;   \
-    default: PB_LAUNCH(FULL, CPW, 2); break;  \
+    case 0: PB_LAUNCH(FORM, CPW, 0); break;   \
+    case 1: PB_LAUNCH(FORM, CPW, 1); break;   \
+    default: PB_LAUNCH(FORM, CPW, 2); break;  \
   }
   // (more than one chunk per wave: the clamped form only -- the row no longer fits one load per lane and what the
   // clamps cost disappears behind it)
@@ -667,12 +667,12 @@ int launch_frames_wide(const DeviceTree& t, const TreePick& pick, const float* d
   const int64_t chains = static_cast<int64_t>(B) * nseg;
   const int64_t blocks = (chains + waves - 1) / waves;
   if (!grid_fits(blocks, 64 * waves)) return PB_EUNSUPPORTED;
-#define PB_SPEC(FULL, RING, SEL, FOREST)                                                                                 \
-  hipLaunchKernelGGL((wide_spec_kernel<FULL, RING, SEL, FOREST>), dim3(static_cast<unsigned>(blocks)), dim3(64 * waves), \
+#define PB_SPEC(FORM, RING, SEL, FOREST)                                                                                 \
+  hipLaunchKernelGGL((wide_spec_kernel<FORM, RING, SEL, FOREST>), dim3(static_cast<unsigned>(blocks)), dim3(64 * waves), \
                      lds, stream, t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B,      \
                      seg_len, nseg, nchp, d_tokens, d_states, d_scores)
-#define PB_LAUNCH(FULL, RING, SEL) PB_SPEC(FULL, RING, SEL, false)
-#define PB_LAUNCH_F(FULL, RING, SEL) PB_SPEC(FULL, RING, SEL, true)
+#define PB_LAUNCH(FORM, RING, SEL) PB_SPEC(FORM, RING, SEL, false)
+#define PB_LAUNCH_F(FORM, RING, SEL) PB_SPEC(FORM, RING, SEL, true)
   if (forest) {
     PB_DISPATCH(kind, sel, PB_LAUNCH_F)
   } else {
@@ -687,12 +687,12 @@ int launch_frames_wide(const DeviceTree& t, const TreePick& pick, const float* d
     while (fw > 1 && row_bytes + fw * tag_bytes > static_cast<size_t>(g_wide_max_lds)) --fw;
     const size_t lds2 = row_bytes + fw * tag_bytes;
     if (lds2 > static_cast<size_t>(g_wide_max_lds)) return PB_EUNSUPPORTED;
-#define PB_FIX(FULL, RING, SEL, FOREST)                                                                                   \
-  hipLaunchKernelGGL((wide_fix_kernel<FULL, RING, SEL, FOREST>), dim3(static_cast<unsigned>(B)), dim3(64 * fw), lds2,     \
+#define PB_FIX(FORM, RING, SEL, FOREST)                                                                                   \
+  hipLaunchKernelGGL((wide_fix_kernel<FORM, RING, SEL, FOREST>), dim3(static_cast<unsigned>(B)), dim3(64 * fw), lds2,     \
                      stream, t, pick, d_logp, frame_stride, row_stride, alpha, T, B, seg_len, nseg, nchp, d_tokens, \
                      d_states, d_scores)
-#define PB_LAUNCH(FULL, RING, SEL) PB_FIX(FULL, RING, SEL, false)
-#define PB_LAUNCH_F(FULL, RING, SEL) PB_FIX(FULL, RING, SEL, true)
+#define PB_LAUNCH(FORM, RING, SEL) PB_FIX(FORM, RING, SEL, false)
+#define PB_LAUNCH_F(FORM, RING, SEL) PB_FIX(FORM, RING, SEL, true)
     if (forest) {
       PB_DISPATCH(kind, sel, PB_LAUNCH_F)
     } else {
@@ -716,11 +716,11 @@ int prepare_wide_kernels(int max_lds_bytes) {
     const int bytes = (want < max_lds_bytes ? want : max_lds_bytes) - 1024;
     const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
     bool ok = true;
-#define PB_SET(FULL, RING, SEL)                                                                                               \
-  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FULL, RING, SEL, false>), attr, bytes) == hipSuccess && \
-       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FULL, RING, SEL, true>), attr, bytes) == hipSuccess &&        \
-       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FULL, RING, SEL, false>), attr, bytes) == hipSuccess &&      \
-       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FULL, RING, SEL, true>), attr, bytes) == hipSuccess
+#define PB_SET(FORM, RING, SEL)                                                                                               \
+  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FORM, RING, SEL, false>), attr, bytes) == hipSuccess && \
+       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_fix_kernel<FORM, RING, SEL, true>), attr, bytes) == hipSuccess &&        \
+       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FORM, RING, SEL, false>), attr, bytes) == hipSuccess &&      \
+       hipFuncSetAttribute(reinterpret_cast<const void*>(wide_spec_kernel<FORM, RING, SEL, true>), attr, bytes) == hipSuccess
     for (int ms = 0; ms < 12; ++ms) PB_DISPATCH(ms / 3, ms % 3, PB_SET)
 #undef PB_SET
     if (ok) {

@@ -169,3 +169,54 @@ def test_step_on_very_wide_rows(V):
         if forest:
             pb.pb_forest_free(forest)
         pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("V", [516, 640, 768, 1000, 1020, 1284, 5000, 10000, 16380])
+def test_aligned_rows_that_end_inside_a_chunk(V):
+    """Whole 16-byte groups, the last chunk part empty: the form without copies (all rules, a table of trees among them)."""
+    rng = np.random.default_rng(34000 + V)
+    for case in range(4):
+        blank = int(rng.choice([0, -1, V - 1, V // 2]))
+        eos = -1 if case == 3 else int(rng.choice([-1, V - 2 if blank != V - 2 else V - 3, V - 1 if blank != V - 1 else 1]))
+        toks, offs, ot, tr = _tree(rng, V, blank, eos, case % 3, float(rng.choice([0.0, 0.5, -0.25])))
+        B = int(rng.choice([1, 3, 6]))
+        T = int(rng.choice([9, 33, 70])) if V <= 1100 else 9
+        x = _rows(rng, T, B, V, blank, toks, offs)
+        stride = V + int(rng.choice([0, 4, 8]))
+        buf, _ = _on_device(x, stride, 0)
+        alpha = float(rng.choice([0.0, 0.5, 1.0, -0.5]))
+        s0 = rng.integers(0, ot.num_states, B).astype(np.int32)
+        last0 = rng.integers(-1, V, B).astype(np.int32)
+        if B > 1:
+            s0[1] = ot.num_states
+        ok = [b for b in range(B) if s0[b] < ot.num_states]
+        forest = pb.pb_forest_build([tr]) if case == 3 else None
+        ids = dev(np.zeros(B, np.int32))
+        for mode in (0, 1, 2):
+            where = dict(V=V, case=case, blank=blank, eos=eos, mode=mode, stride=stride, T=T, B=B, alpha=alpha)
+            print("groups", where, flush=True)
+            o = [torch.full((B,), -7, dtype=torch.int32, device=DEV), torch.full((B,), -7, dtype=torch.int32, device=DEV),
+                 torch.zeros(B, device=DEV)]
+            if forest:
+                pb.pb_fuse_step_forest(forest, buf, stride, ids, dev(s0), dev(last0), alpha, B, mode, o[0], o[1], o[2], 0)
+            else:
+                pb.pb_fuse_step_select(tr, buf, stride, dev(s0), dev(last0), alpha, B, mode, o[0], o[1], o[2], 0)
+            torch.cuda.synchronize()
+            _check(o, ot.fuse_step_select(np.ascontiguousarray(x[0, ok]), s0[ok], last0[ok], alpha, mode), ok, where)
+            want = ot.fuse_frames_select(np.ascontiguousarray(x[:, ok]), s0[ok], last0[ok], alpha, mode)
+            need = pb.pb_fuse_frames_workspace_bytes(tr, T, B)
+            ws = torch.full((max(need, 8) // 4,), 0x7f7f7f7f, dtype=torch.int32, device=DEV)
+            for with_ws in (False, True):
+                o = [torch.full((T, B), -7, dtype=torch.int32, device=DEV), torch.full((T, B), -7, dtype=torch.int32, device=DEV),
+                     torch.zeros((T, B), device=DEV)]
+                if forest and not with_ws:
+                    pb.pb_fuse_frames_forest(forest, buf, B * stride, stride, ids, dev(s0), dev(last0), alpha, T, B, mode,
+                                             o[0], o[1], o[2], 0)
+                else:
+                    pb.pb_fuse_frames_ws(tr, buf, B * stride, stride, dev(s0), dev(last0), alpha, T, B, mode, o[0], o[1],
+                                         o[2], ws, need, 0)
+                torch.cuda.synchronize()
+                _check(o, want, ok, where)
+        if forest:
+            pb.pb_forest_free(forest)
+        pb.pb_free(tr)
