@@ -122,8 +122,8 @@ __device__ __forceinline__ int tok_of(int j, int lane) { return 256 * (j >> 2) +
 // Does the lane's slot j hold chunk-relative token `rel` (wave-uniform)?  Written so that the slot
 // test stays on the scalar side and no per-slot token ids have to live in vector registers.
 __device__ __forceinline__ bool slot_is(int j, int lane, int rel) {
-  const int slot = ((rel >> 8) << 2) | (rel & 3);  // uniform; (a position behind the lanes' slots, or -1, matches none)
-  return (slot == j) && (lane == ((rel >> 2) & 63));
+  const int slot = ((rel >> 8) << 2) | (rel & 3);  // uniform
+  return (slot == j) && (lane == ((rel >> 2) & 63)) && (static_cast<unsigned>(rel) < 2u * kChunk);
 }
 
 // The slot in which this lane holds chunk-relative token `rel` (wave-uniform), -1 in every other lane: a test of
@@ -269,22 +269,25 @@ __device__ __forceinline__ float group_maxima(const float (&f)[NS], float (&g)[N
 template <int FORM, int NS>
 __device__ __forceinline__ void load_row(const float* __restrict__ base, int cb, int V, int lane, float (&x)[NS],
                                          float fill = -INFINITY) {
-  typedef float vf4 __attribute__((ext_vector_type(4)));
+  // (float4 where it is aligned, and the cascade of first_pos_equal, are what the register allocator does best with: with
+  // vectors and a loop the decoder of 1024 tokens spilled 397 scalar registers instead of 300 under the CTC rule, 4 % of
+  // its time)
   typedef float vf4_any __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
   for (int i = 0; i < NS / 4; ++i) {
     const int u = cb + 256 * i + 4 * lane;
-    vf4 q;
+    float4 q;
     if constexpr (FORM == kWhole) {
-      q = *reinterpret_cast<const vf4*>(base + u);
+      q = *reinterpret_cast<const float4*>(base + u);
     } else if constexpr (FORM == kGroups) {
       if (u < V) {
-        q = *reinterpret_cast<const vf4*>(base + u);
+        q = *reinterpret_cast<const float4*>(base + u);
       } else {
-        q = vf4{fill, fill, fill, fill};
+        q = make_float4(fill, fill, fill, fill);
       }
     } else {
-      q = *reinterpret_cast<const vf4_any*>(base + static_cast<unsigned>(min(u, V - 4)));
+      const vf4_any h = *reinterpret_cast<const vf4_any*>(base + static_cast<unsigned>(min(u, V - 4)));
+      q = make_float4(h.x, h.y, h.z, h.w);
     }
     x[4 * i + 0] = q.x; x[4 * i + 1] = q.y; x[4 * i + 2] = q.z; x[4 * i + 3] = q.w;
   }
@@ -300,22 +303,31 @@ __device__ __forceinline__ void store_row_lds(float* row, int lane, const float 
 // Lowest position whose fused value equals M; g are the lane's group maxima.
 template <int NS>
 __device__ __forceinline__ int first_pos_equal(const float (&f)[NS], const float (&g)[NS / 4], float M, int lane) {
-  u64 b[NS / 4];
-#pragma unroll
-  for (int i = 0; i < NS / 4; ++i) b[i] = __ballot(g[i] == M);
   int gi = -1;
   u64 bm = 0, e0 = 0, e1 = 0, e2 = 0;  // the fourth token of a group needs no ballot: it is the one left
+  auto look = [&](int i, u64 have) {
+    gi = i;
+    bm = have;
+    e0 = __ballot(f[4 * i] == M);
+    e1 = __ballot(f[4 * i + 1] == M);
+    e2 = __ballot(f[4 * i + 2] == M);
+  };
+  if constexpr (NS == 16) {
+    const u64 b0 = __ballot(g[0] == M), b1 = __ballot(g[1] == M), b2 = __ballot(g[2] == M), b3 = __ballot(g[3] == M);
+    if (b0) look(0, b0);
+    else if (b1) look(1, b1);
+    else if (b2) look(2, b2);
+    else if (b3) look(3, b3);
+    else return 0;  // only with NaN inputs (precondition violation): stay in range
+  } else {
+    u64 b[NS / 4];
 #pragma unroll
-  for (int i = 0; i < NS / 4; ++i) {
-    if (gi < 0 && b[i] != 0) {
-      gi = i;
-      bm = b[i];
-      e0 = __ballot(f[4 * i] == M);
-      e1 = __ballot(f[4 * i + 1] == M);
-      e2 = __ballot(f[4 * i + 2] == M);
-    }
+    for (int i = 0; i < NS / 4; ++i) b[i] = __ballot(g[i] == M);
+#pragma unroll
+    for (int i = 0; i < NS / 4; ++i)
+      if (gi < 0 && b[i] != 0) look(i, b[i]);
+    if (gi < 0) return 0;  // only with NaN inputs (precondition violation): stay in range
   }
-  if (gi < 0) return 0;  // only with NaN inputs (precondition violation): stay in range
   const int L = first_lane(bm);
   const u64 bit = 1ull << L;
   const int k = (e0 & bit) ? 0 : (e1 & bit) ? 1 : (e2 & bit) ? 2 : 3;

@@ -175,13 +175,13 @@ __device__ __forceinline__ void row_winners(const TreeView& t, const float* __re
                                             const float* rs, int nch, int lane, int& v0, int& w) {
   LaneBest fb = lane_best_init(), rb = lane_best_init(), gb = lane_best_init();
   float x[2][16];
-  load_row<FORM>(rowp, 0, t.V, lane, x[0]);
+  load_chunk<FORM>(rowp, 0, t.V, lane, x[0]);
   for (int ch0 = 0; ch0 < nch; ch0 += 2) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int ch = ch0 + u;
       if (ch < nch) {
-        if (ch + 1 < nch) load_row<FORM>(rowp, (ch + 1) * kChunk, t.V, lane, x[(u + 1) % 2]);
+        if (ch + 1 < nch) load_chunk<FORM>(rowp, (ch + 1) * kChunk, t.V, lane, x[(u + 1) % 2]);
         float rw[16];
         read_rs_lds(rs, ch * kChunk, lane, rw);
         wide_chunk<SEL, true>(x[u], rw, ch, 0.0f, alpha, fb, rb, gb);
@@ -253,7 +253,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
   // the buffer the chunk before the current one has just left, at the start of a chunk's turn.
   float xb[RING][16];
 #pragma unroll
-  for (int u = 0; u + 1 < RING; ++u) load_row<FORM>(rp, u * kChunk, V, lane, xb[u]);
+  for (int u = 0; u + 1 < RING; ++u) load_chunk<FORM>(rp, u * kChunk, V, lane, xb[u]);
   StoredLane<SEL == 2> stored;
   if (COMPARE) stored.fetch(lane, f0, f1, B, b, tokens, states);
   int s = uniform_i(s_in);
@@ -294,7 +294,7 @@ __device__ __forceinline__ bool run_frames_wide(const TreeView& t, const float* 
           // compiler wait for exactly the chunk it needs and keep the others in flight.
           const int nx = ch + RING - 1;
           const bool wrap = nx >= nchp;
-          load_row<FORM>(wrap ? rpn : rp, (wrap ? nx - nchp : nx) * kChunk, V, lane, xb[(u + RING - 1) % RING]);
+          load_chunk<FORM>(wrap ? rpn : rp, (wrap ? nx - nchp : nx) * kChunk, V, lane, xb[(u + RING - 1) % RING]);
           float rw[16];
           read_rs_lds(rs, ch * kChunk, lane, rw);
           wide_chunk<SEL, TRACK>(xb[u], rw, ch, cur.p_root, alpha, fb, rb, gb);
@@ -483,9 +483,9 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
   const float* rowp = logp + static_cast<size_t>(b) * row_stride;
   const float* rsp = LEAN ? root_score : t.root_score;
   float x[CPW][16], rw[16];
-  load_row<FORM>(rsp, wave * CPW * kChunk, t.V, lane, rw);
+  load_chunk<FORM>(rsp, wave * CPW * kChunk, t.V, lane, rw);
 #pragma unroll
-  for (int c = 0; c < CPW; ++c) load_row<FORM>(rowp, (wave * CPW + c) * kChunk, t.V, lane, x[c]);
+  for (int c = 0; c < CPW; ++c) load_chunk<FORM>(rowp, (wave * CPW + c) * kChunk, t.V, lane, x[c]);
   int s = tree_ok ? states_in[b] : -1;  // an unknown tree marks the hypothesis like an invalid state
   __builtin_amdgcn_sched_barrier(0);
   s = uniform_i(s);
@@ -524,7 +524,7 @@ __global__ void __launch_bounds__(1024) step_wide_kernel(
 #pragma unroll
   for (int c = 0; c < CPW; ++c) {
     float next_rw[16];
-    if (c + 1 < CPW) load_row<FORM>(rsp, (wave * CPW + c + 1) * kChunk, t.V, lane, next_rw);
+    if (c + 1 < CPW) load_chunk<FORM>(rsp, (wave * CPW + c + 1) * kChunk, t.V, lane, next_rw);
     wide_chunk<SEL, false>(x[c], rw, wave * CPW + c, p_root, alpha, fb, rb, gb);
     if (c + 1 < CPW) {
 #pragma unroll
