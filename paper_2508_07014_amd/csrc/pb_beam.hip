@@ -16,13 +16,13 @@
 //  * An utterance of dead beams (hypothesis scores of -inf: a finished one in a batch, mostly) has only totals of -inf, so
 //    its survivors are the first K flat indices; the rows are not looked at (put_dead).
 //
-// U x K, V: 32 x 4, 1024 7.8 -> 7.0 us against a kernel with a wave per beam and K rounds of arg-max in each; against the
-// workgroup-per-utterance row build (launch_beam) 16 x 8, 1025, a table of trees 35.9 -> 8.2, 32 x 8, 8192 81.9 -> 17.8,
-// 16 x 16, 50000 1130 -> 99.  With one dead utterance among
-// 32 a step takes what it takes without (32 x 8, 8192: 17 us; K rounds of arg-max over its rows took 182), with constant
-// rows everywhere about twice that (38; rounds 187).  With thousands of utterances of one or two beams (4096 x 2,
-// V = 1024) the wave-per-beam kernel was up to 6 % faster (14.5 us against 15.4), with four beams it was slower (34.4
-// against 27).
+// U x K, V: 32 x 4, 1024 7.0 -> 5.9 us (graph replay) against a kernel with a wave per beam and K rounds of arg-max in
+// each; against the workgroup-per-utterance row build (launch_beam) 16 x 8, 1025, a table of trees 35.9 -> 8.2, 32 x 8,
+// 8192 81.9 -> 17.0, 16 x 16, 50000 1130 -> 93.  With one dead utterance among 32 a step takes what it takes without
+// (32 x 8, 8192: 17 us; K rounds of arg-max over its rows took 182), with constant rows everywhere about twice that (38;
+// rounds 187).
+//
+// A few beams over aligned narrow rows keep the wave-per-beam kernel (see wave_beams).
 //
 // Rows whose share of a wave fits its registers are read once (beam_regs_kernel); longer ones are streamed, with the
 // maximum of every chunk kept, and only the chunks that reach the bound are read again (beam_stream_kernel).
@@ -676,6 +676,143 @@ __global__ void __launch_bounds__(64 * kBeamWaves) beam_stream_kernel(
   write_ranked(sh, t, u, n, K, states_in, out);
 }
 
+// ---- few beams over aligned rows of 516 .. 1024 tokens ---------------------------------------------------------------------
+// A wave per beam.  It keeps the raw row in LDS, where the arcs of the failure chain (one per lane, deepest state first)
+// find their log-probs and leave their fused values and children; the beam's K best totals are taken in K rounds of
+// arg-max (a taken entry becomes NaN, which no maximum or equality test selects), and wave 0 merges the K * K.  For one to
+// three beams that is less than a bound and a list (see wave_beams).
+constexpr int kWaveBeams = 3;
+constexpr int kWaveLdsFloats = 2 * kChunk + kTagWords;  // row and values, children, marks
+constexpr int kWaveCands = 16;                           // candidates (a multiple of four: the rows behind them are aligned)
+static_assert(kWaveBeams * kWaveBeams <= kWaveCands, "the merge holds every wave's best");
+constexpr size_t wave_beam_lds(int K) { return (3 * kWaveCands + static_cast<size_t>(K) * kWaveLdsFloats) * sizeof(float); }
+
+template <int FORM>
+__global__ void __launch_bounds__(64 * kWaveBeams) beam_wave_kernel(
+    const float* __restrict__ logp, int64_t row_stride, const float* hyp, const int32_t* __restrict__ states_in,
+    const float* __restrict__ root_score, float alpha, int K, int32_t* __restrict__ tokens, int32_t* __restrict__ parents,
+    int32_t* __restrict__ states_out, float* scores_out, DeviceTree dt) {
+  extern __shared__ __align__(16) char lds_bytes[];
+  float* lds = reinterpret_cast<float*>(lds_bytes);
+  const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
+  const int u = blockIdx.x, h = u * K + wave;
+  const TreeView t = make_view(dt);
+  const int V = t.V;
+  const float* lrow = logp + static_cast<size_t>(h) * row_stride;
+  float x[16], c[16];
+  load_row<FORM>(root_score, 0, V, lane, c, 0.0f);  // (the tree's array, as a leading argument: in registers at the start)
+  load_row<FORM>(lrow, 0, V, lane, x);
+  const int sk = states_in[u * K + min(lane, K - 1)];  // every wave sees all K states
+  const float hs_in = hyp[h];
+  __builtin_amdgcn_sched_barrier(0);  // (all of the above is in flight before the first wait)
+  // per-slot multiplier of the boost (alpha; 0 in the blank's slot), formed while the states are on their way
+  float am[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    am[j] = slot_is(j, lane, t.blank) ? 0.0f : alpha;
+    asm volatile("" : "+v"(am[j]));  // (formed here, not where it is used)
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  float* cand_val = lds;  // [K * K], then the flat indices and the children
+  int* cand_idx = reinterpret_cast<int*>(lds + kWaveCands);
+  int* cand_nxt = cand_idx + kWaveCands;
+  float* ov = lds + 3 * kWaveCands + wave * kWaveLdsFloats;
+  int* ov_next = reinterpret_cast<int*>(ov + kChunk);
+  unsigned* tags = reinterpret_cast<unsigned*>(ov + 2 * kChunk);
+  const bool bad = __ballot(!valid_state(t, sk)) != 0;  // (marked as a whole at the end)
+  const int s = bad ? 0 : __builtin_amdgcn_readlane(sk, wave);
+  const float hs = uniform_f(hs_in);
+  const Cursor cur = cursor_at(t, s);
+  __builtin_amdgcn_sched_barrier(0);  // (the parts of the cursor are requested together)
+#pragma unroll
+  for (int j = 0; j < 16; ++j) c[j] = __fmul_rn(am[j], __fadd_rn(cur.p_root, c[j]));  // base boosts, in place
+  tags_clear(tags, lane);
+  store_row_lds(ov, lane, x);
+  {
+    float p = 0.0f;
+    for (int xs = s; xs != 0;) {
+      const Rec r = load_rec(t, xs);
+      for (int j = lane; j < r.count; j += 64) {
+        const ArcRec a = t.arc[r.begin + j];
+        if (!tag_test(tags, a.token)) {  // tokens of one state are distinct: no lane races for an entry
+          tag_set(tags, a.token);
+          ov[a.token] = __fadd_rn(ov[a.token], __fmul_rn(alpha, __fadd_rn(p, a.score)));
+          ov_next[a.token] = r.begin + j + 1;
+        }
+      }
+      p = __fadd_rn(p, r.backoff);
+      xs = uniform_i(r.fail);
+    }
+  }
+  float tv[16];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int v0 = 256 * i + 4 * lane;
+    const unsigned bits = tags[v0 >> 5] >> (v0 & 31);
+    const float4 o = *reinterpret_cast<const float4*>(ov + v0);
+    const float oa[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float expansion = ((bits >> k) & 1u) ? oa[k] : __fadd_rn(x[4 * i + k], c[4 * i + k]);
+      // positions past V hold -inf: the real tokens, which come first, are taken before them
+      tv[4 * i + k] = (FORM == kWhole || v0 + k < V) ? __fadd_rn(hs, expansion) : -INFINITY;
+    }
+  }
+  if (t.eos >= 0) {  // EOS rule (Sec. II-C): boosted by the value tabulated for the state; no arc carries the token
+    const float ce = __fmul_rn(alpha, cur.eos_boost);
+    const int ln = opaque(lane);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) tv[j] = slot_is(j, ln, t.eos) ? __fadd_rn(hs, __fadd_rn(x[j], ce)) : tv[j];
+  }
+  for (int r = 0; r < K; ++r) {
+    float g[4];
+    const float M = ukey_val(wave_max_u(ukey(group_maxima(tv, g))));
+    const int v = uniform_i(pos_token<FORM>(t, first_pos_equal(tv, g, M, lane)));
+    int nx = s;  // the blank and the EOS keep the state
+    if (v != t.blank && v != t.eos) nx = tag_test(tags, v) ? ov_next[v] : t.root_next[v];
+    if (lane == 0) {
+      cand_val[wave * K + r] = M;
+      cand_idx[wave * K + r] = wave * V + v;
+      cand_nxt[wave * K + r] = nx;
+    }
+    const int taken = slot_in_lane(opaque(lane), v);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) tv[j] = taken == j ? NAN : tv[j];
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const int n = K * K;
+  const bool have = lane < n;
+  const float val = have ? cand_val[lane] : 0.0f;
+  const int idx = have ? cand_idx[lane] : INT_MAX, nxt = have ? cand_nxt[lane] : 0;
+  bool live = have;
+  for (int j = 0; j < K; ++j) {
+    const float M = ukey_val(wave_max_u(live ? ukey(val) : 0u));
+    const int best = wave_min_nn((live && val == M) ? idx : INT_MAX);
+    if (live && idx == best) {
+      tokens[u * K + j] = bad ? -1 : idx % V;
+      parents[u * K + j] = bad ? -1 : idx / V;
+      states_out[u * K + j] = bad ? -1 : nxt;
+      scores_out[u * K + j] = bad ? NAN : val;
+      live = false;
+    }
+  }
+}
+
+// Which calls the wave-per-beam kernel is for: one tree, aligned rows of more than 512 tokens (up to there the other kernel
+// holds fewer positions per lane and is faster), one beam until the chip is full several times over, two or three where
+// the chip is about full (us, this kernel / the other one):
+//   V = 1024, K = 1: U = 1 3.64/3.71, 1024 5.13/5.41, 4096 6.43/7.31, 16384 19.5/19.9; V = 640: 4096 6.95/7.34, 16384 19.3/18.6
+//   V = 1024, K = 2: U = 512 5.95/5.91, 768 6.19/7.23, 2048 7.46/8.68, 3072 10.4/10.2, 16384 40.3/38.7; V = 640: 2048 7.64/8.51
+//   V = 1024, K = 3: U = 256 6.52/5.76, 768 7.39/7.85, 1536 9.11/9.74, 2048 12.6/11.1; V = 640: 1536 9.34/9.35
+bool wave_beams(const DeviceTree& t, const TreePick& pick, const float* logp, int64_t row_stride, int K, int64_t U) {
+  auto aligned16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+  if (pick.table != nullptr || K > kWaveBeams || t.vocab_size <= 512 || t.vocab_size > kChunk || t.vocab_size % 4 != 0 ||
+      row_stride % 4 != 0 || !aligned16(logp) || !aligned16(t.root_score))
+    return false;
+  return K == 1 ? U <= 8192 : U * K > 1024 && U * K <= 4608;
+}
+
 int g_beam_max_lds = 48 * 1024;  // dynamic LDS the device allows these kernels, set once
 
 struct BeamPlan {
@@ -715,6 +852,19 @@ int launch_beam_wave(const DeviceTree& t, const TreePick& pick, const float* d_l
                      const int32_t* d_states_in, float alpha, int32_t U, int32_t K, int32_t* d_tokens,
                      int32_t* d_parents, int32_t* d_states_out, float* d_scores_out, hipStream_t stream) {
   const int V = t.vocab_size;
+  if (wave_beams(t, pick, d_logp, row_stride, K, U)) {
+#define PB_WAVE(FORM)                                                                                                     \
+  hipLaunchKernelGGL(beam_wave_kernel<FORM>, dim3(static_cast<unsigned>(U)), dim3(static_cast<unsigned>(64 * K)),         \
+                     wave_beam_lds(K), stream, d_logp, row_stride, d_hyp, d_states_in, t.root_score, alpha, K, d_tokens,  \
+                     d_parents, d_states_out, d_scores_out, t)
+    if (V == kChunk) {
+      PB_WAVE(kWhole);
+    } else {
+      PB_WAVE(kGroups);
+    }
+#undef PB_WAVE
+    return hipGetLastError() == hipSuccess ? PB_OK : PB_EHIP;
+  }
   const BeamPlan p = plan_beam(V, K, U);
   const dim3 grid(static_cast<unsigned>(U)), block(static_cast<unsigned>(64 * p.waves));
   const bool forest = pick.table != nullptr;

@@ -183,3 +183,29 @@ def test_dead_utterances_with_a_table_of_trees(V, K):
         _compare(o, want, rows, (V, K, u))
     assert all(bool((g[2 * K:] == -1).all()) for g in o[:3]) and bool(torch.isnan(o[3][2 * K:]).all())
     pb.pb_forest_free(forest)
+
+
+@pytest.mark.parametrize("V", [516, 1000, 1024])
+@pytest.mark.parametrize("K,U", [(1, 3), (1, 8192), (1, 8193), (2, 512), (2, 513), (2, 2304), (2, 2305), (3, 342), (3, 1536), (3, 1537)])
+def test_few_beams_on_both_sides_of_the_dispatch(V, K, U):
+    """Aligned rows: a wave per beam or a list of survivors, by the number of utterances; ties, dead beams, a bad state."""
+    rng = np.random.default_rng(56000 + V + U)
+    blank, eos = int(rng.choice([0, -1, V - 1])), int(rng.choice([-1, V - 2]))
+    toks, offs, ot, tr = _tree(rng, V, blank, eos, 1, 0.25)
+    x = torch.randn((U * K, V), device=DEV) * 2
+    x = torch.round(x * 4) / 4                        # (many exact ties)
+    x[rng.integers(0, U * K, 5)] = -float("inf")
+    hyp = np.round(-3 * rng.random(U * K) * 4).astype(np.float32) / 4
+    hyp[rng.random(U * K) < 0.2] = -np.inf
+    states = rng.integers(0, ot.num_states, U * K).astype(np.int32)
+    states[K * (U // 2)] = ot.num_states
+    o = _outputs(U * K)
+    print("few", V, K, U, flush=True)
+    pb.pb_fuse_step_beam(tr, x, V, dev(hyp), dev(states), 0.5, U, K, o[0], o[1], o[2], o[3], 0)
+    torch.cuda.synchronize()
+    assert all(bool((g[K * (U // 2):K * (U // 2 + 1)] == -1).all()) for g in o[:3])
+    look = [u for u in sorted({0, 1, U - 1, *rng.integers(0, U, 40).tolist()}) if u != U // 2]
+    rows = [u * K + k for u in look for k in range(K)]
+    xs = x[torch.tensor(rows, device=DEV)].cpu().numpy()
+    _compare(o, ot.fuse_step_beam(xs, hyp[rows], states[rows], 0.5, len(look), K), rows, (V, K, U))
+    pb.pb_free(tr)
