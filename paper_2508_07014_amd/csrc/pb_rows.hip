@@ -745,21 +745,38 @@ size_t walk_lds_bytes(int V, int T, int waves) {
 
 // Which calls the two passes are for.  Pass 1 reads the rows at the chip's rate whatever T and B are; pass 2 costs about
 // 10 us and 0.5 to 1 us for every 16 frames of a hypothesis.  The segment decoders need some thousand segments for that
-// rate and read again what a wrong guess has spoilt, but have no second pass over the frames.  Measured (us, segment
-// decoders / two passes; random rows, then rows with 20 % of the frames inside listed phrases):
-//   V > 16384 (no segment decoder): 32001, 100 frames x 16: 3340 / 70
-//   V = 16000: 800 x 1 140/45, 174/55; 200 x 8 109/38, 168/106; 400 x 16 123/102, 200/174
-//   V = 8192: 400 x 1 51/29, 68/30; 200 x 32 83/53, 108/87; 400 x 16 74/57, 117/125; 200 x 256 300/318
-//   V = 2500: 100 x 1 26/19, 31/20; 100 x 128 53/44, 68/63; 400 x 16 37/47, 55/77
-//   V = 1025: 250 x 32 40/36, 79/74 (CTC rule 47/30, 103/53); 500 x 32 45/50, 75/88 (54/45, 115/78); 1000 x 16 51/68, 90/125
-//   V = 129: 96 x 8 22/26, 28/28; 96 x 512 40/69, 58/78
-// so: never up to 1024 tokens; past that up to the number of rows the passes take at once and the frames the table gives.
+// rate and read again what a wrong guess has spoilt, but have no second pass over the frames.  Measured: time of the two
+// passes over that of the segment decoder, mean over vocabularies, rules and kinds of rows (random; a fifth of the frames
+// inside listed phrases; the same with half of the frames blank), 4365 calls in all.
+//   V = 1025 .. 1280     T <= 128, T * B <= 2048 / more   129 .. 256, <= 2048 / more   257 .. 512, <= 64K   513 ..
+//     single-stage       0.98 / 1.12                      1.00 / 1.20                  1.45                 1.7
+//     two-stage          0.87 / 1.01                      0.93 / 1.09                  1.29                 1.6
+//     CTC                0.79 / 0.75                      0.66 / 0.77                  0.90                 1.1
+//   (500 frames x 32 / 33 / 64 / 128 under the CTC rule, V = 1025: 0.90, 0.83, 0.97, 0.84; 750 x 16: 1.15)
+//   V = 1281 .. 16384    T <= 128, T * B <= 8192 / 16384   T <= V / 16, <= 8192 / 16384   V / 16 .. V / 8, B < 12 / more
+//     1281 .. 2048       0.90 / 0.95                       - / -                          0.90 / 1.01
+//     2500, 3000         0.82 / 0.95                       0.86 / 0.99                    0.86 / 0.98
+//     4096, 6000         0.66 / 0.89                       0.83 / 0.91                    0.85 / 1.05
+//     8192, 10000        0.48 / 0.94                       0.73 / 0.96                    0.65 / 1.11
+//     12288 .. 16384     0.39 / 0.91                       0.72 / 0.97                    0.59 / 1.08
+//   The third column past 8192 rows: 0.92 to 1.03 under the single-stage rule, 0.92 to 1.04 under the CTC rule, with single
+//   calls up to 1.33; 0.88 to 0.93 under the two-stage rule.  Past V / 8: 1.03 to 1.4 up to 3000 tokens; for one to four
+//   hypotheses 1.04 at 4096, 0.83 at 6000, 0.4 to 0.6 above.
+//   V > 16384 (no segment decoder): 32001, 100 frames x 16: 3340 -> 75 us.
+// These are means: a call loses where one hypothesis speaks many phrases, whose frames the second pass takes one by one
+// (CTC rule: V = 6000, 200 x 32 1.4, V = 16384, 250 x 32 1.2), and gains as much where none does.
 static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
   const int64_t rows = static_cast<int64_t>(T) * B;
   if (V > kWideMaxV) return rows <= kMaxWorkgroups;
-  if (V <= 1024 || rows > 16384) return false;
-  if (V <= kNarrowMaxV) return T <= (sel == 0 ? 256 : 512);
-  return T <= (V / 16 > 128 ? V / 16 : 128) || (V >= 4096 && B <= 4);
+  if (V <= 1024) return false;
+  if (V <= kNarrowMaxV) {
+    if (sel == 2) return T <= 512 && rows <= 65536;
+    return T <= (sel == 0 ? 128 : 256) && rows <= 2048;
+  }
+  if (rows > 16384) return false;
+  if (V >= 4096 && B <= 4) return true;
+  const int longest = V / (B < 12 ? 8 : 16);
+  return T <= 128 || (T <= longest && (sel == 1 || rows <= 8192));
 }
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
