@@ -51,7 +51,7 @@ __device__ __forceinline__ int root_choice(const TreeView& t, float alpha, float
   return t.blank >= 0 && (fb > M || (fb == M && t.blank < w)) ? t.blank : w;
 }
 
-// ---- pass 1, rows of up to 64 * NS positions: a wave per row, root scores kept in registers -------------------------
+// ---- pass 1, rows of 1025 .. 64 * NS positions: a wave per row, root scores kept in registers -------------------------
 // A wave takes frames s, s + strips, ... of hypothesis b, the next row requested while one is looked at.
 template <int NS, int SEL>
 __global__ void __launch_bounds__(256) rows_narrow_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
@@ -793,28 +793,17 @@ int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d
     int64_t strips = (8192 + B - 1) / B;  // waves per hypothesis: two rounds of what the chip holds
     if (strips > T) strips = T;
     const int64_t blocks = (strips * B + 3) / 4;
-#define PB_ROWS(NS, SEL)                                                                                              \
-  hipLaunchKernelGGL((rows_narrow_kernel<NS, SEL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, t, pick, \
-                     d_logp, frame_stride, row_stride, alpha, T, B, static_cast<int>(strips), d_tokens, d_states)
-#define PB_SHAPE(SEL)     \
-  if (V <= 256) {         \
-    PB_ROWS(4, SEL);      \
-  } else if (V <= 512) {  \
-    PB_ROWS(8, SEL);      \
-  } else if (V <= 1024) { \
-    PB_ROWS(16, SEL);     \
-  } else {                \
-    PB_ROWS(20, SEL);     \
-  }
+#define PB_ROWS(SEL)                                                                                                      \
+  hipLaunchKernelGGL((rows_narrow_kernel<kNarrowMaxV / 64, SEL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, \
+                     t, pick, d_logp, frame_stride, row_stride, alpha, T, B, static_cast<int>(strips), d_tokens, d_states)
     if (sel == 0) {
-      PB_SHAPE(0)
+      PB_ROWS(0);
     } else {
-      PB_SHAPE(1)
+      PB_ROWS(1);
     }
-#undef PB_SHAPE
 #undef PB_ROWS
   } else {
-    // Waves per row: one per four chunks where the rows alone fill the chip, up to one per chunk where they do not.
+    // Waves per row: one per eight chunks where the rows alone fill the chip, up to one per chunk where they do not.
     const int nch = (V + kChunk - 1) / kChunk;
     int waves = static_cast<int>((8192 + rows - 1) / rows);
     if (waves < (nch + 7) / 8) waves = (nch + 7) / 8;
