@@ -174,6 +174,8 @@ int pb_fuse_step(const pb_tree* tree, const float* d_logp, int64_t row_stride, c
  * d_states): element b is read before anything of hypothesis b is written.  Such a call takes the plain kernel, one
  * workgroup per hypothesis and frame after frame; with start states of their own the faster decoders run.  No other
  * overlap of the outputs with the inputs or with each other is supported.
+ * PB_EUNSUPPORTED (also from the calls below) for more hypotheses than one launch holds (from 4194304 on, by the rows'
+ * width); the single steps, beam steps and dense queries take any number.
  */
 int pb_fuse_frames(const pb_tree* tree, const float* d_logp, int64_t frame_stride, int64_t row_stride,
                    const int32_t* d_states0, float alpha, int32_t T, int32_t B, int32_t* d_tokens,

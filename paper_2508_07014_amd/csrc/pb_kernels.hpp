@@ -44,7 +44,7 @@ constexpr int kStepMaxV = 65536;     // widest row of the single step that one w
 #ifndef PB_WIDE_TARGET_CHAINS
 #define PB_WIDE_TARGET_CHAINS 1024
 #endif
-constexpr int kWideTargetChains = PB_WIDE_TARGET_CHAINS;  // the same for rows wider than 1024 tokens (one wave per SIMD:
+constexpr int kWideTargetChains = PB_WIDE_TARGET_CHAINS;  // the same for rows wider than kNarrowMaxV (one wave per SIMD:
                                                           // a wave keeps three 4-KiB chunks of its rows in flight)
 
 struct SegPlan {

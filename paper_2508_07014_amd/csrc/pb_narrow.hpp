@@ -69,7 +69,7 @@ constexpr int row_slots(int row) { return row == 2 ? 20 : row == 3 ? 4 : row == 
 constexpr int spec_waves(int row) { return row == 2 ? 2 : 4; }
 
 // ------------------------------------------------------------------------------------------------
-// Base boosts of a row with V <= 1024 for the lane's 16 tokens; the root scores come from memory
+// Base boosts of a row for the positions of a lane; the root scores come from memory
 // (cache-resident) because they are needed only when the accumulated backoff of the state changes.
 template <int ROW, int SEL>
 __device__ __forceinline__ void rebuild_base_boost(const TreeView& t, int lane, float p_root, float alpha,
@@ -81,7 +81,7 @@ __device__ __forceinline__ void rebuild_base_boost(const TreeView& t, int lane, 
   make_base_boost<FORM, SEL>(t, ln, p_root, alpha, rw, c);
 }
 
-// One frame of a row with V <= 1024 (a single chunk).  `cur` is the hypothesis' state with its
+// One frame of a row that one wave holds whole.  `cur` is the hypothesis' state with its
 // record; on return it is the state after the chosen token.  Returns the token and fused value.
 //   x     lane's raw log-probs (registers); `next_row()` requests a later frame's row into other
 //         registers
@@ -354,7 +354,7 @@ __device__ __forceinline__ void frame_1k(const TreeView& t, Cursor& cur, const f
   out_val = uniform_f(out_val);
 }
 
-// Boundary guess of the multi-frame decoder for rows of up to 1024 tokens: the state (and label) assumed after
+// Boundary guess of the multi-frame decoder: the state (and label) assumed after
 // frame f, from the rows alone.  Going back from frame f, a frame whose winner under root-state boosts keeps the
 // state (the blank; under the two-stage rules a blank raw arg-max) is skipped; the first frame that moves the
 // state gives root_next[its winner] -- what the true decode does in most frames.  Reaching the first frame of
@@ -470,7 +470,7 @@ __device__ __forceinline__ int run_on_1k(const TreeView& t, const float* __restr
   return 0;
 }
 
-// Decodes frames [f0, f1) of hypothesis b (V <= 1024) starting in state s_in with previous label
+// Decodes frames [f0, f1) of hypothesis b starting in state s_in with previous label
 // last_in (values that may still be in flight from a load: they are first looked at after the row
 // loads have been issued; an invalid state marks the frames).  With COMPARE set, stops after the
 // first frame whose outcome equals the one already stored -- the out-state in `states` and, under
@@ -732,8 +732,6 @@ __global__ void __launch_bounds__(LEAN ? 64 : 256) step_wave_kernel(
   if constexpr (!LEAN) tree_ok = pick_tree(pick, b, mine);
   TreeView t = make_view(mine);
   t.V = V;  // (the tree's, as a leading argument: the clamped row requests need it)
-  // (arc batches requested up front, for the state and for the state its failure link leads to; the lone wave of
-  // the small-batch form has registers to spare under every rule)
   // Arc batches requested up front, for the state and for the state its failure link leads to.  The lone wave of the
   // small-batch form pays for every instruction, also for the addresses of batches most states do not have: one
   // batch up front measured fastest there under every rule (3.11 against 3.21 us per step with four and four).

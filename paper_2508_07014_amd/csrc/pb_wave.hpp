@@ -352,7 +352,7 @@ __device__ __forceinline__ void plain_argmax(const TreeView& t, const float (&x)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Multi-frame decoding in speculative segments: what the row layouts (rows of up to 1024 tokens, wider
+// Multi-frame decoding in speculative segments: what the row layouts (rows that a wave holds whole, wider
 // rows) share.
 //
 // The T frames of a hypothesis are cut into segments decoded concurrently, one wave each (pass 1).  A

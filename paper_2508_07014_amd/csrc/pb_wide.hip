@@ -1,9 +1,9 @@
-// Wave kernels for rows wider than 1024 tokens (gfx950, wave64): the multi-frame greedy decoder and the
+// Wave kernels for rows wider than 1280 tokens (gfx950, wave64): the multi-frame greedy decoder and the
 // single greedy step with their selection rules (Alg. 1 Stage 3, Eq. 1; Sec. II-C).
 //
 //  * A row is consumed in chunks of 1024 tokens in the 16-tokens-per-lane layout of the narrow kernels.  In
-//    the multi-frame decoder one wave owns a hypothesis segment and streams its rows through a ring of four
-//    register buffers that runs across frame boundaries: while a frame is being decided the first chunks of
+//    the multi-frame decoder one wave owns a hypothesis segment and streams its rows through a ring of two to four
+//    register buffers (ring_of) that runs across frame boundaries: while a frame is being decided the first chunks of
 //    the next one are already in flight.  The root scores of the row sit in LDS, shared by the workgroup.
 //  * Base candidates.  Every lane keeps a running maximum of logp[v] + alpha * (p_root + root_score[v])
 //    over its tokens in ascending order (strictly greater replaces, so the lowest token among equal values
