@@ -290,7 +290,7 @@ def side_measurements(torch, pb, W, dev, stream, cfg, toks, offs, tree, info, lo
     if ot is not None:
         from oracle import OracleTree
     extra = {}
-    # ---- what a plain device copy reaches on this box (read + write bytes), and the headline against it
+    # ---- what a plain device copy reaches on this machine (read + write bytes), and the headline against it
     src = torch.ones(64 << 20, dtype=torch.float32, device=dev)
     dst = torch.empty_like(src)
     dst.copy_(src)
