@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -45,6 +46,24 @@ int lookup_scratch(int device) {
 
 size_t padded(size_t bytes) { return (bytes + kAlign - 1) / kAlign * kAlign; }
 
+// The table of arcs by (state, token), see ArcSlot; null where there is no memory for it.
+std::unique_ptr<pb::ArcSlot[]> arc_slots(const pb::HostTree& h, size_t& size) {
+  const size_t arcs = h.arc.size() - static_cast<size_t>(h.root_degree);
+  size = 2;
+  while (size < 2 * arcs) size *= 2;
+  std::unique_ptr<pb::ArcSlot[]> slots(new (std::nothrow) pb::ArcSlot[size]);
+  if (!slots) return slots;
+  std::fill(slots.get(), slots.get() + size, pb::ArcSlot{-1, -1, -1, 0});
+  for (size_t s = 1; s < h.state.size(); ++s) {
+    for (int32_t j = h.arc_begin[s]; j < h.arc_begin[s] + h.arc_count[s]; ++j) {
+      size_t at = pb::arc_hash(static_cast<int32_t>(s), h.arc_token[j]) & (size - 1);
+      while (slots[at].state >= 0) at = (at + 1) & (size - 1);
+      slots[at] = pb::ArcSlot{static_cast<int32_t>(s), h.arc_token[j], j + 1, 0};
+    }
+  }
+  return slots;
+}
+
 // Uploads the flat arrays as one device allocation.  The device stays current only inside the call.
 int upload(pb_tree* tr, int device) {
   const pb::HostTree& h = tr->host;
@@ -55,8 +74,12 @@ int upload(pb_tree* tr, int device) {
   const size_t n_pr = h.p_root.size() * sizeof(float);
   const size_t n_rr = h.root_rec.size() * sizeof(pb::RootRec);
   const size_t n_es = h.eos_score.size() * sizeof(float);
+  size_t n_slots = 0;
+  const std::unique_ptr<pb::ArcSlot[]> slots = arc_slots(h, n_slots);
+  if (!slots) return PB_ENOMEM;
+  const size_t n_as = n_slots * sizeof(pb::ArcSlot);
   const size_t total =
-      padded(n_state) + padded(n_arc) + padded(n_rs) + padded(n_rn) + padded(n_pr) + padded(n_rr) + padded(n_es);
+      padded(n_state) + padded(n_arc) + padded(n_rs) + padded(n_rn) + padded(n_pr) + padded(n_rr) + padded(n_es) + padded(n_as);
   // The wave kernels request the first arcs of a state without a condition, with the index clamped into the
   // state's arc range; for a state without arcs (the last state of the table included) that reads the entry
   // at arc_begin, i.e. up to one ArcRec past the arc table.  The sub-arrays that follow the arc table in the
@@ -85,6 +108,8 @@ int upload(pb_tree* tr, int device) {
     tr->dev.p_root = static_cast<const float*>(put(h.p_root.data(), n_pr));
     tr->dev.root_rec = static_cast<const pb::RootRec*>(put(h.root_rec.data(), n_rr));
     tr->dev.eos_score = n_es ? static_cast<const float*>(put(h.eos_score.data(), n_es)) : nullptr;
+    tr->dev.arc_slot = static_cast<const pb::ArcSlot*>(put(slots.get(), n_as));
+    tr->dev.arc_mask = static_cast<uint32_t>(n_slots - 1);
     tr->dev.eos_id = h.eos_id;
     if (rc == PB_OK) rc = pb::prepare_wave_kernels();
     if (rc == PB_OK) rc = lookup_scratch(device);

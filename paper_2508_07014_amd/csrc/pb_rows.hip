@@ -14,16 +14,21 @@
 //    A row with another token within that band (near_band: 12 and 6, the slack covers the band's own rounding) is
 //    marked, and its frame decided by a plain pass over the row -- unless log-prob and root score are the winner's
 //    own, as they are for most exact ties: equal operands give equal values in every state, and the lower token wins.
-//  * Pass 2 (walk_kernel; one workgroup per hypothesis) runs the automaton on the winners: a wave per segment, from
-//    the state the last winner before it leads to.  A frame gathers a handful of log-probs (winner, blank, the arcs
-//    of the chain) instead of a row, and those of sixteen frames are requested at once for the states the winners lead
-//    to.  Runs of frames whose outcomes fit together are taken over whole, the others -- inside a spoken phrase,
-//    mostly -- are decided one after the other.  The outcomes sit in LDS; segments that started from a wrong guess are decoded again until they meet what
-//    is there (equal state and label: equal future), in rounds between barriers.
+//  * Pass 2 (walk_kernel; one workgroup per hypothesis) runs the automaton on the winners, a frame per lane.  The states
+//    that the winners alone lead to come first: every lane carries the state of the frame before it over its own winner,
+//    again until nothing changes, so a spoken phrase of n tokens takes n turns, all phrases side by side, and a turn is one
+//    access to the table of arcs by (state, token).  Then all frames are decided from those states at once, their arcs
+//    shared out over the lanes.  A frame that comes out differently sends the ones behind it round again, until every
+//    frame was decided from what the frame before it led to; the waves hand on their ends between barriers.  Frames that
+//    the winners do not settle (near ties, a barred label under the CTC rule) take a pass over their row by all waves.
 //
-// Between the passes the winners travel in the call's own outputs: tokens holds w (~w for a marked row), states the
-// raw arg-max (single-stage rule: the blank where it wins under root boosts, else w), so the outputs must not overlap
-// what pass 2 reads (frames_apart).
+// What bounds pass 2 is how many scattered lines one CU takes in (a frame's winners, root scores, records, arcs and their
+// log-probs: about 8 cycles a line), then the chain of dependent accesses.  Against deciding frames one after the other
+// inside a phrase, in segments (medians of a trace): 500 frames x 32, V = 1025, CTC rule 62.6 -> 53.2 us; 100 x 16,
+// V = 32001 32.4 -> 20.1.
+//
+// Between the passes the winners travel in the call's own outputs (put_winners), so the outputs must not overlap what pass 2
+// reads (frames_apart).
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -51,7 +56,25 @@ __device__ __forceinline__ int root_choice(const TreeView& t, float alpha, float
   return t.blank >= 0 && (fb > M || (fb == M && t.blank < w)) ? t.blank : w;
 }
 
-// ---- pass 1, rows of 1025 .. 64 * NS positions: a wave per row, root scores kept in registers -------------------------
+// The winners of a row between the passes: w, v0 and the mark in one word where the vocabulary allows it (the words of a
+// hypothesis lie B apart, a cache line each, and what pass 2 waits for is lines).
+constexpr int kPackedV = 1 << 15;
+__device__ __forceinline__ void put_winners(int V, size_t o, int w, int v0, bool marked, int32_t* tokens, int32_t* states) {
+  if (V <= kPackedV) {
+    tokens[o] = w | v0 << 15 | (marked ? 1 << 30 : 0);
+  } else {
+    tokens[o] = marked ? ~w : w;
+    states[o] = v0;
+  }
+}
+__device__ __forceinline__ void get_winners(int V, int word, int word2, int& w, int& v0, bool& marked) {
+  const bool packed = V <= kPackedV;
+  marked = packed ? (word >> 30 & 1) != 0 : word < 0;
+  w = packed ? word & (kPackedV - 1) : word < 0 ? ~word : word;
+  v0 = packed ? word >> 15 & (kPackedV - 1) : word2;
+}
+
+// ---- pass 1, rows of up to 64 * NS positions: a wave per row, root scores kept in registers -------------------------
 // A wave takes frames s, s + strips, ... of hypothesis b, the next row requested while one is looked at.
 template <int NS, int SEL>
 __global__ void __launch_bounds__(256) rows_narrow_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
@@ -111,11 +134,7 @@ __global__ void __launch_bounds__(256) rows_narrow_kernel(DeviceTree dt, TreePic
     } else {
       v0 = root_choice(t, alpha, x_blank, M, w);
     }
-    if (lane == 0) {
-      const size_t o = static_cast<size_t>(f) * B + b;
-      tokens[o] = marked ? ~w : w;
-      states[o] = v0;
-    }
+    if (lane == 0) put_winners(V, static_cast<size_t>(f) * B + b, w, v0, marked, tokens, states);
 #pragma unroll
     for (int j = 0; j < NS; ++j) x[j] = xn[j];
   }
@@ -225,436 +244,404 @@ __global__ void __launch_bounds__(1024) rows_wide_kernel(DeviceTree dt, TreePick
     }
     marked = __syncthreads_or(differs) != 0;
   }
-  if (threadIdx.x == 0) {
-    const size_t o = static_cast<size_t>(f) * B + b;
-    tokens[o] = marked ? ~w : w;
-    states[o] = v0;
-  }
+  if (threadIdx.x == 0) put_winners(V, static_cast<size_t>(f) * B + b, w, v0, marked, tokens, states);
 }
 
 // ---- pass 2 --------------------------------------------------------------------------------------------------------------
-constexpr int kWalkBlock = 1024;  // frames whose winners and outcomes sit in LDS at a time
-constexpr int kWalkGroup = 16;    // frames whose arcs and log-probs are requested together
-constexpr int kWalkLook = 64;     // frames a segment's guess may look back over (one per lane)
+constexpr int kWalkPairs = 256;  // (frame, arc) pairs looked at together: four a lane
 
-struct WalkLds {  // per block of frames; `tags` is this wave's
-  int *w, *v0, *st, *tok;
-  float* sc;
-  unsigned* tags;
+// What the lanes of a wave tell each other about their frames while they share out the arcs.
+struct alignas(16) WalkMeta {
+  int start, c0, c1, c2;  // first pair of the frame; arcs on the chain's first level, first two, first three
+  int o0, o1, o2, o3;     // arc of pair j of the frame: j + the offset of its level
+  float p1, p2, p3;       // backoff paid before the levels
+  int w;
 };
+struct WalkLds {  // of a wave
+  WalkMeta meta[64];
+  u64 best[64];        // largest (value, lowest arc) of the frame's arcs
+  unsigned flag[64];   // 1: an arc overrides the base winner, 2: two tokens of equal value on two levels
+  int owner[kWalkPairs];
+};
+struct WalkJob {  // a frame that needs a pass over its row
+  int s, frame, excl, label;
+  float x_blank, x_eos;
+};
+constexpr int kWalkJobs = 64;  // taken at a time
+struct WalkBest {  // of a wave's share of such a row
+  float val;
+  int tok, child;
+};
+struct WalkShared {  // of the workgroup
+  int jobs;  // wanted
+  WalkJob job[kWalkJobs];
+  WalkBest part[16];
+  int end[16], end_label[16];  // state and label every wave's frames end in
+};
+
+// A frame, one per lane: what pass 1 knows of its row, the state and label it is taken to start from, and its outcome.
+struct WalkFrame {
+  int w, v0, target;           // winner, raw arg-max (single-stage rule: see root_choice), where w leads from the root
+  bool marked;
+  float xw, x0, xe, rsw;       // log-probs of w, v0 (single-stage rule: the blank) and the EOS; root score of w
+  int s, label;                // start
+  int tok, next, moving;       // outcome: token, state after it; the token the frame emits when it moves the state
+  bool moves, decided;         // the token moves the state; the outcome is the rule's (else: assumed)
+  int hard;                    // the outcome waits for a pass over the row: 1, or 2: the label is known to be barred there
+  float val;
+};
+
+// (Known to lie in device memory: the accesses through pointers of a tree out of a table are flat ones otherwise, which
+// LDS accesses wait for.)
+#define PB_AS1 __attribute__((address_space(1)))
+typedef int v2i __attribute__((ext_vector_type(2)));
 
 template <int SEL>
 struct Walker {
   TreeView t;
-  const float* hyp;  // logp of frame 0 of the block
+  const v4i PB_AS1* states;  // StateRec, two to a state
+  const v2i PB_AS1* arc;     // ArcRec: token, score bits
+  const v4i PB_AS1* slots;   // ArcSlot
+  unsigned slot_mask;
+  const int PB_AS1* root_next;
+  const float PB_AS1 *p_root, *eos_score, *root_score;
+  const float* hyp;  // logp of the frame of lane 0
   int64_t frame_stride;
   float alpha;
-  WalkLds L;
-  int tag_words, nch, lane;
+  WalkLds& L;
+  int lane;
 
-  // The state and label a segment that begins at frame f0 > 0 is guessed to start from: the last winner that moves
-  // the state (block_s: the state the block starts in, for a block that only keeps it).
-  __device__ __forceinline__ void guess(int f0, int block_s, int& s, int& label) const {
-    const int f = f0 - 1 - lane;
-    const int v0 = f >= 0 ? L.v0[f] : 0, wm = f >= 0 ? L.w[f] : 0, w = wm < 0 ? ~wm : wm;
-    bool moves = f >= 0 && v0 != t.blank;
-    if (SEL == 2 && f >= 1) {  // a repeat of the label before it keeps the state
-      const int pm = L.w[f - 1], pv = L.v0[f - 1];
-      moves = moves && v0 != (pv == t.blank ? pv : (pm < 0 ? ~pm : pm)) && v0 != pv;
-    }
-    const u64 mask = __ballot(moves);
-    if (mask != 0) {
-      s = uniform_i(t.root_next[__builtin_amdgcn_readlane(SEL == 0 ? v0 : w, first_lane(mask))]);
-    } else {
-      s = f0 <= kWalkLook ? block_s : 0;
-    }
-    label = __builtin_amdgcn_readlane(SEL == 0 || !(mask & 1) ? v0 : w, 0);
+  // The lanes go on from here together.  Needed (a) between what they write and read of each other in LDS: the operations
+  // of one wave are executed in order, but without the fences the compiler hands a lane what it has written itself; (b) at
+  // the end of a loop body whose last branch differs from lane to lane: the lanes that take it and those that do not get a
+  // way back of their own otherwise, the compiler makes two nested loops of the two, and the inner one runs its ballots and
+  // shuffles with half of the lanes.  (No instruction comes of it.)
+  __device__ __forceinline__ static void together() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 
-  // Decodes frames [f0, f1) of the block from (s, last).  COMPARE: stops at the frame that meets the stored outcome
-  // and returns true; false when the end was reached.
-  //   Frames are first decided side by side, a lane holding one, from the states the winners before them lead to; then
-  //   runs of frames whose outcome is the state the next one was decided from are taken over whole, and what lies
-  //   between them -- mostly inside a spoken phrase -- is decided frame by frame.  (Frame by frame throughout took
-  //   about 1 us a frame, a chain of dependent reductions.)
-  template <bool COMPARE>
-  __device__ __forceinline__ bool run(int f0, int f1, int s, int last) const {
-    Cursor cur = cursor_at(t, s);
+  // The state that the arc of state s on token v leads to, 0 if there is none (per lane).
+  __device__ __forceinline__ int child(int s, int v) const {
 #pragma unroll 1
-    for (int fb = f0; fb < f1; fb += 64) {
-      const int n = min(64, f1 - fb);
-      // ---- one frame per lane: its winner and what the winner's value and target need --------------------------
-      const int lf = fb + min(lane, n - 1);
-      const float* lrow = hyp + static_cast<int64_t>(lf) * frame_stride;
-      const int wm = L.w[lf], w = wm < 0 ? ~wm : wm, v0 = L.v0[lf];
-      const int old_st = COMPARE ? L.st[lf] : 0, old_tok = COMPARE ? L.tok[lf] : 0;
-      const float xw = lrow[w];
-      const float x0 = SEL != 0 ? lrow[v0] : (t.blank >= 0 ? lrow[t.blank] : 0.0f);
-      const float xe = t.eos >= 0 ? lrow[t.eos] : 0.0f;
-      const float rsw = t.root_score[w];
-      const v8i rr = reinterpret_cast<const v8i*>(root_rec)[w];
-      int out_st = 0, out_tok = 0;
-      float out_sc = 0.0f;
-      Ahead g{};
-      if constexpr (!COMPARE) g = decide_ahead(cur, last, fb, n, wm, w, v0, xw, x0, xe, rsw, rr);
-      int met = -1;
-#pragma unroll 1
-      for (int l = 0; l < n && met < 0;) {
-        if (!COMPARE && ((g.settled >> l) & 1) && cur.s == __builtin_amdgcn_readlane(g.s, l) &&
-            (SEL != 2 || last == __builtin_amdgcn_readlane(g.label, l))) {
-          const int e = min(n - 1, l + __builtin_ctzll(~(g.linked >> l)));  // (linked has no bit for the last lane)
-          const bool in = lane >= l && lane <= e;
-          out_st = in ? g.next : out_st;
-          out_tok = in ? g.tok : out_tok;
-          out_sc = in ? g.val : out_sc;
-          const int kind = __builtin_amdgcn_readlane(g.kind, e);
-          if (kind == kByArc) {
-            cur = cursor_at(t, __builtin_amdgcn_readlane(g.next, e));
-          } else if (kind == kByRoot) {
-            cur = cursor_from_root_rec(lane_rec(rr, e));
-          } else {
-            cur = Cursor{__builtin_amdgcn_readlane(g.s, e), Rec{__builtin_amdgcn_readlane(g.begin, e),
-                         __builtin_amdgcn_readlane(g.count, e), 0, 0.0f}, Rec{0, 0, 0, 0.0f}, lane_f(g.p_root, e),
-                         lane_f(g.eos_boost, e)};
-          }
-          last = __builtin_amdgcn_readlane(g.tok, e);
-          l = e + 1;
-          continue;
-        }
-        const float* row = hyp + static_cast<int64_t>(fb + l) * frame_stride;
-        const int fw = __builtin_amdgcn_readlane(w, l), fv0 = __builtin_amdgcn_readlane(v0, l);
-        const float fx0 = lane_f(x0, l);
-        FrameOut o{fx0, fv0, false, 0};
-        if (SEL == 0 || (fv0 != t.blank && (SEL != 2 || fv0 != last))) {
-          const bool marked = __builtin_amdgcn_readlane(wm, l) < 0;
-          const float M = __fadd_rn(lane_f(xw, l), __fmul_rn(alpha, __fadd_rn(cur.p_root, lane_f(rsw, l))));
-          Cursor child;
-          bool child_known;
-          o = decide(cur, row, M, fw, marked, fx0, lane_f(xe, l), last, child, child_known);
-          if (o.arc) {
-            cur = child_known ? child : cursor_at(t, o.child);
-          } else if (o.tok == fw && fw != t.blank && fw != t.eos) {
-            cur = cursor_from_root_rec(lane_rec(rr, l));
-          } else if (o.tok != t.blank && o.tok != t.eos) {
-            const v8i r = t.root_rec[o.tok];
-            cur = cursor_from_root_rec(r);
-          }
-        }
-        if (lane == l) {
-          out_st = cur.s;
-          out_tok = o.tok;
-          out_sc = o.val;
-        }
-        last = o.tok;
-        if (COMPARE && __builtin_amdgcn_readlane(old_st, l) == cur.s &&
-            (SEL != 2 || __builtin_amdgcn_readlane(old_tok, l) == o.tok))
-          met = l;  // (this frame is written too, its score may differ; the rest stands)
-        ++l;
-      }
-      if (lane < (met >= 0 ? met + 1 : n)) {
-        L.st[fb + lane] = out_st;
-        L.tok[fb + lane] = out_tok;
-        L.sc[fb + lane] = out_sc;
-      }
-      if (met >= 0) return true;
+    for (unsigned at = arc_hash(s, v);; ++at) {
+      const v4i q = slots[at & slot_mask];
+      if (q.x == s && q.y == v) return q.z;
+      if (q.x < 0) return 0;
     }
-    return false;
+  }
+  // The state after token v in state s (per lane); target: where v leads from the root.
+  __device__ __forceinline__ int step_to(int s, int v, int target) const {
+#pragma unroll 1
+    while (s != 0) {
+      const int fail = states[2 * static_cast<size_t>(s)].z;
+      const int next = child(s, v);
+      if (next > 0) return next;
+      s = fail;
+    }
+    return target;
   }
 
-  // Outcomes of a batch of frames, one per lane, each decided from the state the winners before it lead to.
-  enum Kind { kKeep = 0, kByArc = 1, kByRoot = 2 };
-  struct Ahead {
-    u64 settled, linked;            // decided; and: the next frame is decided, from this frame's outcome
-    int s, begin, count;            // the state it was decided from
-    float p_root, eos_boost;
-    int label;                      // ... and the label before it (CTC rule)
-    int tok, next, kind;
-    float val;
-  };
-  __device__ __forceinline__ Ahead decide_ahead(const Cursor& cur, int last, int fb, int n, int wm, int w, int v0, float xw,
-                                                float x0, float xe, float rsw, const v8i& rr) const {
-    Ahead g;
-    // ---- where each frame starts: in the state the last moving frame before it leads to, else in the batch's own ----
-    bool moves = v0 != t.blank;
-    const int pv = __shfl_up(v0, 1), pw = __shfl_up(w, 1);
-    if (SEL == 2) moves = moves && (lane == 0 ? v0 != last : v0 != pv && v0 != pw);
-    const u64 before = __ballot(moves) & ((1ull << lane) - 1);
-    const int src = before ? 63 - __builtin_clzll(before) : 0;
-    g.s = __shfl(rr.s0, src);
-    g.begin = __shfl(rr.s1, src);
-    g.count = __shfl(rr.s2, src);
-    g.p_root = __int_as_float(__shfl(rr.s5, src));
-    g.eos_boost = __int_as_float(__shfl(rr.s6, src));
-    bool settled = wm >= 0 && lane < n;
-    if (!before) {
-      g.s = cur.s;
-      g.begin = cur.rec.begin;
-      g.count = cur.rec.count;
-      g.p_root = cur.p_root;
-      g.eos_boost = cur.eos_boost;
-      settled = settled && (cur.s == 0 || cur.rec.fail == 0);  // (one level of arcs: all that is looked at here)
-    }
-    if (g.s == 0) g.count = 0;  // (the root's arcs are the root row)
-    // ---- the best arc of every frame's state: the arcs of a frame on the lanes, kWalkGroup frames at a time -----------
-    float am = -INFINITY;
-    int at = INT_MAX, ac = -1;
-    bool overridden = false;
-    const u64 with_arcs = __ballot(g.count > 0 && lane < n);
+  // Carries the outcomes of the frames to the starts of those behind them until nothing changes.  A frame whose start
+  // has changed is undecided again and taken to emit what it did.  (At most 64 turns; a phrase takes as many as it has
+  // tokens, side by side with all others.)  Frames lo .. hi - 1; the first starts from (from, from_label).
+  __device__ __forceinline__ void settle_starts(WalkFrame& f, int lo, int hi, int from, int from_label) const {
+    const u64 lower = (1ull << lane) - 1;
+    const bool mine = lane >= lo && lane < hi;
+    bool any;
 #pragma unroll 1
-    for (int l0 = 0; l0 < n; l0 += kWalkGroup) {
-      if (((with_arcs >> l0) & ((1ull << kWalkGroup) - 1)) == 0) continue;
-      ArcRec arcs[kWalkGroup];
-      float xa[kWalkGroup];
-#pragma unroll
-      for (int i = 0; i < kWalkGroup; ++i) {
-        const int gb = __builtin_amdgcn_readlane(g.begin, l0 + i), gc = __builtin_amdgcn_readlane(g.count, l0 + i);
-        arcs[i] = t.arc[gb + max(0, min(lane, gc - 1))];
+    do {
+      const u64 before = __ballot(f.moves && mine) & lower;
+      const int got = __shfl(f.next, before ? 63 - __builtin_clzll(before) : 0);
+      const int s = before ? got : from;
+      int label = -1;
+      if (SEL == 2) {
+        label = __shfl_up(f.tok, 1);
+        label = lane == lo ? from_label : label;
       }
-#pragma unroll
-      for (int i = 0; i < kWalkGroup; ++i) {
-        const int gc = __builtin_amdgcn_readlane(g.count, l0 + i);
-        const float* row = hyp + static_cast<int64_t>(fb + min(l0 + i, n - 1)) * frame_stride;
-        xa[i] = row[lane < gc ? arcs[i].token : 0];
+      const bool changed = mine && (s != f.s || (SEL == 2 && label != f.label));
+      any = __ballot(changed) != 0;
+      if (changed) {
+        f.s = s;
+        f.label = label;
+        f.decided = false;
+        f.hard = 0;
+        if (SEL != 0) {
+          f.moves = f.v0 != t.blank && (SEL != 2 || f.v0 != label);
+          f.tok = f.moves ? f.moving : f.v0;
+        }
+        f.next = s;
+        if (f.moves) f.next = step_to(s, f.tok, f.tok == f.w ? f.target : root_next[f.tok]);
       }
-#pragma unroll
-      for (int i = 0; i < kWalkGroup; ++i) {
-        const int l = l0 + i, gb = __builtin_amdgcn_readlane(g.begin, l), gc = __builtin_amdgcn_readlane(g.count, l);
-        const int fw = __builtin_amdgcn_readlane(w, l);
-        float best = lane < gc ? __fadd_rn(xa[i], __fmul_rn(alpha, __fadd_rn(0.0f, arcs[i].score))) : -INFINITY;
-        int tok = lane < gc ? arcs[i].token : INT_MAX, child = gb + lane + 1;
-        bool hit = tok == fw;
-        if (gc > 64) {  // uniform
-          const float* row = hyp + static_cast<int64_t>(fb + min(l, n - 1)) * frame_stride;
-#pragma unroll 1
-          for (int j = 64 + lane; j < gc; j += 64) {
-            const ArcRec a = t.arc[gb + j];
-            hit = hit || a.token == fw;
-            const float fa = __fadd_rn(row[a.token], __fmul_rn(alpha, __fadd_rn(0.0f, a.score)));
-            if (fa > best) {  // (tokens ascend with j: an equal one stays behind)
-              best = fa;
-              tok = a.token;
-              child = gb + j + 1;
+      together();
+    } while (any);
+  }
+
+  // Decides the frames of `need` from their starts.
+  __device__ __forceinline__ void decide_frames(WalkFrame& f, u64 need) const {
+    const bool mine = (need >> lane) & 1;
+    const bool kept = SEL != 0 && (f.v0 == t.blank || (SEL == 2 && f.v0 == f.label));
+    // ---- the first four levels of every frame's chain as one list of arcs, deepest state first -------------------------
+    int s1 = 0, s2 = 0, c0 = 0, c1 = 0, c2 = 0, total = 0, o0 = 0, o1 = 0, o2 = 0, o3 = 0;
+    float p1 = 0.0f, p2 = 0.0f, p3 = 0.0f, pr = 0.0f, eb = 0.0f;
+    bool hard = f.marked;
+    if (mine && !kept && !hard) {
+      if (t.eos >= 0) eb = eos_score[f.s];
+      if (f.s != 0) {
+        const v4i q = states[2 * static_cast<size_t>(f.s)], q1 = states[2 * static_cast<size_t>(f.s) + 1];
+        c0 = q.y;
+        pr = p1 = __fadd_rn(0.0f, __int_as_float(q.w));  // (the backoffs in chain order: what p_root holds)
+        o0 = q.x;
+        c1 = c2 = total = c0;
+        s1 = q.z;
+        s2 = q1.z;
+        if (s1 != 0) {
+          pr = p2 = __fadd_rn(p1, __int_as_float(q1.w));
+          o1 = q1.x - c0;
+          c1 = c2 = total = c0 + q1.y;
+          if (s2 != 0) {
+            const v4i z = states[2 * static_cast<size_t>(s2)], z1 = states[2 * static_cast<size_t>(s2) + 1];
+            pr = p3 = __fadd_rn(p2, __int_as_float(z.w));
+            o2 = z.x - c1;
+            c2 = total = c1 + z.y;
+            if (z.z != 0) {
+              pr = __fadd_rn(p3, __int_as_float(z1.w));
+              o3 = z1.x - c2;
+              total = c2 + z1.y;
+              hard = z1.z != 0;  // a longer chain
             }
           }
         }
-        const float top = ukey_val(wave_max_u(ukey(best)));
-        u64 who = __ballot(best == top && tok != INT_MAX);
-        if (gc > 64 && (who & (who - 1)) != 0) {  // equal ones in two lanes: the lower token need not be in the lower lane
-          const int low = wave_min_nn(best == top ? tok : INT_MAX);
-          who = __ballot(best == top && tok == low);
-        }
-        const int from = who != 0 ? first_lane(who) : 0;
-        const bool any_hit = __ballot(hit) != 0;
-        const int wtok = __builtin_amdgcn_readlane(tok, from), wchild = __builtin_amdgcn_readlane(child, from);
-        if (lane == l && who != 0) {
-          am = top;
-          at = wtok;
-          ac = wchild;
-          overridden = any_hit;
-        }
       }
     }
-    // ---- the frames' decisions, as in decide(), one per lane ------------------------------------------------------------
-    const float M = __fadd_rn(xw, __fmul_rn(alpha, __fadd_rn(g.p_root, rsw)));
-    settled = settled && M != -INFINITY;
+    const float M = __fadd_rn(f.xw, __fmul_rn(alpha, __fadd_rn(pr, f.rsw)));
+    hard = hard || M == -INFINITY;
+    // ---- the best arc of every frame: the arcs of all frames shared out over the lanes ----------------------------------
+    // (One loop of little code: the same with the arcs of a frame on the lanes, eight frames unrolled, spent its time on
+    // fetching instructions that no wave had run before.)
+    const int arcs = mine && !kept && !hard ? total : 0;
+    const int end = prefix_sum(arcs);
+    const int start = end - arcs, pairs = lane_i(end, 63);
+    L.meta[lane] = WalkMeta{start, c0, c1, c2, o0, o1, o2, o3, p1, p2, p3, f.w};
+    L.best[lane] = 0;
+    L.flag[lane] = 0;
+    together();
+#pragma unroll 1
+    for (int base = 0; base < pairs; base += kWalkPairs) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) L.owner[64 * k + lane] = 0;
+      together();
+      if (arcs > 0 && end > base && start < base + kWalkPairs) L.owner[max(start - base, 0)] = lane + 1;
+      together();
+      int fr[4], lo[4], len[4], at[4], fw[4];
+      float p[4], xa[4];
+      v2i a[4];
+      int before = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) fr[k] = L.owner[64 * k + lane];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        fr[k] = max(before, prefix_max(fr[k]));
+        before = lane_i(fr[k], 63);
+        fr[k] -= 1;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const WalkMeta m = L.meta[fr[k]];
+        const int j = min(base + 64 * k + lane, pairs - 1) - m.start;
+        int off = m.o0, first = 0, end_j = m.c0;
+        p[k] = 0.0f;
+        if (j >= m.c0) { off = m.o1; first = m.c0; end_j = m.c1; p[k] = m.p1; }
+        if (j >= m.c1) { off = m.o2; first = m.c1; end_j = m.c2; p[k] = m.p2; }
+        if (j >= m.c2) { off = m.o3; first = m.c2; end_j = m.c2; p[k] = m.p3; }  // (its end is not at hand)
+        lo[k] = off + first;
+        len[k] = end_j - first;
+        at[k] = j + off;
+        fw[k] = m.w;
+        a[k] = arc[at[k]];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) xa[k] = hyp[static_cast<int64_t>(fr[k]) * frame_stride + a[k].x];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (base + 64 * k + lane < pairs) {
+          const unsigned key = ukey(__fadd_rn(xa[k], __fmul_rn(alpha, __fadd_rn(p[k], __int_as_float(a[k].y)))));
+          const u64 old = atomicMax(&L.best[fr[k]], (static_cast<u64>(key) << 32) | ~static_cast<unsigned>(at[k]));
+          const int old_at = static_cast<int>(~static_cast<unsigned>(old));
+          // (two of a level: the lower arc is the lower token; the same token on two levels: see below)
+          bool tie = static_cast<unsigned>(old >> 32) == key && !in_level(old_at - lo[k], 0, len[k]);
+          if (tie) tie = arc[old_at].x != a[k].x;
+          const unsigned say = (a[k].x == fw[k] ? 1u : 0u) | (tie ? 2u : 0u);
+          if (say != 0) atomicOr(&L.flag[fr[k]], say);
+        }
+      }
+      together();
+    }
+    float am = -INFINITY;
+    int at = INT_MAX, ac = -1;
+    const unsigned flag = L.flag[lane];
+    const bool overridden = (flag & 1u) != 0;
+    if (arcs > 0) {
+      const u64 key = L.best[lane];
+      ac = static_cast<int>(~static_cast<unsigned>(key));
+      am = ukey_val(static_cast<unsigned>(key >> 32));
+      at = arc[ac].x;
+      // A token belongs to the deepest state that has it: where a deeper state's arcs hold the winner's token, it stands
+      // if it has the same value there (after a whole phrase the backoff is 0), and leads where that arc leads.  (A
+      // shadowed arc that does not win changes nothing.)
+      const int level = in_level(ac - o0, 0, c0) ? 0 : in_level(ac - o1, c0, c1) ? 1 : in_level(ac - o2, c1, c2) ? 2 : 3;
+      hard = hard || (flag & 2u) != 0;
+      int x = f.s;
+#pragma unroll 1
+      for (int l = 0; l < level; ++l) {
+        const int next = child(x, at);
+        if (next > 0) {
+          const float p = l == 0 ? 0.0f : l == 1 ? p1 : p2, v = hyp[static_cast<int64_t>(lane) * frame_stride + at];
+          ac = next - 1;
+          hard = hard || __fadd_rn(v, __fmul_rn(alpha, __fadd_rn(p, __int_as_float(arc[ac].y)))) != am;
+          break;
+        }
+        x = l == 0 ? s1 : s2;
+      }
+      ac += 1;
+    }
+    // ---- the frames' decisions, one per lane ----------------------------------------------------------------------------
     auto special = [&](int token, float fv) {
       const bool take = fv > am || (fv == am && token < at);
       am = take ? fv : am;
       at = take ? token : at;
       ac = take ? -1 : ac;
     };
-    if (SEL == 0 && t.blank >= 0) special(t.blank, __fadd_rn(x0, __fmul_rn(alpha, 0.0f)));
-    if (t.eos >= 0) special(t.eos, __fadd_rn(xe, __fmul_rn(alpha, g.eos_boost)));
-    const bool take = at != INT_MAX && (am > M || (!overridden && am == M && at < w));
-    settled = settled && !(overridden && !take);
-    const int dtok = take ? at : w;
-    bool kept = false;
-    g.tok = dtok;
-    g.label = -1;
-    if (SEL != 0) {
-      kept = v0 == t.blank;
-      g.tok = kept ? v0 : dtok;
-      if (SEL == 2) {
-        // repeats depend on the labels before them: taken from the outcomes without repeats, then checked
-        int prev = __shfl_up(g.tok, 1);
-        prev = lane == 0 ? last : prev;
-        const bool repeat = v0 == prev;
-        g.tok = kept || repeat ? v0 : dtok;
-        prev = __shfl_up(g.tok, 1);
-        g.label = lane == 0 ? last : prev;
-        const bool blank_frame = kept;
-        kept = kept || repeat;
-        // (a frame whose repeat this gets wrong, or whose token the rule bars, is decided frame by frame)
-        settled = kept ? lane < n && (blank_frame || repeat == (v0 == g.label))
-                       : settled && v0 != g.label && dtok != g.label;
-      } else if (kept) {
-        settled = lane < n;
-      }
+    if (SEL == 0 && t.blank >= 0) special(t.blank, __fadd_rn(f.x0, __fmul_rn(alpha, 0.0f)));
+    if (t.eos >= 0) special(t.eos, __fadd_rn(f.xe, __fmul_rn(alpha, eb)));
+    // (at == w: the winner's own arc has the base value, as it does after a whole phrase; the other tokens of that value
+    // are higher ones)
+    const bool take = at != INT_MAX && (am > M || (am == M && at <= f.w));
+    hard = hard || (overridden && !take);  // the base winner is shadowed by an arc that does not beat it
+    const int dtok = take ? at : f.w;
+    const bool barred = SEL == 2 && !hard && dtok == f.label;  // the rule bars the previous label
+    if (mine) {
+      f.decided = true;
+      f.hard = kept ? 0 : hard ? 1 : barred ? 2 : 0;  // (what follows is only likely then)
+      f.tok = kept ? f.v0 : dtok;
+      f.val = kept ? f.x0 : take ? am : M;
+      f.moves = !kept && (!take || ac >= 0);
+      f.next = !f.moves ? f.s : take ? ac : f.target;
+      if (f.moves) f.moving = dtok;
     }
-    g.val = kept ? x0 : take ? am : M;
-    g.kind = kept ? kKeep : take ? (ac >= 0 ? kByArc : kKeep) : kByRoot;
-    g.next = g.kind == kByArc ? ac : g.kind == kByRoot ? rr.s0 : g.s;
-    if (kept && !before && cur.s != 0 && cur.rec.fail != 0) settled = false;  // (its record is not a single level)
-    g.settled = __ballot(settled);
-    const int next_s = __shfl_down(g.s, 1);
-    g.linked = __ballot(g.next == next_s && lane + 1 < n) & (g.settled >> 1);
-    return g;
   }
 
-  const RootRec* root_rec;  // (of the tree, for accesses that differ from lane to lane)
-  const StateRec* states;
-  const float *p_root, *eos_score;
-
-  __device__ __forceinline__ static Rec lane_half(const v4i& r, int l) {
-    return Rec{__builtin_amdgcn_readlane(r.x, l), __builtin_amdgcn_readlane(r.y, l), __builtin_amdgcn_readlane(r.z, l),
-               __int_as_float(__builtin_amdgcn_readlane(r.w, l))};
-  }
-  __device__ __forceinline__ static float lane_f(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-  }
-  __device__ __forceinline__ static v8i lane_rec(const v8i& r, int l) {
-    v8i o;
-    o.s0 = __builtin_amdgcn_readlane(r.s0, l);
-    o.s1 = __builtin_amdgcn_readlane(r.s1, l);
-    o.s2 = __builtin_amdgcn_readlane(r.s2, l);
-    o.s3 = __builtin_amdgcn_readlane(r.s3, l);
-    o.s4 = __builtin_amdgcn_readlane(r.s4, l);
-    o.s5 = __builtin_amdgcn_readlane(r.s5, l);
-    o.s6 = __builtin_amdgcn_readlane(r.s6, l);
-    o.s7 = 0;
-    return o;
-  }
-
-  // One frame from state cur whose base winner is w with value M (marked: not certain, see near_band).
-  //   x_blank, x_eos: log-probs of those columns
-  //   An arc's target comes back in `child` when `child_known` (o.arc): its record is requested with the log-probs of
-  //   the arcs, so that following a phrase costs no access of its own.
-  __device__ __forceinline__ FrameOut decide(const Cursor& cur, const float* row, float M, int w, bool marked, float x_blank,
-                                             float x_eos, int last, Cursor& child, bool& child_known) const {
-    const Rec rec0 = cur.rec;
-    const bool chain = cur.s != 0, multi = chain && rec0.fail != 0;
-    float bf = -INFINITY;
-    int btok = INT_MAX, bchild = 0;
-    bool hit = false;
-    bool settled = !marked && M != -INFINITY;
-    v4i kid0 = {0, 0, 0, 0}, kid1 = kid0;  // the record of this lane's first arc's target
-    float kid_p = 0.0f, kid_e = 0.0f;
-    int kid = -1;
-    if (settled && chain) {
-      // The first four levels of the chain (two records) as one list of arcs, deepest state first: their arcs and
-      // their log-probs are two accesses, however many levels there are.
-      const Rec none{0, 0, 0, 0.0f};
-      const Rec r1 = multi ? cur.rec1 : none;
-      Rec2 r23{none, none};
-      if (multi && r1.fail != 0) r23 = load_rec2(t, r1.fail);
-      if (r23.a.fail == 0) r23.b = none;
-      const int c0 = rec0.count, c1 = c0 + r1.count, c2 = c1 + r23.a.count, total = c2 + r23.b.count;
-      const float p1 = __fadd_rn(0.0f, rec0.backoff), p2 = __fadd_rn(p1, r1.backoff), p3 = __fadd_rn(p2, r23.a.backoff);
-      auto consider = [&](int tk, float score, float xv, float p, int next, bool valid, bool shadowed) {
-        hit = hit || (valid && tk == w);
-        const float fa = __fadd_rn(xv, __fmul_rn(alpha, __fadd_rn(p, score)));
-        const bool take = valid && !shadowed && (fa > bf || (fa == bf && tk < btok));
-        bf = take ? fa : bf;
-        btok = take ? tk : btok;
-        bchild = take ? next : bchild;
-      };
+  // One frame from state q.s by a pass over its row, any case, by all waves of the workgroup: tokens that a chain state has
+  // an arc on are marked, deepest state first (wave 0), the others follow with their base boosts.  q.excl: a token barred
+  // from the selection, or -1.  The outcome comes back in every thread.
+  __device__ __forceinline__ WalkBest row_pass(const WalkJob& q, const float* row, WalkShared& W, unsigned* tags, int wave,
+                                               int nwaves) const {
+    WalkBest o{-INFINITY, INT_MAX, -1};
+    auto offer = [&](int tk, float v, int next) {
+      const bool take = v > o.val || (v == o.val && tk < o.tok);
+      o.val = take ? v : o.val;
+      o.tok = take ? tk : o.tok;
+      o.child = take ? next : o.child;
+    };
+    for (int i = 64 * wave + lane; i < (t.V + 31) / 32; i += 64 * nwaves) tags[i] = 0u;
+    __syncthreads();
+    if (wave == 0) {
+      float p = 0.0f;
 #pragma unroll 1
-      for (int j0 = 0; j0 < total; j0 += 64) {
-        const int i = j0 + lane;
-        const bool valid = i < total;
-        const int lv = (i >= c0 ? 1 : 0) + (i >= c1 ? 1 : 0) + (i >= c2 ? 1 : 0);
-        const int at = i < c0 ? rec0.begin + i : i < c1 ? r1.begin + i - c0 : i < c2 ? r23.a.begin + i - c1 : r23.b.begin + i - c2;
-        const ArcRec a = t.arc[valid ? at : rec0.begin];
-        const int tk = valid ? a.token : 0;  // an unused entry may hold anything: keep the indices in range
-        const float xv = row[tk];
-        if (j0 == 0) {
-          kid = valid ? at + 1 : 0;
-          const StateRec* k = states + kid;
-          kid0 = reinterpret_cast<const v4i*>(k)[0];
-          kid1 = reinterpret_cast<const v4i*>(k)[1];
-          kid_p = p_root[kid];
-          if (t.eos >= 0) kid_e = eos_score[kid];
-        }
-        bool shadowed = false;
-        if (multi) {  // a deeper chain state owns its tokens (the marks are all clear between frames)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (valid && lv == q) {
-              if (q > 0) shadowed = tag_test(L.tags, tk);
-              tag_set(L.tags, tk);
-            }
-          }
-        }
-        consider(tk, a.score, xv, lv == 0 ? 0.0f : lv == 1 ? p1 : lv == 2 ? p2 : p3, at + 1, valid, shadowed);
-      }
-      float p = __fadd_rn(p3, r23.b.backoff);
-#pragma unroll 1
-      for (int x = r23.b.fail; x != 0;) {  // longer chains, level by level
+      for (int x = q.s; x != 0;) {
         const Rec r = load_rec(t, x);
 #pragma unroll 1
-        for (int j = lane; j < r.count; j += 64) {
-          const ArcRec a = t.arc[r.begin + j];
-          const bool shadowed = tag_test(L.tags, a.token);
-          tag_set(L.tags, a.token);
-          consider(a.token, a.score, row[a.token], p, r.begin + j + 1, true, shadowed);
+        for (int j = lane; j < r.count; j += 64) {  // (tokens of one state are distinct: no two lanes meet on a mark)
+          const v2i a = arc[r.begin + j];
+          if (!tag_test(tags, a.x)) {
+            tag_set(tags, a.x);
+            if (SEL != 2 || a.x != q.excl)
+              offer(a.x, __fadd_rn(row[a.x], __fmul_rn(alpha, __fadd_rn(p, __int_as_float(a.y)))), r.begin + j + 1);
+          }
         }
         p = __fadd_rn(p, r.backoff);
         x = uniform_i(r.fail);
+        together();
       }
-      if (multi) tags_clear_n(L.tags, tag_words, lane);
+      // the blank (single-stage rule: boost 0, state kept) and the EOS token (boost tabulated per state, state kept)
+      if (SEL == 0 && t.blank >= 0 && lane == 0) offer(t.blank, __fadd_rn(q.x_blank, __fmul_rn(alpha, 0.0f)), -1);
+      if (t.eos >= 0 && lane == 0 && (SEL != 2 || t.eos != q.excl))
+        offer(t.eos, __fadd_rn(q.x_eos, __fmul_rn(alpha, t.eos_score[q.s])), -1);
     }
-    child_known = false;
-    // the blank (single-stage rule: boost 0, state kept) and the EOS token (boost tabulated per state, state kept)
-    if (SEL == 0 && t.blank >= 0 && lane == 63) {
-      const float fv = __fadd_rn(x_blank, __fmul_rn(alpha, 0.0f));
-      const bool take = fv > bf || (fv == bf && t.blank < btok);
-      bf = take ? fv : bf;
-      btok = take ? t.blank : btok;
-      bchild = take ? -1 : bchild;
-    }
-    if (t.eos >= 0 && lane == 62) {
-      const float fv = __fadd_rn(x_eos, __fmul_rn(alpha, cur.eos_boost));
-      const bool take = fv > bf || (fv == bf && t.eos < btok);
-      bf = take ? fv : bf;
-      btok = take ? t.eos : btok;
-      bchild = take ? -1 : bchild;
-    }
-    FrameOut o{M, w, false, 0};
-    const bool mine0 = btok != INT_MAX;
-    if (settled && __ballot(mine0) != 0) {
-      const float MA = ukey_val(wave_max_u(mine0 ? ukey(bf) : 0u));
-      const bool overridden = __ballot(hit) != 0;
-      if (overridden || MA >= M) {
-        const bool mine = mine0 && bf == MA;
-        const int va = wave_min_nn(mine ? btok : INT_MAX);
-        const int next = __builtin_amdgcn_readlane(bchild, first_lane(__ballot(mine && btok == va)));
-        if (MA > M || (!overridden && MA == M && va < w)) {
-          o = FrameOut{MA, va, next >= 0, next};
-          const u64 holds = __ballot(kid == next && next > 0);
-          if (holds != 0) {
-            const int q = first_lane(holds);
-            child = Cursor{next, lane_half(kid0, q), lane_half(kid1, q), lane_f(kid_p, q), lane_f(kid_e, q)};
-            child_known = true;
-          }
-        } else if (overridden) {
-          settled = false;  // the base winner is shadowed by an arc that does not beat it
-        }
+    __syncthreads();
+    const float pr = t.p_root[q.s];
+    constexpr int kAhead = 4;
+#pragma unroll 1
+    for (int v0 = 64 * kAhead * wave; v0 < t.V; v0 += 64 * kAhead * nwaves) {
+      float x[kAhead], rs[kAhead];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) {
+        const int v = min(v0 + 64 * i + lane, t.V - 1);
+        x[i] = row[v];
+        rs[i] = root_score[v];
       }
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) {
+        const int v = v0 + 64 * i + lane;
+        const bool in = v < t.V && v != t.blank && v != t.eos && (SEL != 2 || v != q.excl) && !tag_test(tags, min(v, t.V - 1));
+        if (in) offer(v, __fadd_rn(x[i], __fmul_rn(alpha, __fadd_rn(pr, rs[i]))), -1);
+      }
+      together();
     }
-    if (settled && SEL == 2 && o.tok == last) settled = false;  // the CTC rule bars the previous label
-    if (!settled) {
-      child_known = false;
-      // (CTC: first without the exclusion -- the label may not even win -- then, if it does win, without the label)
-      o = slow_frame<false, SEL>(t, cur, row, alpha, -1, L.tags, tag_words, nch, lane);
-      if (SEL == 2 && o.tok == last) o = slow_frame<false, SEL>(t, cur, row, alpha, last, L.tags, tag_words, nch, lane);
-      tags_clear_n(L.tags, tag_words, lane);
-    }
-    o.val = uniform_f(o.val);
-    o.tok = uniform_i(o.tok);
-    o.child = uniform_i(o.child);
+    o = best_of(o);
+    if (lane == 0) W.part[wave] = o;
+    __syncthreads();
+    o = lane < nwaves ? W.part[lane] : WalkBest{-INFINITY, INT_MAX, -1};
+    o = best_of(o);
+    if (o.tok == INT_MAX) o = WalkBest{0.0f, 0, -1};  // (a row of NaN, a precondition violation: stay in range)
     return o;
   }
+  // The best of the lanes' candidates (tok == INT_MAX: none), in every lane.
+  __device__ __forceinline__ static WalkBest best_of(const WalkBest& o) {
+    const unsigned best = wave_max_u(o.tok != INT_MAX ? ukey(o.val) : 0u);
+    const bool mine = o.tok != INT_MAX && ukey(o.val) == best;
+    const int tok = wave_min_nn(mine ? o.tok : INT_MAX);
+    const u64 who = __ballot(mine && o.tok == tok);
+    const int from = who != 0 ? first_lane(who) : 0;
+    return WalkBest{lane_f(o.val, from), tok, lane_i(o.child, from)};
+  }
+
+  __device__ __forceinline__ static bool in_level(int j, int from, int to) { return j >= from && j < to; }
+  template <int CTRL, int ROWS>
+  __device__ __forceinline__ static int from_lane(int v) {  // 0 where there is no such lane
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+  }
+  // Sum of the lanes up to this one.
+  __device__ __forceinline__ static int prefix_sum(int v) {
+    v += from_lane<0x111, 0xf>(v);  // row_shr:1
+    v += from_lane<0x112, 0xf>(v);  // row_shr:2
+    v += from_lane<0x114, 0xf>(v);  // row_shr:4
+    v += from_lane<0x118, 0xf>(v);  // row_shr:8
+    v += from_lane<0x142, 0xa>(v);  // row_bcast:15
+    v += from_lane<0x143, 0xc>(v);  // row_bcast:31
+    return v;
+  }
+  // Largest value of the lanes up to this one (values >= 0).
+  __device__ __forceinline__ static int prefix_max(int v) {
+    v = max(v, from_lane<0x111, 0xf>(v));
+    v = max(v, from_lane<0x112, 0xf>(v));
+    v = max(v, from_lane<0x114, 0xf>(v));
+    v = max(v, from_lane<0x118, 0xf>(v));
+    v = max(v, from_lane<0x142, 0xa>(v));
+    v = max(v, from_lane<0x143, 0xc>(v));
+    return v;
+  }
+  __device__ __forceinline__ static int lane_i(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+  __device__ __forceinline__ static float lane_f(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+  }
 };
+
+// The first frame that the lanes of a wave with frames f0 .. f1 - 1 hold: the last few before f0 tell what state those start
+// in.
+constexpr int kWalkLook = 16;
+__device__ __forceinline__ int first_held(int f0, int f1) { return max(max(f0 - kWalkLook, f1 - 64), 0); }
 
 template <int SEL>
 __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
@@ -662,15 +649,20 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
                                                     const int32_t* __restrict__ states0,
                                                     const int32_t* __restrict__ last0, float alpha, int T, int B,
                                                     int32_t* tokens, int32_t* states, float* __restrict__ scores) {
-  extern __shared__ int lds[];
+  extern __shared__ __align__(16) unsigned char lds[];
   const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
   const int b = blockIdx.x;
   DeviceTree mine = dt;
   const bool tree_ok = pick_tree(pick, b, mine);
   const TreeView t = make_view(mine);
-  const RootRec* root_rec = mine.root_rec;
-  const StateRec* state_recs = mine.state;
-  const float *p_root = mine.p_root, *eos_score = mine.eos_score;
+  // (the frames of the first block are requested with the state, not behind it)
+  const int wave_end = static_cast<int>(static_cast<int64_t>(wave + 1) * min(64 * nwaves, T) / nwaves);
+  const int my_frame = first_held(static_cast<int>(static_cast<int64_t>(wave) * min(64 * nwaves, T) / nwaves), wave_end) + lane;
+  int w_first = 0, v0_first = 0;
+  if (my_frame < wave_end) {
+    w_first = tokens[static_cast<size_t>(my_frame) * B + b];
+    if (t.V > kPackedV) v0_first = states[static_cast<size_t>(my_frame) * B + b];
+  }
   int s = tree_ok ? uniform_i(states0[b]) : -1;  // an unknown tree marks the hypothesis like an invalid state
   int last = SEL == 2 && last0 != nullptr ? uniform_i(last0[b]) : -1;
   if (!tree_ok || !valid_state(t, s)) {
@@ -682,106 +674,171 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
     }
     return;
   }
-  const int nch = (t.V + kChunk - 1) / kChunk, tag_words = nch * kTagWords, cap = min(T, kWalkBlock);
-  WalkLds L;
-  L.w = lds;
-  L.v0 = lds + cap;
-  L.st = lds + 2 * cap;
-  L.tok = lds + 3 * cap;
-  L.sc = reinterpret_cast<float*>(lds + 4 * cap);
-  L.tags = reinterpret_cast<unsigned*>(lds + 5 * cap) + wave * tag_words;
-  tags_clear_n(L.tags, tag_words, lane);
-  for (int F0 = 0; F0 < T; F0 += kWalkBlock) {
-    const int n = min(kWalkBlock, T - F0);
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-      const size_t o = static_cast<size_t>(F0 + i) * B + b;
-      L.w[i] = tokens[o];
-      L.v0[i] = states[o];
-    }
-    __syncthreads();
-    const Walker<SEL> walk{t, logp + static_cast<int64_t>(F0) * frame_stride + static_cast<int64_t>(b) * row_stride,
-                           frame_stride, alpha, L, tag_words, nch, lane, root_rec, state_recs, p_root, eos_score};
-    const int f0 = static_cast<int>(static_cast<int64_t>(wave) * n / nwaves);
-    const int f1 = static_cast<int>(static_cast<int64_t>(wave + 1) * n / nwaves);
-    int from = s, from_tok = last;
-    if (f0 > 0) walk.guess(f0, s, from, from_tok);
-    if (f0 < f1) walk.template run<false>(f0, f1, from, from_tok);
-    __syncthreads();
-    for (;;) {  // (segment k is final after k rounds at the latest: the one before it then is)
-      bool dirty = false;
-      int have = from, have_tok = from_tok;
-      if (f0 > 0 && f0 < f1) {
-        have = uniform_i(L.st[f0 - 1]);
-        have_tok = uniform_i(L.tok[f0 - 1]);
+  WalkLds* shared = reinterpret_cast<WalkLds*>(lds);
+  WalkShared& W = *reinterpret_cast<WalkShared*>(shared + nwaves);
+  unsigned* tags = reinterpret_cast<unsigned*>(&W + 1);  // a bit per token
+  for (int F0 = 0; F0 < T; F0 += 64 * nwaves) {
+    // A wave's frames f0 .. f1 - 1 are its last lanes; those before hold the frames before, from which the state that
+    // its own start in is found.
+    const int count = min(64 * nwaves, T - F0);
+    const int f0 = static_cast<int>(static_cast<int64_t>(wave) * count / nwaves);
+    const int f1 = static_cast<int>(static_cast<int64_t>(wave + 1) * count / nwaves);
+    const int base = first_held(f0, f1), lo = f0 - base, hi = f1 - base, fr = base + lane;
+    const Walker<SEL> walk{t, (const v4i PB_AS1*)mine.state, (const v2i PB_AS1*)mine.arc, (const v4i PB_AS1*)mine.arc_slot,
+                           mine.arc_mask, (const int PB_AS1*)mine.root_next,
+                           (const float PB_AS1*)mine.p_root, (const float PB_AS1*)mine.eos_score, (const float PB_AS1*)mine.root_score,
+                           logp + static_cast<int64_t>(F0 + base) * frame_stride + static_cast<int64_t>(b) * row_stride,
+                           frame_stride, alpha, shared[wave], lane};
+    WalkFrame f{};
+    const size_t o = static_cast<size_t>(F0 + fr) * B + b;
+    if (lane < hi) {
+      int word = w_first, word2 = v0_first;
+      if (F0 > 0) {
+        word = tokens[o];
+        word2 = t.V > kPackedV ? states[o] : 0;
       }
-      __syncthreads();  // (every outcome is read before any segment is decoded again)
-      if (have != from || (SEL == 2 && have_tok != from_tok)) {
+      get_winners(t.V, word, word2, f.w, f.v0, f.marked);
+      f.moves = f.v0 != t.blank;
+      if (SEL == 0 || f.moves) f.target = walk.root_next[f.w];
+      if (lane >= lo) {
+        const float* row = walk.hyp + static_cast<int64_t>(lane) * frame_stride;
+        if (SEL == 0 || f.moves) {
+          f.xw = row[f.w];
+          f.rsw = walk.root_score[f.w];
+        }
+        f.x0 = SEL != 0 ? row[f.v0] : (t.blank >= 0 ? row[t.blank] : 0.0f);
+        f.xe = t.eos >= 0 ? row[t.eos] : 0.0f;
+      }
+      f.s = -1;
+      f.tok = f.moves ? f.w : f.v0;
+      f.moving = f.w;
+      f.next = f.target;
+    }
+    // First the states that the winners alone lead to, then the frames' decisions from there.
+    int first = 0, from = base == 0 ? s : 0, from_label = base == 0 ? last : -1;
+    for (bool decide = false;;) {
+      walk.settle_starts(f, first, hi, from, from_label);
+      if (!decide) {
+        decide = true;
+        if (lo > 0) {
+          from = Walker<SEL>::lane_i(f.next, lo - 1);
+          from_label = Walker<SEL>::lane_i(f.tok, lo - 1);
+        }
+        first = lo;
+      }
+      const u64 need = __ballot(lane >= lo && lane < hi && !f.decided);
+      if (need != 0) {
+        walk.decide_frames(f, need);
+        continue;
+      }
+      int end = Walker<SEL>::lane_i(f.next, max(hi - 1, 0)), end_label = Walker<SEL>::lane_i(f.tok, max(hi - 1, 0));
+      if (lo == hi) {
+        end = from;
+        end_label = from_label;
+      }
+      if (lane == 0) {
+        W.end[wave] = end;
+        W.end_label[wave] = end_label;
+      }
+      __syncthreads();
+      bool changed = false;
+      if (wave > 0) {
+        const int have = uniform_i(W.end[wave - 1]), have_label = uniform_i(W.end_label[wave - 1]);
+        changed = have != from || (SEL == 2 && have_label != from_label);
         from = have;
-        from_tok = have_tok;
-        dirty = !walk.template run<true>(f0, f1, from, from_tok);
+        from_label = have_label;
       }
-      if (!__syncthreads_or(dirty)) break;
+      const int hard = lane >= lo && lane < hi ? f.hard : 0;
+      if (__syncthreads_or(changed)) continue;  // (wave k starts where it should after k rounds at the latest)
+      if (!__syncthreads_or(hard != 0)) break;  // (frames that need their row wait until the starts agree)
+      // ---- what the winners do not settle: a pass over the row, all waves together ---------------------------------------
+      if (threadIdx.x == 0) W.jobs = 0;
+      __syncthreads();
+      if (hard != 0) {
+        const int at = atomicAdd(&W.jobs, 1);
+        // (CTC: first without the exclusion -- the label may not even win -- then, if it does win, without the label)
+        if (at < kWalkJobs) W.job[at] = WalkJob{f.s, base + lane, hard == 2 ? f.label : -1, f.label, f.x0, f.xe};
+      }
+      __syncthreads();
+      const int jobs = min(uniform_i(W.jobs), kWalkJobs);
+#pragma unroll 1
+      for (int i = 0; i < jobs; ++i) {
+        WalkJob q = W.job[i];
+        q.s = uniform_i(q.s);
+        q.frame = uniform_i(q.frame);
+        q.excl = uniform_i(q.excl);
+        q.label = uniform_i(q.label);
+        const float* row = walk.hyp + static_cast<int64_t>(q.frame - base) * frame_stride;
+        WalkBest o = walk.row_pass(q, row, W, tags, wave, nwaves);
+        if (SEL == 2 && q.excl < 0 && o.tok == q.label) {
+          __syncthreads();
+          q.excl = q.label;
+          o = walk.row_pass(q, row, W, tags, wave, nwaves);
+        }
+        const bool stays = o.child < 0 && (o.tok == t.blank || o.tok == t.eos);
+        const int next = o.child >= 0 ? o.child : stays ? q.s : uniform_i(t.root_next[o.tok]);
+        if (lane >= lo && q.frame == fr) {
+          f.hard = 0;
+          f.tok = o.tok;
+          f.val = o.val;
+          f.moves = !stays;
+          f.next = next;
+          if (!stays) f.moving = o.tok;
+        }
+        __syncthreads();  // (the next one's marks and parts take the place of these)
+      }
     }
-    s = uniform_i(L.st[n - 1]);
-    last = uniform_i(L.tok[n - 1]);
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-      const size_t o = static_cast<size_t>(F0 + i) * B + b;
-      tokens[o] = L.tok[i];
-      states[o] = L.st[i];
-      scores[o] = L.sc[i];
+    s = uniform_i(W.end[nwaves - 1]);
+    last = uniform_i(W.end_label[nwaves - 1]);
+    if (lane >= lo && lane < hi) {
+      tokens[o] = f.tok;
+      states[o] = f.next;
+      scores[o] = f.val;
     }
-    __syncthreads();  // (the next block overwrites what has just been read)
+    if (F0 + count < T) __syncthreads();  // (the next block's ends take the place of these)
   }
 }
 
 int g_walk_max_lds = 63 * 1024;  // dynamic LDS the device allows the walk kernel, set once
 
-size_t walk_lds_bytes(int V, int T, int waves) {
-  const int cap = T < kWalkBlock ? T : kWalkBlock;
-  return sizeof(int) * (static_cast<size_t>(5) * cap + static_cast<size_t>(waves) * ((V + kChunk - 1) / kChunk) * kTagWords);
+size_t walk_lds_bytes(int V, int waves) {
+  return static_cast<size_t>(waves) * sizeof(WalkLds) + sizeof(WalkShared) + sizeof(unsigned) * ((static_cast<size_t>(V) + 31) / 32);
 }
 
 }  // namespace
 
-// Which calls the two passes are for.  Pass 1 reads the rows at the chip's rate whatever T and B are; pass 2 costs about
-// 10 us and 0.5 to 1 us for every 16 frames of a hypothesis.  The segment decoders need some thousand segments for that
-// rate and read again what a wrong guess has spoilt, but have no second pass over the frames.  Measured: time of the two
-// passes over that of the segment decoder, mean over vocabularies, rules and kinds of rows (random; a fifth of the frames
-// inside listed phrases; the same with half of the frames blank), 4365 calls in all.
-//   V = 1025 .. 1280     T <= 128, T * B <= 2048 / more   129 .. 256, <= 2048 / more   257 .. 512, <= 64K   513 ..
-//     single-stage       0.98 / 1.12                      1.00 / 1.20                  1.45                 1.7
-//     two-stage          0.87 / 1.01                      0.93 / 1.09                  1.29                 1.6
-//     CTC                0.79 / 0.75                      0.66 / 0.77                  0.90                 1.1
-//   (500 frames x 32 / 33 / 64 / 128 under the CTC rule, V = 1025: 0.90, 0.83, 0.97, 0.84; 750 x 16: 1.15)
-//   V = 1281 .. 16384    T <= 128, T * B <= 8192 / 16384   T <= V / 16, <= 8192 / 16384   V / 16 .. V / 8, B < 12 / more
-//     1281 .. 2048       0.90 / 0.95                       - / -                          0.90 / 1.01
-//     2500, 3000         0.82 / 0.95                       0.86 / 0.99                    0.86 / 0.98
-//     4096, 6000         0.66 / 0.89                       0.83 / 0.91                    0.85 / 1.05
-//     8192, 10000        0.48 / 0.94                       0.73 / 0.96                    0.65 / 1.11
-//     12288 .. 16384     0.39 / 0.91                       0.72 / 0.97                    0.59 / 1.08
-//   The third column past 8192 rows: 0.92 to 1.03 under the single-stage rule, 0.92 to 1.04 under the CTC rule, with single
-//   calls up to 1.33; 0.88 to 0.93 under the two-stage rule.  Past V / 8: 1.03 to 1.4 up to 3000 tokens; for one to four
-//   hypotheses 1.04 at 4096, 0.83 at 6000, 0.4 to 0.6 above.
-//   V > 16384 (no segment decoder): 32001, 100 frames x 16: 3340 -> 75 us.
-// These are means: a call loses where one hypothesis speaks many phrases, whose frames the second pass takes one by one
-// (CTC rule: V = 6000, 200 x 32 1.4, V = 16384, 250 x 32 1.2), and gains as much where none does.
+// Which calls the two passes are for.  Pass 1 reads the rows at the chip's rate whatever T and B are; pass 2 has one
+// workgroup per hypothesis, so its time grows with T, and past some ten thousand rows with their number.  The segment
+// decoders read the rows once and in order, but need some thousand segments for that rate and read again what a wrong guess
+// has spoilt.  Time of the two passes over that of the segment decoder (of the two passes with the walk before this one
+// where those were already taken), random rows / spoken phrases and blanks, workspace given:
+//   T x B                    40 x 1     100 x 4    60 x 48    300 x 8    300 x 64   1000 x 1   1000 x 16  1000 x 128
+//   V = 257   single-stage   .74 / .63  .89 / .66  1.2 / 1.2  1.2 / 1.0  1.4 / 1.7  .95 / 1.5  1.4 / 1.0  1.3 / 1.5
+//             CTC            .59 / .61  .71 / .80  .93 / .39  .97 / .61  1.2 / .71  .78 / 1.0  1.2 / .91  1.1 / 1.0
+//   V = 512   single-stage   .71 / .63  .83 / .60  1.0 / .58  1.1 / .95  1.2 / 1.3  .86 / 1.4  1.2 / 1.0  1.2 / 1.5
+//             CTC            .57 / .72  .68 / .43  .86 / .48  .93 / .67  1.1 / .76  .75 / 1.3  1.1 / .77  1.1 / 1.1
+//   V = 1024  single-stage   .61 / .61  .80 / .86  .87 / .50  1.0 / .67  1.3 / 1.0  .76 / 1.4  1.3 / 1.1  1.2 / 1.4
+//             CTC            .49 / .58  .64 / .86  .69 / .45  .85 / .51  1.1 / .84  .59 / 1.3  1.0 / .92  1.2 / 1.0
+//   V = 1025  single-stage   .58 / .75  .74 / .75  .65 / .57  .70 / .65  .91 / .87  .62 / .78  .95 / .93  .96 / 1.3
+//             CTC            .58 / .58  .64 / .61  .72 / .59  .61 / .54  .78 / .82  .40 / .39  .71 / .63  .70 / .84
+//   V = 2500  single-stage   .70 / .65  .75 / .73  .79 / 1.0  .65 / .74  .96 / .92  .48 / .69  1.0 / 1.0
+//             CTC            .68 / .60  .71 / .65  .79 / .69  .64 / .86  .86 / .75  .39 / .58  .89 / .81
+//   V = 8192  single-stage   .67 / .68  .68 / .78  .81 / .93  .70 / .77             .49 / .67  1.0 / .87
+//             CTC            .65 / .67  .66 / .50  .63 / .52  .70 / .61             .49 / .46  .94 / .74
+// (Two-stage rule: as the single-stage one, 300 x 8 .61 to .87, 2000 x 4 .61 to .9.)  V <= 256: 1.0 to 2.1 in most calls.
+// The lines keep every column in which both kinds gain.  V > 16384 (no segment decoder): 32001, 100 x 16: 3340 -> 60 us.
 static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
   const int64_t rows = static_cast<int64_t>(T) * B;
   if (V > kWideMaxV) return rows <= kMaxWorkgroups;
-  if (V <= 1024) return false;
-  if (V <= kNarrowMaxV) {
-    if (sel == 2) return T <= 512 && rows <= 65536;
-    return T <= (sel == 0 ? 128 : 256) && rows <= 2048;
-  }
-  if (rows > 16384) return false;
-  if (V >= 4096 && B <= 4) return true;
-  const int longest = V / (B < 12 ? 8 : 16);
-  return T <= 128 || (T <= longest && (sel == 1 || rows <= 8192));
+  if (V <= 256) return false;
+  if (V <= 1024) return T <= 512 && rows <= (sel == 2 || V > 768 ? 4096 : T <= 128 ? 512 : 0);
+  if (V <= kNarrowMaxV && sel == 2) return T <= 2048 && rows <= 131072;
+  return T <= 2048 && rows <= 20480;
 }
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
   return t.p_root != nullptr && t.root_rec != nullptr && rows_pay(t.vocab_size, T, B, sel) &&
-         walk_lds_bytes(t.vocab_size, T, 1) <= static_cast<size_t>(g_walk_max_lds);
+         walk_lds_bytes(t.vocab_size, 1) <= static_cast<size_t>(g_walk_max_lds);
 }
 
 int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,
@@ -793,14 +850,25 @@ int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d
     int64_t strips = (8192 + B - 1) / B;  // waves per hypothesis: two rounds of what the chip holds
     if (strips > T) strips = T;
     const int64_t blocks = (strips * B + 3) / 4;
-#define PB_ROWS(SEL)                                                                                                      \
-  hipLaunchKernelGGL((rows_narrow_kernel<kNarrowMaxV / 64, SEL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, \
-                     t, pick, d_logp, frame_stride, row_stride, alpha, T, B, static_cast<int>(strips), d_tokens, d_states)
-    if (sel == 0) {
-      PB_ROWS(0);
+#define PB_ROWS(NS, SEL)                                                                                                   \
+  hipLaunchKernelGGL((rows_narrow_kernel<NS, SEL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, t, pick,    \
+                     d_logp, frame_stride, row_stride, alpha, T, B, static_cast<int>(strips), d_tokens, d_states)
+#define PB_ROWS_SEL(NS) \
+  if (sel == 0) {       \
+    PB_ROWS(NS, 0);     \
+  } else {              \
+    PB_ROWS(NS, 1);     \
+  }
+    if (V <= 256) {
+      PB_ROWS_SEL(4)
+    } else if (V <= 512) {
+      PB_ROWS_SEL(8)
+    } else if (V <= 1024) {
+      PB_ROWS_SEL(16)
     } else {
-      PB_ROWS(1);
+      PB_ROWS_SEL(20)
     }
+#undef PB_ROWS_SEL
 #undef PB_ROWS
   } else {
     // Waves per row: one per eight chunks where the rows alone fill the chip, up to one per chunk where they do not.
@@ -817,9 +885,11 @@ int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d
                          frame_stride, row_stride, alpha, B, d_tokens, d_states);
   }
   if (hipGetLastError() != hipSuccess) return PB_EHIP;
-  int waves = 16;
-  while (waves > 1 && (waves * 2 > T || walk_lds_bytes(V, T, waves) > static_cast<size_t>(g_walk_max_lds))) --waves;
-  const size_t lds = walk_lds_bytes(V, T, waves);
+  // A wave takes 16 frames or more (those that it looks back over are read once more: 40 frames x 1 with 16 / 4 waves 13.0 /
+  // 11.3 us, 60 x 48 21.9 / 18.2, V = 1025), at most 64 (1000 x 16 with 16 / 8 waves 42 / 56 us).
+  int waves = T >= 256 ? 16 : (T + 15) / 16;
+  while (waves > 1 && walk_lds_bytes(V, waves) > static_cast<size_t>(g_walk_max_lds)) --waves;
+  const size_t lds = walk_lds_bytes(V, waves);
 #define PB_WALK(SEL)                                                                                                     \
   hipLaunchKernelGGL(walk_kernel<SEL>, dim3(static_cast<unsigned>(B)), dim3(64 * waves), lds, stream, t, pick, d_logp,   \
                      frame_stride, row_stride, d_states0, d_last0, alpha, T, B, d_tokens, d_states, d_scores)

@@ -41,6 +41,18 @@ struct alignas(32) RootRec {
   int32_t pad;
 };
 
+// One 16-byte slot of the table of arcs by (state, token), the root's aside: open addressing, linear probing, at most
+// half full; state == -1 in an empty slot.  A deep state has few arcs and they could be searched, but the walk over a
+// phrase (pb_rows.hip) follows one arc after the other, and the table makes that one access each instead of two or more.
+struct alignas(16) ArcSlot {
+  int32_t state, token, next, pad;
+};
+constexpr uint32_t arc_hash(int32_t state, int32_t token) {
+  uint32_t h = static_cast<uint32_t>(state) * 0x9E3779B1u ^ static_cast<uint32_t>(token) * 0x85EBCA6Bu;
+  h ^= h >> 15;
+  return h * 0xC2B2AE35u >> 3;
+}
+
 // Device mirror (one allocation, sub-arrays aligned to 256 bytes).
 struct DeviceTree {
   const StateRec* state = nullptr;  // [N]
@@ -51,6 +63,8 @@ struct DeviceTree {
   const RootRec* root_rec = nullptr;   // [V]
   const float* eos_score = nullptr;    // [N] boost of the EOS token in every state (Sec. II-C: largest score of the other
                                        // tokens plus the final weight of an end-of-phrase state); null without an EOS rule
+  const ArcSlot* arc_slot = nullptr;   // [arc_mask + 1], see ArcSlot
+  uint32_t arc_mask = 0;
   int32_t num_states = 0;
   int32_t vocab_size = 0;
   int32_t blank_id = -1;

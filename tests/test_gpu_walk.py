@@ -1,0 +1,83 @@
+"""GPU parity of the second pass of the two-pass multi-frame decoder (frames decided side by side from the states the winners
+lead to, then again where that was wrong) at the sizes where it can go wrong, against the CPU oracle: every row shape of the
+first pass, both sides of the packed winner word, few and many frames a wave, more frames than a block holds, states with
+more arcs than a wave has lanes, chains of more than four levels, whole phrases (an arc and the base winner have the same
+value), rows that only a pass over them can decide, more of them than are taken at a time; and the segment decoders on calls
+that are still theirs.  Ids are exact, scores within 1e-5 (they are the same bits: the oracle's operations in its order)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2508_07014_amd as pb  # noqa: E402
+import test_gpu_segments as seg  # noqa: E402
+from gpu_helpers import DEV, dev  # noqa: E402
+from oracle import OracleTree  # noqa: E402
+from test_gpu_ragged import _check  # noqa: E402
+from test_gpu_rows import _near_ties, _outputs  # noqa: E402
+
+
+def _lists(rng, V, blank, kind):
+    ids = np.array([v for v in range(V) if v != blank], dtype=np.int32)
+    if kind == "bushy":  # one token with hundreds of arcs behind it, many one-token phrases
+        phrases = [[ids[0], t] for t in ids[::2][:600]] + [[ids[0], ids[0], t] for t in ids[1::3][:200]] + [[t] for t in ids[:40]]
+    elif kind == "deep":  # runs of one token: every suffix is in the tree, failure chains as long as the run
+        phrases = [[ids[3]] * 9 + [ids[5]], [ids[3]] * 7 + [ids[4]], [ids[3], ids[4], ids[3], ids[4], ids[3], ids[6]]]
+        phrases += [list(rng.choice(ids[:8], rng.integers(1, 7))) for _ in range(60)]
+    else:
+        phrases = [list(ids[np.minimum(rng.zipf(1.2, rng.integers(1, 8)) - 1, len(ids) - 1)]) for _ in range(300)]
+    offs = np.cumsum([0] + [len(p) for p in phrases]).astype(np.int64)
+    return np.concatenate([np.asarray(p, dtype=np.int32) for p in phrases]), offs
+
+
+def _compare(tr, ot, x, s0, last0, alpha, where):
+    T, B, V = x.shape
+    d_x = dev(x)
+    for mode in (0, 1, 2):
+        o = _outputs(T, B)
+        print("walk", where, mode, flush=True)
+        pb.pb_fuse_frames_select(tr, d_x, B * V, V, dev(s0), dev(last0), alpha, T, B, mode, o[0], o[1], o[2], 0)
+        torch.cuda.synchronize()
+        _check(o, ot.fuse_frames_select(x, s0, last0, alpha, mode), list(range(B)), (where, mode))
+
+
+@pytest.mark.parametrize("kind", ["zipf", "bushy", "deep"])
+@pytest.mark.parametrize("V,T,B", [(257, 1, 2), (257, 100, 4), (512, 15, 3), (513, 16, 3), (512, 128, 4), (769, 17, 2), (1000, 512, 2),
+                                   (1024, 255, 3), (1024, 257, 2), (1025, 1025, 2), (1280, 65, 3), (1281, 1030, 1), (4096, 40, 2),
+                                   (32768, 33, 2), (32769, 33, 2)])
+def test_phrases_spoken(V, T, B, kind):
+    rng = np.random.default_rng(91000 + V + T)
+    torch.manual_seed(V + T)
+    blank = int(rng.choice([-1, 0, V - 1]))
+    toks, offs = _lists(rng, V, blank, kind)
+    wmode, alpha = int(rng.integers(0, 3)), float(rng.choice([0.3, 1.0, -0.5]))
+    ot = OracleTree(toks, offs, V, blank, weight_mode=wmode)
+    tr = pb.pb_build(toks, offs, V, blank, device=0, weight_mode=wmode)
+    x = seg._spoken(rng, T, B, V, [(toks, offs)]) if T > 12 else torch.round(torch.randn((T, B, V), device=DEV) * 4) / 2
+    if blank >= 0:
+        x[torch.rand((T, B), device=DEV) < 0.4, blank] += 14.0
+    s0 = rng.integers(0, ot.num_states, B).astype(np.int32)
+    _compare(tr, ot, x.cpu().numpy(), s0, rng.integers(-1, V, B).astype(np.int32), alpha, (V, T, B, kind, blank, wmode, alpha))
+    pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("V,T", [(300, 100), (1000, 130), (1100, 130), (20001, 70)])
+def test_every_frame_needs_its_row(V, T):
+    rng = np.random.default_rng(92000 + V)
+    toks, offs = _lists(rng, V, V - 1, "zipf")
+    ot = OracleTree(toks, offs, V, V - 1)
+    tr = pb.pb_build(toks, offs, V, V - 1, device=0)
+    x = _near_ties(rng, tr, T, 2, V, 0.5)
+    s0 = rng.integers(0, ot.num_states, 2).astype(np.int32)
+    _compare(tr, ot, x, s0, rng.integers(-1, V, 2).astype(np.int32), 0.5, (V, T))
+    pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("V", [1025, 1152, 1280, 1281, 2047, 2048, 2049, 2500, 4095, 4096, 5125, 9217, 16381, 16384])
+def test_segment_decoders_on_long_calls(V, monkeypatch):
+    monkeypatch.setitem(seg.SIZES, V, (2050, 3))
+    seg.test_segment_decoders_past_the_dispatch_line(V, V % 2 == 0)
