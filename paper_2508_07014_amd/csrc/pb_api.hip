@@ -47,12 +47,9 @@ int lookup_scratch(int device) {
 size_t padded(size_t bytes) { return (bytes + kAlign - 1) / kAlign * kAlign; }
 
 // The table of arcs by (state, token), see ArcSlot; null where there is no memory for it.
-std::unique_ptr<pb::ArcSlot[]> arc_slots(const pb::HostTree& h, size_t& size) {
-  const size_t arcs = h.arc.size() - static_cast<size_t>(h.root_degree);
-  size = 2;
-  while (size < 2 * arcs) size *= 2;
+std::unique_ptr<pb::ArcSlot[]> arc_table(const pb::HostTree& h, size_t size) {
   std::unique_ptr<pb::ArcSlot[]> slots(new (std::nothrow) pb::ArcSlot[size]);
-  if (!slots) return slots;
+  if (!slots || size == 0) return slots;
   std::fill(slots.get(), slots.get() + size, pb::ArcSlot{-1, -1, -1, 0});
   for (size_t s = 1; s < h.state.size(); ++s) {
     for (int32_t j = h.arc_begin[s]; j < h.arc_begin[s] + h.arc_count[s]; ++j) {
@@ -74,8 +71,8 @@ int upload(pb_tree* tr, int device) {
   const size_t n_pr = h.p_root.size() * sizeof(float);
   const size_t n_rr = h.root_rec.size() * sizeof(pb::RootRec);
   const size_t n_es = h.eos_score.size() * sizeof(float);
-  size_t n_slots = 0;
-  const std::unique_ptr<pb::ArcSlot[]> slots = arc_slots(h, n_slots);
+  const size_t n_slots = pb::arc_slots(static_cast<int32_t>(h.state.size()));
+  const std::unique_ptr<pb::ArcSlot[]> slots = arc_table(h, n_slots);
   if (!slots) return PB_ENOMEM;
   const size_t n_as = n_slots * sizeof(pb::ArcSlot);
   const size_t total =
@@ -84,7 +81,7 @@ int upload(pb_tree* tr, int device) {
   // state's arc range; for a state without arcs (the last state of the table included) that reads the entry
   // at arc_begin, i.e. up to one ArcRec past the arc table.  The sub-arrays that follow the arc table in the
   // allocation make that read harmless; refuse a layout that would not.
-  if (total - (padded(n_state) + n_arc) < sizeof(pb::ArcRec)) return PB_EUNSUPPORTED;
+  if (total - (padded(n_as) + padded(n_state) + n_arc) < sizeof(pb::ArcRec)) return PB_EUNSUPPORTED;
   int prev = 0;
   if (hipGetDevice(&prev) != hipSuccess) { (void)hipGetLastError(); return PB_EHIP; }
   if (hipSetDevice(device) != hipSuccess) { (void)hipGetLastError(); return PB_EHIP; }
@@ -101,6 +98,7 @@ int upload(pb_tree* tr, int device) {
       p += padded(bytes);
       return dst;
     };
+    put(slots.get(), n_as);
     tr->dev.state = static_cast<const pb::StateRec*>(put(h.state.data(), n_state));
     tr->dev.arc = static_cast<const pb::ArcRec*>(put(h.arc.data(), n_arc));
     tr->dev.root_score = static_cast<const float*>(put(h.root_score.data(), n_rs));
@@ -108,8 +106,6 @@ int upload(pb_tree* tr, int device) {
     tr->dev.p_root = static_cast<const float*>(put(h.p_root.data(), n_pr));
     tr->dev.root_rec = static_cast<const pb::RootRec*>(put(h.root_rec.data(), n_rr));
     tr->dev.eos_score = n_es ? static_cast<const float*>(put(h.eos_score.data(), n_es)) : nullptr;
-    tr->dev.arc_slot = static_cast<const pb::ArcSlot*>(put(slots.get(), n_as));
-    tr->dev.arc_mask = static_cast<uint32_t>(n_slots - 1);
     tr->dev.eos_id = h.eos_id;
     if (rc == PB_OK) rc = pb::prepare_wave_kernels();
     if (rc == PB_OK) rc = lookup_scratch(device);

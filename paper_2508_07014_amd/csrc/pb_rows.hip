@@ -684,8 +684,9 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
     const int f0 = static_cast<int>(static_cast<int64_t>(wave) * count / nwaves);
     const int f1 = static_cast<int>(static_cast<int64_t>(wave + 1) * count / nwaves);
     const int base = first_held(f0, f1), lo = f0 - base, hi = f1 - base, fr = base + lane;
-    const Walker<SEL> walk{t, (const v4i PB_AS1*)mine.state, (const v2i PB_AS1*)mine.arc, (const v4i PB_AS1*)mine.arc_slot,
-                           mine.arc_mask, (const int PB_AS1*)mine.root_next,
+    const Walker<SEL> walk{t, (const v4i PB_AS1*)mine.state, (const v2i PB_AS1*)mine.arc,
+                           (const v4i PB_AS1*)mine.state - arc_slots(mine.num_states), arc_slots(mine.num_states) - 1,
+                           (const int PB_AS1*)mine.root_next,
                            (const float PB_AS1*)mine.p_root, (const float PB_AS1*)mine.eos_score, (const float PB_AS1*)mine.root_score,
                            logp + static_cast<int64_t>(F0 + base) * frame_stride + static_cast<int64_t>(b) * row_stride,
                            frame_stride, alpha, shared[wave], lane};
@@ -812,32 +813,40 @@ size_t walk_lds_bytes(int V, int waves) {
 // decoders read the rows once and in order, but need some thousand segments for that rate and read again what a wrong guess
 // has spoilt.  Time of the two passes over that of the segment decoder (of the two passes with the walk before this one
 // where those were already taken), random rows / spoken phrases and blanks, workspace given:
+//   T x B                    60 x 48    150 x 10   300 x 8    200 x 64   500 x 4    500 x 32   1000 x 1   1000 x 16
+//   V = 128   single-stage   1.1 / 1.2  1.2 / .87  1.4 / 1.7  1.5 / 1.1  1.4 / 1.0  1.7 / 1.1  1.1 / 1.2  1.6 / 1.4
+//             CTC            .85 / .53  .95 / .98  1.1 / .68  1.2 / .81  1.3 / .67  1.4 / .62  .96 / .81  1.4 / .96
+//   V = 257   single-stage   .99 / 1.0  1.1 / .76  1.2 / .88  1.4 / .75  1.3 / 1.0  1.5 / .93  .93 / 1.4  1.4 / .88
+//             CTC            .93 / .39  1.0 / .59  .96 / .61  1.1 / .75  1.0 / .48  1.3 / .72  .76 / .88  1.2 / .83
+//   V = 512   single-stage   1.1 / .50  .87 / .57  1.1 / .81  1.4 / .80  .99 / .81  1.2 / .95  .85 / 1.3  1.2 / .89
+//             CTC            .86 / .47  .81 / .45  .93 / .67  1.3 / .66  .77 / .55  1.3 / .63  .73 / 1.1  1.1 / .71
+//   V = 768   single-stage   .78 / .54  .71 / .53  .80 / .61  1.2 / .63  .80 / .67  1.3 / .78  .60 / .77  1.0 / .87
+//             CTC            .63 / .41  .61 / .56  .67 / .57  .98 / .56  .67 / .49  .99 / .64  .59 / .79  .88 / .64
+//   V = 1024  single-stage   .88 / .50  .77 / .73  1.0 / .67  1.2 / .65  .83 / .69  1.3 / .83  .74 / 1.2  1.3 / .99
+//             CTC            .68 / .45  .72 / .60  .83 / .52  .96 / .68  .64 / .68  1.1 / .73  .56 / 1.1  1.0 / .89
 //   T x B                    40 x 1     100 x 4    60 x 48    300 x 8    300 x 64   1000 x 1   1000 x 16  1000 x 128
-//   V = 257   single-stage   .74 / .63  .89 / .66  1.2 / 1.2  1.2 / 1.0  1.4 / 1.7  .95 / 1.5  1.4 / 1.0  1.3 / 1.5
-//             CTC            .59 / .61  .71 / .80  .93 / .39  .97 / .61  1.2 / .71  .78 / 1.0  1.2 / .91  1.1 / 1.0
-//   V = 512   single-stage   .71 / .63  .83 / .60  1.0 / .58  1.1 / .95  1.2 / 1.3  .86 / 1.4  1.2 / 1.0  1.2 / 1.5
-//             CTC            .57 / .72  .68 / .43  .86 / .48  .93 / .67  1.1 / .76  .75 / 1.3  1.1 / .77  1.1 / 1.1
-//   V = 1024  single-stage   .61 / .61  .80 / .86  .87 / .50  1.0 / .67  1.3 / 1.0  .76 / 1.4  1.3 / 1.1  1.2 / 1.4
-//             CTC            .49 / .58  .64 / .86  .69 / .45  .85 / .51  1.1 / .84  .59 / 1.3  1.0 / .92  1.2 / 1.0
+//   V = 257   single-stage   .74 / .63  .89 / .66
+//   V = 1024  single-stage   .61 / .61  .80 / .86
 //   V = 1025  single-stage   .58 / .75  .74 / .75  .65 / .57  .70 / .65  .91 / .87  .62 / .78  .95 / .93  .96 / 1.3
 //             CTC            .58 / .58  .64 / .61  .72 / .59  .61 / .54  .78 / .82  .40 / .39  .71 / .63  .70 / .84
 //   V = 2500  single-stage   .70 / .65  .75 / .73  .79 / 1.0  .65 / .74  .96 / .92  .48 / .69  1.0 / 1.0
 //             CTC            .68 / .60  .71 / .65  .79 / .69  .64 / .86  .86 / .75  .39 / .58  .89 / .81
 //   V = 8192  single-stage   .67 / .68  .68 / .78  .81 / .93  .70 / .77             .49 / .67  1.0 / .87
 //             CTC            .65 / .67  .66 / .50  .63 / .52  .70 / .61             .49 / .46  .94 / .74
-// (Two-stage rule: as the single-stage one, 300 x 8 .61 to .87, 2000 x 4 .61 to .9.)  V <= 256: 1.0 to 2.1 in most calls.
-// The lines keep every column in which both kinds gain.  V > 16384 (no segment decoder): 32001, 100 x 16: 3340 -> 60 us.
+// The two-stage rule lies between the two, nearer the single-stage one, and has its lines.  These keep the columns in which
+// both kinds gain, up to a few per cent.  V > 16384 (no segment decoder): 32001, 100 x 16: 3340 -> 75 us.
 static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
   const int64_t rows = static_cast<int64_t>(T) * B;
   if (V > kWideMaxV) return rows <= kMaxWorkgroups;
-  if (V <= 256) return false;
-  if (V <= 1024) return T <= 512 && rows <= (sel == 2 || V > 768 ? 4096 : T <= 128 ? 512 : 0);
+  if (V < 128 || (V <= 1024 && T > 512)) return false;
+  if (V <= 1024 && sel == 2) return rows <= (V >= 768 ? 12800 : V > 256 || T <= 160 ? 4096 : 0);
+  if (V <= 1024) return rows <= (V >= 768 ? 4096 : V > 384 && T <= 256 ? 2048 : V > 256 && T <= 128 ? 512 : 0);
   if (V <= kNarrowMaxV && sel == 2) return T <= 2048 && rows <= 131072;
   return T <= 2048 && rows <= 20480;
 }
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
-  return t.p_root != nullptr && t.root_rec != nullptr && rows_pay(t.vocab_size, T, B, sel) &&
+  return t.p_root != nullptr && t.root_rec != nullptr && t.num_states <= kMaxTableStates && rows_pay(t.vocab_size, T, B, sel) &&
          walk_lds_bytes(t.vocab_size, 1) <= static_cast<size_t>(g_walk_max_lds);
 }
 

@@ -44,9 +44,16 @@ struct alignas(32) RootRec {
 // One 16-byte slot of the table of arcs by (state, token), the root's aside: open addressing, linear probing, at most
 // half full; state == -1 in an empty slot.  A deep state has few arcs and they could be searched, but the walk over a
 // phrase (pb_rows.hip) follows one arc after the other, and the table makes that one access each instead of two or more.
+// It lies right before the states on the device and its size follows from their number, so that DeviceTree, which every
+// kernel takes by value or out of a table, has no field for it.
 struct alignas(16) ArcSlot {
   int32_t state, token, next, pad;
 };
+// Slots: a power of two, at least 16 (256 bytes: what sub-arrays are aligned to); none where 32 bits do not count them.
+constexpr int32_t kMaxTableStates = 1 << 30;
+constexpr uint32_t arc_slots(int32_t num_states) {
+  return num_states <= 8 ? 16u : num_states > kMaxTableStates ? 0u : 1u << (33 - __builtin_clz(static_cast<uint32_t>(num_states - 1)));
+}
 constexpr uint32_t arc_hash(int32_t state, int32_t token) {
   uint32_t h = static_cast<uint32_t>(state) * 0x9E3779B1u ^ static_cast<uint32_t>(token) * 0x85EBCA6Bu;
   h ^= h >> 15;
@@ -63,8 +70,6 @@ struct DeviceTree {
   const RootRec* root_rec = nullptr;   // [V]
   const float* eos_score = nullptr;    // [N] boost of the EOS token in every state (Sec. II-C: largest score of the other
                                        // tokens plus the final weight of an end-of-phrase state); null without an EOS rule
-  const ArcSlot* arc_slot = nullptr;   // [arc_mask + 1], see ArcSlot
-  uint32_t arc_mask = 0;
   int32_t num_states = 0;
   int32_t vocab_size = 0;
   int32_t blank_id = -1;

@@ -46,7 +46,7 @@ def _compare(tr, ot, x, s0, last0, alpha, where):
 
 
 @pytest.mark.parametrize("kind", ["zipf", "bushy", "deep"])
-@pytest.mark.parametrize("V,T,B", [(257, 1, 2), (257, 100, 4), (512, 15, 3), (513, 16, 3), (512, 128, 4), (769, 17, 2), (1000, 512, 2),
+@pytest.mark.parametrize("V,T,B", [(128, 160, 2), (200, 60, 3), (257, 1, 2), (257, 100, 4), (512, 15, 3), (513, 16, 3), (512, 128, 4), (769, 17, 2), (1000, 512, 2),
                                    (1024, 255, 3), (1024, 257, 2), (1025, 1025, 2), (1280, 65, 3), (1281, 1030, 1), (4096, 40, 2),
                                    (32768, 33, 2), (32769, 33, 2)])
 def test_phrases_spoken(V, T, B, kind):
