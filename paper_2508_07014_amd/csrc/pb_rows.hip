@@ -834,15 +834,17 @@ size_t walk_lds_bytes(int V, int waves) {
 //   V = 8192  single-stage   .67 / .68  .68 / .78  .81 / .93  .70 / .77             .49 / .67  1.0 / .87
 //             CTC            .65 / .67  .66 / .50  .63 / .52  .70 / .61             .49 / .46  .94 / .74
 // The two-stage rule lies between the two, nearer the single-stage one, and has its lines.  These keep the columns in which
-// both kinds gain, up to a few per cent.  V > 16384 (no segment decoder): 32001, 100 x 16: 3340 -> 75 us.
+// both kinds gain, up to a few per cent, with room for long lists outside the CTC rule, whose states have more arcs than the
+// table's lists of 2000 phrases (8539 phrases spoken, V = 1152, 248 x 29, two-stage: 55 us and 78 with the two passes).  V > 16384 (no segment decoder): 32001, 100 x 16: 3340 -> 75 us.
 static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
   const int64_t rows = static_cast<int64_t>(T) * B;
   if (V > kWideMaxV) return rows <= kMaxWorkgroups;
   if (V < 128 || (V <= 1024 && T > 512)) return false;
   if (V <= 1024 && sel == 2) return rows <= (V >= 768 ? 12800 : V > 256 || T <= 160 ? 4096 : 0);
   if (V <= 1024) return rows <= (V >= 768 ? 4096 : V > 384 && T <= 256 ? 2048 : V > 256 && T <= 128 ? 512 : 0);
-  if (V <= kNarrowMaxV && sel == 2) return T <= 2048 && rows <= 131072;
-  return T <= 2048 && rows <= 20480;
+  if (T > 2048) return false;
+  if (V <= kNarrowMaxV) return rows <= (sel == 2 ? 131072 : 4096);
+  return rows <= (sel == 2 || V >= 4096 || T <= 128 ? 20480 : 8192);
 }
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
