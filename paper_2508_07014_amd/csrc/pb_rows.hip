@@ -466,12 +466,15 @@ struct Walker {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         if (base + 64 * k + lane < pairs) {
-          const unsigned key = ukey(__fadd_rn(xa[k], __fmul_rn(alpha, __fadd_rn(p[k], __int_as_float(a[k].y)))));
+          const float v = __fadd_rn(xa[k], __fmul_rn(alpha, __fadd_rn(p[k], __int_as_float(a[k].y))));
+          const unsigned key = ukey(v);
           const u64 old = atomicMax(&L.best[fr[k]], (static_cast<u64>(key) << 32) | ~static_cast<unsigned>(at[k]));
+          const unsigned old_key = static_cast<unsigned>(old >> 32);
           const int old_at = static_cast<int>(~static_cast<unsigned>(old));
-          // (two of a level: the lower arc is the lower token; the same token on two levels: see below)
-          bool tie = static_cast<unsigned>(old >> 32) == key && !in_level(old_at - lo[k], 0, len[k]);
-          if (tie) tie = arc[old_at].x != a[k].x;
+          // (two of a level: the lower arc is the lower token; the same token on two levels: see below; zeros of both
+          // signs are equal values with different keys)
+          bool tie = ukey_val(old_key) == v;
+          if (tie && old_key == key) tie = !in_level(old_at - lo[k], 0, len[k]) && arc[old_at].x != a[k].x;
           const unsigned say = (a[k].x == fw[k] ? 1u : 0u) | (tie ? 2u : 0u);
           if (say != 0) atomicOr(&L.flag[fr[k]], say);
         }
@@ -599,8 +602,8 @@ struct Walker {
   }
   // The best of the lanes' candidates (tok == INT_MAX: none), in every lane.
   __device__ __forceinline__ static WalkBest best_of(const WalkBest& o) {
-    const unsigned best = wave_max_u(o.tok != INT_MAX ? ukey(o.val) : 0u);
-    const bool mine = o.tok != INT_MAX && ukey(o.val) == best;
+    const float best = ukey_val(wave_max_u(o.tok != INT_MAX ? ukey(o.val) : 0u));
+    const bool mine = o.tok != INT_MAX && o.val == best;  // (zeros of both signs are equal)
     const int tok = wave_min_nn(mine ? o.tok : INT_MAX);
     const u64 who = __ballot(mine && o.tok == tok);
     const int from = who != 0 ? first_lane(who) : 0;

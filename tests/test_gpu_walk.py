@@ -81,3 +81,20 @@ def test_every_frame_needs_its_row(V, T):
 def test_segment_decoders_on_long_calls(V, monkeypatch):
     monkeypatch.setitem(seg.SIZES, V, (2050, 3))
     seg.test_segment_decoders_past_the_dispatch_line(V, V % 2 == 0)
+
+
+@pytest.mark.parametrize("V", [300, 1025, 2500])
+def test_zeros_of_both_signs(V):
+    """0.0 and -0.0 are equal values: the lower token wins, among arcs and among the tokens of a row that needs a pass."""
+    rng = np.random.default_rng(93000 + V)
+    toks, offs = _lists(rng, V, V - 1, "bushy")
+    weights = np.where(rng.random(len(offs) - 1) < 0.5, 1.0, -1.0).astype(np.float32)
+    ot = OracleTree(toks, offs, V, V - 1, weights=weights)
+    tr = pb.pb_build(toks, offs, V, V - 1, weights=weights, device=0)
+    T, B = 70, 2
+    x = np.where(rng.random((T, B, V)) < 0.05, np.where(rng.random((T, B, V)) < 0.5, 0.0, -0.0), -1.0).astype(np.float32)
+    x[::3, :, 0] = 0.0                                   # (the token with hundreds of arcs behind it)
+    s0 = rng.integers(0, ot.num_states, B).astype(np.int32)
+    for alpha in (0.0, -0.0):                            # (times a negative score, or a positive one: -0.0)
+        _compare(tr, ot, x, s0, rng.integers(-1, V, B).astype(np.int32), alpha, (V, alpha))
+    pb.pb_free(tr)
