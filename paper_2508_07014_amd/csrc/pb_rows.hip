@@ -250,17 +250,24 @@ __global__ void __launch_bounds__(1024) rows_wide_kernel(DeviceTree dt, TreePick
 // ---- pass 2 --------------------------------------------------------------------------------------------------------------
 constexpr int kWalkPairs = 256;  // (frame, arc) pairs looked at together: four a lane
 
+// The order of a frame's arcs: by value, then the lower token, then the level of the chain, deepest state first (11 bits;
+// levels past the last one counted are told apart by a pass over the row).
+constexpr int kLevelBits = 11, kLastLevel = (1 << kLevelBits) - 1, kMaxWalkV = 1 << (32 - kLevelBits);
+__device__ __forceinline__ u64 arc_key(float value, int token, int level) {
+  const unsigned low = static_cast<unsigned>(token) << kLevelBits | static_cast<unsigned>(min(level, kLastLevel));
+  return static_cast<u64>(ukey(value)) << 32 | ~low;
+}
+
 // What the lanes of a wave tell each other about their frames while they share out the arcs.
 struct alignas(16) WalkMeta {
-  int start, c0, c1, c2;  // first pair of the frame; arcs on the chain's first level, first two, first three
-  int o0, o1, o2, o3;     // arc of pair j of the frame: j + the offset of its level
-  float p1, p2, p3;       // backoff paid before the levels
-  int w;
+  int start, c0, c1, c2;    // first pair of the frame; arcs on the first of four levels of the chain, first two, first three
+  int o0, o1, o2, o3;       // arc of pair j of the frame: j + the offset of its level
+  float p0, p1, p2, p3;     // backoff paid before the levels
 };
 struct WalkLds {  // of a wave
   WalkMeta meta[64];
-  u64 best[64];        // largest (value, lowest arc) of the frame's arcs
-  unsigned flag[64];   // 1: an arc overrides the base winner, 2: two tokens of equal value on two levels
+  u64 best[64];        // largest (value, lowest token, deepest state) of the frame's arcs, see arc_key
+  unsigned flag[64];   // 1: an arc overrides the base winner, 2: an arc of value -0.0
   int owner[kWalkPairs];
 };
 struct WalkJob {  // a frame that needs a pass over its row
@@ -382,139 +389,119 @@ struct Walker {
   __device__ __forceinline__ void decide_frames(WalkFrame& f, u64 need) const {
     const bool mine = (need >> lane) & 1;
     const bool kept = SEL != 0 && (f.v0 == t.blank || (SEL == 2 && f.v0 == f.label));
-    // ---- the first four levels of every frame's chain as one list of arcs, deepest state first -------------------------
-    int s1 = 0, s2 = 0, c0 = 0, c1 = 0, c2 = 0, total = 0, o0 = 0, o1 = 0, o2 = 0, o3 = 0;
-    float p1 = 0.0f, p2 = 0.0f, p3 = 0.0f, pr = 0.0f, eb = 0.0f;
+    // ---- the best arc of every frame: four levels of every frame's chain as one list of arcs, deepest state first, shared
+    // out over the lanes ---------------------------------------------------------------------------------------------------
+    // (One loop of little code: the same with the arcs of a frame on the lanes, eight frames unrolled, spent its time on
+    // fetching instructions that no wave had run before.)
+    float pr = 0.0f, eb = 0.0f;  // pr: the backoffs in chain order, at last what p_root holds
+    int x = 0;                   // the next state of the chain
     bool hard = f.marked;
     if (mine && !kept && !hard) {
       if (t.eos >= 0) eb = eos_score[f.s];
-      if (f.s != 0) {
-        const v4i q = states[2 * static_cast<size_t>(f.s)], q1 = states[2 * static_cast<size_t>(f.s) + 1];
+      x = f.s;
+    }
+    L.best[lane] = 0;
+    L.flag[lane] = 0;
+#pragma unroll 1
+    for (int level = 0; __ballot(x != 0) != 0; level += 4) {  // (a second turn for chains of more than four states)
+      int c0 = 0, c1 = 0, c2 = 0, total = 0, o0 = 0, o1 = 0, o2 = 0, o3 = 0;
+      const float p0 = pr;
+      float p1 = 0.0f, p2 = 0.0f, p3 = 0.0f;
+      if (x != 0) {
+        const v4i q = states[2 * static_cast<size_t>(x)], q1 = states[2 * static_cast<size_t>(x) + 1];
         c0 = q.y;
-        pr = p1 = __fadd_rn(0.0f, __int_as_float(q.w));  // (the backoffs in chain order: what p_root holds)
+        pr = p1 = __fadd_rn(p0, __int_as_float(q.w));
         o0 = q.x;
         c1 = c2 = total = c0;
-        s1 = q.z;
-        s2 = q1.z;
-        if (s1 != 0) {
+        x = q.z;
+        if (x != 0) {
+          x = q1.z;
           pr = p2 = __fadd_rn(p1, __int_as_float(q1.w));
           o1 = q1.x - c0;
           c1 = c2 = total = c0 + q1.y;
-          if (s2 != 0) {
-            const v4i z = states[2 * static_cast<size_t>(s2)], z1 = states[2 * static_cast<size_t>(s2) + 1];
+          if (x != 0) {
+            const v4i z = states[2 * static_cast<size_t>(x)], z1 = states[2 * static_cast<size_t>(x) + 1];
+            x = z.z;
             pr = p3 = __fadd_rn(p2, __int_as_float(z.w));
             o2 = z.x - c1;
             c2 = total = c1 + z.y;
-            if (z.z != 0) {
+            if (x != 0) {
+              x = z1.z;
               pr = __fadd_rn(p3, __int_as_float(z1.w));
               o3 = z1.x - c2;
               total = c2 + z1.y;
-              hard = z1.z != 0;  // a longer chain
             }
           }
         }
       }
+      const int end = prefix_sum(total);
+      const int start = end - total, pairs = lane_i(end, 63);
+      L.meta[lane] = WalkMeta{start, c0, c1, c2, o0, o1, o2, o3, p0, p1, p2, p3};
+      together();
+#pragma unroll 1
+      for (int base = 0; base < pairs; base += kWalkPairs) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) L.owner[64 * k + lane] = 0;
+        together();
+        if (total > 0 && end > base && start < base + kWalkPairs) L.owner[max(start - base, 0)] = lane + 1;
+        together();
+        int fr[4], lv[4];
+        float p[4], xa[4];
+        v2i a[4];
+        int before = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fr[k] = L.owner[64 * k + lane];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          fr[k] = max(before, prefix_max(fr[k]));
+          before = lane_i(fr[k], 63);
+          fr[k] -= 1;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const WalkMeta m = L.meta[fr[k]];
+          const int j = min(base + 64 * k + lane, pairs - 1) - m.start;
+          int off = m.o0;
+          p[k] = m.p0;
+          lv[k] = 0;
+          if (j >= m.c0) { off = m.o1; p[k] = m.p1; lv[k] = 1; }
+          if (j >= m.c1) { off = m.o2; p[k] = m.p2; lv[k] = 2; }
+          if (j >= m.c2) { off = m.o3; p[k] = m.p3; lv[k] = 3; }
+          a[k] = arc[j + off];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xa[k] = hyp[static_cast<int64_t>(fr[k]) * frame_stride + a[k].x];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float v = __fadd_rn(xa[k], __fmul_rn(alpha, __fadd_rn(p[k], __int_as_float(a[k].y))));
+          const int w = __shfl(f.w, fr[k]);
+          if (base + 64 * k + lane < pairs) {
+            atomicMax(&L.best[fr[k]], arc_key(v, a[k].x, level + lv[k]));
+            const unsigned say = (a[k].x == w ? 1u : 0u) | (__float_as_uint(v) == 0x80000000u ? 2u : 0u);
+            if (say != 0) atomicOr(&L.flag[fr[k]], say);
+          }
+        }
+        together();
+      }
     }
+    together();
     const float M = __fadd_rn(f.xw, __fmul_rn(alpha, __fadd_rn(pr, f.rsw)));
     hard = hard || M == -INFINITY;
-    // ---- the best arc of every frame: the arcs of all frames shared out over the lanes ----------------------------------
-    // (One loop of little code: the same with the arcs of a frame on the lanes, eight frames unrolled, spent its time on
-    // fetching instructions that no wave had run before.)
-    const int arcs = mine && !kept && !hard ? total : 0;
-    const int end = prefix_sum(arcs);
-    const int start = end - arcs, pairs = lane_i(end, 63);
-    L.meta[lane] = WalkMeta{start, c0, c1, c2, o0, o1, o2, o3, p1, p2, p3, f.w};
-    L.best[lane] = 0;
-    L.flag[lane] = 0;
-    together();
-#pragma unroll 1
-    for (int base = 0; base < pairs; base += kWalkPairs) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) L.owner[64 * k + lane] = 0;
-      together();
-      if (arcs > 0 && end > base && start < base + kWalkPairs) L.owner[max(start - base, 0)] = lane + 1;
-      together();
-      int fr[4], lo[4], len[4], at[4], fw[4];
-      float p[4], xa[4];
-      v2i a[4];
-      int before = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) fr[k] = L.owner[64 * k + lane];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        fr[k] = max(before, prefix_max(fr[k]));
-        before = lane_i(fr[k], 63);
-        fr[k] -= 1;
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const WalkMeta m = L.meta[fr[k]];
-        const int j = min(base + 64 * k + lane, pairs - 1) - m.start;
-        int off = m.o0, first = 0, end_j = m.c0;
-        p[k] = 0.0f;
-        if (j >= m.c0) { off = m.o1; first = m.c0; end_j = m.c1; p[k] = m.p1; }
-        if (j >= m.c1) { off = m.o2; first = m.c1; end_j = m.c2; p[k] = m.p2; }
-        if (j >= m.c2) { off = m.o3; first = m.c2; end_j = m.c2; p[k] = m.p3; }  // (its end is not at hand)
-        lo[k] = off + first;
-        len[k] = end_j - first;
-        at[k] = j + off;
-        fw[k] = m.w;
-        a[k] = arc[at[k]];
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) xa[k] = hyp[static_cast<int64_t>(fr[k]) * frame_stride + a[k].x];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (base + 64 * k + lane < pairs) {
-          const float v = __fadd_rn(xa[k], __fmul_rn(alpha, __fadd_rn(p[k], __int_as_float(a[k].y))));
-          const unsigned key = ukey(v);
-          const u64 old = atomicMax(&L.best[fr[k]], (static_cast<u64>(key) << 32) | ~static_cast<unsigned>(at[k]));
-          const unsigned old_key = static_cast<unsigned>(old >> 32);
-          const int old_at = static_cast<int>(~static_cast<unsigned>(old));
-          // (two of a level: the lower arc is the lower token; the same token on two levels: see below; zeros of both
-          // signs are equal values with different keys)
-          bool tie = ukey_val(old_key) == v;
-          if (tie && old_key == key) tie = !in_level(old_at - lo[k], 0, len[k]) && arc[old_at].x != a[k].x;
-          const unsigned say = (a[k].x == fw[k] ? 1u : 0u) | (tie ? 2u : 0u);
-          if (say != 0) atomicOr(&L.flag[fr[k]], say);
-        }
-      }
-      together();
-    }
-    float am = -INFINITY;
-    int at = INT_MAX, ac = -1;
     const unsigned flag = L.flag[lane];
+    const u64 key = L.best[lane];
+    const unsigned low = ~static_cast<unsigned>(key);
     const bool overridden = (flag & 1u) != 0;
-    if (arcs > 0) {
-      const u64 key = L.best[lane];
-      ac = static_cast<int>(~static_cast<unsigned>(key));
-      am = ukey_val(static_cast<unsigned>(key >> 32));
-      at = arc[ac].x;
-      // A token belongs to the deepest state that has it: where a deeper state's arcs hold the winner's token, it stands
-      // if it has the same value there (after a whole phrase the backoff is 0), and leads where that arc leads.  (A
-      // shadowed arc that does not win changes nothing.)
-      const int level = in_level(ac - o0, 0, c0) ? 0 : in_level(ac - o1, c0, c1) ? 1 : in_level(ac - o2, c1, c2) ? 2 : 3;
-      hard = hard || (flag & 2u) != 0;
-      int x = f.s;
-#pragma unroll 1
-      for (int l = 0; l < level; ++l) {
-        const int next = child(x, at);
-        if (next > 0) {
-          const float p = l == 0 ? 0.0f : l == 1 ? p1 : p2, v = hyp[static_cast<int64_t>(lane) * frame_stride + at];
-          ac = next - 1;
-          hard = hard || __fadd_rn(v, __fmul_rn(alpha, __fadd_rn(p, __int_as_float(arc[ac].y)))) != am;
-          break;
-        }
-        x = l == 0 ? s1 : s2;
-      }
-      ac += 1;
-    }
+    float am = key != 0 ? ukey_val(static_cast<unsigned>(key >> 32)) : -INFINITY;
+    int at = key != 0 ? static_cast<int>(low >> kLevelBits) : INT_MAX;
+    bool by_arc = key != 0;
+    // (the order tells -0.0 from 0.0, which are equal values: the lower token may be the other one's)
+    hard = hard || ((flag & 2u) != 0 && am == 0.0f);
     // ---- the frames' decisions, one per lane ----------------------------------------------------------------------------
     auto special = [&](int token, float fv) {
       const bool take = fv > am || (fv == am && token < at);
       am = take ? fv : am;
       at = take ? token : at;
-      ac = take ? -1 : ac;
+      by_arc = by_arc && !take;
     };
     if (SEL == 0 && t.blank >= 0) special(t.blank, __fadd_rn(f.x0, __fmul_rn(alpha, 0.0f)));
     if (t.eos >= 0) special(t.eos, __fadd_rn(f.xe, __fmul_rn(alpha, eb)));
@@ -522,6 +509,22 @@ struct Walker {
     // are higher ones)
     const bool take = at != INT_MAX && (am > M || (am == M && at <= f.w));
     hard = hard || (overridden && !take);  // the base winner is shadowed by an arc that does not beat it
+    // A token belongs to the deepest state that has it.  Where that is another one than the winning arc's, its value there
+    // is a lower one (of equal ones the deepest is taken), and another token may win.  (A shadowed arc that does not win
+    // changes nothing.)
+    int next = f.target;
+    by_arc = by_arc && take;
+    if (mine && !kept && !hard && by_arc) {
+      const int level = static_cast<int>(low) & kLastLevel;
+      int l = 0, c = f.s;
+#pragma unroll 1
+      for (;; ++l) {
+        next = child(c, at);
+        if (next > 0 || c == 0) break;  // (some state of the chain has it)
+        c = states[2 * static_cast<size_t>(c)].z;
+      }
+      hard = l != level || level == kLastLevel;
+    }
     const int dtok = take ? at : f.w;
     const bool barred = SEL == 2 && !hard && dtok == f.label;  // the rule bars the previous label
     if (mine) {
@@ -529,8 +532,8 @@ struct Walker {
       f.hard = kept ? 0 : hard ? 1 : barred ? 2 : 0;  // (what follows is only likely then)
       f.tok = kept ? f.v0 : dtok;
       f.val = kept ? f.x0 : take ? am : M;
-      f.moves = !kept && (!take || ac >= 0);
-      f.next = !f.moves ? f.s : take ? ac : f.target;
+      f.moves = !kept && (!take || by_arc);
+      f.next = f.moves ? next : f.s;
       if (f.moves) f.moving = dtok;
     }
   }
@@ -610,7 +613,6 @@ struct Walker {
     return WalkBest{lane_f(o.val, from), tok, lane_i(o.child, from)};
   }
 
-  __device__ __forceinline__ static bool in_level(int j, int from, int to) { return j >= from && j < to; }
   template <int CTRL, int ROWS>
   __device__ __forceinline__ static int from_lane(int v) {  // 0 where there is no such lane
     return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
@@ -852,7 +854,7 @@ static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
   return t.p_root != nullptr && t.root_rec != nullptr && t.num_states <= kMaxTableStates && rows_pay(t.vocab_size, T, B, sel) &&
-         walk_lds_bytes(t.vocab_size, 1) <= static_cast<size_t>(g_walk_max_lds);
+         t.vocab_size <= kMaxWalkV && walk_lds_bytes(t.vocab_size, 1) <= static_cast<size_t>(g_walk_max_lds);
 }
 
 int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,

@@ -98,3 +98,28 @@ def test_zeros_of_both_signs(V):
     for alpha in (0.0, -0.0):                            # (times a negative score, or a positive one: -0.0)
         _compare(tr, ot, x, s0, rng.integers(-1, V, B).astype(np.int32), alpha, (V, alpha))
     pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("V", [300, 1025, 2500])
+def test_chains_longer_than_a_turn_and_than_the_levels_counted(V):
+    """Runs of one token: failure chains of up to 2100 states, the winning arc in any of them, also where an arc's order has
+    counted its last level (2047)."""
+    rng = np.random.default_rng(94000 + V)
+    n, a = 2100, 3
+    depths = [1, 2, 5, 50, 52, 53, 54, 55, 1000, 2095, 2096, 2097, 2099]
+    phrases = [[a] * n] + [[a] * k + [20 + i] for i, k in enumerate(depths)]
+    offs = np.cumsum([0] + [len(p) for p in phrases]).astype(np.int64)
+    toks = np.concatenate([np.asarray(p, dtype=np.int32) for p in phrases])
+    weights = np.full(len(phrases), 0.001, dtype=np.float32)
+    ot = OracleTree(toks, offs, V, V - 1, weights=weights)
+    tr = pb.pb_build(toks, offs, V, V - 1, weights=weights, device=0)
+    T, B = 12, len(depths)
+    x = np.round(rng.standard_normal((T, B, V)).astype(np.float32) * 4) / 4
+    for i in range(B):
+        x[int(rng.integers(0, 3)), i, 20 + i] += 12.0
+        x[6:, i, a] += 12.0
+    deepest = int(np.argmax(pb.pb_host_arrays(tr)["depth"]))
+    s0 = np.full(B, deepest, dtype=np.int32)
+    s0[::3] -= rng.integers(0, 40, len(s0[::3])).astype(np.int32)
+    _compare(tr, ot, x, s0, rng.integers(-1, V, B).astype(np.int32), 0.5, (V,))
+    pb.pb_free(tr)
