@@ -270,17 +270,16 @@ struct WalkLds {  // of a wave
   unsigned flag[64];   // 1: an arc overrides the base winner, 2: an arc of value -0.0
   int owner[kWalkPairs];
 };
-struct WalkJob {  // a frame that needs a pass over its row
-  int s, frame, excl, label;
-  float x_blank, x_eos;
+struct WalkJob {  // a frame of the block that needs a pass over its row, from state s, token excl barred (-1: none)
+  int s, frame, excl;
 };
-constexpr int kWalkJobs = 64;  // taken at a time
+constexpr int kWalkJobs = 64;  // listed at a time
 struct WalkBest {  // of a wave's share of such a row
   float val;
   int tok, child;
 };
 struct WalkShared {  // of the workgroup
-  int jobs;  // wanted
+  int hard[16];  // frames of every wave that need a pass over their row
   WalkJob job[kWalkJobs];
   WalkBest part[16];
   int end[16], end_label[16];  // state and label every wave's frames end in
@@ -294,7 +293,7 @@ struct WalkFrame {
   int s, label;                // start
   int tok, next, moving;       // outcome: token, state after it; the token the frame emits when it moves the state
   bool moves, decided;         // the token moves the state; the outcome is the rule's (else: assumed)
-  int hard;                    // the outcome waits for a pass over the row: 1, or 2: the label is known to be barred there
+  bool hard;                   // the outcome waits for a pass over the row (it is only likely until then)
   float val;
 };
 
@@ -373,7 +372,7 @@ struct Walker {
         f.s = s;
         f.label = label;
         f.decided = false;
-        f.hard = 0;
+        f.hard = false;
         if (SEL != 0) {
           f.moves = f.v0 != t.blank && (SEL != 2 || f.v0 != label);
           f.tok = f.moves ? f.moving : f.v0;
@@ -529,7 +528,7 @@ struct Walker {
     const bool barred = SEL == 2 && !hard && dtok == f.label;  // the rule bars the previous label
     if (mine) {
       f.decided = true;
-      f.hard = kept ? 0 : hard ? 1 : barred ? 2 : 0;  // (what follows is only likely then)
+      f.hard = !kept && (hard || barred);
       f.tok = kept ? f.v0 : dtok;
       f.val = kept ? f.x0 : take ? am : M;
       f.moves = !kept && (!take || by_arc);
@@ -538,11 +537,11 @@ struct Walker {
     }
   }
 
-  // One frame from state q.s by a pass over its row, any case, by all waves of the workgroup: tokens that a chain state has
-  // an arc on are marked, deepest state first (wave 0), the others follow with their base boosts.  q.excl: a token barred
-  // from the selection, or -1.  The outcome comes back in every thread.
-  __device__ __forceinline__ WalkBest row_pass(const WalkJob& q, const float* row, WalkShared& W, unsigned* tags, int wave,
-                                               int nwaves) const {
+  // A frame from state q.s by a pass over its row, any case, a share of it: part of `parts` waves.  Tokens that a chain
+  // state has an arc on are marked, deepest state first, by wave 0 of them, the others follow with their base boosts.
+  // Every wave of the workgroup gets here as often, with or without a row: several waves meet at barriers.
+  __device__ __forceinline__ WalkBest row_pass(const WalkJob& q, const float* row, unsigned* tags, bool active, int part,
+                                               int parts) const {
     WalkBest o{-INFINITY, INT_MAX, -1};
     auto offer = [&](int tk, float v, int next) {
       const bool take = v > o.val || (v == o.val && tk < o.tok);
@@ -550,9 +549,16 @@ struct Walker {
       o.tok = take ? tk : o.tok;
       o.child = take ? next : o.child;
     };
-    for (int i = 64 * wave + lane; i < (t.V + 31) / 32; i += 64 * nwaves) tags[i] = 0u;
-    __syncthreads();
-    if (wave == 0) {
+    auto meet = [&]() {
+      if (parts > 1)
+        __syncthreads();
+      else
+        together();
+    };
+    if (active)
+      for (int i = 64 * part + lane; i < (t.V + 31) / 32; i += 64 * parts) tags[i] = 0u;
+    meet();
+    if (active && part == 0) {
       float p = 0.0f;
 #pragma unroll 1
       for (int x = q.s; x != 0;) {
@@ -571,36 +577,33 @@ struct Walker {
         together();
       }
       // the blank (single-stage rule: boost 0, state kept) and the EOS token (boost tabulated per state, state kept)
-      if (SEL == 0 && t.blank >= 0 && lane == 0) offer(t.blank, __fadd_rn(q.x_blank, __fmul_rn(alpha, 0.0f)), -1);
+      if (SEL == 0 && t.blank >= 0 && lane == 0) offer(t.blank, __fadd_rn(row[t.blank], __fmul_rn(alpha, 0.0f)), -1);
       if (t.eos >= 0 && lane == 0 && (SEL != 2 || t.eos != q.excl))
-        offer(t.eos, __fadd_rn(q.x_eos, __fmul_rn(alpha, t.eos_score[q.s])), -1);
+        offer(t.eos, __fadd_rn(row[t.eos], __fmul_rn(alpha, t.eos_score[q.s])), -1);
     }
-    __syncthreads();
-    const float pr = t.p_root[q.s];
-    constexpr int kAhead = 4;
+    meet();
+    if (active) {
+      const float pr = t.p_root[q.s];
+      constexpr int kAhead = 4;
 #pragma unroll 1
-    for (int v0 = 64 * kAhead * wave; v0 < t.V; v0 += 64 * kAhead * nwaves) {
-      float x[kAhead], rs[kAhead];
+      for (int v0 = 64 * kAhead * part; v0 < t.V; v0 += 64 * kAhead * parts) {
+        float x[kAhead], rs[kAhead];
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) {
-        const int v = min(v0 + 64 * i + lane, t.V - 1);
-        x[i] = row[v];
-        rs[i] = root_score[v];
-      }
+        for (int i = 0; i < kAhead; ++i) {
+          const int v = min(v0 + 64 * i + lane, t.V - 1);
+          x[i] = row[v];
+          rs[i] = root_score[v];
+        }
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) {
-        const int v = v0 + 64 * i + lane;
-        const bool in = v < t.V && v != t.blank && v != t.eos && (SEL != 2 || v != q.excl) && !tag_test(tags, min(v, t.V - 1));
-        if (in) offer(v, __fadd_rn(x[i], __fmul_rn(alpha, __fadd_rn(pr, rs[i]))), -1);
+        for (int i = 0; i < kAhead; ++i) {
+          const int v = v0 + 64 * i + lane;
+          const bool in = v < t.V && v != t.blank && v != t.eos && (SEL != 2 || v != q.excl) && !tag_test(tags, min(v, t.V - 1));
+          if (in) offer(v, __fadd_rn(x[i], __fmul_rn(alpha, __fadd_rn(pr, rs[i]))), -1);
+        }
+        together();
       }
-      together();
+      o = best_of(o);
     }
-    o = best_of(o);
-    if (lane == 0) W.part[wave] = o;
-    __syncthreads();
-    o = lane < nwaves ? W.part[lane] : WalkBest{-INFINITY, INT_MAX, -1};
-    o = best_of(o);
-    if (o.tok == INT_MAX) o = WalkBest{0.0f, 0, -1};  // (a row of NaN, a precondition violation: stay in range)
     return o;
   }
   // The best of the lanes' candidates (tok == INT_MAX: none), in every lane.
@@ -652,7 +655,7 @@ template <int SEL>
 __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick, const float* __restrict__ logp,
                                                     int64_t frame_stride, int64_t row_stride,
                                                     const int32_t* __restrict__ states0,
-                                                    const int32_t* __restrict__ last0, float alpha, int T, int B,
+                                                    const int32_t* __restrict__ last0, float alpha, int T, int B, int side,
                                                     int32_t* tokens, int32_t* states, float* __restrict__ scores) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
@@ -681,7 +684,8 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
   }
   WalkLds* shared = reinterpret_cast<WalkLds*>(lds);
   WalkShared& W = *reinterpret_cast<WalkShared*>(shared + nwaves);
-  unsigned* tags = reinterpret_cast<unsigned*>(&W + 1);  // a bit per token
+  const int tag_words = (t.V + 31) / 32;
+  unsigned* tags = reinterpret_cast<unsigned*>(&W + 1);  // a bit per token, for each of `side` rows
   for (int F0 = 0; F0 < T; F0 += 64 * nwaves) {
     // A wave's frames f0 .. f1 - 1 are its last lanes; those before hold the frames before, from which the state that
     // its own start in is found.
@@ -742,9 +746,11 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
         end = from;
         end_label = from_label;
       }
+      const u64 hard = __ballot(lane >= lo && lane < hi && f.hard);
       if (lane == 0) {
         W.end[wave] = end;
         W.end_label[wave] = end_label;
+        W.hard[wave] = __builtin_popcountll(hard);
       }
       __syncthreads();
       bool changed = false;
@@ -754,44 +760,45 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
         from = have;
         from_label = have_label;
       }
-      const int hard = lane >= lo && lane < hi ? f.hard : 0;
+      const int upto = Walker<SEL>::prefix_sum(lane < nwaves ? W.hard[lane] : 0);
+      const int total = Walker<SEL>::lane_i(upto, 63), own = wave > 0 ? Walker<SEL>::lane_i(upto, wave - 1) : 0;
       if (__syncthreads_or(changed)) continue;  // (wave k starts where it should after k rounds at the latest)
-      if (!__syncthreads_or(hard != 0)) break;  // (frames that need their row wait until the starts agree)
-      // ---- what the winners do not settle: a pass over the row, all waves together ---------------------------------------
-      if (threadIdx.x == 0) W.jobs = 0;
+      if (total == 0) break;  // (frames that need their row wait until the starts agree)
+      // ---- what the winners do not settle: passes over the rows, in the order of the frames, several side by side -------
+      // (The label is barred from the start: where it would not win, barring it changes nothing.)
+      const int at = own + __builtin_popcountll(hard & ((1ull << lane) - 1));
+      const bool listed = ((hard >> lane) & 1) && at < kWalkJobs;
+      if (listed) W.job[at] = WalkJob{f.s, fr, SEL == 2 ? f.label : -1};
       __syncthreads();
-      if (hard != 0) {
-        const int at = atomicAdd(&W.jobs, 1);
-        // (CTC: first without the exclusion -- the label may not even win -- then, if it does win, without the label)
-        if (at < kWalkJobs) W.job[at] = WalkJob{f.s, base + lane, hard == 2 ? f.label : -1, f.label, f.x0, f.xe};
-      }
-      __syncthreads();
-      const int jobs = min(uniform_i(W.jobs), kWalkJobs);
+      const int jobs = min(total, kWalkJobs);
 #pragma unroll 1
-      for (int i = 0; i < jobs; ++i) {
-        WalkJob q = W.job[i];
+      for (int i = 0; i < jobs; i += side) {
+        const int n = min(jobs - i, side), parts = nwaves / n, which = wave / parts;
+        WalkJob q = W.job[i + min(which, n - 1)];
         q.s = uniform_i(q.s);
         q.frame = uniform_i(q.frame);
         q.excl = uniform_i(q.excl);
-        q.label = uniform_i(q.label);
-        const float* row = walk.hyp + static_cast<int64_t>(q.frame - base) * frame_stride;
-        WalkBest o = walk.row_pass(q, row, W, tags, wave, nwaves);
-        if (SEL == 2 && q.excl < 0 && o.tok == q.label) {
-          __syncthreads();
-          q.excl = q.label;
-          o = walk.row_pass(q, row, W, tags, wave, nwaves);
-        }
-        const bool stays = o.child < 0 && (o.tok == t.blank || o.tok == t.eos);
-        const int next = o.child >= 0 ? o.child : stays ? q.s : uniform_i(t.root_next[o.tok]);
-        if (lane >= lo && q.frame == fr) {
-          f.hard = 0;
-          f.tok = o.tok;
-          f.val = o.val;
+        const WalkBest o = walk.row_pass(q, walk.hyp + static_cast<int64_t>(q.frame - base) * frame_stride,
+                                         tags + min(which, n - 1) * tag_words, which < n, wave - which * parts, parts);
+        if (lane == 0) W.part[wave] = o;
+        __syncthreads();
+        if (listed && at >= i && at < i + n) {
+          WalkBest best = W.part[(at - i) * parts];
+#pragma unroll 1
+          for (int k = 1; k < parts; ++k) {
+            const WalkBest p = W.part[(at - i) * parts + k];
+            if (p.tok != INT_MAX && (best.tok == INT_MAX || p.val > best.val || (p.val == best.val && p.tok < best.tok))) best = p;
+          }
+          if (best.tok == INT_MAX) best = WalkBest{0.0f, 0, -1};  // (a row of NaN, a precondition violation: stay in range)
+          const bool stays = best.child < 0 && (best.tok == t.blank || best.tok == t.eos);
+          f.hard = false;
+          f.tok = best.tok;
+          f.val = best.val;
           f.moves = !stays;
-          f.next = next;
-          if (!stays) f.moving = o.tok;
+          f.next = best.child >= 0 ? best.child : stays ? f.s : walk.root_next[best.tok];
+          if (!stays) f.moving = best.tok;
         }
-        __syncthreads();  // (the next one's marks and parts take the place of these)
+        __syncthreads();  // (the next ones' marks and parts take the place of these)
       }
     }
     s = uniform_i(W.end[nwaves - 1]);
@@ -807,8 +814,8 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
 
 int g_walk_max_lds = 63 * 1024;  // dynamic LDS the device allows the walk kernel, set once
 
-size_t walk_lds_bytes(int V, int waves) {
-  return static_cast<size_t>(waves) * sizeof(WalkLds) + sizeof(WalkShared) + sizeof(unsigned) * ((static_cast<size_t>(V) + 31) / 32);
+size_t walk_lds_bytes(int V, int waves, int side) {
+  return static_cast<size_t>(waves) * sizeof(WalkLds) + sizeof(WalkShared) + side * sizeof(unsigned) * ((static_cast<size_t>(V) + 31) / 32);
 }
 
 }  // namespace
@@ -854,7 +861,7 @@ static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
   return t.p_root != nullptr && t.root_rec != nullptr && t.num_states <= kMaxTableStates && rows_pay(t.vocab_size, T, B, sel) &&
-         t.vocab_size <= kMaxWalkV && walk_lds_bytes(t.vocab_size, 1) <= static_cast<size_t>(g_walk_max_lds);
+         t.vocab_size <= kMaxWalkV && walk_lds_bytes(t.vocab_size, 1, 1) <= static_cast<size_t>(g_walk_max_lds);
 }
 
 int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,
@@ -904,11 +911,18 @@ int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d
   // A wave takes 16 frames or more (those that it looks back over are read once more: 40 frames x 1 with 16 / 4 waves 13.0 /
   // 11.3 us, 60 x 48 21.9 / 18.2, V = 1025), at most 64 (1000 x 16 with 16 / 8 waves 42 / 56 us).
   int waves = T >= 256 ? 16 : (T + 15) / 16;
-  while (waves > 1 && walk_lds_bytes(V, waves) > static_cast<size_t>(g_walk_max_lds)) --waves;
-  const size_t lds = walk_lds_bytes(V, waves);
+  const size_t room = static_cast<size_t>(g_walk_max_lds);
+  while (waves > 1 && walk_lds_bytes(V, waves, 1) > room) --waves;
+  // Rows that are passed over side by side: a wave each up to 4096 tokens, more waves to wider ones (V = 4096, 250 x 8,
+  // log-probs of bf16 logits: one wave a row 45.9 us, four 48.2, all waves to one row after the other 49.8; V = 32001,
+  // 100 x 16, CTC rule, where 7 waves take one row: 96 us and 100 with a wave each).
+  int side = static_cast<int>(static_cast<int64_t>(waves) * 4096 / V);
+  side = side < 1 ? 1 : side > waves ? waves : side;
+  while (side > 1 && walk_lds_bytes(V, waves, side) > room) --side;
+  const size_t lds = walk_lds_bytes(V, waves, side);
 #define PB_WALK(SEL)                                                                                                     \
   hipLaunchKernelGGL(walk_kernel<SEL>, dim3(static_cast<unsigned>(B)), dim3(64 * waves), lds, stream, t, pick, d_logp,   \
-                     frame_stride, row_stride, d_states0, d_last0, alpha, T, B, d_tokens, d_states, d_scores)
+                     frame_stride, row_stride, d_states0, d_last0, alpha, T, B, side, d_tokens, d_states, d_scores)
   if (sel == 0) {
     PB_WALK(0);
   } else if (sel == 1) {
