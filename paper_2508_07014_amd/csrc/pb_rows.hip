@@ -273,6 +273,7 @@ struct WalkLds {  // of a wave
 struct WalkJob {  // a frame of the block that needs a pass over its row, from state s, token excl barred (-1: none)
   int s, frame, excl;
 };
+constexpr int kWalkFollow = 6;  // frames of a wave that do not fit: up to this many are decided one after the other
 constexpr int kWalkJobs = 64;  // listed at a time
 struct WalkBest {  // of a wave's share of such a row
   float val;
@@ -310,6 +311,7 @@ struct Walker {
   const v4i PB_AS1* slots;   // ArcSlot
   unsigned slot_mask;
   const int PB_AS1* root_next;
+  const RootRec* root_rec;
   const float PB_AS1 *p_root, *eos_score, *root_score;
   const float* hyp;  // logp of the frame of lane 0
   int64_t frame_stride;
@@ -349,23 +351,34 @@ struct Walker {
     return target;
   }
 
+  // The state and label that the outcomes before a lane's frame lead to.  Frames lo .. hi - 1; the first starts from (from,
+  // from_label).
+  __device__ __forceinline__ void start_of(const WalkFrame& f, int lo, int hi, int from, int from_label, int& s, int& label) const {
+    const u64 before = __ballot(f.moves && lane >= lo && lane < hi) & ((1ull << lane) - 1);
+    const int got = __shfl(f.next, before ? 63 - __builtin_clzll(before) : 0);
+    s = before ? got : from;
+    label = -1;
+    if (SEL == 2) {
+      label = __shfl_up(f.tok, 1);
+      label = lane == lo ? from_label : label;
+    }
+  }
+  // The frames that were not decided from there, and where they start.
+  __device__ __forceinline__ u64 misfits(const WalkFrame& f, int lo, int hi, int from, int from_label, int& s, int& label) const {
+    start_of(f, lo, hi, from, from_label, s, label);
+    return __ballot(lane >= lo && lane < hi && (!f.decided || s != f.s || (SEL == 2 && label != f.label)));
+  }
+
   // Carries the outcomes of the frames to the starts of those behind them until nothing changes.  A frame whose start
   // has changed is undecided again and taken to emit what it did.  (At most 64 turns; a phrase takes as many as it has
   // tokens, side by side with all others.)  Frames lo .. hi - 1; the first starts from (from, from_label).
   __device__ __forceinline__ void settle_starts(WalkFrame& f, int lo, int hi, int from, int from_label) const {
-    const u64 lower = (1ull << lane) - 1;
     const bool mine = lane >= lo && lane < hi;
     bool any;
 #pragma unroll 1
     do {
-      const u64 before = __ballot(f.moves && mine) & lower;
-      const int got = __shfl(f.next, before ? 63 - __builtin_clzll(before) : 0);
-      const int s = before ? got : from;
-      int label = -1;
-      if (SEL == 2) {
-        label = __shfl_up(f.tok, 1);
-        label = lane == lo ? from_label : label;
-      }
+      int s, label;
+      start_of(f, lo, hi, from, from_label, s, label);
       const bool changed = mine && (s != f.s || (SEL == 2 && label != f.label));
       any = __ballot(changed) != 0;
       if (changed) {
@@ -537,6 +550,142 @@ struct Walker {
     }
   }
 
+  // Decides frames one after the other, the arcs of one on the lanes: the first of `wrong` (see misfits, `starts` and
+  // `labels` are what it says) and those behind it until one was already decided from where this leads, then the next of
+  // those that still do not fit.  Two dependent accesses a frame, about 1 us, where carrying the starts on and deciding
+  // them side by side takes about ten, however few they are: this is for the few.  Returns the frame that it stops at
+  // because its arcs are too many, a bit, or 0.
+  __device__ __forceinline__ u64 follow(WalkFrame& f, u64 wrong, int starts, int labels, int lo, int hi, int from,
+                                        int from_label) const {
+    // (the records of where the winners lead from the root)
+    const v4i *rec0 = reinterpret_cast<const v4i*>(root_rec + f.w);
+    const v4i ra = ((const v4i PB_AS1*)rec0)[0], rb = ((const v4i PB_AS1*)rec0)[1];
+    int l = first_lane(wrong);
+    int s = lane_i(starts, l), label = lane_i(labels, l);
+    Cursor cur = cursor_at(t, s);
+#pragma unroll 1
+    for (;;) {
+      const int w = lane_i(f.w, l), v0 = lane_i(f.v0, l), target = lane_i(f.target, l);
+      const float x0 = lane_f(f.x0, l);
+      const bool kept = SEL != 0 && (v0 == t.blank || (SEL == 2 && v0 == label));
+      int tok = v0, next = s, from_arc = -1;
+      bool moves = false, hard = false, by_root = false;
+      float val = x0;
+      v4i k0 = {0, 0, 0, 0}, k1 = k0;  // the record of the state that this lane's arc leads to
+      float kp = 0.0f, ke = 0.0f;
+      if (!kept) {
+        const float M = __fadd_rn(lane_f(f.xw, l), __fmul_rn(alpha, __fadd_rn(cur.p_root, lane_f(f.rsw, l))));
+        hard = lane_i(f.marked ? 1 : 0, l) != 0 || M == -INFINITY;
+        float am = -INFINITY;
+        int at = INT_MAX;
+        bool overridden = false, by_arc = false;
+        if (!hard && s != 0) {
+          // ---- four levels of the chain, deepest state first ----------------------------------------------------------
+          const Rec none{0, 0, 0, 0.0f};
+          const Rec r1 = cur.rec.fail != 0 ? cur.rec1 : none;
+          Rec2 r{none, none};
+          if (r1.fail != 0) r = load_rec2(t, r1.fail);
+          if (r.a.fail == 0) r.b = none;
+          const int c0 = cur.rec.count, c1 = c0 + r1.count, c2 = c1 + r.a.count, total = c2 + r.b.count;
+          if (total > 64 || r.b.fail != 0) {
+            if (lane == l) {
+              f.s = s;
+              f.label = label;
+              f.decided = false;
+            }
+            return 1ull << l;
+          }
+          const float p1 = __fadd_rn(0.0f, cur.rec.backoff), p2 = __fadd_rn(p1, r1.backoff), p3 = __fadd_rn(p2, r.a.backoff);
+          const bool valid = lane < total;
+          const int lv = (lane >= c0 ? 1 : 0) + (lane >= c1 ? 1 : 0) + (lane >= c2 ? 1 : 0);
+          int mine = INT_MAX, a_tok = -1;
+          float v = -INFINITY;
+          if (valid) {
+            const int i = lv == 0 ? cur.rec.begin + lane : lv == 1 ? r1.begin + lane - c0 : lv == 2 ? r.a.begin + lane - c1 : r.b.begin + lane - c2;
+            const float p = lv == 0 ? 0.0f : lv == 1 ? p1 : lv == 2 ? p2 : p3;
+            const v2i a = arc[i];
+            const float xa = hyp[static_cast<int64_t>(l) * frame_stride + a.x];
+            k0 = states[2 * static_cast<size_t>(i + 1)];
+            k1 = states[2 * static_cast<size_t>(i + 1) + 1];
+            kp = p_root[i + 1];
+            if (t.eos >= 0) ke = eos_score[i + 1];
+            a_tok = a.x;
+            v = __fadd_rn(xa, __fmul_rn(alpha, __fadd_rn(p, __int_as_float(a.y))));
+            mine = i + 1;
+          }
+          together();
+          // the largest value, the lowest token of that, its deepest state
+          const float top = ukey_val(wave_max_u(valid ? ukey(v) : 0u));
+          const bool best = valid && v == top;
+          const int low = wave_min_nn(best ? a_tok << 2 | lv : INT_MAX);
+          const u64 who = __ballot(best && (a_tok << 2 | lv) == low);
+          overridden = __ballot(valid && a_tok == w) != 0;
+          if (who != 0) {
+            from_arc = first_lane(who);
+            am = lane_f(v, from_arc);
+            at = low >> 2;
+            by_arc = true;
+            next = lane_i(mine, from_arc);
+            // (a deeper state has the token too, with a lower value: another token may win)
+            hard = __ballot(valid && a_tok == at && lv < (low & 3)) != 0;
+          }
+        }
+        auto special = [&](int token, float fv) {
+          if (fv > am || (fv == am && token < at)) {
+            am = fv;
+            at = token;
+            by_arc = false;
+          }
+        };
+        if (SEL == 0 && t.blank >= 0) special(t.blank, __fadd_rn(x0, __fmul_rn(alpha, 0.0f)));
+        if (t.eos >= 0) special(t.eos, __fadd_rn(lane_f(f.xe, l), __fmul_rn(alpha, cur.eos_boost)));
+        const bool take = at != INT_MAX && (am > M || (am == M && at <= w));
+        by_arc = by_arc && take;
+        by_root = !take;
+        hard = hard || (overridden && !take);
+        tok = take ? at : w;
+        hard = hard || (SEL == 2 && tok == label);
+        val = take ? am : M;
+        moves = by_root || by_arc;
+        next = by_arc ? next : by_root ? target : s;
+        if (!by_arc) from_arc = -1;
+      }
+      if (lane == l) {
+        f.s = s;
+        f.label = label;
+        f.decided = true;
+        f.hard = hard;
+        f.tok = tok;
+        f.val = val;
+        f.moves = moves;
+        f.next = next;
+        if (moves) f.moving = tok;
+      }
+      together();
+      // ---- on to the next frame ----------------------------------------------------------------------------------------
+      s = next;
+      label = tok;
+      if (++l >= hi) return 0;
+      const bool fits = lane_i(f.decided ? 1 : 0, l) != 0 && lane_i(f.s, l) == s && (SEL != 2 || lane_i(f.label, l) == label);
+      if (fits) {
+        wrong = misfits(f, lo, hi, from, from_label, starts, labels);
+        if (wrong == 0) return 0;
+        l = first_lane(wrong);
+        s = lane_i(starts, l);
+        label = lane_i(labels, l);
+        cur = cursor_at(t, s);
+      } else if (from_arc >= 0) {
+        cur = Cursor{s, Rec{lane_i(k0.x, from_arc), lane_i(k0.y, from_arc), lane_i(k0.z, from_arc), __int_as_float(lane_i(k0.w, from_arc))},
+                     Rec{lane_i(k1.x, from_arc), lane_i(k1.y, from_arc), lane_i(k1.z, from_arc), __int_as_float(lane_i(k1.w, from_arc))},
+                     lane_f(kp, from_arc), lane_f(ke, from_arc)};
+      } else if (by_root) {
+        const int q = l - 1;
+        cur = Cursor{s, Rec{lane_i(ra.y, q), lane_i(ra.z, q), lane_i(ra.w, q), __int_as_float(lane_i(rb.x, q))}, Rec{0, 0, 0, 0.0f},
+                     __int_as_float(lane_i(rb.y, q)), __int_as_float(lane_i(rb.z, q))};
+      }
+    }
+  }
+
   // A frame from state q.s by a pass over its row, any case, a share of it: part of `parts` waves.  Tokens that a chain
   // state has an arc on are marked, deepest state first, by wave 0 of them, the others follow with their base boosts.
   // Every wave of the workgroup gets here as often, with or without a row: several waves meet at barriers.
@@ -695,7 +844,7 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
     const int base = first_held(f0, f1), lo = f0 - base, hi = f1 - base, fr = base + lane;
     const Walker<SEL> walk{t, (const v4i PB_AS1*)mine.state, (const v2i PB_AS1*)mine.arc,
                            (const v4i PB_AS1*)mine.state - arc_slots(mine.num_states), arc_slots(mine.num_states) - 1,
-                           (const int PB_AS1*)mine.root_next,
+                           (const int PB_AS1*)mine.root_next, mine.root_rec,
                            (const float PB_AS1*)mine.p_root, (const float PB_AS1*)mine.eos_score, (const float PB_AS1*)mine.root_score,
                            logp + static_cast<int64_t>(F0 + base) * frame_stride + static_cast<int64_t>(b) * row_stride,
                            frame_stride, alpha, shared[wave], lane};
@@ -724,21 +873,29 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
       f.moving = f.w;
       f.next = f.target;
     }
-    // First the states that the winners alone lead to, then the frames' decisions from there.
-    int first = 0, from = base == 0 ? s : 0, from_label = base == 0 ? last : -1;
-    for (bool decide = false;;) {
-      walk.settle_starts(f, first, hi, from, from_label);
-      if (!decide) {
-        decide = true;
-        if (lo > 0) {
-          from = Walker<SEL>::lane_i(f.next, lo - 1);
-          from_label = Walker<SEL>::lane_i(f.tok, lo - 1);
+    // First the states that the winners alone lead to, then the frames' decisions from there.  What does not fit then is
+    // carried on and decided again once -- behind a surprise the winners are mostly right again -- and after that, where it
+    // is few frames, one after the other: where most frames surprise the winners (log-depth weights, alpha = 1, phrases
+    // without blanks) carrying on further was 1.6 .. 2.7 times as slow (V = 1025, 250 x 16, CTC rule 221 -> 112 us; V = 512,
+    // 250 x 8 194 -> 94), without the second turn runs inside phrases of few tokens were (V = 1024, 500 x 4 52 -> 87).
+    int from = base == 0 ? s : 0, from_label = base == 0 ? last : -1;
+    for (int carries = 0;;) {
+      int starts = 0, labels = 0;
+      const u64 wrong = carries > 0 ? walk.misfits(f, lo, hi, from, from_label, starts, labels) : ~0ull;
+      if (wrong != 0) {
+        u64 need;
+        if (carries < 2 || __builtin_popcountll(wrong) > kWalkFollow) {
+          walk.settle_starts(f, carries > 0 ? lo : 0, hi, from, from_label);
+          if (carries == 0 && lo > 0) {
+            from = Walker<SEL>::lane_i(f.next, lo - 1);
+            from_label = Walker<SEL>::lane_i(f.tok, lo - 1);
+          }
+          ++carries;
+          need = __ballot(lane >= lo && lane < hi && !f.decided);
+        } else {
+          need = walk.follow(f, wrong, starts, labels, lo, hi, from, from_label);
         }
-        first = lo;
-      }
-      const u64 need = __ballot(lane >= lo && lane < hi && !f.decided);
-      if (need != 0) {
-        walk.decide_frames(f, need);
+        if (need != 0) walk.decide_frames(f, need);
         continue;
       }
       int end = Walker<SEL>::lane_i(f.next, max(hi - 1, 0)), end_label = Walker<SEL>::lane_i(f.tok, max(hi - 1, 0));

@@ -123,3 +123,38 @@ def test_chains_longer_than_a_turn_and_than_the_levels_counted(V):
     s0[::3] -= rng.integers(0, 40, len(s0[::3])).astype(np.int32)
     _compare(tr, ot, x, s0, rng.integers(-1, V, B).astype(np.int32), 0.5, (V,))
     pb.pb_free(tr)
+
+
+@pytest.mark.parametrize("kind", ["zipf", "bushy", "deep"])
+@pytest.mark.parametrize("V,T", [(200, 130), (513, 40), (1000, 510), (1025, 130), (1281, 300), (20001, 70)])
+def test_most_frames_surprise_the_winners(V, T, kind):
+    """Log-depth weights at alpha 1 on rows without blanks: frames come out otherwise than the winners say, one after the other,
+    in states of few arcs and of hundreds, on chains of any length, with and without EOS, one tree and a table of two."""
+    rng = np.random.default_rng(95000 + V + T)
+    torch.manual_seed(V + T)
+    B = 2
+    for blank, eos, table in ((V - 1, -1, False), (-1, V - 2, False), (0, -1, True)):
+        lists = [_lists(rng, V, blank, kind) for _ in range(2 if table else 1)]
+        if eos >= 0:
+            lists = [(np.where(t == eos, 1, t).astype(np.int32), o) for t, o in lists]
+        ots = [OracleTree(t, o, V, blank, weight_mode=1, eos_id=eos, final_eos_score=0.75) for t, o in lists]
+        trs = [pb.pb_build(t, o, V, blank, device=0, weight_mode=1, eos_id=eos, final_eos_score=0.75) for t, o in lists]
+        x = seg._spoken(rng, T, B, V, lists)
+        s0 = np.array([rng.integers(0, ots[b % len(ots)].num_states) for b in range(B)], dtype=np.int32)
+        last0 = rng.integers(-1, V, B).astype(np.int32)
+        if not table:
+            _compare(trs[0], ots[0], x.cpu().numpy(), s0, last0, 1.0, (V, T, kind, blank, eos))
+        else:
+            forest = pb.pb_forest_build(trs)
+            for mode in (0, 1, 2):
+                o = _outputs(T, B)
+                print("walk forest", V, T, kind, mode, flush=True)
+                pb.pb_fuse_frames_forest(forest, x, B * V, V, dev(np.arange(B, dtype=np.int32)), dev(s0), dev(last0), 1.0, T, B, mode,
+                                         o[0], o[1], o[2], 0)
+                torch.cuda.synchronize()
+                for b in range(B):
+                    want = ots[b].fuse_frames_select(np.ascontiguousarray(x[:, b:b + 1].cpu().numpy()), s0[b:b + 1], last0[b:b + 1], 1.0, mode)
+                    _check([g[:, b:b + 1] for g in o], want, [0], (V, T, kind, mode, b))
+            pb.pb_forest_free(forest)
+        for t in trs:
+            pb.pb_free(t)
