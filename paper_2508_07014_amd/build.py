@@ -18,7 +18,7 @@ SOURCES = ["pb_narrow_1024.hip", "pb_narrow_any.hip", "pb_narrow_groups.hip", "p
 # the Python side of the entry points that are called once per step (host code only, loads beside the library)
 CALL_LIB = os.path.join(PKG, "_pbcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 CALL_SOURCES = [os.path.join(CSRC, "pb_python.cpp"), os.path.join(ROOT, "include", "pb.h")]
-HEADERS = ["pb_tree.hpp", "pb_kernels.hpp", "pb_wave.hpp", "pb_chunk.hpp", "pb_narrow.hpp", os.path.join(ROOT, "include", "pb.h")]
+HEADERS = ["pb_lines.hpp", "pb_tree.hpp", "pb_kernels.hpp", "pb_wave.hpp", "pb_chunk.hpp", "pb_narrow.hpp", os.path.join(ROOT, "include", "pb.h")]
 OBJDIR = os.path.join(PKG, "_build")
 
 FLAGS = [

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "pb_lines.hpp"
 #include "pb_tree.hpp"
 
 namespace pb {
@@ -38,8 +39,6 @@ constexpr int kTargetChains = PB_TARGET_CHAINS;  // concurrent decode chains aim
 constexpr int kMinSegLen = 8;        // shortest speculative segment, in frames
 constexpr int kMaxSegments = 64;     // segments per hypothesis (one lane each in the validation pass)
 
-constexpr int kNarrowMaxV = 1280;    // widest row that one wave holds in registers
-constexpr int kWideMaxV = 16384;     // widest row of the multi-frame wave kernels (the root scores of a row live in LDS)
 constexpr int kStepMaxV = 65536;     // widest row of the single step that one workgroup holds in registers
 #ifndef PB_WIDE_TARGET_CHAINS
 #define PB_WIDE_TARGET_CHAINS 1024
@@ -105,8 +104,6 @@ int launch_frames_wave(const DeviceTree& t, const TreePick& pick, const float* d
 // A grid counts its threads in 32 bits, and a larger one is cut without an error: the workgroups behind the cut never
 // run.  kMaxWorkgroups of any size fit; steps, beam steps and dense rows of more rows go out in slices, and the
 // multi-frame kernels, whose outputs interleave the hypotheses, check (grid_fits).
-constexpr int64_t kMaxThreads = 0xffffffffll;
-constexpr int64_t kMaxWorkgroups = kMaxThreads / 1024;
 inline bool grid_fits(int64_t groups, int64_t threads) { return groups <= kMaxThreads / threads; }
 
 // Whether the outputs of a multi-frame call lie apart from its start states, previous labels and tree ids and from each

@@ -977,47 +977,8 @@ size_t walk_lds_bytes(int V, int waves, int side) {
 
 }  // namespace
 
-// Which calls the two passes are for.  Pass 1 reads the rows at the chip's rate whatever T and B are; pass 2 has one
-// workgroup per hypothesis, so its time grows with T, and past some ten thousand rows with their number.  The segment
-// decoders read the rows once and in order, but need some thousand segments for that rate and read again what a wrong guess
-// has spoilt.  Time of the two passes over that of the segment decoder (of the two passes with the walk before this one
-// where those were already taken), random rows / spoken phrases and blanks, workspace given:
-//   T x B                    60 x 48    150 x 10   300 x 8    200 x 64   500 x 4    500 x 32   1000 x 1   1000 x 16
-//   V = 128   single-stage   1.1 / 1.2  1.2 / .87  1.4 / 1.7  1.5 / 1.1  1.4 / 1.0  1.7 / 1.1  1.1 / 1.2  1.6 / 1.4
-//             CTC            .85 / .53  .95 / .98  1.1 / .68  1.2 / .81  1.3 / .67  1.4 / .62  .96 / .81  1.4 / .96
-//   V = 257   single-stage   .99 / 1.0  1.1 / .76  1.2 / .88  1.4 / .75  1.3 / 1.0  1.5 / .93  .93 / 1.4  1.4 / .88
-//             CTC            .93 / .39  1.0 / .59  .96 / .61  1.1 / .75  1.0 / .48  1.3 / .72  .76 / .88  1.2 / .83
-//   V = 512   single-stage   1.1 / .50  .87 / .57  1.1 / .81  1.4 / .80  .99 / .81  1.2 / .95  .85 / 1.3  1.2 / .89
-//             CTC            .86 / .47  .81 / .45  .93 / .67  1.3 / .66  .77 / .55  1.3 / .63  .73 / 1.1  1.1 / .71
-//   V = 768   single-stage   .78 / .54  .71 / .53  .80 / .61  1.2 / .63  .80 / .67  1.3 / .78  .60 / .77  1.0 / .87
-//             CTC            .63 / .41  .61 / .56  .67 / .57  .98 / .56  .67 / .49  .99 / .64  .59 / .79  .88 / .64
-//   V = 1024  single-stage   .88 / .50  .77 / .73  1.0 / .67  1.2 / .65  .83 / .69  1.3 / .83  .74 / 1.2  1.3 / .99
-//             CTC            .68 / .45  .72 / .60  .83 / .52  .96 / .68  .64 / .68  1.1 / .73  .56 / 1.1  1.0 / .89
-//   T x B                    40 x 1     100 x 4    60 x 48    300 x 8    300 x 64   1000 x 1   1000 x 16  1000 x 128
-//   V = 257   single-stage   .74 / .63  .89 / .66
-//   V = 1024  single-stage   .61 / .61  .80 / .86
-//   V = 1025  single-stage   .58 / .75  .74 / .75  .65 / .57  .70 / .65  .91 / .87  .62 / .78  .95 / .93  .96 / 1.3
-//             CTC            .58 / .58  .64 / .61  .72 / .59  .61 / .54  .78 / .82  .40 / .39  .71 / .63  .70 / .84
-//   V = 2500  single-stage   .70 / .65  .75 / .73  .79 / 1.0  .65 / .74  .96 / .92  .48 / .69  1.0 / 1.0
-//             CTC            .68 / .60  .71 / .65  .79 / .69  .64 / .86  .86 / .75  .39 / .58  .89 / .81
-//   V = 8192  single-stage   .67 / .68  .68 / .78  .81 / .93  .70 / .77             .49 / .67  1.0 / .87
-//             CTC            .65 / .67  .66 / .50  .63 / .52  .70 / .61             .49 / .46  .94 / .74
-// The two-stage rule lies between the two, nearer the single-stage one, and has its lines.  These keep the columns in which
-// both kinds gain, up to a few per cent, with room for long lists outside the CTC rule, whose states have more arcs than the
-// table's lists of 2000 phrases (8539 phrases spoken, V = 1152, 248 x 29, two-stage: 55 us and 78 with the two passes).  V > 16384 (no segment decoder): 32001, 100 x 16: 3340 -> 75 us.
-static bool rows_pay(int V, int32_t T, int32_t B, int sel) {
-  const int64_t rows = static_cast<int64_t>(T) * B;
-  if (V > kWideMaxV) return rows <= kMaxWorkgroups;
-  if (V < 128 || (V <= 1024 && T > 512)) return false;
-  if (V <= 1024 && sel == 2) return rows <= (V >= 768 ? 12800 : V > 256 || T <= 160 ? 4096 : 0);
-  if (V <= 1024) return rows <= (V >= 768 ? 4096 : V > 384 && T <= 256 ? 2048 : V > 256 && T <= 128 ? 512 : 0);
-  if (T > 2048) return false;
-  if (V <= kNarrowMaxV) return rows <= (sel == 2 ? 131072 : 4096);
-  return rows <= (sel == 2 || V >= 4096 || T <= 128 ? 20480 : 8192);
-}
-
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
-  return t.p_root != nullptr && t.root_rec != nullptr && t.num_states <= kMaxTableStates && rows_pay(t.vocab_size, T, B, sel) &&
+  return t.p_root != nullptr && t.root_rec != nullptr && t.num_states <= kMaxTableStates && rows_pay(t.vocab_size, T, B, sel, t.num_states) &&
          t.vocab_size <= kMaxWalkV && walk_lds_bytes(t.vocab_size, 1, 1) <= static_cast<size_t>(g_walk_max_lds);
 }
 
@@ -1040,7 +1001,7 @@ int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d
     PB_ROWS(NS, 1);     \
   }
     if (V <= 256) {
-      PB_ROWS_SEL(4)
+      PB_ROWS(4, 1);  // (CTC rule only)
     } else if (V <= 512) {
       PB_ROWS_SEL(8)
     } else if (V <= 1024) {
