@@ -106,7 +106,7 @@ def test_forest_build_rejects_mismatched_trees():
     pb.pb_forest_free(pb.pb_forest_build([a, a]))
 
 
-@pytest.mark.parametrize("V,T,B", [(128, 50, 9), (1024, 150, 12), (2048, 20, 5), (130, 30, 7)])
+@pytest.mark.parametrize("V,T,B", [(128, 50, 9), (128, 170, 9), (1024, 150, 12), (1024, 520, 6), (2048, 20, 5), (130, 30, 7)])
 def test_forest_frames(V, T, B):
     """All frames in one call, a tree per hypothesis: wave kernels (V % 4 == 0) and the workgroup kernel."""
     ots, forest = make_forest(V)

@@ -334,7 +334,7 @@ def test_fuse_overridden_base_winner_and_shadowed_arcs(seed):
     assert_scores(gotf[2], wantf[2])
 
 
-@pytest.mark.parametrize("idx,T,B", [(2, 200, 4), (3, 260, 8), (1, 97, 3), (5, 64, 8)])
+@pytest.mark.parametrize("idx,T,B", [(2, 200, 4), (2, 530, 4), (3, 260, 8), (3, 530, 8), (1, 97, 3), (5, 64, 8)])
 def test_fuse_frames_long_phrases_across_segment_boundaries(idx, T, B):
     """Few hypotheses: many short speculative segments.  Almost every frame follows a listed phrase, so
     a segment started from the root keeps disagreeing with the true state for longer than a segment

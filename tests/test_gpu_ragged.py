@@ -1,8 +1,8 @@
 """GPU parity of the wave kernels on rows of any length and alignment: vocabularies that are no multiple of 4, rows
 that start 4, 8 or 12 bytes off a 16-byte boundary, the edges of the row shapes (a wave's 1024 and 1280 positions, whole
 and partial chunks), blank and EOS in the last tokens (behind the last whole group), exact ties and rows of -inf.  Every
-output against the CPU oracle: ids bit-exact, scores within 1e-5.  (Past 1024 tokens the multi-frame calls here are short
-enough for the two-pass decoder; test_gpu_segments has the longer ones.)"""
+output against the CPU oracle: ids bit-exact, scores within 1e-5.  (From 257 tokens on, under the CTC rule from 128, the
+multi-frame calls here are short enough for the two-pass decoder; test_gpu_segments has the longer ones.)"""
 import numpy as np
 import pytest
 

@@ -1,7 +1,8 @@
-"""GPU parity of the segment decoders past 1024 tokens, on calls well past the lines to the two-pass decoder: the 1025 .. 1280
-shape and every ring of the wide decoder, whole and ragged rows, a tree with EOS and a table of trees (one id unknown),
-padded and shifted rows, exact ties, rows of -inf, phrases spoken, negative alpha, an invalid start state, every selection
-rule.  Some hypotheses of each call against the CPU oracle: ids bit-exact, scores within 1e-5."""
+"""GPU parity of the segment decoders on calls past the lines to the two-pass decoder (sizes.SEGMENTS, which test_dispatch.py
+holds the dispatch to): every row shape of the narrow ones and every ring of the wide one, whole and ragged rows, with a
+workspace and without, a tree with EOS and a table of trees (one id unknown), padded and shifted rows, exact ties, rows of
+-inf, phrases spoken, negative alpha, an invalid start state, every selection rule; and calls on either side of every line.
+Some hypotheses of each call against the CPU oracle: ids bit-exact, scores within 1e-5."""
 import numpy as np
 import pytest
 
@@ -14,12 +15,8 @@ if not torch.cuda.is_available():
 import paper_2508_07014_amd as pb  # noqa: E402
 from gpu_helpers import DEV, dev  # noqa: E402
 from test_gpu_ragged import _check, _on_device, _tree  # noqa: E402
+from sizes import LINES, SEGMENTS  # noqa: E402
 from test_gpu_rows import _near_ties, _outputs  # noqa: E402
-
-# (T, B): past 512 frames up to 1280 tokens; more than 16384 rows, or more than V / 8 frames, past that
-SIZES = {1025: (530, 4), 1027: (530, 3), 1152: (530, 3), 1280: (530, 3), 1281: (340, 13), 2047: (340, 13), 2048: (340, 13),
-         2049: (340, 13), 2500: (340, 13), 4095: (130, 130), 4096: (130, 130), 5125: (130, 130), 9217: (130, 130),
-         16381: (130, 130), 16384: (130, 130)}
 
 
 def _spoken(rng, T, B, V, lists):
@@ -42,17 +39,17 @@ def _spoken(rng, T, B, V, lists):
     return x
 
 
+# (a row of whole vectors also at a stride and an address that are none: another shape up to 1024 tokens)
 @pytest.mark.parametrize("table", [False, True])
-@pytest.mark.parametrize("V", sorted(SIZES))
-def test_segment_decoders_past_the_dispatch_line(V, table):
+@pytest.mark.parametrize("V,whole", [(V, V % 4 == 0) for V in sorted(SEGMENTS)] + [(512, False), (1024, False), (2048, False)])
+def test_segment_decoders_past_the_dispatch_line(V, whole, table):
     rng = np.random.default_rng(81000 + 2 * V + table)
     torch.manual_seed(V)
-    T, B = SIZES[V]
+    T, B = SEGMENTS[V]
     blank = int(rng.choice([0, -1, V - 1]))
     eos = -1 if table else V - 2
     trees = [_tree(rng, V, blank, eos, i, 0.25 if i == 1 else 0.0) for i in range(3 if table else 1)]
     x = _spoken(rng, T, B, V, [(p[0], p[1]) for p in trees])
-    whole = V % 4 == 0
     stride, shift = (V + (4 if V % 1024 else 0), 0) if whole else (V + 3, 1)
     buf = torch.full((T * B * stride + shift,), float("nan"), dtype=torch.float32, device=DEV)
     buf[shift:].view(T, B, stride)[:, :, :V] = x
@@ -71,7 +68,7 @@ def test_segment_decoders_past_the_dispatch_line(V, table):
     forest = pb.pb_forest_build([p[3] for p in trees]) if table else None
     for mode in (0, 1, 2):
         o = _outputs(T, B)
-        print("segments", V, T, B, table, mode, flush=True)
+        print("segments", V, T, B, whole, table, mode, flush=True)
         if table:
             pb.pb_fuse_frames_forest(forest, ptr, B * stride, stride, dev(ids), dev(s0), dev(last0), alpha, T, B, mode, o[0],
                                      o[1], o[2], 0)
@@ -79,9 +76,16 @@ def test_segment_decoders_past_the_dispatch_line(V, table):
             pb.pb_fuse_frames_select(trees[0][3], ptr, B * stride, stride, dev(s0), dev(last0), alpha, T, B, mode, o[0], o[1],
                                      o[2], 0)
         torch.cuda.synchronize()
+        need = 0 if table else pb.pb_fuse_frames_workspace_bytes(trees[0][3], T, B)
+        if need > 0:  # (wrong guesses repaired by patches instead of in the second pass: the same bits)
+            ws, p = torch.full((need // 4,), 0x7f7f7f7f, dtype=torch.int32, device=DEV), _outputs(T, B)
+            pb.pb_fuse_frames_ws(trees[0][3], ptr, B * stride, stride, dev(s0), dev(last0), alpha, T, B, mode, p[0], p[1], p[2], ws,
+                                 need, 0)
+            torch.cuda.synchronize()
+            assert all(torch.equal(g.view(torch.int32), q.view(torch.int32)) for g, q in zip(o, p)), (V, whole, mode)
         for q, h in enumerate(look):
             want = trees[ids[h]][2].fuse_frames_select(np.ascontiguousarray(xs[:, q:q + 1]), s0[h:h + 1], last0[h:h + 1], alpha, mode)
-            _check([g[:, h:h + 1] for g in o], want, [0], (V, table, mode, h, blank, alpha))
+            _check([g[:, h:h + 1] for g in o], want, [0], (V, whole, table, mode, h, blank, alpha))
         assert bool((o[0][:, B - 1] == -1).all()) and bool((o[1][:, B - 1] == -1).all()) and bool(torch.isnan(o[2][:, B - 1]).all())
     if forest:
         pb.pb_forest_free(forest)
@@ -111,11 +115,9 @@ def test_near_ties_in_the_narrow_two_pass_decoder(V):
         pb.pb_free(tr)
 
 
-@pytest.mark.parametrize("V,T,B", [(1025, 128, 16), (1025, 128, 17), (1100, 129, 2), (1280, 256, 8), (1280, 257, 2), (1152, 512, 3),
-                                   (1152, 513, 3), (1025, 100, 660), (2000, 250, 11), (2000, 251, 11), (2000, 128, 128),
-                                   (2000, 128, 129), (2304, 144, 12), (2304, 145, 12), (4095, 300, 2), (4096, 300, 4), (4096, 513, 5)])
+@pytest.mark.parametrize("V,T,B", [c[:3] for c in LINES if c[0] * c[1] * c[2] <= 1 << 28])
 def test_both_sides_of_the_lines(V, T, B):
-    """Sizes on either side of every line between the two passes and the segment decoders, phrases spoken, every rule."""
+    """Sizes on either side of the lines between the two passes and the segment decoders, phrases spoken, every rule."""
     rng = np.random.default_rng(83000 + V + T)
     torch.manual_seed(T)
     toks, offs, ot, tr = _tree(rng, V, V - 1, -1, T % 3, 0.0)

@@ -183,7 +183,7 @@ def test_frames_select_config5_large_vocab(mode):
     assert np.array_equal(got1[0], want[0][0]) and np.array_equal(got1[1], want[1][0])
 
 
-@pytest.mark.parametrize("idx,T,B", [(2, 230, 4), (1, 97, 3), (3, 300, 6)])
+@pytest.mark.parametrize("idx,T,B", [(2, 230, 4), (2, 270, 4), (1, 97, 3), (3, 300, 6)])
 def test_frames_select_ctc_across_segment_boundaries(idx, T, B):
     """Few hypotheses: many short speculative segments, each started without a previous label; repeats
     and long planted phrases straddle the boundaries, so the re-run and the ordered repair both work on

@@ -1,6 +1,6 @@
 """GPU parity of the second pass of the two-pass multi-frame decoder (frames decided side by side from the states the winners
 lead to, then again where that was wrong) at the sizes where it can go wrong, against the CPU oracle: every row shape of the
-first pass, both sides of the packed winner word, few and many frames a wave, more frames than a block holds, states with
+first pass (up to 256 tokens the CTC rule alone takes the two passes), both sides of the packed winner word, few and many frames a wave, more frames than a block holds, states with
 more arcs than a wave has lanes, chains of more than four levels, whole phrases (an arc and the base winner have the same
 value), rows that only a pass over them can decide, more of them than are taken at a time; and the segment decoders on calls
 that are still theirs.  Ids are exact, scores within 1e-5 (they are the same bits: the oracle's operations in its order)."""
@@ -79,8 +79,24 @@ def test_every_frame_needs_its_row(V, T):
 
 @pytest.mark.parametrize("V", [1025, 1152, 1280, 1281, 2047, 2048, 2049, 2500, 4095, 4096, 5125, 9217, 16381, 16384])
 def test_segment_decoders_on_long_calls(V, monkeypatch):
-    monkeypatch.setitem(seg.SIZES, V, (2050, 3))
-    seg.test_segment_decoders_past_the_dispatch_line(V, V % 2 == 0)
+    monkeypatch.setitem(seg.SEGMENTS, V, (2050, 3))
+    seg.test_segment_decoders_past_the_dispatch_line(V, V % 4 == 0, V % 2 == 0)
+
+
+@pytest.mark.parametrize("V,T", [(32768, 1030), (32769, 1025), (40961, 1100)])
+def test_more_frames_than_a_block_holds_in_one_word_and_in_two(V, T):
+    """Past 32768 tokens what the first pass finds of a row lies in two output words, and the frames past the first block
+    read both of them."""
+    rng = np.random.default_rng(96000 + V)
+    torch.manual_seed(V)
+    toks, offs = _lists(rng, V, V - 1, "zipf")
+    ot = OracleTree(toks, offs, V, V - 1, weight_mode=1)
+    tr = pb.pb_build(toks, offs, V, V - 1, device=0, weight_mode=1)
+    x = seg._spoken(rng, T, 1, V, [(toks, offs)])
+    x[torch.rand((T, 1), device=DEV) < 0.4, V - 1] += 14.0
+    s0 = rng.integers(0, ot.num_states, 1).astype(np.int32)
+    _compare(tr, ot, x.cpu().numpy(), s0, rng.integers(-1, V, 1).astype(np.int32), 0.5, (V, T))
+    pb.pb_free(tr)
 
 
 @pytest.mark.parametrize("V", [300, 1025, 2500])

@@ -38,7 +38,7 @@ def test_static_scratch_matches_workspace_form_on_two_calls_in_a_row():
     toks, offs = W.make_phrases(cfg)
     tree = pb.pb_build(toks, offs, cfg.vocab_size, cfg.blank_id, device=0)
     V = cfg.vocab_size
-    for (T, B, mode) in ((300, 48, 2), (120, 7, 0)):           # the second call is the smaller one
+    for (T, B, mode) in ((300, 48, 2), (530, 7, 0)):           # the second call has the fewer segment boundaries; both are the segment decoder's
         shape = W.Config(9, "na", V, cfg.blank_id, 1, 1, 8, "uniform", 1.1, B, 1, T, 2.0)
         logp = W.make_logp(shape, seed=T, planting=W.Planting(toks, offs, cover=0.5), blank_bias=6.0, blank_frac=0.3)
         d_logp = torch.from_numpy(logp).to(DEV)
