@@ -299,7 +299,8 @@ int pb_fuse_step_beam_forest(const pb_forest* forest, const float* d_logp, int64
  * pb_validate -- debug aid (host-side, O(N + V)): bounds-checks every index the kernels follow in the compiled
  * tree -- arc rows tile the arc table and stay inside it, tokens in [0, V) and strictly ascending per row, arc j
  * leads to state j + 1 one level deeper, failure links lead to strictly shallower states, the root row points at
- * depth-1 states on the right token, the packed records equal the flat arrays.  PB_OK, or PB_ERANGE at the first
+ * depth-1 states on the right token, the packed records equal the flat arrays, the hashed table of arcs finds every arc
+ * and nothing else.  PB_OK, or PB_ERANGE at the first
  * violation.  pb_build runs it by itself when the environment variable PB_DEBUG is set to anything but "0".
  * pb_validate_states -- the same for a HOST array of n state ids: PB_ERANGE and *first_bad (may be NULL) = the
  * first index whose id is outside [0, num_states).  (On the device an id outside the range never faults: see the

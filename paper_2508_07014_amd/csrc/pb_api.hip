@@ -7,7 +7,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -46,21 +45,6 @@ int lookup_scratch(int device) {
 
 size_t padded(size_t bytes) { return (bytes + kAlign - 1) / kAlign * kAlign; }
 
-// The table of arcs by (state, token), see ArcSlot; null where there is no memory for it.
-std::unique_ptr<pb::ArcSlot[]> arc_table(const pb::HostTree& h, size_t size) {
-  std::unique_ptr<pb::ArcSlot[]> slots(new (std::nothrow) pb::ArcSlot[size]);
-  if (!slots || size == 0) return slots;
-  std::fill(slots.get(), slots.get() + size, pb::ArcSlot{-1, -1, -1, 0});
-  for (size_t s = 1; s < h.state.size(); ++s) {
-    for (int32_t j = h.arc_begin[s]; j < h.arc_begin[s] + h.arc_count[s]; ++j) {
-      size_t at = pb::arc_hash(static_cast<int32_t>(s), h.arc_token[j]) & (size - 1);
-      while (slots[at].state >= 0) at = (at + 1) & (size - 1);
-      slots[at] = pb::ArcSlot{static_cast<int32_t>(s), h.arc_token[j], j + 1, 0};
-    }
-  }
-  return slots;
-}
-
 // Uploads the flat arrays as one device allocation.  The device stays current only inside the call.
 int upload(pb_tree* tr, int device) {
   const pb::HostTree& h = tr->host;
@@ -71,23 +55,28 @@ int upload(pb_tree* tr, int device) {
   const size_t n_pr = h.p_root.size() * sizeof(float);
   const size_t n_rr = h.root_rec.size() * sizeof(pb::RootRec);
   const size_t n_es = h.eos_score.size() * sizeof(float);
-  const size_t n_slots = pb::arc_slots(static_cast<int32_t>(h.state.size()));
-  const std::unique_ptr<pb::ArcSlot[]> slots = arc_table(h, n_slots);
-  if (!slots) return PB_ENOMEM;
-  const size_t n_as = n_slots * sizeof(pb::ArcSlot);
-  const size_t total =
-      padded(n_state) + padded(n_arc) + padded(n_rs) + padded(n_rn) + padded(n_pr) + padded(n_rr) + padded(n_es) + padded(n_as);
+  std::vector<pb::ArcSlot> slots;
+  if (pb::wants_arc_table(h.vocab_size)) slots = pb::build_arc_table(h);
+  size_t n_as = slots.size() * sizeof(pb::ArcSlot);
+  const size_t arrays =
+      padded(n_state) + padded(n_arc) + padded(n_rs) + padded(n_rn) + padded(n_pr) + padded(n_rr) + padded(n_es);
   // The wave kernels request the first arcs of a state without a condition, with the index clamped into the
   // state's arc range; for a state without arcs (the last state of the table included) that reads the entry
   // at arc_begin, i.e. up to one ArcRec past the arc table.  The sub-arrays that follow the arc table in the
   // allocation make that read harmless; refuse a layout that would not.
-  if (total - (padded(n_as) + padded(n_state) + n_arc) < sizeof(pb::ArcRec)) return PB_EUNSUPPORTED;
+  if (arrays - (padded(n_state) + n_arc) < sizeof(pb::ArcRec)) return PB_EUNSUPPORTED;
   int prev = 0;
   if (hipGetDevice(&prev) != hipSuccess) { (void)hipGetLastError(); return PB_EHIP; }
   if (hipSetDevice(device) != hipSuccess) { (void)hipGetLastError(); return PB_EHIP; }
   int rc = PB_OK;
   char* slab = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(&slab), total) != hipSuccess) {
+  hipError_t got = hipMalloc(reinterpret_cast<void**>(&slab), arrays + padded(n_as));
+  if (got != hipSuccess && n_as > 0) {  // the tree does without its table
+    (void)hipGetLastError();
+    n_as = 0;
+    got = hipMalloc(reinterpret_cast<void**>(&slab), arrays);
+  }
+  if (got != hipSuccess) {
     (void)hipGetLastError();
     rc = PB_ENOMEM;
   } else {
@@ -98,7 +87,6 @@ int upload(pb_tree* tr, int device) {
       p += padded(bytes);
       return dst;
     };
-    put(slots.get(), n_as);
     tr->dev.state = static_cast<const pb::StateRec*>(put(h.state.data(), n_state));
     tr->dev.arc = static_cast<const pb::ArcRec*>(put(h.arc.data(), n_arc));
     tr->dev.root_score = static_cast<const float*>(put(h.root_score.data(), n_rs));
@@ -106,6 +94,8 @@ int upload(pb_tree* tr, int device) {
     tr->dev.p_root = static_cast<const float*>(put(h.p_root.data(), n_pr));
     tr->dev.root_rec = static_cast<const pb::RootRec*>(put(h.root_rec.data(), n_rr));
     tr->dev.eos_score = n_es ? static_cast<const float*>(put(h.eos_score.data(), n_es)) : nullptr;
+    put(slots.data(), n_as);  // (found behind these, see arc_table_of)
+    tr->has_table = n_as > 0;
     tr->dev.eos_id = h.eos_id;
     if (rc == PB_OK) rc = pb::prepare_wave_kernels();
     if (rc == PB_OK) rc = lookup_scratch(device);
@@ -125,7 +115,7 @@ int upload(pb_tree* tr, int device) {
   (void)hipSetDevice(prev);
   if (rc == PB_OK) {
     tr->slab = slab;
-    tr->device_bytes = static_cast<int64_t>(total);
+    tr->device_bytes = static_cast<int64_t>(arrays + padded(n_as));
     tr->device = device;
   }
   return rc;
@@ -305,13 +295,14 @@ int pb_fuse_step(const pb_tree* tree, const float* d_logp, int64_t row_stride, c
 
 namespace {
 
-// The kernels of a multi-frame call (d_patches: the optional workspace, null: none).
-int launch_frames(const pb::DeviceTree& t, const pb::TreePick& pick, const float* d_logp, int64_t frame_stride,
+// The kernels of a multi-frame call (has_table: the tree, or every member of the table of trees, has its table of arcs;
+// d_patches: the optional workspace, null: none).
+int launch_frames(const pb::DeviceTree& t, bool has_table, const pb::TreePick& pick, const float* d_logp, int64_t frame_stride,
                   int64_t row_stride, const int32_t* d_states0, const int32_t* d_last0, float alpha, int32_t T, int32_t B,
                   int32_t mode, int32_t* d_tokens, int32_t* d_states, float* d_scores, int32_t* d_patches,
                   hipStream_t stream) {
   if (pb::frames_apart(pick, d_states0, d_last0, T, B, d_tokens, d_states, d_scores)) {
-    if (pb::frames_rows_ok(t, T, B, mode))
+    if (has_table && pb::frames_rows_ok(t, T, B, mode))
       return pb::launch_frames_rows(t, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
                                     d_tokens, d_states, d_scores, stream);
     // (the segment decoder keeps a flag in bit 30 of the state words it stores: larger trees take the plain kernel; the
@@ -333,7 +324,7 @@ int fuse_frames_any(const pb_tree* tree, const float* d_logp, int64_t frame_stri
   if (B == 0 || T == 0) return PB_OK;
   if (!d_logp || !d_states0 || !d_tokens || !d_states || !d_scores) return PB_EINVAL;
   if (row_stride < tree->dev.vocab_size || frame_stride < 0) return PB_EINVAL;
-  return launch_frames(tree->dev, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
+  return launch_frames(tree->dev, tree->has_table, pb::TreePick{}, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode,
                        d_tokens, d_states, d_scores, d_patches, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -454,6 +445,8 @@ int pb_forest_build(const pb_tree* const* trees, int32_t n_trees, pb_forest** ou
     return rc;
   }
   f->proto = first->dev;
+  f->has_table = true;
+  for (int32_t i = 0; i < n_trees; ++i) f->has_table = f->has_table && trees[i]->has_table;
   for (int32_t i = 0; i < n_trees; ++i)  // the largest member decides what the others may rely on (see pb_fuse_frames_forest)
     if (trees[i]->dev.num_states > f->proto.num_states) f->proto.num_states = trees[i]->dev.num_states;
   f->count = n_trees;
@@ -508,7 +501,7 @@ int pb_fuse_frames_forest(const pb_forest* forest, const float* d_logp, int64_t 
   if (!d_logp || !d_tree_ids || !d_states0 || !d_tokens || !d_states || !d_scores) return PB_EINVAL;
   if (row_stride < forest->proto.vocab_size || frame_stride < 0) return PB_EINVAL;
   const pb::TreePick pick{forest->d_table, d_tree_ids, forest->count};
-  return launch_frames(forest->proto, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
+  return launch_frames(forest->proto, forest->has_table, pick, d_logp, frame_stride, row_stride, d_states0, d_last0, alpha, T, B, mode, d_tokens,
                        d_states, d_scores, nullptr, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -576,6 +569,8 @@ int pb_validate(const pb_tree* tree) {
         r.backoff != h.backoff[n] || r.p_root != h.p_root[n])
       return PB_ERANGE;
   }
+  const std::vector<pb::ArcSlot> slots = pb::build_arc_table(h);  // (empty: no memory for it)
+  if (!slots.empty() && !pb::arc_table_ok(h, slots)) return PB_ERANGE;
   return PB_OK;
 }
 

@@ -263,4 +263,42 @@ int compile_tree(const int32_t* tokens, const int64_t* offsets, int64_t n_phrase
   return PB_OK;
 }
 
+std::vector<ArcSlot> build_arc_table(const HostTree& h) {
+  const size_t size = arc_slots(static_cast<int32_t>(h.state.size()));
+  std::vector<ArcSlot> slots;
+  try {
+    slots.assign(size, ArcSlot{-1, -1, -1, 0});
+  } catch (const std::bad_alloc&) {
+    return {};
+  }
+  if (size == 0) return slots;
+  for (size_t s = 1; s < h.state.size(); ++s) {
+    for (int32_t j = h.arc_begin[s]; j < h.arc_begin[s] + h.arc_count[s]; ++j) {
+      size_t at = arc_hash(static_cast<int32_t>(s), h.arc_token[j]) & (size - 1);
+      while (slots[at].state >= 0) at = (at + 1) & (size - 1);
+      slots[at] = ArcSlot{static_cast<int32_t>(s), h.arc_token[j], j + 1, 0};
+    }
+  }
+  return slots;
+}
+
+int32_t find_arc(const std::vector<ArcSlot>& slots, int32_t s, int32_t v) {
+  for (size_t at = arc_hash(s, v);; ++at) {
+    const ArcSlot& q = slots[at & (slots.size() - 1)];
+    if (q.state == s && q.token == v) return q.next;
+    if (q.state < 0) return 0;
+  }
+}
+
+bool arc_table_ok(const HostTree& h, const std::vector<ArcSlot>& slots) {
+  if (slots.size() != arc_slots(static_cast<int32_t>(h.state.size()))) return false;
+  size_t used = 0;
+  for (const ArcSlot& q : slots) used += q.state >= 0 ? 1 : 0;
+  if (used != h.arc.size() - static_cast<size_t>(h.arc_count[0]) || 2 * used > slots.size()) return false;
+  for (size_t s = 1; s < h.state.size(); ++s)
+    for (int32_t j = h.arc_begin[s]; j < h.arc_begin[s] + h.arc_count[s]; ++j)
+      if (find_arc(slots, static_cast<int32_t>(s), h.arc_token[j]) != j + 1) return false;
+  return true;
+}
+
 }  // namespace pb

@@ -253,6 +253,7 @@ constexpr int kWalkPairs = 256;  // (frame, arc) pairs looked at together: four 
 // The order of a frame's arcs: by value, then the lower token, then the level of the chain, deepest state first (11 bits;
 // levels past the last one counted are told apart by a pass over the row).
 constexpr int kLevelBits = 11, kLastLevel = (1 << kLevelBits) - 1, kMaxWalkV = 1 << (32 - kLevelBits);
+static_assert(kMaxWalkV >= kMaxTableV);
 __device__ __forceinline__ u64 arc_key(float value, int token, int level) {
   const unsigned low = static_cast<unsigned>(token) << kLevelBits | static_cast<unsigned>(min(level, kLastLevel));
   return static_cast<u64>(ukey(value)) << 32 | ~low;
@@ -302,6 +303,13 @@ struct WalkFrame {
 // LDS accesses wait for.)
 #define PB_AS1 __attribute__((address_space(1)))
 typedef int v2i __attribute__((ext_vector_type(2)));
+
+// The table of arcs: the first aligned address behind the other sub-arrays (256 bytes, as all of them are aligned).
+__device__ __forceinline__ const v4i PB_AS1* arc_table_of(const DeviceTree& t) {
+  const uintptr_t end = t.eos_score != nullptr ? reinterpret_cast<uintptr_t>(t.eos_score + t.num_states)
+                                               : reinterpret_cast<uintptr_t>(t.root_rec + t.vocab_size);
+  return (const v4i PB_AS1*)((end + 255) & ~static_cast<uintptr_t>(255));
+}
 
 template <int SEL>
 struct Walker {
@@ -843,7 +851,7 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
     const int f1 = static_cast<int>(static_cast<int64_t>(wave + 1) * count / nwaves);
     const int base = first_held(f0, f1), lo = f0 - base, hi = f1 - base, fr = base + lane;
     const Walker<SEL> walk{t, (const v4i PB_AS1*)mine.state, (const v2i PB_AS1*)mine.arc,
-                           (const v4i PB_AS1*)mine.state - arc_slots(mine.num_states), arc_slots(mine.num_states) - 1,
+                           arc_table_of(mine), arc_slots(mine.num_states) - 1,
                            (const int PB_AS1*)mine.root_next, mine.root_rec,
                            (const float PB_AS1*)mine.p_root, (const float PB_AS1*)mine.eos_score, (const float PB_AS1*)mine.root_score,
                            logp + static_cast<int64_t>(F0 + base) * frame_stride + static_cast<int64_t>(b) * row_stride,
@@ -978,8 +986,8 @@ size_t walk_lds_bytes(int V, int waves, int side) {
 }  // namespace
 
 bool frames_rows_ok(const DeviceTree& t, int32_t T, int32_t B, int sel) {
-  return t.p_root != nullptr && t.root_rec != nullptr && t.num_states <= kMaxTableStates && rows_pay(t.vocab_size, T, B, sel, t.num_states) &&
-         t.vocab_size <= kMaxWalkV && walk_lds_bytes(t.vocab_size, 1, 1) <= static_cast<size_t>(g_walk_max_lds);
+  return t.p_root != nullptr && t.root_rec != nullptr && rows_pay(t.vocab_size, T, B, sel, t.num_states) &&
+         walk_lds_bytes(t.vocab_size, 1, 1) <= static_cast<size_t>(g_walk_max_lds);
 }
 
 int launch_frames_rows(const DeviceTree& t, const TreePick& pick, const float* d_logp, int64_t frame_stride,

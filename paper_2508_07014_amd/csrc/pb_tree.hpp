@@ -44,8 +44,9 @@ struct alignas(32) RootRec {
 // One 16-byte slot of the table of arcs by (state, token), the root's aside: open addressing, linear probing, at most
 // half full; state == -1 in an empty slot.  A deep state has few arcs and they could be searched, but the walk over a
 // phrase (pb_rows.hip) follows one arc after the other, and the table makes that one access each instead of two or more.
-// It lies right before the states on the device and its size follows from their number, so that DeviceTree, which every
-// kernel takes by value or out of a table, has no field for it.
+// It lies behind the other sub-arrays on the device and its size follows from the number of states, so that DeviceTree, which
+// every kernel takes by value or out of a table, has no field for it.  Only the two-pass decoder reads it: a tree of a
+// vocabulary that never gets there has none, nor has one for which there is no memory, and its calls take the other decoders.
 struct alignas(16) ArcSlot {
   int32_t state, token, next, pad;
 };
@@ -59,6 +60,10 @@ constexpr uint32_t arc_hash(int32_t state, int32_t token) {
   h ^= h >> 15;
   return h * 0xC2B2AE35u >> 3;
 }
+
+// Whether calls on a tree of this vocabulary may take the two passes (see rows_pay and arc_key in pb_rows.hip).
+constexpr int32_t kMinTableV = 128, kMaxTableV = 1 << 21;
+constexpr bool wants_arc_table(int32_t vocab_size) { return vocab_size >= kMinTableV && vocab_size <= kMaxTableV; }
 
 // Device mirror (one allocation, sub-arrays aligned to 256 bytes).
 struct DeviceTree {
@@ -100,12 +105,20 @@ struct HostTree {
 // Alg. 1 Stages 1-2 on the host.  Returns a pb_status.
 int compile_tree(const int32_t* tokens, const int64_t* offsets, int64_t n_phrases, const float* weights,
                  const pb_build_opts& opts, HostTree& out);
+// The table of arcs by (state, token); empty where there is no memory for it or more states than 32 bits count slots for.
+std::vector<ArcSlot> build_arc_table(const HostTree& tree);
+// The state an arc of state s on token v leads to, 0 if there is none: what the kernel does.
+int32_t find_arc(const std::vector<ArcSlot>& slots, int32_t s, int32_t v);
+// Every arc but the root's is found where it leads, nothing else is in the table, and at least half of it is empty (so that
+// every search ends).
+bool arc_table_ok(const HostTree& tree, const std::vector<ArcSlot>& slots);
 
 }  // namespace pb
 
 struct pb_forest {
   pb::DeviceTree* d_table = nullptr;  // device copy of the members' DeviceTree records
   pb::DeviceTree proto;               // vocabulary size and blank id common to all members
+  bool has_table = false;             // every member has its table of arcs
   int32_t count = 0;
   int device = -1;
 };
@@ -114,6 +127,7 @@ struct pb_tree {
   pb::HostTree host;
   pb::DeviceTree dev;
   void* slab = nullptr;  // device allocation backing `dev`
+  bool has_table = false;  // ... with the table of arcs
   int64_t device_bytes = 0;
   int device = -1;
 };

@@ -49,6 +49,24 @@ static void invariants(const pb::HostTree& t, int V, int64_t total_tokens) {
     }
   }
   CHECK(arcs == N - 1);
+  // the table of arcs by (state, token): every arc, nothing else, and a change to it is noticed
+  std::vector<pb::ArcSlot> slots = pb::build_arc_table(t);
+  CHECK(slots.size() >= 16 && pb::arc_table_ok(t, slots));
+  for (int s = 1; s < N; ++s)
+    for (int v = 0; v < V; ++v) {
+      int want = 0;
+      for (int j = t.arc_begin[s]; j < t.arc_begin[s] + t.arc_count[s]; ++j)
+        if (t.arc_token[j] == v) want = j + 1;
+      CHECK(pb::find_arc(slots, s, v) == want);
+    }
+  for (size_t i = 0; i < slots.size(); ++i) {
+    if (slots[i].state < 0) continue;
+    ++slots[i].next;
+    CHECK(!pb::arc_table_ok(t, slots));
+    slots[i].state = -1;
+    CHECK(!pb::arc_table_ok(t, slots));
+    break;
+  }
   for (int v = 0; v < V; ++v) CHECK(t.root_next[v] >= 0 && t.root_next[v] < N && t.root_rec[v].next == t.root_next[v]);
 }
 
@@ -81,6 +99,12 @@ int main() {
     if (rc == PB_OK) invariants(t, V, static_cast<int64_t>(toks.size()));
     if (rc == PB_OK && eos >= 0) CHECK(static_cast<int>(t.final_score.size()) == static_cast<int>(t.state.size()));
   }
+  // sizes of the table: a power of two, at least half empty, none past 2^30 states
+  for (int64_t n : {1ll, 8ll, 9ll, 16ll, 17ll, 1000ll, 65536ll, 65537ll, (1ll << 30) - 1, 1ll << 30}) {
+    const uint64_t size = pb::arc_slots(static_cast<int32_t>(n));
+    CHECK(size >= 16 && (size & (size - 1)) == 0 && size >= static_cast<uint64_t>(2 * n) && (n <= 8 || size < static_cast<uint64_t>(4 * n)));
+  }
+  CHECK(pb::arc_slots((1 << 30) + 1) == 0);
   // malformed inputs: an error code, never a crash
   {
     pb::HostTree t;

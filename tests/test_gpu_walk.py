@@ -83,6 +83,26 @@ def test_segment_decoders_on_long_calls(V, monkeypatch):
     seg.test_segment_decoders_past_the_dispatch_line(V, V % 4 == 0, V % 2 == 0)
 
 
+def test_which_trees_have_a_table_of_arcs():
+    """Trees of vocabularies whose calls never take the two passes do without."""
+    rng = np.random.default_rng(97000)
+    pad = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    for V in (100, 127, 128, 1000, 20001):
+        for eos in (-1, V - 2):
+            toks, offs = _lists(rng, V, V - 1, "deep")
+            toks = np.where(toks == eos, 1, toks).astype(np.int32)
+            tr = pb.pb_build(toks, offs, V, V - 1, device=0, eos_id=eos)
+            n = pb.pb_info(tr)["num_states"]
+            arrays = pad(32 * n) + pad(8 * (n - 1)) + 2 * pad(4 * V) + pad(4 * n) + pad(32 * V) + (pad(4 * n) if eos >= 0 else 0)
+            slots = 16 * max(16, 2 << (n - 1).bit_length()) if V >= 128 else 0
+            assert pb.pb_info(tr)["device_bytes"] == arrays + pad(slots)
+            ot = OracleTree(toks, offs, V, V - 1, eos_id=eos)
+            s0 = rng.integers(0, n, 2).astype(np.int32)
+            x = seg._spoken(rng, 40, 2, V, [(toks, offs)])
+            _compare(tr, ot, x.cpu().numpy(), s0, rng.integers(-1, V, 2).astype(np.int32), 0.5, (V, eos))
+            pb.pb_free(tr)
+
+
 @pytest.mark.parametrize("V,T", [(32768, 1030), (32769, 1025), (40961, 1100)])
 def test_more_frames_than_a_block_holds_in_one_word_and_in_two(V, T):
     """Past 32768 tokens what the first pass finds of a row lies in two output words, and the frames past the first block
