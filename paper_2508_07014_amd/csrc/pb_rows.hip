@@ -560,9 +560,9 @@ struct Walker {
 
   // Decides frames one after the other, the arcs of one on the lanes: the first of `wrong` (see misfits, `starts` and
   // `labels` are what it says) and those behind it until one was already decided from where this leads, then the next of
-  // those that still do not fit.  Two dependent accesses a frame, about 1 us, where carrying the starts on and deciding
+  // those that still do not fit.  Two dependent accesses a frame of up to 64 arcs, about 1.3 us, where carrying the starts on and deciding
   // them side by side takes about ten, however few they are: this is for the few.  Returns the frame that it stops at
-  // because its arcs are too many, a bit, or 0.
+  // because its chain has more than four states, a bit, or 0.
   __device__ __forceinline__ u64 follow(WalkFrame& f, u64 wrong, int starts, int labels, int lo, int hi, int from,
                                         int from_label) const {
     // (the records of where the winners lead from the root)
@@ -579,8 +579,9 @@ struct Walker {
       int tok = v0, next = s, from_arc = -1;
       bool moves = false, hard = false, by_root = false;
       float val = x0;
-      v4i k0 = {0, 0, 0, 0}, k1 = k0;  // the record of the state that this lane's arc leads to
+      v4i k0 = {0, 0, 0, 0}, k1 = k0;  // the record of the state that this lane's first arc leads to
       float kp = 0.0f, ke = 0.0f;
+      int kid = 0;
       if (!kept) {
         const float M = __fadd_rn(lane_f(f.xw, l), __fmul_rn(alpha, __fadd_rn(cur.p_root, lane_f(f.rsw, l))));
         hard = lane_i(f.marked ? 1 : 0, l) != 0 || M == -INFINITY;
@@ -595,7 +596,7 @@ struct Walker {
           if (r1.fail != 0) r = load_rec2(t, r1.fail);
           if (r.a.fail == 0) r.b = none;
           const int c0 = cur.rec.count, c1 = c0 + r1.count, c2 = c1 + r.a.count, total = c2 + r.b.count;
-          if (total > 64 || r.b.fail != 0) {
+          if (r.b.fail != 0) {  // (a longer chain)
             if (lane == l) {
               f.s = s;
               f.label = label;
@@ -604,38 +605,54 @@ struct Walker {
             return 1ull << l;
           }
           const float p1 = __fadd_rn(0.0f, cur.rec.backoff), p2 = __fadd_rn(p1, r1.backoff), p3 = __fadd_rn(p2, r.a.backoff);
-          const bool valid = lane < total;
-          const int lv = (lane >= c0 ? 1 : 0) + (lane >= c1 ? 1 : 0) + (lane >= c2 ? 1 : 0);
-          int mine = INT_MAX, a_tok = -1;
+          int low = INT_MAX, to = 0, a_tok = -1, a_lv = 0;  // this lane's best: token and level, target; its first arc
           float v = -INFINITY;
-          if (valid) {
-            const int i = lv == 0 ? cur.rec.begin + lane : lv == 1 ? r1.begin + lane - c0 : lv == 2 ? r.a.begin + lane - c1 : r.b.begin + lane - c2;
-            const float p = lv == 0 ? 0.0f : lv == 1 ? p1 : lv == 2 ? p2 : p3;
-            const v2i a = arc[i];
-            const float xa = hyp[static_cast<int64_t>(l) * frame_stride + a.x];
-            k0 = states[2 * static_cast<size_t>(i + 1)];
-            k1 = states[2 * static_cast<size_t>(i + 1) + 1];
-            kp = p_root[i + 1];
-            if (t.eos >= 0) ke = eos_score[i + 1];
-            a_tok = a.x;
-            v = __fadd_rn(xa, __fmul_rn(alpha, __fadd_rn(p, __int_as_float(a.y))));
-            mine = i + 1;
+          bool hit = false;
+#pragma unroll 1
+          for (int j0 = 0; j0 < total; j0 += 64) {
+            const int j = j0 + lane;
+            const int lv = (j >= c0 ? 1 : 0) + (j >= c1 ? 1 : 0) + (j >= c2 ? 1 : 0);
+            if (j < total) {
+              const int i = lv == 0 ? cur.rec.begin + j : lv == 1 ? r1.begin + j - c0 : lv == 2 ? r.a.begin + j - c1 : r.b.begin + j - c2;
+              const float p = lv == 0 ? 0.0f : lv == 1 ? p1 : lv == 2 ? p2 : p3;
+              const v2i a = arc[i];
+              const float xa = hyp[static_cast<int64_t>(l) * frame_stride + a.x];
+              if (j0 == 0) {
+                k0 = states[2 * static_cast<size_t>(i + 1)];
+                k1 = states[2 * static_cast<size_t>(i + 1) + 1];
+                kp = p_root[i + 1];
+                if (t.eos >= 0) ke = eos_score[i + 1];
+                kid = i + 1;
+                a_tok = a.x;
+                a_lv = lv;
+              }
+              const float fa = __fadd_rn(xa, __fmul_rn(alpha, __fadd_rn(p, __int_as_float(a.y))));
+              const int code = a.x << 2 | lv;
+              const bool up = fa > v || (fa == v && code < low);
+              v = up ? fa : v;
+              low = up ? code : low;
+              to = up ? i + 1 : to;
+              hit = hit || a.x == w;
+            }
+            together();
           }
-          together();
           // the largest value, the lowest token of that, its deepest state
-          const float top = ukey_val(wave_max_u(valid ? ukey(v) : 0u));
-          const bool best = valid && v == top;
-          const int low = wave_min_nn(best ? a_tok << 2 | lv : INT_MAX);
-          const u64 who = __ballot(best && (a_tok << 2 | lv) == low);
-          overridden = __ballot(valid && a_tok == w) != 0;
+          const float top = ukey_val(wave_max_u(low != INT_MAX ? ukey(v) : 0u));
+          const bool best = low != INT_MAX && v == top;
+          const int first = wave_min_nn(best ? low : INT_MAX);
+          const u64 who = __ballot(best && low == first);
+          overridden = __ballot(hit) != 0;
           if (who != 0) {
             from_arc = first_lane(who);
             am = lane_f(v, from_arc);
-            at = low >> 2;
+            at = first >> 2;
             by_arc = true;
-            next = lane_i(mine, from_arc);
+            next = lane_i(to, from_arc);
             // (a deeper state has the token too, with a lower value: another token may win)
-            hard = __ballot(valid && a_tok == at && lv < (low & 3)) != 0;
+            const int lv = first & 3;
+            hard = __ballot(a_tok == at && a_lv < lv) != 0;
+            if (total > 64 && lv > 0)
+              hard = hard || child(s, at) != 0 || (lv > 1 && child(cur.rec.fail, at) != 0) || (lv > 2 && child(r1.fail, at) != 0);
           }
         }
         auto special = [&](int token, float fv) {
@@ -681,6 +698,8 @@ struct Walker {
         l = first_lane(wrong);
         s = lane_i(starts, l);
         label = lane_i(labels, l);
+        cur = cursor_at(t, s);
+      } else if (from_arc >= 0 && lane_i(kid, from_arc) != s) {
         cur = cursor_at(t, s);
       } else if (from_arc >= 0) {
         cur = Cursor{s, Rec{lane_i(k0.x, from_arc), lane_i(k0.y, from_arc), lane_i(k0.z, from_arc), __int_as_float(lane_i(k0.w, from_arc))},
