@@ -85,7 +85,7 @@ typedef struct {
   int32_t vocab_size;
   int32_t blank_id;
   int32_t eos_id;         /* -1 if the tree has no EOS rule            */
-  int64_t device_bytes;   /* size of the uploaded tree, 0 if host-only */
+  int64_t device_bytes;   /* size of the uploaded tree (its table of arcs included), 0 if host-only */
 } pb_tree_info;
 
 /* Host view of the flat arrays the kernels read (owned by the tree; valid until pb_free). */
@@ -211,8 +211,9 @@ int pb_fuse_frames_select(const pb_tree* tree, const float* d_logp, int64_t fram
                           int32_t mode, int32_t* d_tokens, int32_t* d_states, float* d_scores, void* hip_stream);
 
 /*
- * pb_fuse_frames_ws -- pb_fuse_frames_select with a caller-owned workspace, the faster form of the same call
- * (identical outputs).  The decoder cuts the T frames of every hypothesis into segments decoded side by side,
+ * pb_fuse_frames_ws -- pb_fuse_frames_select with a caller-owned workspace, the faster form of the same call where the
+ * segment decoder takes it, and the same one elsewhere (identical outputs; the workspace is asked for in either case).
+ * The segment decoder cuts the T frames of every hypothesis into segments decoded side by side,
  * each from a guess of the state the frame before it ends in; with the workspace a segment that finds the
  * guess for its right neighbour wrong repairs the neighbour's first frames itself and leaves them there
  * (comparing with the first frames the neighbour has decoded, which every segment leaves there too), and
@@ -230,11 +231,12 @@ int pb_fuse_frames_ws(const pb_tree* tree, const float* d_logp, int64_t frame_st
                       void* hip_stream);
 
 /*
- * pb_fuse_frames_plan -- how pb_fuse_frames* would cut the T frames of a call with B hypotheses into segments (host
- * only, nothing is launched; for tests and for sizing).  Writes the number of segments to *n_segments and, if
+ * pb_fuse_frames_plan -- how the segment decoder cuts the T frames of a call with B hypotheses into segments, which is
+ * what the workspace is sized for (host only, nothing is launched; for tests and for sizing).  Writes the number of segments to *n_segments and, if
  * `bounds` is not NULL, n_segments + 1 frame indices to it (host array with room for 65 entries): segment j covers
  * frames bounds[j] .. bounds[j + 1] - 1, bounds[0] = 0, bounds[n_segments] = T; every hypothesis is cut the same way.
- * (Calls of few or very wide rows are not cut: they find the winners of all rows first and run the states over those.)
+ * (Calls of up to some thousand rows, tens of thousands under the CTC rule, and all of very wide ones are not cut: they
+ * find the winners of all rows first and run the states over those, if a table of arcs was uploaded with the tree.)
  * T == 0 or B == 0 gives zero segments.  PB_EINVAL for a null tree or n_segments, or negative sizes.
  */
 int pb_fuse_frames_plan(const pb_tree* tree, int32_t T, int32_t B, int32_t* n_segments, int32_t* bounds);
@@ -300,8 +302,7 @@ int pb_fuse_step_beam_forest(const pb_forest* forest, const float* d_logp, int64
  * tree -- arc rows tile the arc table and stay inside it, tokens in [0, V) and strictly ascending per row, arc j
  * leads to state j + 1 one level deeper, failure links lead to strictly shallower states, the root row points at
  * depth-1 states on the right token, the packed records equal the flat arrays, the hashed table of arcs finds every arc
- * and nothing else.  PB_OK, or PB_ERANGE at the first
- * violation.  pb_build runs it by itself when the environment variable PB_DEBUG is set to anything but "0".
+ * and nothing else.  PB_OK, or PB_ERANGE at the first violation.  pb_build runs it by itself when the environment variable PB_DEBUG is set to anything but "0".
  * pb_validate_states -- the same for a HOST array of n state ids: PB_ERANGE and *first_bad (may be NULL) = the
  * first index whose id is outside [0, num_states).  (On the device an id outside the range never faults: see the
  * conventions above.)

@@ -39,7 +39,7 @@ constexpr int64_t kMaxWorkgroups = kMaxThreads / 1024;
 //                 1025     .86 .91 .81      .75 .84 .80      .87 .90 .87      .75 .87 1.00     .87 1.05 1.33    .93 1.10 1.30
 //                 4096     .72 .75 .76      .83 .88 .93                       .88 1.00 1.05    .55 .60 .66      .90 1.03 1.16
 // The two-stage rule lies between the two, nearer the single-stage one, and has its lines.  Vocabularies past 16384 have no
-// segment decoder (32001, 100 x 16, two-stage: 3340 us with a workgroup per hypothesis, 68).
+// segment decoder (32001, 100 x 16, two-stage: 3340 us with a workgroup per hypothesis, 65).
 inline bool rows_pay(int V, int32_t T, int32_t B, int sel, int32_t num_states) {
   const int64_t rows = static_cast<int64_t>(T) * B;
   const bool ctc = sel == 2;

@@ -18,14 +18,16 @@
 //    that the winners alone lead to come first: every lane carries the state of the frame before it over its own winner,
 //    again until nothing changes, so a spoken phrase of n tokens takes n turns, all phrases side by side, and a turn is one
 //    access to the table of arcs by (state, token).  Then all frames are decided from those states at once, their arcs
-//    shared out over the lanes.  A frame that comes out differently sends the ones behind it round again, until every
-//    frame was decided from what the frame before it led to; the waves hand on their ends between barriers.  Frames that
-//    the winners do not settle (near ties, a barred label under the CTC rule) take a pass over their row by all waves.
+//    shared out over the lanes.  A frame that comes out differently sends the ones behind it round again, once side by side,
+//    then one frame after the other where they are few, until every frame was decided from what the frame before it led to;
+//    the waves hand on their ends between barriers.  Frames that the winners do not settle (near ties, a base winner shadowed
+//    by a weaker arc, a barred label under the CTC rule) take passes over their rows, a wave or a few to each.
 //
 // What bounds pass 2 is how many scattered lines one CU takes in (a frame's winners, root scores, records, arcs and their
-// log-probs: about 8 cycles a line), then the chain of dependent accesses.  Against deciding frames one after the other
-// inside a phrase, in segments (medians of a trace): 500 frames x 32, V = 1025, CTC rule 62.6 -> 53.2 us; 100 x 16,
-// V = 32001 32.4 -> 20.1.
+// log-probs: about 8 cycles a line), then the chain of dependent accesses, and where most frames surprise the winners the
+// instructions of one wave that follows them (about 4000 cycles a frame).  Against deciding frames one after the other inside
+// a phrase, in segments (medians of a trace): 500 frames x 32, V = 1025, CTC rule 62.6 -> 43.3 us; 100 x 16, V = 32001
+// 32.4 -> 21.4.
 //
 // Between the passes the winners travel in the call's own outputs (put_winners), so the outputs must not overlap what pass 2
 // reads (frames_apart).
@@ -560,8 +562,9 @@ struct Walker {
 
   // Decides frames one after the other, the arcs of one on the lanes: the first of `wrong` (see misfits, `starts` and
   // `labels` are what it says) and those behind it until one was already decided from where this leads, then the next of
-  // those that still do not fit.  Two dependent accesses a frame of up to 64 arcs, about 1.3 us, where carrying the starts on and deciding
-  // them side by side takes about ten, however few they are: this is for the few.  Returns the frame that it stops at
+  // those that still do not fit.  Two dependent accesses a frame of up to 64 arcs, about 1.5 us, where carrying the starts
+  // on and deciding them side by side takes about ten, however few they are: this is for the few.  Bounded by the
+  // instructions of one wave: requesting several turns of arcs together made it slower.  Returns the frame that it stops at
   // because its chain has more than four states, a bit, or 0.
   __device__ __forceinline__ u64 follow(WalkFrame& f, u64 wrong, int starts, int labels, int lo, int hi, int from,
                                         int from_label) const {
