@@ -909,8 +909,8 @@ __global__ void __launch_bounds__(1024) walk_kernel(DeviceTree dt, TreePick pick
     // First the states that the winners alone lead to, then the frames' decisions from there.  What does not fit then is
     // carried on and decided again once -- behind a surprise the winners are mostly right again -- and after that, where it
     // is few frames, one after the other: where most frames surprise the winners (log-depth weights, alpha = 1, phrases
-    // without blanks) carrying on further was 1.6 .. 2.7 times as slow (V = 1025, 250 x 16, CTC rule 221 -> 112 us; V = 512,
-    // 250 x 8 194 -> 94), without the second turn runs inside phrases of few tokens were (V = 1024, 500 x 4 52 -> 87).
+    // without blanks) carrying on further was 1.6 .. 2.7 times as slow (V = 1025, 250 x 16, CTC rule 221 -> 116 us; V = 512,
+    // 250 x 8 194 -> 89), without the second turn runs inside phrases of few tokens were (V = 1024, 500 x 4 52 -> 87).
     int from = base == 0 ? s : 0, from_label = base == 0 ? last : -1;
     for (int carries = 0;;) {
       int starts = 0, labels = 0;
